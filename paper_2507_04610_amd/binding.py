@@ -26,17 +26,22 @@ class Any4Error(RuntimeError):
 
 
 _lib = None
+_native_gemm = None          # _any4_torch.gemm once the library is loaded
 
 
 def load_library() -> ctypes.CDLL:
     """Load libany4.so from the package directory (build it with
     `python -m paper_2507_04610_amd.build`); raises if it is not there."""
-    global _lib
+    global _lib, _native_gemm
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise Any4Error(f"{LIB_PATH} is missing: run `python -m paper_2507_04610_amd.build` first")
     lib = ctypes.CDLL(LIB_PATH)
+    try:
+        from . import _any4_torch
+    except ImportError as e:
+        raise Any4Error(f"the torch extension beside {LIB_PATH} does not load ({e}): run `python -m paper_2507_04610_amd.build`")
     i64, vp, ci = ctypes.c_int64, ctypes.c_void_p, ctypes.c_int
     lib.any4_pack.restype = ci
     lib.any4_pack.argtypes = [vp, i64, i64, ci, vp, vp]
@@ -76,6 +81,7 @@ def load_library() -> ctypes.CDLL:
     lib.any4_strerror.argtypes = [ci]
     lib.any4_version.restype = ci
     lib.any4_version.argtypes = []
+    _native_gemm = _any4_torch.gemm
     _lib = lib
     return lib
 
@@ -188,6 +194,7 @@ def any4_dequant(codes: torch.Tensor, lut: torch.Tensor | None, scale: torch.Ten
 
 
 def _gemm(entry: str, x, codes, N, lut, scale, offset, bits, out, workspace, group=None):
+    """the checked call, one argument after the other: what the native call below says no to comes here to be named"""
     lib = load_library()
     M, K = x.shape
     dt = x.dtype if isinstance(x, torch.Tensor) and x.dtype == torch.float16 else torch.bfloat16
@@ -224,6 +231,16 @@ def _gemm(entry: str, x, codes, N, lut, scale, offset, bits, out, workspace, gro
     return out
 
 
+def _native(x, codes, lut, scale, offset, bits, out, workspace, group, repacked):
+    """a plain valid call in native code (csrc/any4_torch.cpp): the output, or None with nothing done"""
+    if _native_gemm is None:
+        load_library()
+    r = _native_gemm(x, codes, lut, scale, offset, bits, out, workspace, group, repacked)
+    if r.__class__ is int:
+        _check(r, "any4_gemm_repacked" if repacked else "any4_gemm")
+    return r
+
+
 def any4_gemm(x: torch.Tensor, codes: torch.Tensor, lut: torch.Tensor | None, scale: torch.Tensor,
               offset: torch.Tensor, bits: int = 4, out: torch.Tensor | None = None,
               workspace: torch.Tensor | None = None, group: int = GROUP) -> torch.Tensor:
@@ -232,6 +249,9 @@ def any4_gemm(x: torch.Tensor, codes: torch.Tensor, lut: torch.Tensor | None, sc
     [1, 2^bits]: one table for the whole matrix, any4_gemm_single_table);
     scale / offset are [N, K / group] (any4_gemm_grouped when group is not 128).
     With x, lut, scale, offset all fp16 the result is fp16 (any4_gemm_f16: groups of 128, a table)."""
+    r = _native(x, codes, lut, scale, offset, bits, out, workspace, group, False)
+    if r is not None:
+        return r
     if group == GROUP:
         return _gemm("any4_gemm", x, codes, codes.shape[0], lut, scale, offset, bits, out, workspace)
     return _gemm("any4_gemm_grouped", x, codes, codes.shape[0], lut, scale, offset, bits, out, workspace, group)
@@ -284,6 +304,9 @@ def any4_gemm_repacked(x: torch.Tensor, rcodes: torch.Tensor, lut: torch.Tensor,
                        offset: torch.Tensor, bits: int = 4, out: torch.Tensor | None = None,
                        workspace: torch.Tensor | None = None) -> torch.Tensor:
     """any4_gemm on codes re-arranged by any4_repack; N is taken from scale."""
+    r = _native(x, rcodes, lut, scale, offset, bits, out, workspace, GROUP, True)
+    if r is not None:
+        return r
     return _gemm("any4_gemm_repacked", x, rcodes, scale.shape[0], lut, scale, offset, bits, out, workspace)
 
 

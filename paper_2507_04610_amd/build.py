@@ -1,4 +1,4 @@
-"""Compile libany4.so (HIP, gfx950) in-tree with hipcc.  `python -m paper_2507_04610_amd.build`."""
+"""Compile libany4.so (HIP, gfx950) in-tree with hipcc, and with g++ the torch extension that calls it.  `python -m paper_2507_04610_amd.build`."""
 from __future__ import annotations
 
 import glob
@@ -10,6 +10,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libany4.so")
+TORCH_SRC = os.path.join(CSRC, "any4_torch.cpp")
+TORCH_EXT = os.path.join(PKG, "_any4_torch.so")
 BENCH_SRC = os.path.join(PKG, "bench_support", "stream_read.hip")
 BENCH_LIB = os.path.join(PKG, "bench_support", "libany4_bench.so")
 
@@ -20,6 +22,19 @@ HIPCC_FLAGS = [
     "-Wall", "-Wno-unused-function", "-Wno-unknown-attributes",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
+
+
+def torch_extension_command():
+    """host code only (no kernels): torch's headers and libraries, linked to libany4.so next to it"""
+    import sysconfig
+    from torch.utils import cpp_extension
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    includes = [os.path.join(ROOT, "include"), *cpp_extension.include_paths(), os.path.join(rocm, "include"),
+                sysconfig.get_paths()["include"]]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-w",
+            *[f"-I{d}" for d in includes], TORCH_SRC, "-o", TORCH_EXT,
+            *[f"-L{d}" for d in cpp_extension.library_paths()], "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
+            "-lc10_hip", f"-L{PKG}", "-lany4", "-Wl,-rpath,$ORIGIN"]
 
 
 def sources():
@@ -44,6 +59,10 @@ def build_library(verbose: bool = True) -> str:
         if p.wait() != 0:
             raise RuntimeError(f"hipcc failed on {src}")
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    cmd = torch_extension_command()
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
