@@ -22,7 +22,6 @@ static bool group_shift(int64_t K, int group, int* lr) {
 
 constexpr int kDecodeMaxM = 16;
 constexpr int kStreamMaxM = 16;
-constexpr int kChunkedMaxM = 128;      // above this the matrix-core kernel is always taken
 constexpr int kFineRows = 8;           // groups of 64 weights: rows of x per launch of the streaming kernel
 
 // Compute units of the current device (256 on MI355X); only shapes the work split, never results.
@@ -47,43 +46,17 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
             return p;
         }
     }
-    if (M > kStreamMaxM && M <= kChunkedMaxM && N <= ((int64_t)1 << 35)) {
-        // A few dozen rows of x fill a fraction of one 256-row tile of the matrix-core kernel, whose
-        // time does not depend on M below 256; streaming the weights once per 16 rows is faster while
-        //   launches * (6.5 us + bytes of codes / 3.8 TB/s)
-        // stays below the matrix-core kernel's time: per round of blocks 8 us + step * K / 64 with
-        // step = 0.95 us (few blocks in flight) .. 1.3 us (every compute unit busy), the last round
-        // divided by its number of K slices plus 3 + 2 * slices us for adding them up (all constants
-        // measured on the two kernels).
-        const int cus = device_compute_units();
-        const double launches = (double)((M + kStreamMaxM - 1) / kStreamMaxM);
-        const double t_stream = launches * (6.5 + (double)N * (double)K * bits / 8.0 / 3.8e6);
-        const PrefillPlan pp = plan_prefill(M, N, K, cus);
-        const double ksteps = (double)(K / 64);
-        const int64_t last = pp.tiles % cus;
-        double t_matrix = (double)(pp.tiles / cus) * (8.0 + 1.3 * ksteps);
-        if (last > 0) {
-            const double busy = (double)(last * pp.tail_s) / cus;
-            t_matrix += 8.0 + (0.95 + 0.35 * (busy < 1.0 ? busy : 1.0)) * ksteps / pp.tail_s +
-                        (pp.tail_s > 1 ? 3.0 + 2.0 * pp.tail_s : 0.0);
+    if (M > kStreamMaxM && M <= kBatchMaxM) {
+        // A few dozen rows of x fill a fraction of one 256-row tile of the matrix-core kernel, whose time does
+        // not depend on M below 256.
+        p.bp = plan_batch(M, N, K, false, device_compute_units());
+        p.bp_fine = plan_batch(M, N, K, true, device_compute_units());
+        if (p.bp.ok && p.bp_fine.ok) {
+            p.workspace = p.bp.workspace > p.bp_fine.workspace ? p.bp.workspace : p.bp_fine.workspace;
+            p.counter_bytes = p.bp.counter_bytes;
+            return p;
         }
-        if (t_stream < t_matrix) {
-            const int tail_rows = (int)(M % kStreamMaxM);
-            const StreamPlan full = plan_stream(kStreamMaxM, N, K, cus);
-            const StreamPlan tail = tail_rows ? plan_stream(tail_rows, N, K, cus) : full;
-            if (full.gw > 0 && tail.gw > 0) {
-                p.decode = p.stream = p.chunked = true;
-                p.sp = full;
-                p.sp_tail = tail;
-                p.ksplit = full.slabs;
-                p.workspace = full.workspace > tail.workspace ? full.workspace : tail.workspace;
-                p.counter_bytes = full.slabs > 1 || tail.slabs > 1 ? splitk_counter_bytes(full.tiles) : 0;
-                // (groups of 64 weights go to the matrix-core kernel for these M: room for either)
-                const size_t wm = prefill_workspace_bytes(M, N, K, cus);
-                if (wm > p.workspace) p.workspace = wm;
-                return p;
-            }
-        }
+        p.bp = p.bp_fine = BatchPlan{};
     }
     p.decode = M <= kDecodeMaxM;
     p.ksplit = 1;
@@ -140,7 +113,9 @@ int gemm_dispatch(const uint16_t* x, const uint32_t* codes, bool repacked, const
     const PackPlan pk = (M <= 4 && lut && lr == 0 && !f16) ? plan_pack(M, N, K, bits, one_table, device_compute_units()) : PackPlan{};
     if (pk.ok) {
         e = launch_decode_pack(x, codes, lut, scale, offset, M, N, K, bits, repacked, one_table, pk, y, s);
-    } else if (lr < 0 && plan.stream && !plan.chunked) {
+    } else if (plan.bp.ok) {
+        e = launch_batch(x, codes, lut, scale, offset, M, N, K, bits, lr, repacked, f16, one_table, lr < 0 ? plan.bp_fine : plan.bp, y, workspace, s);
+    } else if (lr < 0 && plan.stream) {
         // groups of 64 weights, M <= 16: the streaming kernel takes 8 rows of x a launch
         e = hipSuccess;
         for (int64_t m0 = 0; m0 < M && e == hipSuccess; m0 += kFineRows) {
@@ -150,14 +125,6 @@ int gemm_dispatch(const uint16_t* x, const uint32_t* codes, bool repacked, const
         }
     } else if (lr < 0) {
         e = launch_prefill(x, codes, lut, scale, offset, M, N, K, bits, lr, false, false, one_table, device_compute_units(), y, workspace, s);
-    } else if (plan.chunked) {
-        // launches run one after the other on the stream and leave the workspace's counters clean
-        e = hipSuccess;
-        for (int64_t m0 = 0; m0 < M && e == hipSuccess; m0 += kStreamMaxM) {
-            const int64_t rows = M - m0 < kStreamMaxM ? M - m0 : kStreamMaxM;
-            e = launch_decode_stream(x + m0 * K, codes, lut, scale, offset, rows, N, K, bits, lr, repacked, f16, one_table,
-                                     rows == kStreamMaxM ? plan.sp : plan.sp_tail, y + m0 * N, workspace, s);
-        }
     } else if (plan.stream) {
         e = launch_decode_stream(x, codes, lut, scale, offset, M, N, K, bits, lr, repacked, f16, one_table, plan.sp, y, workspace, s);
     } else if (plan.decode) {

@@ -49,14 +49,27 @@ hipError_t launch_decode_pack(const uint16_t* x, const uint32_t* codes, const ui
                               int64_t K, int bits, bool repacked, bool one_table, const PackPlan& pl, uint16_t* y,
                               hipStream_t stream);
 
+// Work split of the kernel for a few dozen rows of x (any4_batch.hip).
+constexpr int kBatchMaxM = 128;
+struct BatchPlan {
+    bool ok;              // the kernel takes this problem
+    int mt, rows;         // 32-row tiles of x per block, 32 * mt
+    int tiles_n, slabs;   // blocks along n, K slabs
+    size_t counter_bytes, workspace;      // arrival counters, and with them the fp32 partial sums (several slabs only)
+};
+BatchPlan plan_batch(int64_t M, int64_t N, int64_t K, bool fine, int cus);
+hipError_t launch_batch(const uint16_t* x, const uint32_t* codes, const uint16_t* lut, const uint16_t* scale,
+                        const uint16_t* offset, int64_t M, int64_t N, int64_t K, int bits, int lr, bool repacked, bool f16,
+                        bool one_table, const BatchPlan& pl, uint16_t* y, void* workspace, hipStream_t stream);
+
 // How any4_gemm runs a given problem; a pure function of (M, N, K, bits) so that
 // any4_gemm_workspace_bytes() and any4_gemm() always agree.
 struct GemmPlan {
     bool decode;          // true: memory-bound small-M kernel, false: matrix-core kernel
     bool stream;          // decode only: persistent streaming kernel; false: one wavefront per (row, K slice)
     StreamPlan sp;
-    bool chunked;         // M just above the small-M range: the streaming kernel, 16 rows of x per launch
-    StreamPlan sp_tail;   // chunked only: the plan of the last launch when M is not a multiple of 16
+    BatchPlan bp;         // M just above the small-M range
+    BatchPlan bp_fine;    // the same for groups of 64 weights (twice the scales to keep in LDS)
     int ksplit;           // number of K slices whose fp32 partials are reduced in a 2nd pass
     size_t workspace;     // bytes of scratch: K-slice partials (decode) or group sums of x (matrix-core path)
     size_t counter_offset, counter_bytes;   // where in the workspace the arrival counters sit (groups of 128)
