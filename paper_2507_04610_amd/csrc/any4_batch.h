@@ -17,13 +17,13 @@
 //
 // Work split.  A block takes 32 MT rows of x (all of them: MT = ceil(M / 32)), 32 WN rows of weights and a slab of
 // K; its 8 wavefronts are WN along n and WK = 8 / WN along k (alternate groups).  A step is one group per k part.
-// x of the coming steps is copied straight into a ring of LDS buffers and the codes into registers, three steps
-// ahead; a step waits for what step t + 2 needs, so the first operand of the next step can be prepared before the
-// barrier.  The parts meet in LDS, slabs of K in the workspace (fp32, added in slab order by the last to arrive).
+// x of the coming steps is copied straight into a ring of LDS buffers, three steps ahead, and the codes are loaded into
+// registers, four steps ahead; a step waits for what step t + 2 needs, so the first operand of the next step can be
+// prepared before the barrier.  The parts meet in LDS, slabs of K in the workspace (fp32, added in slab order by the last to arrive).
 //
 // What bounds it: vector instructions.  8 codes are 23 of them for 32 MT rows of x, a group of a wavefront ~250 next
 // to 8 MT matrix instructions; a step of M = 64 takes 1.4 us of issue at the clock the chip keeps under this
-// load and 2.0 us with its loads (28672 x 4096: 35 us; the four linears of an 8B layer at M = 64 / 32: 95 / 84 us,
+// load and 2.0 us with its loads (28672 x 4096: 36 us; the four linears of an 8B layer at M = 64 / 32: 99 / 82 us,
 // where streaming the weights once per 16 rows took 199 / 105).  The rest of a launch is fixed: 5 us until
 // the first steps have landed, 2 - 3 us for the end, 4 us more where slabs meet.
 #pragma once
@@ -58,7 +58,8 @@ constexpr int wn_of(int mt) { return mt <= 2 ? 4 : 8; }
 template <int MT, int WN> struct Shape {
     static constexpr int WK = kWaves / WN, ROWS = 32 * MT, BN = 32 * WN;
     static constexpr int XBUF = WK * ROWS * kRowBytes;            // x of one step: one group per k part
-    static constexpr int DEPTH = 3;                               // steps from a load's issue to its use
+    static constexpr int DEPTH = 3;                               // steps from the issue of x's loads to their use
+    static constexpr int CODE_DEPTH = MT == 4 ? 3 : 4;            // ... of the codes' (a fourth set does not fit next to four tiles)
     static constexpr int XS = (DEPTH + 1) * XBUF;                 // group sums of x: [2][WK][ROWS][8] packed hi, lo
     static constexpr int XS_SET = WK * ROWS * 32;
     static constexpr int SC = XS + 2 * XS_SET;                    // the slab's scales, then its offsets: [BN] rows of sc_stride bytes
@@ -93,26 +94,17 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // at most LEFT of this wavefront's vector memory operations are outstanding
 template <int LEFT> __device__ __forceinline__ void loads_left() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LEFT) : "memory"); }
 
-// The loads of the main loop are issued and waited for by hand: they go to registers and to LDS, return
-// in order, and the compiler, which cannot see the second kind, would count wrong.  A register loaded here
-// must not be touched before loads_left() and landed().
+// The copies to LDS are issued and waited for by hand: the compiler would wait for all of them in front of every LDS
+// read.  It does not see them, and loads return in order, so that its own waits (for codes) are for no less than
+// they need.
 // 64 lanes x 16 bytes straight from memory to LDS: lane l's piece goes to lds + 16 l
 __device__ __forceinline__ void copy_to_lds(uint32_t lds, const void* base, uint32_t voff) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
 }
-__device__ __forceinline__ void load_words(u32x4& d, const void* base, uint32_t voff) {
-    asm volatile("global_load_dwordx4 %0, %1, %2" : "=&v"(d) : "v"(voff), "s"(base) : "memory");
-}
-__device__ __forceinline__ void load_words(u32x3& d, const void* base, uint32_t voff) {
-    asm volatile("global_load_dwordx3 %0, %1, %2" : "=&v"(d) : "v"(voff), "s"(base) : "memory");
-}
-__device__ __forceinline__ void load_words(u32x2& d, const void* base, uint32_t voff) {
-    asm volatile("global_load_dwordx2 %0, %1, %2" : "=&v"(d) : "v"(voff), "s"(base) : "memory");
-}
 template <int BITS, int MT, int WN, bool F16, bool FINE>
 __device__ __forceinline__ void batch_body(const Params& p) {
     using S = Shape<MT, WN>;
-    constexpr int WK = S::WK, ROWS = S::ROWS, BN = S::BN, D = S::DEPTH;
+    constexpr int WK = S::WK, ROWS = S::ROWS, BN = S::BN, D = S::DEPTH, CD = S::CODE_DEPTH;
     auto mma = [](const u32x4& a, const u32x4& b, const f32x16& c) -> f32x16 {
         if constexpr (F16) return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
         else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
@@ -160,11 +152,17 @@ __device__ __forceinline__ void batch_body(const Params& p) {
     };
     using words = std::conditional_t<BITS == 4, u32x4, std::conditional_t<BITS == 3, u32x3, u32x2>>;
     struct Codes { words w[2]; };
-    auto fetch_codes = [&](Codes& c, int t) {
+    auto fetch_codes = [&](Codes& c, int t) {                     // (past the last step: a piece of the slab once more)
         const int g = min(group_of(t, wk), g_hi - 1);
-        load_words(c.w[0], cbase + (int64_t)g * cgroup, coff);
-        load_words(c.w[1], cbase + (int64_t)g * cgroup + chalf, coff);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            struct packed { uint32_t v[BITS]; };
+            const packed v = *reinterpret_cast<const packed*>(cbase + (int64_t)g * cgroup + i * chalf + coff);
+#pragma unroll
+            for (int j = 0; j < BITS; ++j) c.w[i][j] = v.v[j];
+        }
     };
+    // (the compiler's wait for these codes goes here: after the copies of x that follow it would be for some of them, too)
     auto landed = [&](Codes& c) { asm volatile("" : "+v"(c.w[0]), "+v"(c.w[1])); };
     constexpr int kLoads = 2 + S::DMA;                            // load instructions per wavefront and step
 
@@ -199,8 +197,7 @@ __device__ __forceinline__ void batch_body(const Params& p) {
         }
     };
 
-    // The prologue's loads are ordinary ones, so that the compiler may arrange the registers of this longer
-    // piece of code as it likes: the row's table and the codes of the first steps.
+    // the row's table and the codes of the first steps
     using table_words = std::conditional_t<BITS == 2, u32x2, u32x4>;
     table_words tw[BITS == 4 ? 2 : 1];
     if (p.lut) {
@@ -208,18 +205,9 @@ __device__ __forceinline__ void batch_body(const Params& p) {
         tw[0] = src[0];
         if constexpr (BITS == 4) tw[1] = src[1];
     }
-    Codes cq[D];
+    Codes cq[CD];
 #pragma unroll
-    for (int t = 0; t < D; ++t) {
-        const char* const src = cbase + (int64_t)min(group_of(min(t, T - 1), wk), g_hi - 1) * cgroup + coff;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            struct packed { uint32_t v[BITS]; };
-            const packed v = *reinterpret_cast<const packed*>(src + i * chalf);
-#pragma unroll
-            for (int j = 0; j < BITS; ++j) cq[t].w[i][j] = v.v[j];
-        }
-    }
+    for (int t = 0; t < CD; ++t) fetch_codes(cq[t], min(t, T - 1));
 #pragma unroll
     for (int t = 0; t < D; ++t)
         if (t < T) fetch_x(t);
@@ -285,8 +273,7 @@ __device__ __forceinline__ void batch_body(const Params& p) {
         b[kk & 1] = u32x4{d[0], d[1], d[2], d[3]};
     };
     auto xbase = [&](int t) -> uint32_t { return xrd + (uint32_t)(t % (D + 1)) * S::XBUF + (uint32_t)(wk * ROWS * kRowBytes); };
-    auto step = [&](Codes& c, Codes& next, int t) {
-        landed(next);
+    auto work = [&](const Codes& c, const Codes& next, int t) {
         if (t + D < T) fetch_x(t + D);
         if (t > 0 && t % kPer == 0) offset_term(t - kPer, (t - 1) / kPer & 1);
         const int slot = t % kPer, set = t / kPer & 1;
@@ -340,16 +327,20 @@ __device__ __forceinline__ void batch_body(const Params& p) {
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else prepare(next, xn, 0);
-        if (t + D < T) fetch_codes(c, t + D);
-        // what step t + 2 needs has landed; the loads of step t + 3 stay in flight
+    };
+    auto step = [&](Codes& c, Codes& next, int t) {
+        landed(next);
+        if (t < T) work(c, next, t);
+        fetch_codes(c, t + CD);
+        // x of step t + 2 has landed; this step's loads (x of step t + 3, codes of step t + CD) stay in flight
         if (t + D < T) loads_left<kLoads>();
-        else loads_left<0>();
+        else if (t + 2 < T) loads_left<2>();
         lds_barrier();
     };
     static_assert(D == 3, "the waits");
     loads_left<0>();
 #pragma unroll
-    for (int t = 0; t < D; ++t) landed(cq[t]);
+    for (int t = 0; t < CD; ++t) landed(cq[t]);
     {
         constexpr int L = 1 << BITS, W = BITS == 2 ? 2 : 4;       // entries; dwords per load
         uint32_t d[L / 2];
@@ -365,10 +356,11 @@ __device__ __forceinline__ void batch_body(const Params& p) {
     }
     lds_barrier();
     prepare(cq[0], xbase(0), 0);
-    for (int t = 0; t < T; t += D) {
+    // (whole turns: a step past the last does nothing.  With a way out in the middle of a turn, or loads left out, the
+    // compiler's wait at the top of the loop would be for all the codes in flight)
+    for (int t = 0; t < T; t += CD) {
 #pragma unroll
-        for (int u = 0; u < D; ++u)
-            if (t + u < T) step(cq[u], cq[(u + 1) % D], t + u);
+        for (int u = 0; u < CD; ++u) step(cq[u], cq[(u + 1) % CD], t + u);
     }
     offset_term((T - 1) / kPer * kPer, (T - 1) / kPer & 1);
 
