@@ -1,5 +1,5 @@
-// Compute-bound any-n GEMM for large M (prompt processing): LDS-staged table lookup feeding
-// bf16 matrix-core (MFMA) tiles with fp32 accumulation.
+// Compute-bound any-n GEMM for large M (prompt processing): table lookup in registers, looked-up tiles in LDS
+// feeding bf16 matrix-core (MFMA) tiles with fp32 accumulation.
 //
 // y[m][n] = sum_k x[m][k] * w[n][k],  w[n][k] = LUT[n][code] * scale[n][k/128] + offset[n][k/128]
 // (any4 paper, section 4.2: weights are dequantised on the fly before the matrix instruction;
@@ -25,8 +25,14 @@
 // the per-group scale fold - while the global loads of later steps are in flight.  Left to
 // itself the compiler emits "all MFMAs, then all staging", and the two wavefronts of a SIMD, which
 // the barrier keeps in step, then leave the matrix cores idle while both stage.
+//
+// What bounds a K step is LDS bandwidth next to the vector instructions issued meanwhile.  A staging thread
+// keeps to one weight row for the whole launch, so the row's table sits in its registers (any4_regtable.h): 46 vector
+// instructions for its 16 codes of a step where a table in LDS took 16 LDS reads and 40 (addresses and packs), and
+// nothing to fill before the first step.  The four linears of an 8B layer at M = 2048 / 512: 1139 / 358 -> 1101 / 350 us.
 #include "any4_device.h"
 #include "any4_internal.h"
+#include "any4_regtable.h"
 #include "any4_splitk.h"
 #include <type_traits>
 
@@ -37,13 +43,12 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) u32x4* lds_u4;
-typedef const __attribute__((address_space(3))) uint32_t* lds_u32;
 
 constexpr int PBM = 256, PBN = 128, PBK = 64;
 constexpr int PTHREADS = 512;
 constexpr int PLD = PBK + 8;          // LDS row stride in bf16 elements (144 B: keeps 16-byte reads spread over banks)
 constexpr uint32_t kXBuf = PBM * PLD * 2, kWBuf = PBN * PLD * 2;   // bytes of one activation / weight buffer
-constexpr uint32_t kTableOff = 2 * kXBuf + 2 * kWBuf;              // 110592 = 0x1B000: the low 12 bits are clear
+constexpr uint32_t kLdsBytes = 2 * kXBuf + 2 * kWBuf;
 
 __device__ __forceinline__ void lds_barrier() {                 // outstanding global loads stay in flight
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -83,17 +88,13 @@ __global__ __launch_bounds__(256) void group_sums_kernel(const uint16_t* __restr
         for (int c = (int)(2 * G) + sub; c < KP; c += lanes) xs[m * KP + c] = 0;
 }
 
-// LDS copy of the block's row tables, laid out so that the 32 lanes LDS serves together never share
-// a bank: a half-wavefront holds 8 rows x 4 quarter-threads, and entry c of (row, quarter) lives at
-// dword (row / 8) * (32 << BITS) + c * 32 + (row % 8) * 4 + quarter (every row is stored 4 times;
-// the bf16 value sits in the low half of the dword).
 // FINE: groups of 64 weights - every K step is a group of its own (scale index 2g, 2g + 1 for the two
 // steps of chunk g; the offset phase runs over 64-weight groups).  Otherwise groups of 128 << lr.
 // F16: activations, table, scales, offsets and output are fp16 instead of bf16.
 // NOLUT: 4-bit codes on the uniform grid (value = code - 8, the int4 format the paper compares with in
 // section 4.2, last paragraph) without any table: a code c becomes the bf16 number 128 + c by OR-ing it
-// into the mantissa of 128.0 (0x4300 | c) - two shifts and two and-or per pair of weights instead of
-// two address computations, two LDS lookups and a pack - and the surplus 136 * scale * X (X = the
+// into the mantissa of 128.0 (0x4300 | c) - two shifts and two and-or per pair of weights, 16 vector
+// instructions for eight codes where the table takes 23 - and the surplus 136 * scale * X (X = the
 // group sum of the activations) is taken off in the offset phase by two more passes over the same
 // group sums whose right operands are the exact bf16 numbers -128 * scale and -8 * scale.
 template <int BITS, bool FINE, bool F16, bool NOLUT = false>
@@ -113,7 +114,6 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
         else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
     };
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    uint32_t* table = reinterpret_cast<uint32_t*>(smem + kTableOff);      // [PBN / 8][L][32]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -160,7 +160,6 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
 #pragma unroll
     for (int j = 0; j < 2; ++j) scol[j] = scale + min(n0 + wn * 64 + j * 32 + (lane & 31), N - 1) * GS;
     // LDS byte addresses (the kernel has no static LDS: dynamic LDS starts at 0)
-    const uint32_t tbase = kTableOff + (uint32_t)((wrow >> 3) * (32 << BITS) + (wrow & 7) * 4 + wq) * 4u;
     const uint32_t xwr = (uint32_t)(xr_row * PLD + xc8 * 8) * 2u;                         // + buf * kXBuf + p * 64 rows
     const uint32_t wwr = 2 * kXBuf + (uint32_t)(wrow * PLD + wq * 16) * 2u;               // + buf * kWBuf + chunk * 16
     const uint32_t ard = (uint32_t)((wm * 64 + (lane & 31)) * PLD + (lane >> 5) * 8) * 2u;
@@ -187,20 +186,21 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
         q[0] = wsrc[wbase];
         q[1] = BITS == 2 ? 0u : wsrc[wbase + 1];
     };
-    // LDS address of the table entry of code j (0..15) of the fetched quarter
-    auto entry_addr = [&](uint32_t lo, uint32_t hi, int j) -> uint32_t {
-        constexpr uint32_t mask = (uint32_t)(L - 1) << 7;
-        const int bit = BITS * j;
-        uint32_t v;
-        if (bit + BITS <= 32) v = bit >= 7 ? lo >> (bit - 7) : lo << (7 - bit);
-        else if (bit >= 32) v = bit - 32 >= 7 ? hi >> (bit - 32 - 7) : hi << (7 - (bit - 32));
-        else v = __builtin_amdgcn_alignbit(hi, lo, bit) << 7;
-        return (v & mask) | tbase;
-    };
     // NOLUT: codes 2p, 2p + 1 of a word of eight as the bf16 pair (128 + c, 128 + c')
     auto grid_pair = [&](uint32_t w, int pi) -> uint32_t {
         const uint32_t t = w >> (8 * pi);
         return (t & 0xFu) | ((t << 12) & 0xF0000u) | 0x43004300u;
+    };
+    // values of codes 8 c + 4 h .. + 3 of the thread's 16 (lo, hi: their bits in order)
+    RowTable<BITS> table;
+    auto lookup = [&](uint32_t lo, uint32_t hi, int c, int h, uint32_t& d0, uint32_t& d1) {
+        if constexpr (NOLUT) {
+            d0 = grid_pair(c ? hi : lo, 2 * h);
+            d1 = grid_pair(c ? hi : lo, 2 * h + 1);
+        } else {
+            const uint32_t w[2] = {lo, hi};
+            table.half(w, c, h, d0, d1);
+        }
     };
     auto code_words = [&](const uint32_t (&q)[2], uint32_t& lo, uint32_t& hi) {
         lo = q[0]; hi = q[1];
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
         constexpr int BUF = decltype(buf_)::value;
         constexpr bool FIRST = decltype(first_)::value, FOLD = decltype(fold_)::value;
         op16x8 a[2][2], b[2][2];
-        uint32_t lk[2][8], wpk[4];
+        uint32_t wpk[4];
         uint32_t lo, hi;
         auto read_ops = [&](int set, int kk) {
 #pragma unroll
@@ -227,17 +227,8 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
                 b[set][i] = __builtin_bit_cast(op16x8, *reinterpret_cast<lds_u4>(brd + BUF * kWBuf + i * (32 * PLD * 2) + kk * 32));
             }
         };
-        auto w_issue = [&](int c, int h) {                      // four of the eight lookups of chunk c
-            if constexpr (NOLUT) return;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) lk[c][h * 4 + t] = *reinterpret_cast<lds_u32>(entry_addr(lo, hi, c * 8 + h * 4 + t));
-        };
-        auto w_finish = [&](int c, int h) {                     // pack half of chunk c; then the 16-byte write
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                if constexpr (NOLUT) wpk[h * 2 + t] = grid_pair(c ? hi : lo, h * 2 + t);
-                else wpk[h * 2 + t] = lk[c][h * 4 + 2 * t] | (lk[c][h * 4 + 2 * t + 1] << 16);
-            }
+        auto w_stage = [&](int c, int h) {                      // look up half of chunk c; then the 16-byte write
+            lookup(lo, hi, c, h, wpk[2 * h], wpk[2 * h + 1]);
             if (h == 1)
                 *reinterpret_cast<lds_u4>(wwr + (BUF ^ 1) * kWBuf + c * 16) = u32x4{wpk[0], wpk[1], wpk[2], wpk[3]};
         };
@@ -254,8 +245,6 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
 
         read_ops(0, 0);
         code_words(q, lo, hi);
-        w_issue(0, 0);
-        w_issue(0, 1);
         ANY4_SB();
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
@@ -267,11 +256,10 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
                 const int i = t >> 1, j = t & 1;
                 part[i][j] = mma(a[cur][i], b[cur][j], (FIRST && kk == 0) ? zero : part[i][j]);
                 if (kk == 0) {
-                    if (t < 2) w_finish(0, t);
-                    else w_issue(1, t - 2);
+                    if (t & 1) w_stage(0, t >> 1);
                 } else if (kk == 1) {
-                    if (t < 2) w_finish(1, t);
-                    else if (t == 2) fetch_q(q, tile_q);        // the set is free: its codes are in lo / hi and used up
+                    if (t & 1) w_stage(1, t >> 1);
+                    if (t == 3) fetch_q(q, tile_q);             // the set is free: its codes are in lo / hi and used up
                 } else if (kk == 2) {
                     x_write(t);
                     if (t == 3) fetch_x(tile_x);                // the registers are free again: a full K step of lead
@@ -312,28 +300,20 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
     fetch_x(S0);                                               // in flight while the tables are filled
     fetch_q(q0, S0);
     fetch_q(q1, S0 + 1);
-    // per-row tables of this block's weight rows (rows past N are clamped: they are never stored):
-    // one thread fetches 8 bytes (4 entries) of a row and writes each entry's 4 adjacent copies at once
+    // the table of the thread's weight row (rows past N are clamped: they are never stored)
     if constexpr (!NOLUT) {
-        constexpr int PIECES = L / 4;                            // 8-byte pieces per row
-        for (int i = tid; i < PBN * PIECES; i += PTHREADS) {
-            const int row = i / PIECES, pc = i % PIECES;
-            uint2 v;
-            if (lut) v = *reinterpret_cast<const uint2*>(lut + (one_table ? 0 : min(n0 + row, N - 1) * L) + pc * 4);
-            else {                                             // no table: the integer grid, entries pc * 4 .. + 3
-                const int c0 = pc * 4 - L / 2;
-                v.x = f32_to_h16<F16>((float)c0) | (f32_to_h16<F16>((float)(c0 + 1)) << 16);
-                v.y = f32_to_h16<F16>((float)(c0 + 2)) | (f32_to_h16<F16>((float)(c0 + 3)) << 16);
-            }
-            uint32_t* dst = table + (row >> 3) * (32 << BITS) + (pc * 4) * 32 + (row & 7) * 4;
-            const uint32_t e0 = v.x & 0xFFFFu, e1 = v.x >> 16, e2 = v.y & 0xFFFFu, e3 = v.y >> 16;
-            *reinterpret_cast<uint4*>(dst) = make_uint4(e0, e0, e0, e0);
-            *reinterpret_cast<uint4*>(dst + 32) = make_uint4(e1, e1, e1, e1);
-            *reinterpret_cast<uint4*>(dst + 64) = make_uint4(e2, e2, e2, e2);
-            *reinterpret_cast<uint4*>(dst + 96) = make_uint4(e3, e3, e3, e3);
+        uint32_t d[L / 2];
+        if (lut) {
+            const uint2* const src = reinterpret_cast<const uint2*>(lut + (one_table ? 0 : wn_glob * L));
+#pragma unroll
+            for (int i = 0; i < L / 4; ++i) { const uint2 v = src[i]; d[2 * i] = v.x; d[2 * i + 1] = v.y; }
+        } else {
+#pragma unroll
+            for (int i = 0; i < L / 2; ++i)                    // no table: the integer grid
+                d[i] = f32_to_h16<F16>((float)(2 * i - L / 2)) | (f32_to_h16<F16>((float)(2 * i + 1 - L / 2)) << 16);
         }
+        table.load(d);
     }
-    lds_barrier();                                             // tables are written
     // K step 0 goes to buffer 0 with nothing to overlap with
     {
 #pragma unroll
@@ -342,16 +322,10 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
         code_words(q0, lo, hi);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            if constexpr (NOLUT) {
-                const uint32_t wd = c ? hi : lo;
-                *reinterpret_cast<lds_u4>(wwr + c * 16) = u32x4{grid_pair(wd, 0), grid_pair(wd, 1), grid_pair(wd, 2), grid_pair(wd, 3)};
-            } else {
-                uint32_t v[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) v[t] = *reinterpret_cast<lds_u32>(entry_addr(lo, hi, c * 8 + t));
-                *reinterpret_cast<lds_u4>(wwr + c * 16) =
-                    u32x4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
-            }
+            uint32_t v[4];
+            lookup(lo, hi, c, 0, v[0], v[1]);
+            lookup(lo, hi, c, 1, v[2], v[3]);
+            *reinterpret_cast<lds_u4>(wwr + c * 16) = u32x4{v[0], v[1], v[2], v[3]};
         }
         fetch_q(q0, min(S0 + 2, T - 1));
         fetch_x(S0 + 1);
@@ -487,10 +461,6 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
         }
 }
 
-constexpr size_t prefill_lds_bytes(int bits) {
-    return (size_t)kTableOff + (size_t)PBN * (1 << bits) * 4 * 4;
-}
-
 // Work split: whole tiles, and K slices for the tiles of a last round that would leave more than
 // half of the compute units idle (also the only round of a small problem).
 PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cus) {
@@ -539,13 +509,13 @@ hipError_t launch_prefill(const uint16_t* x, const uint32_t* codes, const uint16
     hipError_t e = hipSuccess;
 #define ANY4_PREFILL_F(B, F, H, NL)                                                                                 \
     do {                                                                                                          \
-        e = ensure_lds<prefill_kernel<B, F, H, NL>>((int)prefill_lds_bytes(B));                                       \
+        e = ensure_lds<prefill_kernel<B, F, H, NL>>((int)kLdsBytes);                                       \
         if (e != hipSuccess) return e;                                                                            \
         if (f16) hipLaunchKernelGGL(group_sums_kernel<true>, dim3((unsigned)sblocks), dim3(256), 0, stream, x, M, K, KP, 0, xsums); \
         else hipLaunchKernelGGL(group_sums_kernel<false>, dim3((unsigned)sblocks), dim3(256), 0, stream, x, M, K, KP, fine ? 1 : 0, xsums); \
         e = hipGetLastError();                                                                                    \
         if (e != hipSuccess) return e;                                                                            \
-        hipLaunchKernelGGL((prefill_kernel<B, F, H, NL>), grid, block, prefill_lds_bytes(B), stream, x, codes, lut, scale, \
+        hipLaunchKernelGGL((prefill_kernel<B, F, H, NL>), grid, block, kLdsBytes, stream, x, codes, lut, scale, \
                            offset, xsums, KP, M, N, K, F ? 0 : lr, (repacked ? 1 : 0) | (one_table ? 2 : 0), gm, tail_first, tail_s, counters, partial, y); \
     } while (0)
 #define ANY4_PREFILL(B)                                                                                           \

@@ -58,11 +58,15 @@ template <> struct RowTable<4> {
         const uint32_t u = v ^ 0x08080808u;
         interleave(vperm(al[1], al[0], v) ^ vperm(bl[1], bl[0], u), vperm(ah[1], ah[0], v) ^ vperm(bh[1], bh[0], u), d0, d1);
     }
+    // codes 8 j + 4 s .. + 3 of the words w -> the four values in order
+    template <int W> __device__ __forceinline__ void half(const uint32_t (&w)[W], int j, int s, uint32_t& d0, uint32_t& d1) const {
+        const uint32_t e = w[j] & 0x0F0F0F0Fu, o = (w[j] >> 4) & 0x0F0F0F0Fu;     // codes 0 2 4 6 / 1 3 5 7
+        four(vperm(o, e, s ? kPairHi : kPairLo), d0, d1);
+    }
     // eight codes (a word) -> the eight values in order
     __device__ __forceinline__ void eight(const uint32_t (&w)[4], int j, uint32_t (&d)[4]) const {
-        const uint32_t e = w[j] & 0x0F0F0F0Fu, o = (w[j] >> 4) & 0x0F0F0F0Fu;     // codes 0 2 4 6 / 1 3 5 7
-        four(vperm(o, e, kPairLo), d[0], d[1]);
-        four(vperm(o, e, kPairHi), d[2], d[3]);
+        half(w, j, 0, d[0], d[1]);
+        half(w, j, 1, d[2], d[3]);
     }
 };
 
@@ -81,11 +85,15 @@ template <> struct RowTable<3> {
         const uint32_t v = (p | (p << 5)) & 0x07070707u;
         interleave(vperm(l[1], l[0], v), vperm(h[1], h[0], v), d0, d1);
     }
-    __device__ __forceinline__ void eight(const uint32_t (&w)[3], int j, uint32_t (&d)[4]) const {
+    // (W = 2: the first 16 codes)
+    template <int W> __device__ __forceinline__ void half(const uint32_t (&w)[W], int j, int s, uint32_t& d0, uint32_t& d1) const {
         const uint32_t f = j == 0 ? w[0] : j == 1 ? __builtin_amdgcn_alignbit(w[1], w[0], 24)
-                         : j == 2 ? __builtin_amdgcn_alignbit(w[2], w[1], 16) : w[2] >> 8;
-        four(f & 0xFFFu, d[0], d[1]);
-        four((f >> 12) & 0xFFFu, d[2], d[3]);
+                         : j == 2 ? __builtin_amdgcn_alignbit(w[W - 1], w[1], 16) : w[W - 1] >> 8;
+        four((s ? f >> 12 : f) & 0xFFFu, d0, d1);
+    }
+    __device__ __forceinline__ void eight(const uint32_t (&w)[3], int j, uint32_t (&d)[4]) const {
+        half(w, j, 0, d[0], d[1]);
+        half(w, j, 1, d[2], d[3]);
     }
 };
 
@@ -102,10 +110,13 @@ template <> struct RowTable<2> {
         const uint32_t v = (p | (p << 6)) & 0x03030303u;
         interleave(vperm(t, t, v), vperm(h, h, v), d0, d1);
     }
-    __device__ __forceinline__ void eight(const uint32_t (&w)[2], int j, uint32_t (&d)[4]) const {
+    template <int W> __device__ __forceinline__ void half(const uint32_t (&w)[W], int j, int s, uint32_t& d0, uint32_t& d1) const {
         const uint32_t f = j & 1 ? w[j >> 1] >> 16 : w[j >> 1];
-        four(f & 0xFFu, d[0], d[1]);
-        four((f >> 8) & 0xFFu, d[2], d[3]);
+        four((s ? f >> 8 : f) & 0xFFu, d0, d1);
+    }
+    __device__ __forceinline__ void eight(const uint32_t (&w)[2], int j, uint32_t (&d)[4]) const {
+        half(w, j, 0, d[0], d[1]);
+        half(w, j, 1, d[2], d[3]);
     }
 };
 
