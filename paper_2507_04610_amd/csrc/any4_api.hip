@@ -51,9 +51,15 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
         // not depend on M below 256.
         p.bp = plan_batch(M, N, K, false, device_compute_units());
         p.bp_fine = plan_batch(M, N, K, true, device_compute_units());
-        if (p.bp.ok && p.bp_fine.ok) {
+        if (p.bp.ok || p.bp_fine.ok) {
             p.workspace = p.bp.workspace > p.bp_fine.workspace ? p.bp.workspace : p.bp_fine.workspace;
-            p.counter_bytes = p.bp.counter_bytes;
+            if (!p.bp.ok || !p.bp_fine.ok) {                   // the other kind of groups goes to the matrix-core kernel
+                const size_t wm = prefill_workspace_bytes(M, N, K, device_compute_units());
+                if (wm > p.workspace) p.workspace = wm;
+                const PrefillPlan pp = plan_prefill(M, N, K, device_compute_units());
+                if (!p.bp.ok) { p.counter_offset = pp.xsums_bytes; p.counter_bytes = pp.counter_bytes; }
+            }
+            if (p.bp.ok) p.counter_bytes = p.bp.counter_bytes;
             return p;
         }
         p.bp = p.bp_fine = BatchPlan{};
@@ -113,7 +119,7 @@ int gemm_dispatch(const uint16_t* x, const uint32_t* codes, bool repacked, const
     const PackPlan pk = (M <= 4 && lut && lr == 0 && !f16) ? plan_pack(M, N, K, bits, one_table, device_compute_units()) : PackPlan{};
     if (pk.ok) {
         e = launch_decode_pack(x, codes, lut, scale, offset, M, N, K, bits, repacked, one_table, pk, y, s);
-    } else if (plan.bp.ok) {
+    } else if (lr < 0 ? plan.bp_fine.ok : plan.bp.ok) {
         e = launch_batch(x, codes, lut, scale, offset, M, N, K, bits, lr, repacked, f16, one_table, lr < 0 ? plan.bp_fine : plan.bp, y, workspace, s);
     } else if (lr < 0 && plan.stream) {
         // groups of 64 weights, M <= 16: the streaming kernel takes 8 rows of x a launch

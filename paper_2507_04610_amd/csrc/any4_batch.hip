@@ -1,4 +1,5 @@
 // Host side of the kernel for a few dozen rows of x (any4_batch.h): its work split and the launch.
+#include "any4.h"
 #include "any4_batch.h"
 
 namespace any4 {
@@ -43,6 +44,17 @@ BatchPlan plan_batch(int64_t M, int64_t N, int64_t K, bool fine, int cus) {
     if (pl.slabs > 1) {
         pl.counter_bytes = splitk_counter_bytes(tiles);
         pl.workspace = pl.counter_bytes + (size_t)tiles * pl.slabs * pl.rows * bn * sizeof(float);
+    }
+    // The sums of slabs stay within what any4_gemm_noalloc has, so that it takes what the kernels before this one
+    // took.  Beyond (100000 rows of weights and more, at up to 64 rows of x) blocks of 32 rows of x go without slabs;
+    // the weights are then read twice, still less than the matrix-core kernel's four-fold padding of x costs.
+    if (pl.workspace > (size_t)ANY4_NOALLOC_SCRATCH_BYTES) {
+        const int v1 = max_slab_values<1>();
+        if (M > 64 || G > (fine ? v1 / 2 : v1)) return BatchPlan{};
+        pl.mt = 1;
+        pl.rows = 32;
+        pl.slabs = 1;
+        pl.counter_bytes = pl.workspace = 0;
     }
     return pl;
 }

@@ -57,3 +57,27 @@ def test_tile_edges(oracle, bits, variant):
         tol = 1e-2 * oracle.rms(y64) + np.abs(y64) * (2.0 ** -11 if f16 else 2.0 ** -8)
         assert np.all(np.abs(got - y64) <= tol), (M, N, K, float((np.abs(got - y64) - tol).max()))
         assert torch.equal(y.view(torch.int16), run().view(torch.int16))     # the workspace is left clean
+
+
+@pytest.mark.parametrize("M,group", ((33, 128), (64, 128), (50, 64)))
+def test_many_rows_of_weights_without_slabs(oracle, M, group):
+    """so many rows of weights that sums of K slabs would not fit the library's scratch: blocks of 32 rows of x, no
+    slabs, no workspace.  300 rows of weights over and over, so that the oracle has only those to do."""
+    import paper_2507_04610_amd as any4
+    lib = any4.load_library()
+    rows, times, K, bits = 300, 330, 128 * 47, 4
+    N = rows * times
+    assert lib.any4_gemm_workspace_bytes(M, N, K, bits) == 0
+    cs = inputs.make_case(M, rows, K, bits, seed=M)
+    sc, of = cs.scale, cs.offset
+    if group == 64:
+        sc, of = (np.ascontiguousarray(np.repeat(a, 2, axis=1)) for a in (sc, of))
+    packed = oracle.pack(cs.codes_u8, bits)
+    y64 = oracle.gemm(cs.x, packed, cs.lut, sc, of, K, bits, threads=8, group=group)
+    many = lambda t: t.repeat(times, 1)
+    y = any4.any4_gemm(dev16(cs.x, False), many(torch.from_numpy(packed.view(np.int32)).cuda()), many(dev16(cs.lut, False)),
+                       many(dev16(sc, False)), many(dev16(of, False)), bits, group=group)
+    y = y.view(M, times, rows)
+    assert torch.equal(y.view(torch.int16), y[:, :1].expand(-1, times, -1).contiguous().view(torch.int16))
+    got = y[:, 0].float().cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(got - y64) <= 1e-2 * oracle.rms(y64) + np.abs(y64) * 2.0 ** -8)
