@@ -77,7 +77,8 @@ def test_many_rows_of_weights_without_slabs(oracle, M, group):
     many = lambda t: t.repeat(times, 1)
     y = any4.any4_gemm(dev16(cs.x, False), many(torch.from_numpy(packed.view(np.int32)).cuda()), many(dev16(cs.lut, False)),
                        many(dev16(sc, False)), many(dev16(of, False)), bits, group=group)
-    y = y.view(M, times, rows)
-    assert torch.equal(y.view(torch.int16), y[:, :1].expand(-1, times, -1).contiguous().view(torch.int16))
-    got = y[:, 0].float().cpu().numpy().astype(np.float64)
-    assert np.all(np.abs(got - y64) <= 1e-2 * oracle.rms(y64) + np.abs(y64) * 2.0 ** -8)
+    # (every copy against the oracle, not against each other: a block's first step along K, and so the order of its
+    # sums, depends on its place among the blocks)
+    want = torch.from_numpy(y64).cuda()[:, None, :]
+    tol = 1e-2 * oracle.rms(y64) + want.abs() * 2.0 ** -8
+    assert bool(((y.view(M, times, rows).double() - want).abs() <= tol).all())
