@@ -99,7 +99,7 @@ template <int LEFT> __device__ __forceinline__ void loads_left() { asm volatile(
 // they need.
 // 64 lanes x 16 bytes straight from memory to LDS: lane l's piece goes to lds + 16 l
 __device__ __forceinline__ void copy_to_lds(uint32_t lds, const void* base, uint32_t voff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "m0", "memory");
 }
 template <int BITS, int MT, int WN, bool F16, bool FINE>
 __device__ __forceinline__ void batch_body(const Params& p) {
