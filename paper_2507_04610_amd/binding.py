@@ -125,6 +125,16 @@ def _check_quant_shapes(codes, lut, scale, offset, N, K, bits, group, repacked=F
     _shape(offset, (N, K // group), "offset")
 
 
+def _scratch(t, device) -> tuple[int, int]:
+    """address and bytes of a caller's workspace, which the kernels write: memory of x's device, as much of it as the
+    tensor has elements (an expanded tensor has fewer, a strided one has another's elements in between)"""
+    if not isinstance(t, torch.Tensor) or t.device != device:
+        raise Any4Error(f"workspace must be a tensor on x's device, {device}")
+    if t.numel() > 0 and sum((n - 1) * s for n, s in zip(t.shape, t.stride())) + 1 != t.numel():
+        raise Any4Error("workspace must be one piece of memory (contiguous)")
+    return t.data_ptr(), t.numel() * t.element_size()
+
+
 def _stream() -> int:
     return torch.cuda.current_stream().cuda_stream
 
@@ -222,8 +232,7 @@ def _gemm(entry: str, x, codes, N, lut, scale, offset, bits, out, workspace, gro
     need = int(lib.any4_gemm_workspace_bytes(M, N, K, bits))
     if workspace is None and need > 0:
         workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-    pw = workspace.data_ptr() if workspace is not None else None
-    wbytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    pw, wbytes = _scratch(workspace, x.device) if workspace is not None else (None, 0)
     if group is None:
         _check(getattr(lib, entry)(px, pc, pl, ps, po, M, N, K, bits, py, pw, wbytes, _stream()), entry)
     else:

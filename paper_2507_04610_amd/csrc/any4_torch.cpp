@@ -57,6 +57,8 @@ PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if ((f16 || one_table || repacked) && group != ANY4_GROUP) Py_RETURN_NONE;
     if ((f16 && (one_table || repacked)) || (one_table && repacked)) Py_RETURN_NONE;
     if (out && !(plain(*out, ty) && shaped(*out, M, N))) Py_RETURN_NONE;
+    // (of any type, but as much memory as it has elements, and on the device)
+    if (ws && !(ws->layout() == at::kStrided && ws->device() == x->device() && ws->is_non_overlapping_and_dense())) Py_RETURN_NONE;
 
     at::Tensor y = out ? *out : at::empty({M, N}, x->options().requires_grad(false));
     at::Tensor scratch;
