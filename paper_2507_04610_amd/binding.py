@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -26,7 +27,7 @@ class Any4Error(RuntimeError):
 
 
 _lib = None
-_native_gemm = None          # _any4_torch.gemm once the library is loaded
+_native_gemm = None          # the native call (_any4_torch.gemm) once the library is loaded
 
 
 def load_library() -> ctypes.CDLL:
@@ -38,10 +39,6 @@ def load_library() -> ctypes.CDLL:
     if not os.path.exists(LIB_PATH):
         raise Any4Error(f"{LIB_PATH} is missing: run `python -m paper_2507_04610_amd.build` first")
     lib = ctypes.CDLL(LIB_PATH)
-    try:
-        from . import _any4_torch
-    except ImportError as e:
-        raise Any4Error(f"the torch extension beside {LIB_PATH} does not load ({e}): run `python -m paper_2507_04610_amd.build`")
     i64, vp, ci = ctypes.c_int64, ctypes.c_void_p, ctypes.c_int
     lib.any4_pack.restype = ci
     lib.any4_pack.argtypes = [vp, i64, i64, ci, vp, vp]
@@ -81,9 +78,23 @@ def load_library() -> ctypes.CDLL:
     lib.any4_strerror.argtypes = [ci]
     lib.any4_version.restype = ci
     lib.any4_version.argtypes = []
-    _native_gemm = _any4_torch.gemm
-    _lib = lib
+    problem = None
+    try:
+        from ._any4_torch import gemm
+    except ImportError as e:
+        # built for another torch, or not built: the checked calls run the same kernels, only the call costs more
+        gemm, problem = _no_native_gemm, str(e)
+    _native_gemm = gemm
+    _lib = lib                   # last: another thread that sees it finds the call as well
+    if problem:
+        warnings.warn(f"the torch extension beside {LIB_PATH} does not load ({problem}): GEMM calls go through ctypes; "
+                      "`python -m paper_2507_04610_amd.build` builds it", RuntimeWarning, stacklevel=2)
     return lib
+
+
+def _no_native_gemm(*args):
+    """in the place of the native call where its extension does not load: never a plain valid call"""
+    return None
 
 
 def _check(rc: int, what: str) -> None:
