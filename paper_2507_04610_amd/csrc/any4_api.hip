@@ -36,8 +36,9 @@ int device_compute_units() {
 
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
     GemmPlan p{};
+    const int cus = p.cus = device_compute_units();
     if (M <= kStreamMaxM && N <= ((int64_t)1 << 35)) {
-        p.sp = plan_stream(M, N, K, device_compute_units());
+        p.sp = plan_stream(M, N, K, cus);
         if (p.sp.gw > 0) {
             p.decode = p.stream = true;
             p.ksplit = p.sp.slabs;
@@ -49,14 +50,14 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
     if (M > kStreamMaxM && M <= kBatchMaxM) {
         // A few dozen rows of x fill a fraction of one 256-row tile of the matrix-core kernel, whose time does
         // not depend on M below 256.
-        p.bp = plan_batch(M, N, K, false, device_compute_units());
-        p.bp_fine = plan_batch(M, N, K, true, device_compute_units());
+        p.bp = plan_batch(M, N, K, false, cus);
+        p.bp_fine = plan_batch(M, N, K, true, cus);
         if (p.bp.ok || p.bp_fine.ok) {
             p.workspace = p.bp.workspace > p.bp_fine.workspace ? p.bp.workspace : p.bp_fine.workspace;
             if (!p.bp.ok || !p.bp_fine.ok) {                   // the other kind of groups goes to the matrix-core kernel
-                const size_t wm = prefill_workspace_bytes(M, N, K, device_compute_units());
+                const size_t wm = prefill_workspace_bytes(M, N, K, cus);
                 if (wm > p.workspace) p.workspace = wm;
-                const PrefillPlan pp = plan_prefill(M, N, K, device_compute_units());
+                const PrefillPlan pp = plan_prefill(M, N, K, cus);
                 if (!p.bp.ok) { p.counter_offset = pp.xsums_bytes; p.counter_bytes = pp.counter_bytes; }
             }
             if (p.bp.ok) p.counter_bytes = p.bp.counter_bytes;
@@ -79,7 +80,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
     }
     if (p.decode) p.workspace = p.ksplit > 1 ? (size_t)p.ksplit * (size_t)M * (size_t)N * sizeof(float) : 0;
     else {
-        const PrefillPlan pp = plan_prefill(M, N, K, device_compute_units());
+        const PrefillPlan pp = plan_prefill(M, N, K, cus);
         p.workspace = pp.xsums_bytes + pp.counter_bytes + pp.partial_bytes;
         p.counter_offset = pp.xsums_bytes;
         p.counter_bytes = pp.counter_bytes;
@@ -116,7 +117,7 @@ int gemm_dispatch(const uint16_t* x, const uint32_t* codes, bool repacked, const
     hipError_t e;
     // one to four rows of x, a table, groups of 128, bf16: the packed-activation kernel (whole K in one
     // block, no workspace) where it takes the shape
-    const PackPlan pk = (M <= 4 && lut && lr == 0 && !f16) ? plan_pack(M, N, K, bits, one_table, device_compute_units()) : PackPlan{};
+    const PackPlan pk = (M <= 4 && lut && lr == 0 && !f16) ? plan_pack(M, N, K, bits, one_table, plan.cus) : PackPlan{};
     if (pk.ok) {
         e = launch_decode_pack(x, codes, lut, scale, offset, M, N, K, bits, repacked, one_table, pk, y, s);
     } else if (lr < 0 ? plan.bp_fine.ok : plan.bp.ok) {
@@ -130,13 +131,13 @@ int gemm_dispatch(const uint16_t* x, const uint32_t* codes, bool repacked, const
                                      y + m0 * N, workspace, s);
         }
     } else if (lr < 0) {
-        e = launch_prefill(x, codes, lut, scale, offset, M, N, K, bits, lr, false, false, one_table, device_compute_units(), y, workspace, s);
+        e = launch_prefill(x, codes, lut, scale, offset, M, N, K, bits, lr, false, false, one_table, plan.cus, y, workspace, s);
     } else if (plan.stream) {
         e = launch_decode_stream(x, codes, lut, scale, offset, M, N, K, bits, lr, repacked, f16, one_table, plan.sp, y, workspace, s);
     } else if (plan.decode) {
         e = launch_decode(x, codes, lut, scale, offset, M, N, K, bits, plan, one_table, y, static_cast<float*>(workspace), s);
     } else {
-        e = launch_prefill(x, codes, lut, scale, offset, M, N, K, bits, lr, repacked, f16, one_table, device_compute_units(), y, workspace, s);
+        e = launch_prefill(x, codes, lut, scale, offset, M, N, K, bits, lr, repacked, f16, one_table, plan.cus, y, workspace, s);
     }
     return e == hipSuccess ? ANY4_OK : ANY4_ERR_HIP;
 }

@@ -67,6 +67,8 @@ template <int MT, int WN> struct Shape {
     // bytes from a row of staged scales to the next: an odd number of 4-byte words, so that 32 rows lie in 32 banks
     static constexpr int sc_stride(int values) { return ((values + 1) / 2 | 1) * 4; }
     static constexpr int DMA = XBUF / (kWaves * 1024);            // 1 KB pieces of x per wavefront and step
+    // the most values a slab may have per row of weights (a row of staged values is an odd number of words)
+    static constexpr int MAX_VALUES = 2 * (((kLdsPerCu - SC) / (8 * BN) - 1) | 1);
     static_assert(XBUF % (kWaves * 1024) == 0, "every wavefront moves whole pieces");
     static_assert(MT * WK <= kWaves, "at most one group sum task per wavefront and step");
     static_assert(MT * WK * WN * 4096 * (WK > 1) <= XS, "the combination of the k parts fits the x buffers");

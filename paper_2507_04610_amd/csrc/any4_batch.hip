@@ -4,12 +4,14 @@
 
 namespace any4 {
 
-template <int MT> static int max_slab_values() {
+// values of scales (and of offsets) per row of weights that a slab may have: what LDS holds
+template <int MT> constexpr int max_slab_values() {
     using S = batch::Shape<MT, batch::wn_of(MT)>;
-    int v = 0;
-    while (S::lds_bytes(S::sc_stride(v + 1)) <= batch::kLdsPerCu) ++v;
-    return v;
+    static_assert(S::lds_bytes(S::sc_stride(S::MAX_VALUES)) <= batch::kLdsPerCu);
+    static_assert(S::lds_bytes(S::sc_stride(S::MAX_VALUES + 1)) > batch::kLdsPerCu);
+    return S::MAX_VALUES;
 }
+constexpr int kMaxSlabValues[4] = {max_slab_values<1>(), max_slab_values<2>(), max_slab_values<3>(), max_slab_values<4>()};
 
 // Work split; a pure function of its arguments.  A block takes 32 mt rows of x, 32 * wn rows of weights and one
 // of `slabs` parts of K.
@@ -20,7 +22,7 @@ BatchPlan plan_batch(int64_t M, int64_t N, int64_t K, bool fine, int cus) {
     pl.rows = 32 * pl.mt;
     const int wn = batch::wn_of(pl.mt), wk = batch::kWaves / wn, bn = 32 * wn;
     const int64_t G = K / kGroup, tiles = (N + bn - 1) / bn;
-    const int values = pl.mt == 1 ? max_slab_values<1>() : pl.mt == 2 ? max_slab_values<2>() : pl.mt == 3 ? max_slab_values<3>() : max_slab_values<4>();
+    const int values = kMaxSlabValues[pl.mt - 1];
     const int64_t most = fine ? values / 2 : values;              // groups whose scales and offsets LDS holds
     // 32-bit offsets inside a block's rows
     if (K * bn >= ((int64_t)1 << 31) || K * 2 * pl.rows >= ((int64_t)1 << 31) || tiles > ((int64_t)1 << 24)) return pl;
@@ -30,7 +32,8 @@ BatchPlan plan_batch(int64_t M, int64_t N, int64_t K, bool fine, int cus) {
     const double step[4] = {1.25, 1.65, 2.1, 2.6};
     const double per_slab = 0.9 * pl.mt * wn / 8.0;
     double best = 0;
-    for (int64_t s = (G + most - 1) / most; s <= 64 && s <= (G + wk - 1) / wk; ++s) {
+    // (no slab count from here on can be better once its sums alone take too long)
+    for (int64_t s = (G + most - 1) / most; s <= 64 && s <= (G + wk - 1) / wk && !(pl.ok && per_slab * (double)s > best); ++s) {
         const int64_t steps = ((G + s - 1) / s + wk - 1) / wk, rounds = (tiles * s + cus - 1) / cus;
         const double t = (double)rounds * (7.5 + step[pl.mt - 1] * (double)steps) + (s > 1 ? per_slab * (double)s : 0.0);
         if (!pl.ok || t < best) {
@@ -49,7 +52,7 @@ BatchPlan plan_batch(int64_t M, int64_t N, int64_t K, bool fine, int cus) {
     // took.  Beyond (100000 rows of weights and more, at up to 64 rows of x) blocks of 32 rows of x go without slabs;
     // the weights are then read twice, still less than the matrix-core kernel's four-fold padding of x costs.
     if (pl.workspace > (size_t)ANY4_NOALLOC_SCRATCH_BYTES) {
-        const int v1 = max_slab_values<1>();
+        const int v1 = kMaxSlabValues[0];
         if (M > 64 || G > (fine ? v1 / 2 : v1)) return BatchPlan{};
         pl.mt = 1;
         pl.rows = 32;

@@ -65,6 +65,7 @@ hipError_t launch_batch(const uint16_t* x, const uint32_t* codes, const uint16_t
 // How any4_gemm runs a given problem; a pure function of (M, N, K, bits) so that
 // any4_gemm_workspace_bytes() and any4_gemm() always agree.
 struct GemmPlan {
+    int cus;              // compute units it was made for
     bool decode;          // true: memory-bound small-M kernel, false: matrix-core kernel
     bool stream;          // decode only: persistent streaming kernel; false: one wavefront per (row, K slice)
     StreamPlan sp;
