@@ -23,6 +23,7 @@ static bool group_shift(int64_t K, int group, int* lr) {
 constexpr int kDecodeMaxM = 16;
 constexpr int kStreamMaxM = 16;
 constexpr int kFineRows = 8;           // groups of 64 weights: rows of x per launch of the streaming kernel
+constexpr int kTwoLaunchMaxM = 24;     // rows of x that two launches of the streaming kernel are considered for
 
 // Compute units of the current device (256 on MI355X); only shapes the work split, never results.
 // Asked of the runtime on every call (the current device may differ from call to call).
@@ -32,6 +33,20 @@ int device_compute_units() {
         hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
         n = 256;
     return n;
+}
+
+// Time in us of the matrix-core kernel at M <= 256 and of the group sums in front of it: per round of blocks 8 us and
+// K / 64 steps of 0.95 us (few blocks in flight) .. 1.3 us (every compute unit busy), the last round divided by its
+// number of K slices, plus 3 + 2 * slices us for adding them up (constants measured, 10 % rms).
+static double prefill_us(const PrefillPlan& pp, int64_t K, int cus) {
+    const double steps = (double)(K / 64);
+    const int64_t last = pp.tiles % cus;
+    double t = 2.0 + (double)(pp.tiles / cus) * (8.0 + 1.3 * steps);
+    if (last > 0) {
+        const double busy = (double)(last * pp.tail_s) / cus;
+        t += 8.0 + (0.95 + 0.35 * (busy < 1.0 ? busy : 1.0)) * steps / pp.tail_s + (pp.tail_s > 1 ? 3.0 + 2.0 * pp.tail_s : 0.0);
+    }
+    return t;
 }
 
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
@@ -52,15 +67,28 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
         // not depend on M below 256.
         p.bp = plan_batch(M, N, K, false, cus);
         p.bp_fine = plan_batch(M, N, K, true, cus);
+        const PrefillPlan pp = plan_prefill(M, N, K, cus);
+        const double matrix = prefill_us(pp, K, cus) / 0.85;      // (only where that is clear: neither estimate is better than 10 %)
+        if (p.bp.us > matrix) p.bp = BatchPlan{};
+        if (p.bp_fine.us > matrix) p.bp_fine = BatchPlan{};
         if (p.bp.ok || p.bp_fine.ok) {
             p.workspace = p.bp.workspace > p.bp_fine.workspace ? p.bp.workspace : p.bp_fine.workspace;
             if (!p.bp.ok || !p.bp_fine.ok) {                   // the other kind of groups goes to the matrix-core kernel
-                const size_t wm = prefill_workspace_bytes(M, N, K, cus);
+                const size_t wm = pp.xsums_bytes + pp.counter_bytes + pp.partial_bytes;
                 if (wm > p.workspace) p.workspace = wm;
-                const PrefillPlan pp = plan_prefill(M, N, K, cus);
                 if (!p.bp.ok) { p.counter_offset = pp.xsums_bytes; p.counter_bytes = pp.counter_bytes; }
             }
             if (p.bp.ok) p.counter_bytes = p.bp.counter_bytes;
+            if (p.bp.ok && M <= kTwoLaunchMaxM) {
+                // Where the streaming kernel has one tile per block and the whole of K in it (4096 x 4096 and below), two
+                // launches of it, 16 rows of x and at most 8, can beat one that adds up slabs: 4096 x 4096 at M = 17 / 24
+                // 13.0 / 13.8 us, the other 14.6 / 14.7.  A launch: a fixed part, the larger of the time of a tile and
+                // that of the codes, a share per row of x (constants measured, 10 % rms).
+                p.sp = plan_stream(kStreamMaxM, N, K, cus);
+                const double tile = 0.68 + 0.025 * p.sp.slab_groups, codes = (double)N * (double)K * bits / 8 / 4.74e6;
+                if (p.sp.gw > 0 && p.sp.slabs == 1 && p.sp.tiles <= p.sp.blocks_per_slab)
+                    p.two_launches = 2 * (3.6 + (tile > codes ? tile : codes)) + 0.15 * (double)M;
+            }
             return p;
         }
         p.bp = p.bp_fine = BatchPlan{};
@@ -120,6 +148,13 @@ int gemm_dispatch(const uint16_t* x, const uint32_t* codes, bool repacked, const
     const PackPlan pk = (M <= 4 && lut && lr == 0 && !f16) ? plan_pack(M, N, K, bits, one_table, plan.cus) : PackPlan{};
     if (pk.ok) {
         e = launch_decode_pack(x, codes, lut, scale, offset, M, N, K, bits, repacked, one_table, pk, y, s);
+    } else if (plan.two_launches > 0 && lut && lr >= 0 && plan.two_launches + (f16 ? 1.4 : 0.0) < 0.97 * plan.bp.us) {
+        // (fp16 takes it 0.7 us more per launch.  Not without a table: the streaming kernel takes the integer grid as 128 + code and off again, whose rounding
+        // the kernel for more rows does not have)
+        e = launch_decode_stream(x, codes, lut, scale, offset, kStreamMaxM, N, K, bits, lr, repacked, f16, one_table, plan.sp, y, workspace, s);
+        if (e == hipSuccess)
+            e = launch_decode_stream(x + kStreamMaxM * K, codes, lut, scale, offset, M - kStreamMaxM, N, K, bits, lr, repacked, f16, one_table,
+                                     plan.sp, y + kStreamMaxM * N, workspace, s);
     } else if (lr < 0 ? plan.bp_fine.ok : plan.bp.ok) {
         e = launch_batch(x, codes, lut, scale, offset, M, N, K, bits, lr, repacked, f16, one_table, lr < 0 ? plan.bp_fine : plan.bp, y, workspace, s);
     } else if (lr < 0 && plan.stream) {

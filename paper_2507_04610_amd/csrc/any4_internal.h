@@ -56,6 +56,7 @@ struct BatchPlan {
     int mt, rows;         // 32-row tiles of x per block, 32 * mt
     int tiles_n, slabs;   // blocks along n, K slabs
     size_t counter_bytes, workspace;      // arrival counters, and with them the fp32 partial sums (several slabs only)
+    double us;            // the time it is expected to take
 };
 BatchPlan plan_batch(int64_t M, int64_t N, int64_t K, bool fine, int cus);
 hipError_t launch_batch(const uint16_t* x, const uint32_t* codes, const uint16_t* lut, const uint16_t* scale,
@@ -70,6 +71,7 @@ struct GemmPlan {
     bool stream;          // decode only: persistent streaming kernel; false: one wavefront per (row, K slice)
     StreamPlan sp;
     BatchPlan bp;         // M just above the small-M range
+    double two_launches;  // expected time of two launches of the streaming kernel instead; 0: not considered
     BatchPlan bp_fine;    // the same for groups of 64 weights (twice the scales to keep in LDS)
     int ksplit;           // number of K slices whose fp32 partials are reduced in a 2nd pass
     size_t workspace;     // bytes of scratch: K-slice partials (decode) or group sums of x (matrix-core path)
@@ -113,7 +115,6 @@ struct PrefillPlan {
     size_t xsums_bytes, counter_bytes, partial_bytes;
 };
 PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cus);
-size_t prefill_workspace_bytes(int64_t M, int64_t N, int64_t K, int cus);
 
 // Quantiser: one block per row, the row lives in LDS, which bounds K.  centre_gap < 0: every row by the
 // per-weight method; otherwise rows of K <= 16384 are sorted once and a row falls back to the per-weight

@@ -484,11 +484,6 @@ PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cus) {
     return p;
 }
 
-size_t prefill_workspace_bytes(int64_t M, int64_t N, int64_t K, int cus) {
-    const PrefillPlan p = plan_prefill(M, N, K, cus);
-    return p.xsums_bytes + p.counter_bytes + p.partial_bytes;
-}
-
 hipError_t launch_prefill(const uint16_t* x, const uint32_t* codes, const uint16_t* lut,
                           const uint16_t* scale, const uint16_t* offset,
                           int64_t M, int64_t N, int64_t K, int bits, int lr, bool repacked, bool f16, bool one_table, int cus,
