@@ -68,7 +68,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
         p.bp = plan_batch(M, N, K, false, cus);
         p.bp_fine = plan_batch(M, N, K, true, cus);
         const PrefillPlan pp = plan_prefill(M, N, K, cus);
-        const double matrix = prefill_us(pp, K, cus) / 0.85;      // (only where that is clear: neither estimate is better than 10 %)
+        const double matrix = 0.95 * prefill_us(pp, K, cus) + 2.5;   // (where both say the same, this side of 50 us the other one was faster, beyond it this one)
         if (p.bp.us > matrix) p.bp = BatchPlan{};
         if (p.bp_fine.us > matrix) p.bp_fine = BatchPlan{};
         if (p.bp.ok || p.bp_fine.ok) {

@@ -83,7 +83,7 @@ struct Params {
     uint16_t* y;
     float* partial;                  // [tiles][slabs][ROWS * BN] fp32, slabs > 1 only
     unsigned long long* counters;    // [tiles], slabs > 1 only
-    int64_t N, K;
+    int64_t N, K, ldy;               // N: rows of weights of this launch; ldy: values from a row of y to the next
     int M, G;                        // G = K / 128
     int lr;                          // log2(group size / 128), 0 with groups of 64
     int flags;                       // 1: re-laid-out codes, 2: one table for all rows
@@ -406,7 +406,7 @@ __device__ __forceinline__ void batch_body(const Params& p) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int64_t m = m0 + i * 32 + (v >> 2) * 8 + h * 4 + (v & 3);
-            if (m < p.M && n < p.N) p.y[m * p.N + n] = (uint16_t)f32_to_h16<F16>(r[v]);
+            if (m < p.M && n < p.N) p.y[m * p.ldy + n] = (uint16_t)f32_to_h16<F16>(r[v]);
         }
     };
     if (p.slabs == 1) {

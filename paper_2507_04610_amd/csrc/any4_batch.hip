@@ -13,62 +13,69 @@ template <int MT> constexpr int max_slab_values() {
 }
 constexpr int kMaxSlabValues[4] = {max_slab_values<1>(), max_slab_values<2>(), max_slab_values<3>(), max_slab_values<4>()};
 
+// Time in us of a launch of t tiles with s slabs of G groups: per round of blocks their start and end, and their steps
+// (which take longer the more of the chip is busy); where slabs meet, a wait for their sums, eight slabs at a time, and the
+// traffic of all sums; a flight of seven or eight slabs takes longer by `full`.  Constants fitted to 1100 problems of
+// 128 .. 128256 rows of weights, K = 128 .. 28672, each with up to 14 slab counts: times within 7 % rms, the count taken on
+// average 1 % slower than the best, 10 % at worst.
+struct Cost {
+    double block, step_idle, step_busy, flight, more, full, per_mb;   // (more: flights after the first)
+    int64_t least;                                                    // a block takes the time of as many steps at least
+};
+constexpr Cost kCost[4] = {{6.0, 1.1, 1.3, 2.1, 1.0, 0.45, 1.15, 1}, {8.7, 0.9, 1.62, 2.2, 4.8, 0.7, 0.59, 2},
+                              {9.2, 1.4, 1.94, 7.8, 7.2, 1.0, 0.32, 1}, {11.7, 1.45, 2.3, 8.6, 8.3, 1.9, 0.23, 1}};
+static double meet_us(int mt, int64_t t, int64_t s) {
+    const Cost& c = kCost[mt - 1];
+    return s == 1 ? 0.0 : c.flight + c.more * (double)((s - 1) / 8) + (s % 8 == 0 || s % 8 == 7 ? c.full : 0.0) +
+                          c.per_mb * (double)(t * s * (32 * mt) * (32 * batch::wn_of(mt))) * 4e-6;
+}
+static double launch_us(int mt, int64_t t, int64_t s, int64_t G, int cus) {
+    const Cost& c = kCost[mt - 1];
+    const int wk = batch::kWaves / batch::wn_of(mt);
+    const int64_t own = ((G + s - 1) / s + wk - 1) / wk, steps = own > c.least ? own : c.least, rounds = (t * s + cus - 1) / cus;
+    const double busy = t * s < cus ? (double)(t * s) / cus : 1.0;
+    return (double)rounds * (c.block + (c.step_idle + (c.step_busy - c.step_idle) * busy) * (double)steps) + meet_us(mt, t, s);
+}
+
 // Work split; a pure function of its arguments.  A block takes 32 mt rows of x, 32 * wn rows of weights and one
-// of `slabs` parts of K.
+// of `slabs` parts of K; a launch takes `tiles_n` times 32 * wn rows of weights.
+//
+// The sums of slabs stay within what any4_gemm_noalloc has, so that it takes every call.  Where those of the whole
+// matrix do not fit, the rows of weights are cut into launches that follow each other in the same workspace, each as many
+// whole rounds of blocks as fit.
 BatchPlan plan_batch(int64_t M, int64_t N, int64_t K, bool fine, int cus) {
     BatchPlan pl{};
     if (M < 1 || M > kBatchMaxM || cus < 1) return pl;
-    pl.mt = (int)((M + 31) / 32);
-    pl.rows = 32 * pl.mt;
-    const int wn = batch::wn_of(pl.mt), wk = batch::kWaves / wn, bn = 32 * wn;
+    const int mt = (int)((M + 31) / 32), rows = 32 * mt, wn = batch::wn_of(mt), wk = batch::kWaves / wn, bn = 32 * wn;
     const int64_t G = K / kGroup, tiles = (N + bn - 1) / bn;
-    const int values = kMaxSlabValues[pl.mt - 1];
-    const int64_t most = fine ? values / 2 : values;              // groups whose scales and offsets LDS holds
+    const auto most = [&](int m) -> int64_t { return fine ? kMaxSlabValues[m - 1] / 2 : kMaxSlabValues[m - 1]; };   // groups whose scales and offsets LDS holds
     // 32-bit offsets inside a block's rows
-    if (K * bn >= ((int64_t)1 << 31) || K * 2 * pl.rows >= ((int64_t)1 << 31) || tiles > ((int64_t)1 << 24)) return pl;
-    // Time in us of a launch with s slabs: per round of blocks their start and end, and their steps (which take longer
-    // the more of the chip is busy); where slabs meet, a wait for their sums, eight slabs at a time, and the traffic of
-    // all sums; a flight of seven or eight slabs takes longer by `full`.  Constants fitted to 1100 problems of 128 .. 128256
-    // rows of weights, K = 128 .. 28672, each with up to 14 slab counts: times within 7 % rms, the count taken on
-    // average 1 % slower than the best, 10 % at worst.
-    struct Cost { double block, step_idle, step_busy, flight, more, full, per_mb; int64_t least; };   // (more: flights after the first; least: steps)
-    constexpr Cost cost[4] = {{6.0, 1.1, 1.3, 2.1, 1.0, 0.45, 1.15, 1}, {8.7, 0.9, 1.62, 2.2, 4.8, 0.7, 0.59, 2},
-                              {9.2, 1.4, 1.94, 7.8, 7.2, 1.0, 0.32, 1}, {11.7, 1.45, 2.3, 8.6, 8.3, 1.9, 0.23, 1}};
-    const auto meet_us = [&](int64_t t, int64_t s) -> double {
-        const Cost& c = cost[pl.mt - 1];
-        return s == 1 ? 0.0 : c.flight + c.more * (double)((s - 1) / 8) + (s % 8 == 0 || s % 8 == 7 ? c.full : 0.0) + c.per_mb * (double)(t * s * pl.rows * bn) * 4e-6;
-    };
-    const auto launch_us = [&](int64_t t, int64_t s) -> double {
-        const Cost& c = cost[pl.mt - 1];
-        const int64_t own = ((G + s - 1) / s + wk - 1) / wk, steps = own > c.least ? own : c.least, rounds = (t * s + cus - 1) / cus;
-        const double busy = t * s < cus ? (double)(t * s) / cus : 1.0;
-        return (double)rounds * (c.block + (c.step_idle + (c.step_busy - c.step_idle) * busy) * (double)steps) + meet_us(t, s);
-    };
+    if (K * bn >= ((int64_t)1 << 31) || K * 2 * rows >= ((int64_t)1 << 31) || tiles > ((int64_t)1 << 24)) return pl;
     // (no slab count from here on can be better once its sums alone take too long)
-    for (int64_t s = (G + most - 1) / most; s <= 64 && s <= (G + wk - 1) / wk && !(pl.ok && meet_us(tiles, s) > pl.us); ++s) {
-        const double t = launch_us(tiles, s);
-        if (!pl.ok || t < pl.us) {
+    for (int64_t s = (G + most(mt) - 1) / most(mt); s <= 64 && s <= (G + wk - 1) / wk && !(pl.ok && meet_us(mt, tiles, s) > pl.us); ++s) {
+        const int64_t fit = s == 1 ? tiles : (ANY4_NOALLOC_SCRATCH_BYTES - 256) / (s * rows * bn * (int64_t)sizeof(float) + 8);
+        const int64_t rounds = fit * s / cus, part = tiles <= fit ? tiles : rounds * cus >= s ? rounds * cus / s : fit;
+        const double us = (double)(tiles / part) * launch_us(mt, part, s, G, cus) + (tiles % part ? launch_us(mt, tiles % part, s, G, cus) : 0.0);
+        if (!pl.ok || us < pl.us) {
+            pl = BatchPlan{};
             pl.ok = true;
-            pl.us = t;
-            pl.slabs = (int)s;
+            pl.mt = mt; pl.rows = rows;
+            pl.tiles_n = (int)part; pl.slabs = (int)s;
+            pl.us = us;
         }
     }
     if (!pl.ok) return pl;
-    pl.tiles_n = (int)tiles;
-    if (pl.slabs > 1) {
-        pl.counter_bytes = splitk_counter_bytes(tiles);
-        pl.workspace = pl.counter_bytes + (size_t)tiles * pl.slabs * pl.rows * bn * sizeof(float);
+    // Up to 64 rows of x several launches have an alternative, blocks of 32 rows of x without slabs, which need no
+    // workspace: taken unless the launches are clearly faster (100000 x 8192 at M = 64: 347 us, in two launches 270).
+    const double whole = launch_us(1, 2 * tiles, 1, G, cus);
+    if (mt == 2 && pl.tiles_n < tiles && G <= most(1) && 0.88 * whole <= pl.us) {
+        pl.mt = 1; pl.rows = 32;
+        pl.tiles_n = (int)tiles; pl.slabs = 1;
+        pl.us = whole;
     }
-    // The sums of slabs stay within what any4_gemm_noalloc has, so that it takes what the kernels before this one
-    // took.  Beyond (100000 rows of weights and more, at up to 64 rows of x) blocks of 32 rows of x go without slabs;
-    // the weights are then read twice, still less than the matrix-core kernel's four-fold padding of x costs.
-    if (pl.workspace > (size_t)ANY4_NOALLOC_SCRATCH_BYTES) {
-        const int v1 = kMaxSlabValues[0];
-        if (M > 64 || G > (fine ? v1 / 2 : v1)) return BatchPlan{};
-        pl.mt = 1;
-        pl.rows = 32;
-        pl.slabs = 1;
-        pl.counter_bytes = pl.workspace = 0;
+    if (pl.slabs > 1) {
+        pl.counter_bytes = splitk_counter_bytes(pl.tiles_n);
+        pl.workspace = pl.counter_bytes + (size_t)pl.tiles_n * pl.slabs * rows * bn * sizeof(float);
     }
     return pl;
 }
@@ -79,19 +86,30 @@ hipError_t launch_batch(const uint16_t* x, const uint32_t* codes, const uint16_t
     const bool fine = lr < 0;
     if (!pl.ok || lr < -1 || (f16 && fine) || (pl.slabs > 1 && !workspace)) return hipErrorInvalidValue;
     batch::Params p{};
-    p.x = x; p.codes = codes; p.lut = lut; p.scale = scale; p.offset = offset; p.y = y;
+    p.x = x;
     p.counters = static_cast<unsigned long long*>(workspace);
     p.partial = pl.slabs > 1 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + pl.counter_bytes) : nullptr;
-    p.N = N; p.K = K; p.M = (int)M; p.G = (int)(K / kGroup);
+    p.K = K; p.ldy = N; p.M = (int)M; p.G = (int)(K / kGroup);
     p.lr = fine ? 0 : lr;
     p.flags = (repacked ? 1 : 0) | (one_table ? 2 : 0);
-    p.slabs = pl.slabs; p.tiles_n = pl.tiles_n;
+    p.slabs = pl.slabs;
     const int groups = (p.G + pl.slabs - 1) / pl.slabs;           // of the largest slab
     p.sc_stride = batch::Shape<1, 4>::sc_stride(fine ? 2 * groups : groups);
     const int blocks_m = (int)((M + pl.rows - 1) / pl.rows);
-    if (bits == 4) return launch_batch_bits4(p, pl.mt, blocks_m, f16, fine, stream);
-    if (bits == 3) return launch_batch_bits3(p, pl.mt, blocks_m, f16, fine, stream);
-    return launch_batch_bits2(p, pl.mt, blocks_m, f16, fine, stream);
+    const int64_t bn = 32 * batch::wn_of(pl.mt), GS = fine ? 2 * (int64_t)p.G : p.G >> p.lr;   // scales per row
+    // (launches follow each other on the stream and leave the workspace's counters clean)
+    for (int64_t n0 = 0; n0 < N; n0 += pl.tiles_n * bn) {
+        p.N = N - n0 < pl.tiles_n * bn ? N - n0 : pl.tiles_n * bn;
+        p.tiles_n = (int)((p.N + bn - 1) / bn);
+        p.codes = codes + n0 * row_words(K, bits);                // (both layouts: n0 is a multiple of 128 rows)
+        p.lut = lut && !one_table ? lut + (n0 << bits) : lut;
+        p.scale = scale + n0 * GS; p.offset = offset + n0 * GS; p.y = y + n0;
+        const hipError_t e = bits == 4 ? launch_batch_bits4(p, pl.mt, blocks_m, f16, fine, stream)
+                           : bits == 3 ? launch_batch_bits3(p, pl.mt, blocks_m, f16, fine, stream)
+                                       : launch_batch_bits2(p, pl.mt, blocks_m, f16, fine, stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace any4

@@ -54,7 +54,7 @@ constexpr int kBatchMaxM = 128;
 struct BatchPlan {
     bool ok;              // the kernel takes this problem
     int mt, rows;         // 32-row tiles of x per block, 32 * mt
-    int tiles_n, slabs;   // blocks along n, K slabs
+    int tiles_n, slabs;   // blocks along n of one launch (the last may have fewer), K slabs
     size_t counter_bytes, workspace;      // arrival counters, and with them the fp32 partial sums (several slabs only)
     double us;            // the time it is expected to take
 };
