@@ -15,15 +15,14 @@ constexpr int kMaxSlabValues[4] = {max_slab_values<1>(), max_slab_values<2>(), m
 
 // Time in us of a launch of t tiles with s slabs of G groups: per round of blocks their start and end, and their steps
 // (which take longer the more of the chip is busy); where slabs meet, a wait for their sums, eight slabs at a time, and the
-// traffic of all sums; a flight of seven or eight slabs takes longer by `full`.  Constants fitted to 1100 problems of
-// 128 .. 128256 rows of weights, K = 128 .. 28672, each with up to 14 slab counts: times within 7 % rms, the count taken on
-// average 1 % slower than the best, 10 % at worst.
+// traffic of all sums; a flight of seven or eight slabs takes longer by `full`.  Constants fitted to 1700 problems of
+// 128 .. 128256 rows of weights, K = 128 .. 28672, each with up to 16 slab counts: times within 7 % rms, the count taken on
+// average 1 % slower than the best, 13 % at worst.
 struct Cost {
     double block, step_idle, step_busy, flight, more, full, per_mb;   // (more: flights after the first)
-    int64_t least;                                                    // a block takes the time of as many steps at least
 };
-constexpr Cost kCost[4] = {{6.0, 1.1, 1.3, 2.1, 1.0, 0.45, 1.15, 1}, {8.7, 0.9, 1.62, 2.2, 4.8, 0.7, 0.59, 2},
-                              {9.2, 1.4, 1.94, 7.8, 7.2, 1.0, 0.32, 1}, {11.7, 1.45, 2.3, 8.6, 8.3, 1.9, 0.23, 1}};
+constexpr Cost kCost[4] = {{6.15, 1.15, 1.32, 2.2, 1.3, 0.57, 0.98}, {7.45, 1.2, 1.7, 3.6, 2.6, 0.66, 0.44},
+                           {9.1, 1.4, 1.91, 7.9, 6.3, 0.94, 0.34}, {11.9, 1.5, 2.3, 10.7, 8.4, 2.0, 0.18}};
 static double meet_us(int mt, int64_t t, int64_t s) {
     const Cost& c = kCost[mt - 1];
     return s == 1 ? 0.0 : c.flight + c.more * (double)((s - 1) / 8) + (s % 8 == 0 || s % 8 == 7 ? c.full : 0.0) +
@@ -32,7 +31,7 @@ static double meet_us(int mt, int64_t t, int64_t s) {
 static double launch_us(int mt, int64_t t, int64_t s, int64_t G, int cus) {
     const Cost& c = kCost[mt - 1];
     const int wk = batch::kWaves / batch::wn_of(mt);
-    const int64_t own = ((G + s - 1) / s + wk - 1) / wk, steps = own > c.least ? own : c.least, rounds = (t * s + cus - 1) / cus;
+    const int64_t steps = ((G + s - 1) / s + wk - 1) / wk, rounds = (t * s + cus - 1) / cus;
     const double busy = t * s < cus ? (double)(t * s) / cus : 1.0;
     return (double)rounds * (c.block + (c.step_idle + (c.step_busy - c.step_idle) * busy) * (double)steps) + meet_us(mt, t, s);
 }
@@ -68,7 +67,7 @@ BatchPlan plan_batch(int64_t M, int64_t N, int64_t K, bool fine, int cus) {
     // Up to 64 rows of x several launches have an alternative, blocks of 32 rows of x without slabs, which need no
     // workspace: taken unless the launches are clearly faster (100000 x 8192 at M = 64: 347 us, in two launches 270).
     const double whole = launch_us(1, 2 * tiles, 1, G, cus);
-    if (mt == 2 && pl.tiles_n < tiles && G <= most(1) && 0.88 * whole <= pl.us) {
+    if (mt == 2 && pl.tiles_n < tiles && G <= most(1) && 0.82 * whole <= pl.us) {
         pl.mt = 1; pl.rows = 32;
         pl.tiles_n = (int)tiles; pl.slabs = 1;
         pl.us = whole;
