@@ -52,3 +52,32 @@ def test_two_streaming_launches(oracle, variant, M):
     apart = torch.cat((gemm(x[:16].contiguous()), gemm(x[16:].contiguous())))
     if variant != "f16":                                          # (fp16: whichever is expected to be faster)
         assert torch.equal(y.view(torch.int16), apart.view(torch.int16)) == (M <= 24 and variant not in ("int4", "g64"))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,repacked", ((20, 4000, 4096, False), (40, 1000, 14336, True), (80, 99000, 8192, False)))
+def test_captured_calls(M, N, K, repacked):
+    """two streaming launches, K slabs, several launches in one workspace: every replay of a captured call gives the eager
+    call's bits, with eager work in between and the output overwritten"""
+    import torch
+    import paper_2507_04610_amd as any4
+    t = inputs.make_case_device(M, N, K, 4, seed=M)
+    codes = any4.any4_pack(t["codes_u8"], 4)
+    del t["codes_u8"]
+    if repacked:
+        codes = any4.any4_repack(codes, 4)
+    gemm = any4.any4_gemm_repacked if repacked else any4.any4_gemm
+    y = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((max(16, any4.any4_gemm_workspace_bytes(M, N, K, 4)),), 0xA5, dtype=torch.uint8, device="cuda")
+    run = lambda: gemm(t["x"], codes, t["lut"], t["scale"], t["offset"], 4, out=y, workspace=ws)
+    want = run().clone()
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        run()
+    for _ in range(4):
+        y.fill_(9.0)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y.view(torch.int16), want.view(torch.int16))
+        assert torch.equal(run().view(torch.int16), want.view(torch.int16))
