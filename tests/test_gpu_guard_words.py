@@ -90,8 +90,8 @@ GEMM_CASES = [
     (1, 333, 4096, 4, "group256"), (8, 100, 2048, 3, "group1024"),
     (1, 333, 4224, 4, "group64"), (13, 100, 4480, 2, "group64"),
     (1, 333, 4224, 4, "f16"), (16, 100, 4480, 3, "f16"),
-    (37, 100, 14336, 4, "plain"),                   # a few dozen rows: 16 per launch
-    (300, 384, 4096, 4, "plain"), (129, 130, 640, 3, "plain"), (2048, 200, 1024, 2, "plain"),   # matrix cores
+    (37, 100, 14336, 4, "plain"),                   # a few dozen rows
+    (300, 384, 4096, 4, "plain"), (129, 130, 640, 3, "plain"), (2048, 200, 1024, 2, "plain"),   # matrix cores (300, 129, 2048, 260 rows)
     (300, 384, 4096, 4, "repacked"), (260, 300, 2048, 4, "group64"), (100, 200, 256, 4, "f16"), (40, 200, 1024, 4, "no_table"),
     (2, 5, 262272, 4, "plain"),                     # the wavefront-per-row kernel
 ]

@@ -270,9 +270,8 @@ def test_gemm_rejects_small_workspace_and_leaves_output_alone(any4):
 @pytest.mark.parametrize("M,N,K", [(17, 64, 4096), (32, 256, 4096), (37, 100, 14336), (64, 512, 2048),
                                    (128, 96, 8192)])
 def test_gemm_few_dozen_rows(any4, oracle, bits, M, N, K):
-    """M just above 16: served by the streaming kernel, 16 rows of x per launch (ragged last launch,
-    K slabs that share one workspace from launch to launch), or by the matrix-core kernel - whichever
-    the library picks, the result must be the same GEMM."""
+    """M just above 16: the kernel for a few dozen rows of x, with and without K slabs, or another one -
+    whichever the library picks, the result must be the same GEMM."""
     run_gemm_case(any4, oracle, M, N, K, bits, seed=inputs.case_seed(6, bits, M))
 
 
@@ -304,7 +303,7 @@ def test_dequant_grouped_bit_exact(any4, oracle, bits, group, N, K):
                                    (32, 256, 4096), (100, 200, 1024), (300, 130, 2048)])
 def test_gemm_grouped(any4, oracle, bits, group, M, N, K):
     """Small M (streaming kernel, every wavefront reads the scales of its own chunks), a few dozen
-    rows (the same kernel, 16 rows per launch) and large M (matrix cores, K slices included)."""
+    rows (a kernel of their own) and large M (matrix cores, K slices included)."""
     if K % group:
         pytest.skip("the group must divide K")
     cs = inputs.make_case(M, N, K, bits, seed=inputs.case_seed(8, bits, group + M))
@@ -343,8 +342,9 @@ def test_dequant_groups_of_64_bit_exact(any4, oracle, bits, N, K):
                                    (260, 300, 8192)])
 def test_gemm_groups_of_64(any4, oracle, bits, M, N, K):
     """Small M: the streaming kernel tells the halves of a chunk of 128 apart on the activation side,
-    8 rows a launch (one launch, two, one or several K slabs, ragged N).  Larger M: the matrix-core
-    kernel folds a scale in after every K step, whole tiles and K slices."""
+    8 rows a launch (one launch, two, one or several K slabs, ragged N).  A few dozen rows: a kernel of
+    their own, two scales a group.  Larger M: the matrix-core kernel folds a scale in after every K step, whole
+    tiles and K slices."""
     cs, sc, of = fine(M, N, K, bits, inputs.case_seed(18, bits, M + N))
     packed = oracle.pack(cs.codes_u8, bits)
     y64 = oracle.gemm(cs.x, packed, cs.lut, sc, of, K, bits, threads=8, group=64)

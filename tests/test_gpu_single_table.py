@@ -2,7 +2,7 @@
 paragraph; section 5, "Speed Comparisons"): any4_gemm_single_table / any4_dequant_single_table against the
 oracle run on the table written out N times, and bit for bit against the per-row entry points fed
 the same N repeated rows.  Every kernel that can serve the call: the streaming kernel (K = 4096 and
-K slabs), the whole-K kernel for M <= 4, 16 rows a launch, the matrix-core kernel (whole tiles and K
+K slabs), the whole-K kernel for M <= 4, the kernel for a few dozen rows, the matrix-core kernel (whole tiles and K
 slices), the wavefront-per-row kernel for very long K."""
 import numpy as np
 import pytest

@@ -64,7 +64,7 @@ PAIRS = [
     ((300, 384, 4096, 4), (100, 200, 256, 4)),
     # no scratch at all after one that used it; 3- and 2-bit codes
     ((16, 100, 28672, 3), (1, 256, 512, 2)),
-    # a few dozen rows: the streaming kernel 16 rows a launch, sharing the counters from launch to launch
+    # a few dozen rows: K slabs of the kernel for them
     ((37, 100, 14336, 4), (17, 64, 4096, 4)),
 ]
 
