@@ -88,11 +88,13 @@ int any4_dequant(const uint32_t* codes, const uint16_t* lut, const uint16_t* sca
  * any4_gemm - y[m][n] = sum_k x[m][k] * w[n][k] with w as defined above, never
  * materialised (section 4.2: weights are dequantised on the fly inside the GEMM).
  * Products are accumulated in fp32 (order unspecified but fixed for given shapes: the
- * result is reproducible run to run); y is rounded to bf16, round-to-nearest-even.
- * Small M (<= 16, token generation) takes a memory-bound kernel, large M a
- * matrix-core kernel, M up to 128 whichever of the two a cost model expects to be
- * faster (the memory-bound kernel then runs once per 16 rows of x); the choice depends
- * only on (M, N, K, bits) and the number of compute units of the device.
+ * result is reproducible run to run); y is rounded to bf16, round-to-nearest-even.  The
+ * order may depend on M, N and the place of a row of weights in the matrix: equal rows, or
+ * the same rows in a matrix cut along N, can differ in the last bit of y.
+ * Small M (<= 16, token generation) takes a memory-bound kernel, 17 <= M <= 128 a kernel
+ * for a few dozen rows of x (where that is expected to be faster, the memory-bound kernel in
+ * two launches, M <= 24, or the matrix-core kernel), larger M a matrix-core kernel; the choice
+ * depends only on (M, N, K, bits), the format and the number of compute units of the device.
  *   x          in   bf16 [M][K]
  *   lut        as for any4_dequant, including NULL = int4 grid for bits = 4
  *   y          out  bf16 [M][N], fully overwritten
@@ -135,7 +137,7 @@ int any4_gemm_f16(const uint16_t* x, const uint32_t* codes, const uint16_t* lut,
  * paper's Table 4 varies the group size): scale and offset are bf16 [N][K/group].
  *   group   64, 128, 256, 512 or 1024 (the range of Table 4), and a divisor of K; anything else
  *           returns ANY4_ERR_SHAPE.  With group = 64 and M <= 16 the weights are streamed once per
- *           8 rows of x (two launches for M > 8); for 16 < M the matrix-core kernel is used.
+ *           8 rows of x (two launches for M > 8).
  * Every other argument, the workspace size (any4_gemm_workspace_bytes) and the error behaviour
  * are those of any4_dequant / any4_gemm; with group = 128 the calls are identical to them.
  * any4_gemm_grouped needs a table (lut != NULL) unless group = 128.

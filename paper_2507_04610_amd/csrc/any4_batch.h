@@ -21,11 +21,15 @@
 // registers, four steps ahead; a step waits for what step t + 2 needs, so the first operand of the next step can be
 // prepared before the barrier.  The parts meet in LDS, slabs of K in the workspace (fp32, added in slab order by the last to arrive).
 //
-// What bounds it: vector instructions.  8 codes are 23 of them for 32 MT rows of x, a group of a wavefront ~250 next
-// to 8 MT matrix instructions; a step of M = 64 takes 1.4 us of issue at the clock the chip keeps under this
-// load and 2.0 us with its loads (28672 x 4096: 36 us; the four linears of an 8B layer at M = 64 / 32: 99 / 82 us,
-// where streaming the weights once per 16 rows took 199 / 105).  The rest of a launch is fixed: 5 us until
-// the first steps have landed, 2 - 3 us for the end, 4 us more where slabs meet.
+// Order of the sums.  A block starts at a step of its own along K (see `rot`), so the last bit of an output can depend on
+// the place of its row of weights in the matrix.
+//
+// What bounds it: no unit by itself.  28672 x 4096 at M = 64 (16 steps, 224 blocks, 40 us under the counters, 1.94 GHz): a
+// wavefront issues 317 vector instructions (20 of them matrix) and 24 LDS instructions a step; vector issue is
+// busy 53 % of the time, the matrix cores of the SIMDs that hold a block 27 %, the LDS pipe 20 %, and wavefronts wait 35 % of
+// theirs.  A step takes 1.7 us with the chip full, 1.2 with few blocks.  The rest of a launch is fixed: 6 - 12 us for start and end of a block (32 .. 128 rows of x),
+// and where slabs meet 2 - 11 us for their sums (any4_batch.hip has the constants).  The four linears of an 8B layer at M = 24 / 64 / 128: 81 / 103 / 183 us,
+// where the kernels for fewer and for more rows took 94 / 197 / 229.
 #pragma once
 #include "any4_device.h"
 #include "any4_internal.h"

@@ -7,8 +7,8 @@
 // yield constants or copies of a sign bit of its operands, so
 //     perm(lower half, code) ^ perm(upper half, code ^ 8)
 // is the wanted entry XOR a byte that depends on the code and on the OTHER half only; that byte is
-// folded into the halves once per row (RowTable::load).  8 codes take 21 (4 bits: 5 to spread the
-// nibbles over bytes in order, 12 lookups, 4 to interleave the planes) vector instructions, no
+// folded into the halves once per row (RowTable::load).  8 codes take 23 (4 bits: 5 to spread the
+// nibbles over bytes in order, 2 for the upper half's selectors, 12 lookups, 4 to interleave the planes) vector instructions, no
 // LDS traffic, no table in LDS to build and no bank conflicts.
 #pragma once
 #include "any4_device.h"
