@@ -65,8 +65,9 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
     if (M > kStreamMaxM && M <= kBatchMaxM) {
         // A few dozen rows of x fill a fraction of one 256-row tile of the matrix-core kernel, whose time does
         // not depend on M below 256.
-        p.bp = plan_batch(M, N, K, false, cus);
-        p.bp_fine = plan_batch(M, N, K, true, cus);
+        const BatchPlans both = plan_batch(M, N, K, cus);
+        p.bp = both.plain;
+        p.bp_fine = both.fine;
         const PrefillPlan pp = plan_prefill(M, N, K, cus);
         const double matrix = 0.95 * prefill_us(pp, K, cus) + 2.5;   // (where both say the same, this side of 50 us the other one was faster, beyond it this one)
         if (p.bp.us > matrix) p.bp = BatchPlan{};

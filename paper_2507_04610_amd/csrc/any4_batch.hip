@@ -23,60 +23,75 @@ struct Cost {
 };
 constexpr Cost kCost[4] = {{6.15, 1.15, 1.32, 2.2, 1.3, 0.57, 0.98}, {7.45, 1.2, 1.7, 3.6, 2.6, 0.66, 0.44},
                            {9.1, 1.4, 1.91, 7.9, 6.3, 0.94, 0.34}, {11.9, 1.5, 2.3, 10.7, 8.4, 2.0, 0.18}};
-static double meet_us(int mt, int64_t t, int64_t s) {
+static double meet_us(int mt, int t, int s) {
     const Cost& c = kCost[mt - 1];
     return s == 1 ? 0.0 : c.flight + c.more * (double)((s - 1) / 8) + (s % 8 == 0 || s % 8 == 7 ? c.full : 0.0) +
-                          c.per_mb * (double)(t * s * (32 * mt) * (32 * batch::wn_of(mt))) * 4e-6;
+                          c.per_mb * ((double)t * s * (32 * mt) * (32 * batch::wn_of(mt))) * 4e-6;
 }
-static double launch_us(int mt, int64_t t, int64_t s, int64_t G, int cus) {
+static double launch_us(int mt, int t, int s, int G, int cus) {
     const Cost& c = kCost[mt - 1];
-    const int wk = batch::kWaves / batch::wn_of(mt);
-    const int64_t steps = ((G + s - 1) / s + wk - 1) / wk, rounds = (t * s + cus - 1) / cus;
-    const double busy = t * s < cus ? (double)(t * s) / cus : 1.0;
+    const int wk = batch::kWaves / batch::wn_of(mt), steps = ((G + s - 1) / s + wk - 1) / wk, blocks = t * s, rounds = (blocks + cus - 1) / cus;
+    const double busy = blocks < cus ? (double)blocks / cus : 1.0;
     return (double)rounds * (c.block + (c.step_idle + (c.step_busy - c.step_idle) * busy) * (double)steps) + meet_us(mt, t, s);
 }
 
-// Work split; a pure function of its arguments.  A block takes 32 mt rows of x, 32 * wn rows of weights and one
-// of `slabs` parts of K; a launch takes `tiles_n` times 32 * wn rows of weights.
+// Work split for groups of 128 and more and for groups of 64 (twice the scales to keep in LDS); a pure function of its arguments.
+// A block takes 32 mt rows of x, 32 * wn rows of weights and one of `slabs` parts of K; a launch takes `tiles_n` times
+// 32 * wn rows of weights.
 //
 // The sums of slabs stay within what any4_gemm_noalloc has, so that it takes every call.  Where those of the whole
 // matrix do not fit, the rows of weights are cut into launches that follow each other in the same workspace, each as many
 // whole rounds of blocks as fit.
-BatchPlan plan_batch(int64_t M, int64_t N, int64_t K, bool fine, int cus) {
-    BatchPlan pl{};
-    if (M < 1 || M > kBatchMaxM || cus < 1) return pl;
+BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
+    BatchPlans both{};
+    if (M < 1 || M > kBatchMaxM || cus < 1) return both;
     const int mt = (int)((M + 31) / 32), rows = 32 * mt, wn = batch::wn_of(mt), wk = batch::kWaves / wn, bn = 32 * wn;
-    const int64_t G = K / kGroup, tiles = (N + bn - 1) / bn;
-    const auto most = [&](int m) -> int64_t { return fine ? kMaxSlabValues[m - 1] / 2 : kMaxSlabValues[m - 1]; };   // groups whose scales and offsets LDS holds
     // 32-bit offsets inside a block's rows
-    if (K * bn >= ((int64_t)1 << 31) || K * 2 * rows >= ((int64_t)1 << 31) || tiles > ((int64_t)1 << 24)) return pl;
-    // (no slab count from here on can be better once its sums alone take too long)
-    for (int64_t s = (G + most(mt) - 1) / most(mt); s <= 64 && s <= (G + wk - 1) / wk && !(pl.ok && meet_us(mt, tiles, s) > pl.us); ++s) {
-        const int64_t fit = s == 1 ? tiles : (ANY4_NOALLOC_SCRATCH_BYTES - 256) / (s * rows * bn * (int64_t)sizeof(float) + 8);
-        const int64_t rounds = fit * s / cus, part = tiles <= fit ? tiles : rounds * cus >= s ? rounds * cus / s : fit;
-        const double us = (double)(tiles / part) * launch_us(mt, part, s, G, cus) + (tiles % part ? launch_us(mt, tiles % part, s, G, cus) : 0.0);
-        if (!pl.ok || us < pl.us) {
-            pl = BatchPlan{};
-            pl.ok = true;
-            pl.mt = mt; pl.rows = rows;
-            pl.tiles_n = (int)part; pl.slabs = (int)s;
-            pl.us = us;
+    if (K * bn >= ((int64_t)1 << 31) || K * 2 * rows >= ((int64_t)1 << 31) || (N + bn - 1) / bn > ((int64_t)1 << 24)) return both;
+    const int G = (int)(K / kGroup), tiles = (int)((N + bn - 1) / bn), most = kMaxSlabValues[mt - 1];   // values per row in LDS
+    const int first = (G + most - 1) / most, first_fine = (2 * G + most / 2 * 2 - 1) / (most / 2 * 2);
+    const size_t tile_bytes = (size_t)rows * bn * sizeof(float);
+    auto take = [&](BatchPlan& pl, int part, int s, double us) {
+        if (pl.ok && us >= pl.us) return;
+        pl = BatchPlan{};
+        pl.ok = true;
+        pl.mt = mt; pl.rows = rows;
+        pl.tiles_n = part; pl.slabs = s;
+        pl.us = us;
+    };
+    for (int s = first; s <= 64 && s <= (G + wk - 1) / wk; ++s) {
+        // no slab count from here on can be better once its sums and as many rounds of blocks take too long
+        const double rounds = (double)tiles * s / cus;
+        if (both.fine.ok && meet_us(mt, tiles, s) + kCost[mt - 1].block * (rounds > 1.0 ? rounds : 1.0) > (both.fine.us > both.plain.us ? both.fine.us : both.plain.us)) break;
+        int part = tiles;
+        if (s > 1 && (size_t)tiles * (s * tile_bytes + 8) + 256 > (size_t)ANY4_NOALLOC_SCRATCH_BYTES) {
+            const int fit = (int)((ANY4_NOALLOC_SCRATCH_BYTES - 256) / (s * tile_bytes + 8)), full = fit * s / cus * cus;
+            part = full >= s ? full / s : fit;
+        }
+        double us = launch_us(mt, part, s, G, cus);
+        if (part < tiles) us = us * (tiles / part) + (tiles % part ? launch_us(mt, tiles % part, s, G, cus) : 0.0);
+        take(both.plain, part, s, us);
+        if (s >= first_fine) take(both.fine, part, s, us);
+    }
+    for (const bool fine : {false, true}) {
+        BatchPlan& pl = fine ? both.fine : both.plain;
+        if (!pl.ok) continue;
+        // Up to 64 rows of x several launches have an alternative, blocks of 32 rows of x without slabs, which need no
+        // workspace: taken unless the launches are clearly faster (100000 x 8192 at M = 64: 347 us, in two launches 270).
+        if (mt == 2 && pl.tiles_n < tiles && (fine ? 2 * G : G) <= kMaxSlabValues[0]) {
+            const double whole = launch_us(1, 2 * tiles, 1, G, cus);
+            if (0.82 * whole <= pl.us) {
+                pl.mt = 1; pl.rows = 32;
+                pl.tiles_n = tiles; pl.slabs = 1;
+                pl.us = whole;
+            }
+        }
+        if (pl.slabs > 1) {
+            pl.counter_bytes = splitk_counter_bytes(pl.tiles_n);
+            pl.workspace = pl.counter_bytes + (size_t)pl.tiles_n * pl.slabs * tile_bytes;
         }
     }
-    if (!pl.ok) return pl;
-    // Up to 64 rows of x several launches have an alternative, blocks of 32 rows of x without slabs, which need no
-    // workspace: taken unless the launches are clearly faster (100000 x 8192 at M = 64: 347 us, in two launches 270).
-    const double whole = launch_us(1, 2 * tiles, 1, G, cus);
-    if (mt == 2 && pl.tiles_n < tiles && G <= most(1) && 0.82 * whole <= pl.us) {
-        pl.mt = 1; pl.rows = 32;
-        pl.tiles_n = (int)tiles; pl.slabs = 1;
-        pl.us = whole;
-    }
-    if (pl.slabs > 1) {
-        pl.counter_bytes = splitk_counter_bytes(pl.tiles_n);
-        pl.workspace = pl.counter_bytes + (size_t)pl.tiles_n * pl.slabs * rows * bn * sizeof(float);
-    }
-    return pl;
+    return both;
 }
 
 hipError_t launch_batch(const uint16_t* x, const uint32_t* codes, const uint16_t* lut, const uint16_t* scale,

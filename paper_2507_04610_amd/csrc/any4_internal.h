@@ -58,7 +58,8 @@ struct BatchPlan {
     size_t counter_bytes, workspace;      // arrival counters, and with them the fp32 partial sums (several slabs only)
     double us;            // the time it is expected to take
 };
-BatchPlan plan_batch(int64_t M, int64_t N, int64_t K, bool fine, int cus);
+struct BatchPlans { BatchPlan plain, fine; };             // groups of 128 and more, groups of 64
+BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus);
 hipError_t launch_batch(const uint16_t* x, const uint32_t* codes, const uint16_t* lut, const uint16_t* scale,
                         const uint16_t* offset, int64_t M, int64_t N, int64_t K, int bits, int lr, bool repacked, bool f16,
                         bool one_table, const BatchPlan& pl, uint16_t* y, void* workspace, hipStream_t stream);
