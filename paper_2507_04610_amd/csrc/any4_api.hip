@@ -69,7 +69,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
         p.bp = both.plain;
         p.bp_fine = both.fine;
         const PrefillPlan pp = plan_prefill(M, N, K, cus);
-        const double matrix = 0.95 * prefill_us(pp, K, cus) + 2.5;   // (where both say the same, this side of 50 us the other one was faster, beyond it this one)
+        const double matrix = 0.92 * prefill_us(pp, K, cus) + 2.5;   // (where both say the same, this side of 30 us the other one was faster, beyond it this one)
         if (p.bp.us > matrix) p.bp = BatchPlan{};
         if (p.bp_fine.us > matrix) p.bp_fine = BatchPlan{};
         if (p.bp.ok || p.bp_fine.ok) {
@@ -150,7 +150,7 @@ int gemm_dispatch(const uint16_t* x, const uint32_t* codes, bool repacked, const
     const PackPlan pk = (M <= 4 && lut && lr == 0 && !f16) ? plan_pack(M, N, K, bits, one_table, plan.cus) : PackPlan{};
     if (pk.ok) {
         e = launch_decode_pack(x, codes, lut, scale, offset, M, N, K, bits, repacked, one_table, pk, y, s);
-    } else if (plan.two_launches > 0 && lut && lr >= 0 && plan.two_launches + (f16 ? 1.4 : 0.0) < 0.97 * plan.bp.us) {
+    } else if (plan.two_launches > 0 && lut && lr >= 0 && plan.two_launches + (f16 ? 1.4 : 0.0) < plan.bp.us) {
         // (fp16 takes it 0.7 us more per launch.  Not without a table: the streaming kernel takes the integer grid as 128 + code and off again, whose rounding
         // the kernel for more rows does not have)
         e = launch_decode_stream(x, codes, lut, scale, offset, kStreamMaxM, N, K, bits, lr, repacked, f16, one_table, plan.sp, y, workspace, s);

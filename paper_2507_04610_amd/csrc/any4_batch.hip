@@ -13,16 +13,17 @@ template <int MT> constexpr int max_slab_values() {
 }
 constexpr int kMaxSlabValues[4] = {max_slab_values<1>(), max_slab_values<2>(), max_slab_values<3>(), max_slab_values<4>()};
 
-// Time in us of a launch of t tiles with s slabs of G groups: per round of blocks their start and end, and their steps
-// (which take longer the more of the chip is busy); where slabs meet, a wait for their sums, eight slabs at a time, and the
-// traffic of all sums; a flight of seven or eight slabs takes longer by `full`.  Constants fitted to 1700 problems of
-// 128 .. 128256 rows of weights, K = 128 .. 28672, each with up to 16 slab counts: times within 7 % rms, the count taken on
-// average 1 % slower than the best, 13 % at worst.
+// Time in us of a launch of t tiles with s slabs of G groups.  Per round of blocks: their start and end (more with the
+// chip full: `crowd`), four steps whose loads are all issued at the start, and the rest, which take longer from a quarter of the chip
+// on; a round that fills the chip to the last compute unit took longer by `even`.  Where slabs meet: a wait for their sums, eight slabs at a time
+// (seven or eight take longer by `full`), and the traffic of all sums.  Constants fitted to 1700 problems of 128 .. 128256
+// rows of weights, K = 128 .. 28672, each with up to 16 slab counts: times within 7 % rms, the count taken on average 0.8 %
+// slower than the best, 11 % at worst.
 struct Cost {
-    double block, step_idle, step_busy, flight, more, full, per_mb;   // (more: flights after the first)
+    double block, crowd, first, rest, rest_busy, even, flight, more, full, per_mb;   // (more: flights after the first)
 };
-constexpr Cost kCost[4] = {{6.15, 1.15, 1.32, 2.2, 1.3, 0.57, 0.98}, {7.45, 1.2, 1.7, 3.6, 2.6, 0.66, 0.44},
-                           {9.1, 1.4, 1.91, 7.9, 6.3, 0.94, 0.34}, {11.9, 1.5, 2.3, 10.7, 8.4, 2.0, 0.18}};
+constexpr Cost kCost[4] = {{6.3, 3.0, 1.02, 1.33, 1.38, 0, 2.6, 1.15, 0.46, 0.16}, {8.5, 0.95, 0.91, 1.75, 1.83, 0, 2.85, 2.6, 0.31, 0.54},
+                           {9.2, 0, 1.32, 1.32, 2.0, 3, 7.7, 9.5, 0.95, 0.36}, {9.9, 0.66, 1.67, 1.34, 2.51, 4, 11.2, 9.6, 1.33, 0.19}};
 static double meet_us(int mt, int t, int s) {
     const Cost& c = kCost[mt - 1];
     return s == 1 ? 0.0 : c.flight + c.more * (double)((s - 1) / 8) + (s % 8 == 0 || s % 8 == 7 ? c.full : 0.0) +
@@ -31,8 +32,10 @@ static double meet_us(int mt, int t, int s) {
 static double launch_us(int mt, int t, int s, int G, int cus) {
     const Cost& c = kCost[mt - 1];
     const int wk = batch::kWaves / batch::wn_of(mt), steps = ((G + s - 1) / s + wk - 1) / wk, blocks = t * s, rounds = (blocks + cus - 1) / cus;
-    const double busy = blocks < cus ? (double)blocks / cus : 1.0;
-    return (double)rounds * (c.block + (c.step_idle + (c.step_busy - c.step_idle) * busy) * (double)steps) + meet_us(mt, t, s);
+    const double busy = blocks < cus ? (double)blocks / cus : 1.0, quarter = busy < 0.25 ? 4 * busy : 1.0;
+    const int first = steps < 4 ? steps : 4;
+    return (double)rounds * (c.block + c.crowd * busy + c.first * first + (c.rest + (c.rest_busy - c.rest) * quarter) * (steps - first)) +
+           (blocks % cus == 0 ? c.even : 0.0) + meet_us(mt, t, s);
 }
 
 // Work split for groups of 128 and more and for groups of 64 (twice the scales to keep in LDS); a pure function of its arguments.
@@ -80,7 +83,7 @@ BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
         // workspace: taken unless the launches are clearly faster (100000 x 8192 at M = 64: 347 us, in two launches 270).
         if (mt == 2 && pl.tiles_n < tiles && (fine ? 2 * G : G) <= kMaxSlabValues[0]) {
             const double whole = launch_us(1, 2 * tiles, 1, G, cus);
-            if (0.82 * whole <= pl.us) {
+            if (0.78 * whole <= pl.us) {
                 pl.mt = 1; pl.rows = 32;
                 pl.tiles_n = tiles; pl.slabs = 1;
                 pl.us = whole;
