@@ -10,8 +10,9 @@
 //      the drawn point walks it (the uniform draws are an input, one per centre);
 //   3. weighted Lloyd iterations in fp64 until a pass changes no code or `iters` centre updates
 //      were made, by one of two methods:
-//      sorted row (K <= 16384): the scaled row is sorted once (bitonic network, 16 elements per
-//        thread in registers, LDS between rounds) and running sums of s and s * w_S are kept per 16
+//      sorted row (K <= 16384): the scaled row is sorted once (into buckets, which then order themselves; rows
+//        that crowd a bucket by a bitonic network, 16 elements per thread in registers, LDS between rounds)
+//        and running sums of s and s * w_S are kept per 16
 //        sorted elements.  A pass is then the work of 2^n lanes of one wavefront: order the centres,
 //        find for each neighbouring pair the first sorted position the upper one wins - a binary
 //        search that evaluates the very predicate of the E-step (squared fp64 distances, ties to the
@@ -578,6 +579,172 @@ __device__ __forceinline__ void sort_round(uint2* kv, int m, int top) {
     __syncthreads();
 }
 
+// Inclusive sum of a u32 over the 64 lanes, min / max of a u32 over the 64 lanes (in every lane).
+__device__ __forceinline__ uint32_t wave_inclusive_sum_u32(uint32_t v, int lane) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+    const uint32_t t0 = __builtin_amdgcn_readlane(v, 15), t1 = __builtin_amdgcn_readlane(v, 31), t2 = __builtin_amdgcn_readlane(v, 47);
+    const int row = lane >> 4;
+    return v + (row == 0 ? 0u : row == 1 ? t0 : row == 2 ? t0 + t1 : t0 + t1 + t2);
+}
+template <bool MAX>
+__device__ __forceinline__ uint32_t wave_minmax_u32(uint32_t v) {
+    auto pick = [](uint32_t a, uint32_t b) { return MAX ? max(a, b) : min(a, b); };
+    auto dpp = [](uint32_t x, auto ctrl) { return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, decltype(ctrl)::value, 0xF, 0xF, false); };
+    v = pick(v, dpp(v, std::integral_constant<int, 0xB1>{}));
+    v = pick(v, dpp(v, std::integral_constant<int, 0x4E>{}));
+    v = pick(v, dpp(v, std::integral_constant<int, 0x141>{}));
+    v = pick(v, dpp(v, std::integral_constant<int, 0x140>{}));
+    const uint32_t a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
+    const uint32_t c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
+    return pick(pick(a, b), pick(c, d));
+}
+
+// Sort by distribution: 32 T buckets of equal width between the row's smallest and largest scaled weight, filled by a
+// counting sort (two 16-bit counters to a word of LDS); then every element counts the smaller ones of its bucket.
+// Group scaling spreads a row over a fixed range, so a bucket holds about one element, and the sort is ~1.5 k
+// instructions per thread where the bitonic network of 16 T elements takes ~8 k (K <= 4096) to ~11 k.  The order among
+// the elements of a bucket is (key, sample weight): the sorted row does not depend on the order in which the counters
+// were bumped.  Bound: LDS latency and vector issue.  6144 x 4096 any4 836 -> 698 us for the whole kernel, of which
+// the sort is 78 now; 4096 x 14336 2704 -> 2070 us, the sort 275 of it.  False, and nothing sorted, where the buckets would not do: a bucket of more than kBucketMost elements
+// (few distinct values, outliers), all weights equal, or a weight that is not finite.
+// `key`, `sv`: the thread's cnt elements; `scan`: 4 W words of scratch; `flag`: one word.  LDS of kv is free on entry
+// once every thread has arrived.
+constexpr int kBucketMost = 32;
+template <int T>
+__device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, int* flag, const uint32_t (&key)[16],
+                                                const float (&sv)[16], int cnt, int K) {
+    constexpr int W = T / kWave;
+    constexpr int NB = 32 * T;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+        if (e < cnt) { lo = min(lo, key[e]); hi = max(hi, key[e]); }
+    lo = wave_minmax_u32<false>(lo);
+    hi = wave_minmax_u32<true>(hi);
+    if (lane == 0) { scan[2 * wv] = lo; scan[2 * wv + 1] = hi; }
+    if (tid == 0) *flag = 0;
+    __syncthreads();                                               // every thread is done with what lay in kv
+    uint32_t* const hist = reinterpret_cast<uint32_t*>(kv);        // [NB / 2] words, and one counter more
+#pragma unroll 1
+    for (int i = 0; i < W; ++i) { lo = min(lo, scan[2 * i]); hi = max(hi, scan[2 * i + 1]); }
+    const float mn = key_f32(lo), range = key_f32(hi) - mn;
+    // (not finite: a NaN or an infinity among the weights, or a range beyond fp32)
+    if (!(range > 0.0f && range < __uint_as_float(0x7F800000u)) || !(fabsf(mn) < __uint_as_float(0x7F800000u))) return false;   // the same in every thread
+    const float inv = (float)NB / range;
+    if (!(inv < __uint_as_float(0x7F800000u))) return false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) reinterpret_cast<uint4*>(hist)[i * T + tid] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    // bucket (monotone in the weight: one subtraction, one product, both rounded monotonically) and place in it
+    uint32_t slot[16];
+    bool crowded = false;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const uint32_t b = min((uint32_t)((key_f32(key[e]) - mn) * inv), (uint32_t)(NB - 1));
+        uint32_t r = 0;
+        if (e < cnt) {
+            const uint32_t old = atomicAdd(&hist[b >> 1], (b & 1) ? 0x10000u : 1u);
+            r = (b & 1) ? old >> 16 : old & 0xFFFFu;
+        }
+        crowded |= r >= (uint32_t)kBucketMost;
+        slot[e] = b | (min(r, 255u) << 16);
+    }
+    if (crowded) *flag = 1;
+    __syncthreads();
+    if (*flag != 0) return false;
+    // counters -> first position of every bucket; a thread has 32 neighbouring ones
+    {
+        uint32_t c[16], sum = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint4 v = reinterpret_cast<const uint4*>(hist)[tid * 4 + i];
+            c[4 * i] = v.x; c[4 * i + 1] = v.y; c[4 * i + 2] = v.z; c[4 * i + 3] = v.w;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum += (c[i] & 0xFFFFu) + (c[i] >> 16);
+        uint32_t run = wave_inclusive_sum_u32(sum, lane);
+        if (lane == 63) scan[2 * W + wv] = run;
+        run -= sum;
+        __syncthreads();
+#pragma unroll 1
+        for (int i = 0; i < wv; ++i) run += scan[2 * W + i];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const uint32_t second = run + (c[i] & 0xFFFFu), next = second + (c[i] >> 16);
+            c[i] = run | (second << 16);
+            run = next;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            reinterpret_cast<uint4*>(hist)[tid * 4 + i] = make_uint4(c[4 * i], c[4 * i + 1], c[4 * i + 2], c[4 * i + 3]);
+        if (tid == T - 1) hist[NB / 2] = run;                      // = K
+    }
+    __syncthreads();
+    // first position (low half) and size of the element's bucket
+    const uint16_t* const first = reinterpret_cast<const uint16_t*>(hist);
+    uint32_t most = 0;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const uint32_t b = slot[e] & 0xFFFFu, r = slot[e] >> 16;
+        const uint32_t f = first[b], size = first[b + 1] - f;
+        slot[e] = f | (size << 16) | (r << 24);
+        most = e < cnt ? max(most, size) : most;
+    }
+    __syncthreads();
+    // into the buckets (no spare elements yet), and what sorts last behind the row: a look beyond a bucket's end
+    // finds larger keys only
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+        if (e < cnt) kv[(slot[e] & 0xFFFFu) + (slot[e] >> 24)] = make_uint2(key[e], __float_as_uint(sv[e]));
+    if (tid < 8) kv[K + tid] = make_uint2(kPadKey, 0u);
+    __syncthreads();
+    most = wave_minmax_u32<true>(most);
+    uint32_t less[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) less[e] = 0;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const uint32_t f = e < cnt ? slot[e] & 0xFFFFu : 0u, size = (slot[e] >> 16) & 0xFFu, r = slot[e] >> 24;
+        const unsigned long long me = ((unsigned long long)key[e] << 32) | __float_as_uint(sv[e]);
+        uint32_t same = 0;
+        auto look = [&](uint32_t i) {
+            const uint2 v = kv[f + i];
+            const unsigned long long o = ((unsigned long long)v.x << 32) | v.y;
+            less[e] += o < me ? 1u : 0u;
+            same += o == me ? 1u : 0u;
+        };
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) look(i);
+        if (most > 4) {
+#pragma unroll 1
+            for (uint32_t i = 4; i < size; i += 4) {               // (reads at most three past the bucket)
+#pragma unroll
+                for (uint32_t t = 0; t < 4; ++t) look(i + t);
+            }
+        }
+        if (same > 1) {                                            // equal pairs: in the order of their places
+#pragma unroll 1
+            for (uint32_t i = 0; i < r; ++i) {
+                const uint2 v = kv[f + i];
+                less[e] += (v.x == key[e] && v.y == __float_as_uint(sv[e])) ? 1u : 0u;
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+        if (e < cnt) kv[pad16((int)((slot[e] & 0xFFFFu) + less[e]))] = make_uint2(key[e], __float_as_uint(sv[e]));
+    for (int p = K + tid; p < 16 * T; p += T) kv[pad16(p)] = make_uint2(kPadKey, 0u);
+    __syncthreads();
+    return true;
+}
+
 template <int BITS, int T>
 __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     const float* __restrict__ w, const float* __restrict__ act, const float* __restrict__ u,
@@ -614,10 +781,10 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     // s * (squared distance to the nearest centre chosen so far) afterwards; as s >= 0, multiplying by s and
     // rounding is monotone, so s * min(d_old, d_new) is min(s * d_old, s * d_new) bit for bit and the
     // distances themselves need not be kept.
+    const int C = (K + T - 1) / T;
+    const int j0 = min(tid * C, K), cnt = min(j0 + C, K) - j0;
+    float xv[16], sv[16];
     {
-        const int C = (K + T - 1) / T;
-        const int j0 = min(tid * C, K), cnt = min(j0 + C, K) - j0;
-        float xv[16], sv[16];
         double mass[16];
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
@@ -681,28 +848,27 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
         }
     }
 
-    // ---- sort the row: elements (order-preserving image of w_S, sample weight), ascending in w_S
+    // ---- sort the row: elements (order-preserving image of w_S, sample weight), ascending; every thread
+    // brings the chunk it holds
     {
-        uint32_t k0[16], s0[16];
+        uint32_t key[16];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int j = tid * 16 + e;
-            k0[e] = j < K ? f32_key(ws[j]) : kPadKey;
-            s0[e] = j < K ? __float_as_uint(sample_weight(j)) : 0u;
-        }
-        __syncthreads();                                           // every thread has read its part of ws
+        for (int e = 0; e < 16; ++e) key[e] = f32_key(xv[e]);
+        if (!sort_by_buckets<T>(kv, reinterpret_cast<uint32_t*>(scan), misc + 3, key, sv, cnt, K)) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) kv[pad16(tid * 16 + e)] = make_uint2(k0[e], s0[e]);
-        __syncthreads();
-        sort_first16<T>(kv);
-        for (int m = 5; m <= LOGKP; ++m) {
-            const int top = m - 1;
-            if constexpr (LOGKP > 12) {
-                if (top >= 12) sort_round<T, 12, LOGKP - 12>(kv, m, top);
+            for (int e = 0; e < 16; ++e)
+                kv[tid * 17 + e] = e < cnt ? make_uint2(key[e], __float_as_uint(sv[e])) : make_uint2(kPadKey, 0u);
+            __syncthreads();
+            sort_first16<T>(kv);
+            for (int m = 5; m <= LOGKP; ++m) {
+                const int top = m - 1;
+                if constexpr (LOGKP > 12) {
+                    if (top >= 12) sort_round<T, 12, LOGKP - 12>(kv, m, top);
+                }
+                if (top >= 8) sort_round<T, 8, 4>(kv, m, min(top, 11));
+                if (top >= 4) sort_round<T, 4, 4>(kv, m, min(top, 7));
+                sort_round<T, 0, 4>(kv, m, min(top, 3));
             }
-            if (top >= 8) sort_round<T, 8, 4>(kv, m, min(top, 11));
-            if (top >= 4) sort_round<T, 4, 4>(kv, m, min(top, 7));
-            sort_round<T, 0, 4>(kv, m, min(top, 3));
         }
     }
 

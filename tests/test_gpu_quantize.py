@@ -194,3 +194,23 @@ def test_quantize_rejects_bad_arguments(any4):
                              out.data_ptr(), out.data_ptr(), None, None) == -1
     assert lib.any4_quantize(w.data_ptr(), None, u.data_ptr(), 1, 128, 4, 0, -1, out.data_ptr(), out.data_ptr(),
                              out.data_ptr(), out.data_ptr(), None, None) == -2
+
+
+@pytest.mark.parametrize("unit_act", (False, True))
+@pytest.mark.parametrize("K", (640, 4096, 4224, 14336))
+def test_quantize_rows_with_crowded_buckets(any4, qoracle, K, unit_act):
+    """The sort places a row's weights in buckets of equal width and hands rows with more than 32 in a bucket to
+    the bitonic network: rows on both sides of that limit, rows with many equal weights (with unit activations also
+    equal sample weights), very small and very large weights."""
+    qc = inputs.make_quant_case(8, K, 4, seed=3 * K)
+    w = qc.w.copy()
+    w[0] = inputs.bf16_bits_to_f32(inputs.f32_to_bf16_bits(w[0]))            # ties inside a group
+    w[1, 5:5 + 32] = w[1, 5]                                                 # a bucket of 32 at least
+    w[2, 256:256 + 31] = w[2, 300]                                           # ... with one more in its place
+    w[3, 128:128 + 33] = w[3, 140]                                           # more than a bucket takes
+    w[4, 384:512] = 0.125                                                    # a constant group: 128 equal weights
+    w[5] *= np.float32(1e-30)
+    w[6] *= np.float32(1e30)
+    w[7] = np.round(w[7] * 2000) / 2000                                      # few distinct values per group
+    for symmetric in (False, True):
+        run_and_compare(any4, qoracle, w, None if unit_act else qc.act, qc.u, 4, symmetric, 20, ("crowded", K, symmetric))
