@@ -907,76 +907,104 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
         if (tid == T - 1) { pre_s[T] = is; pre_sx[T] = isx; }
         __syncthreads();
     }
-    // ---- 3, sorted row: the Lloyd passes on wavefront 0, four lanes per centre (lane = 4 q + sub: the four
-    // hold the same centre and split the searches and the partial sums).  Lanes 4 q .. 4 q + 3 hold centre q;
-    // after ordering, lanes 4 i .. 4 i + 3 also hold the centre of rank i: value d, index own, range [start, end).
+    // ---- 3, sorted row: the Lloyd passes on wavefront 0.  Lane 16 sub + i holds the centre of rank i (by value, then
+    // index): value d, original index own, its range of sorted positions in the last pass.  The four rows of 16 lanes hold
+    // the same and split the searches and the sums (sub = 0 .. 3), so a neighbouring centre is a DPP move away.  A pass
+    // is one chain of dependent steps, ~20 of them per row of weights, and nothing else of the block runs meanwhile: what
+    // counts is its latency.  So a boundary is sought among the first elements of the running sums' chunks, first around
+    // where it should have moved to since the last pass (most often the only round of probes), and the one chunk that holds
+    // it is read once, for its place in it and for its sums.  4096 x 14336 any4 2070 -> 1698 us, 6144 x 4096 698 -> 588 us
+    // against a search of all positions, four neighbouring lanes per centre (a pass of a long row 2.2 -> 1.0 us).
     if (wv == 0) {
-        const int q4 = lane >> 2, sub = lane & 3, lane4 = lane & ~3;
-        const bool live = q4 < L;
-        double c = live ? cen[q4] : 0.0;
+        const int i = lane & 15, sub = lane >> 4;
+        const bool live = i < L;
+        const int nch = K >> 4;                                    // chunks (K is a multiple of 128)
+        double d = live ? cen[i] : 0.0;
+        int own = i;
         const double maxabs = fmax(fabs((double)key_f32(kv[0].x)), fabs((double)key_f32(kv[pad16(K - 1)].x)));
         const double tol = centre_gap * maxabs;
-        int prev_s = -2, prev_e = -2;                              // range of centre q in the previous pass
-        int done = 0;
-        bool fallback = false;
-        double d = 0.0;
-        int start = 0, end = 0;
-        bool rep = false, ranked = false;
-        int r = 0;
-        // sum over the four lanes of a centre: two DPP moves inside the group of four per half
-        auto quad_sum = [](double v) {
-            v += __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0xB1, 0xF, 0xF, false),
-                                  __builtin_amdgcn_update_dpp(0, __double2loint(v), 0xB1, 0xF, 0xF, false));
-            v += __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x4E, 0xF, 0xF, false),
-                                  __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x4E, 0xF, 0xF, false));
-            return v;
+        int prev_s = -2, prev_e = -2;
+        int done = 0, chunk = 0;                                   // chunk: where the centre's lower boundary was last
+        float last_mid = 0.0f, density = 0.0f;
+        bool fallback = false, some = false;
+        int start = 0;
+        auto below_f64 = [](double v) { return row_shr_f64<1>(v); };
+        auto below_i32 = [](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false); };
+        auto above_i32 = [](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x101, 0xF, 0xF, false); };
+        auto above_f64 = [&](double v) { return __hiloint2double(above_i32(__double2hiint(v)), above_i32(__double2loint(v))); };
+        // sum over the four rows of lanes, (row 0 + row 1) + (row 2 + row 3), in every lane
+        auto rows_sum = [](double v) {
+            const auto h1 = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+            const auto l1 = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+            v = __hiloint2double(h1[0], l1[0]) + __hiloint2double(h1[1], l1[1]);
+            const auto h2 = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+            const auto l2 = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+            return __hiloint2double(h2[0], l2[0]) + __hiloint2double(h2[1], l2[1]);
+        };
+        // how many of a centre's four lanes say yes
+        auto count4 = [&](bool b) -> int {
+            const unsigned long long m = __ballot(b) >> i;
+            return __popc((unsigned)m & 0x00010001u) + __popc((unsigned)(m >> 32) & 0x00010001u);
         };
         for (;;) {
-            // order the centres by (value, index): rank r of centre q; the lanes of rank i take that centre.
-            // The order of the last pass is tried first (one permutation and a comparison of neighbours; the
-            // centres of a one-dimensional k-means hardly ever overtake each other) and the ranks counted anew,
-            // 2^n comparisons per centre, only if it no longer holds.
-            int own = 0;
-            for (int attempt = ranked ? 0 : 1; attempt < 2; ++attempt) {
-                if (attempt == 1) {
-                    r = 0;
-                    static_for<L>([&](auto p_) {
-                        constexpr int p = decltype(p_)::value;
-                        const double cp = lane_f64<4 * p>(c);
-                        r += (cp < c || (cp == c && p < q4)) ? 1 : 0;
-                    });
-                }
-                const int to = ((live ? r : q4) * 4 + sub) * 4;    // the ranks are a permutation of the live centres
-                d = __hiloint2double(__builtin_amdgcn_ds_permute(to, __double2hiint(c)),
-                                     __builtin_amdgcn_ds_permute(to, __double2loint(c)));
-                own = __builtin_amdgcn_ds_permute(to, q4);
-                if (attempt == 1) break;
-                const double below_d = shfl_up_f64(d, 4);
-                const int below_own = __shfl_up(own, 4);
-                const bool in_order = !live || q4 == 0 || below_d < d || (below_d == d && below_own < own);
-                if (__ballot(!in_order) == 0ull) break;
+            // the centres in order of (value, index)?  Ranked anew, 2^n comparisons per centre, only where they are not
+            // (the centres of a one-dimensional k-means hardly ever overtake each other)
+            double dprev = below_f64(d);
+            int own_prev = below_i32(own);
+            if (__ballot(live && i > 0 && !(dprev < d || (dprev == d && own_prev < own))) != 0ull) {
+                int r = 0;
+                static_for<L>([&](auto p_) {
+                    constexpr int p = decltype(p_)::value;
+                    const double dp = lane_f64<p>(d);
+                    const int op = __builtin_amdgcn_readlane(own, p);
+                    r += (dp < d || (dp == d && op < own)) ? 1 : 0;
+                });
+                const int to = ((lane & 48) | (live ? r : i)) * 4;   // the ranks are a permutation of the live centres
+                d = __hiloint2double(__builtin_amdgcn_ds_permute(to, __double2hiint(d)),
+                                     __builtin_amdgcn_ds_permute(to, __double2loint(d)));
+                own = __builtin_amdgcn_ds_permute(to, own);
+                prev_s = __builtin_amdgcn_ds_permute(to, prev_s);
+                prev_e = __builtin_amdgcn_ds_permute(to, prev_e);
+                dprev = below_f64(d);
+                own_prev = below_i32(own);
             }
-            ranked = true;
             // equal centres: only the lowest index ever wins a weight; it stands for the run
-            const double dprev = shfl_up_f64(d, 4);
-            rep = live && (q4 == 0 || dprev != d);
-            const unsigned long long repmask = __ballot(rep && sub == 0);
-            const unsigned long long below = repmask & ((1ull << lane4) - 1ull);
-            const int prv = below ? 63 - __clzll(below) : 0;       // the previous run's first lane
-            const int a_own = __shfl(own, prv);
-            bool bad = rep && q4 > 0 && (d - dprev) <= tol;
-            // first sorted position at which this centre beats the one below it (the E-step's own comparison, which
-            // is false up to that position and true from it on): each round the four lanes probe the four
-            // inner fifths of the open range
-            int lo = 0, hi = (rep && q4 > 0) ? K : 0;              // the answer lies in [lo, hi]
-            while (__ballot(lo < hi) != 0ull) {
-                const int span = hi - lo;
-                const int probe = lo + (span * (sub + 1)) / 5;     // lo <= probe < hi while the range is open
-                const double x = (double)key_f32(kv[pad16(min(probe, K - 1))].x);
+            const bool rep = live && (i == 0 || dprev != d);
+            const unsigned repmask = (unsigned)__ballot(rep) & 0xFFFFu;
+            const bool distinct = repmask == (1u << L) - 1u;
+            const unsigned above = repmask & ~((2u << i) - 1u);
+            const int nxt = above ? __ffs((int)above) - 1 : -1;    // the next run's centre
+            int a_own = own_prev;                                  // index of the run below
+            if (!distinct) {
+                const unsigned below = repmask & ((1u << i) - 1u);
+                a_own = __shfl(own, below ? 31 - __clz((int)below) : 0);
+            }
+            const bool seek = rep && i > 0;
+            bool bad = seek && (d - dprev) <= tol;
+            // the E-step's own comparison: does this centre win x from the one below it?  False up to some position
+            // of the sorted row and true from there on.
+            auto wins = [&](double x) {
                 const double da = x - dprev, db = x - d;
                 const double dda = da * da, ddb = db * db;
-                const bool win = ddb < dda || (ddb == dda && own < a_own);
-                const int losses = __popc((unsigned)(__ballot(!win) >> lane4) & 15u);   // 0 .. 4, the first ones
+                return (ddb < dda) | ((ddb == dda) & (own < a_own));   // (no branches: they cost more than the comparison)
+            };
+            auto first_of = [&](int c) { return (double)key_f32(kv[c * 17].x); };
+            // lo = the number of chunks whose first element it does not win, in [lo, hi]; a round probes four of them
+            int lo = 0, hi = seek ? nch : 0;
+            const float mid = 0.5f * (float)(dprev + d);
+            if (done > 0) {                                        // where it should be, as it moved by mid - last_mid
+                const int guess = chunk + (int)rintf(fminf(fmaxf((mid - last_mid) * density, -16384.0f), 16384.0f));
+                auto at = [&](int k) { return min(max(guess - 1 + k, 0), nch - 1); };
+                const int losses = count4(!wins(first_of(at(sub))));
+                if (seek) {
+                    if (losses > 0) lo = at(losses - 1) + 1;
+                    if (losses < 4) hi = at(losses);
+                }
+            }
+            while (__ballot(lo < hi) != 0ull) {                    // the inner fifths of the open range
+                const int span = hi - lo;
+                const int probe = lo + (span * (sub + 1)) / 5;     // lo <= probe < hi while the range is open
+                const int losses = count4(!wins(first_of(min(probe, nch - 1))));
                 if (lo < hi) {
                     const int lo2 = losses > 0 ? lo + (span * losses) / 5 + 1 : lo;
                     const int hi2 = losses < 4 ? lo + (span * (losses + 1)) / 5 : hi;
@@ -984,51 +1012,60 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
                     hi = hi2;
                 }
             }
-            start = lo;
-            // running sums before that position: the entry of its group of 16, then the group's first elements,
-            // four apart per lane
+            chunk = min(max(lo - 1, 0), nch - 1);
+            // its place in the chunk, and the running sums before it: four elements per lane
             double ss = 0.0, sx = 0.0;
-            {
-                const int chunk = start >> 4, nrem = start & 15;
+            int before = 0;
+            uint2 v[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int e = sub + 4 * i;
-                    double x, sw;
-                    element(min(chunk * 16 + e, K - 1), x, sw);
-                    if (e < nrem) { ss += sw; sx += sw * x; }
-                }
-                ss = quad_sum(ss) + pre_s[chunk];
-                sx = quad_sum(sx) + pre_sx[chunk];
+            for (int k = 0; k < 4; ++k) v[k] = kv[chunk * 17 + sub + 4 * k];
+            const int c0 = max(chunk - 2, 0), c1 = min(chunk + 2, nch - 1);
+            const uint32_t key0 = kv[c0 * 17].x, key1 = kv[c1 * 17].x;
+            const double run_s = pre_s[chunk], run_sx = pre_sx[chunk];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double x = (double)key_f32(v[k].x), sw = (double)__uint_as_float(v[k].y);
+                const bool lose = seek & !wins(x);
+                const double sw0 = lose ? sw : 0.0, sx0 = lose ? sw * x : 0.0;
+                ss += sw0;
+                sx += sx0;
+                before += count4(lose);
             }
-            const unsigned long long above = lane4 >= 60 ? 0ull : (repmask & ~((1ull << (lane4 + 4)) - 1ull));
-            const int nxt = above ? __ffsll((long long)above) - 1 : -1;
-            const int s_nxt = __shfl(start, nxt < 0 ? 0 : nxt);
-            end = nxt < 0 ? K : s_nxt;
+            start = seek ? chunk * 16 + before : 0;
+            ss = rows_sum(ss) + run_s;
+            sx = rows_sum(sx) + run_sx;
+            last_mid = mid;                                        // chunks per unit of weight around it, for the next guess
+            density = (float)(c1 - c0) * __builtin_amdgcn_rcpf(key_f32(key1) - key_f32(key0));
+            // the range ends where the next run's begins
+            int s_nxt = above_i32(start);
+            double e_ss = above_f64(ss), e_sx = above_f64(sx);
+            if (!distinct) {
+                s_nxt = __shfl(start, max(nxt, 0));
+                e_ss = shfl_f64(ss, max(nxt, 0));
+                e_sx = shfl_f64(sx, max(nxt, 0));
+            }
+            const int end = nxt < 0 ? K : s_nxt;
             bad = bad || (rep && end < start);
-            const double e_ss = shfl_f64(ss, nxt < 0 ? 0 : nxt), e_sx = shfl_f64(sx, nxt < 0 ? 0 : nxt);
-            const double den = (nxt < 0 ? pre_s[K >> 4] : e_ss) - ss;   // K is a multiple of 16: the sums before position K
-            const double num = (nxt < 0 ? pre_sx[K >> 4] : e_sx) - sx;
-            double cn = d;
-            if (rep && den > 0.0) cn = num / den;                   // M-step, Eq. (B); no weight: the centre stays
+            const double den = (nxt < 0 ? pre_s[nch] : e_ss) - ss;
+            const double num = (nxt < 0 ? pre_sx[nch] : e_sx) - sx;
             // did any weight change its centre?  compare every centre's range with the previous pass
-            const bool some = rep && start < end;
+            some = rep && start < end;
             const int rs = some ? start : -1, re = some ? end : -1;
-            const int qs = __shfl(rs, r * 4), qe = __shfl(re, r * 4);
-            const bool changed = __ballot(live && (qs != prev_s || qe != prev_e)) != 0ull;
+            const bool changed = __ballot(live && (rs != prev_s || re != prev_e)) != 0ull;
             if (__ballot(bad) != 0ull) { fallback = true; break; }
             if ((done > 0 && !changed) || done >= iters) break;
-            prev_s = qs;
-            prev_e = qe;
-            c = shfl_f64(cn, r * 4);
+            prev_s = rs;
+            prev_e = re;
+            if (rep && den > 0.0) d = num / den;                   // M-step, Eq. (B); no weight: the centre stays
             ++done;
         }
         if (lane == 0) misc[2] = fallback ? 1 : 0;
         if (!fallback) {
-            // ---- 4. lanes 4 i hold the centre of rank i: table entry i, and code i for every weight from the
-            // first of its range up to the first of the next non-empty range
+            // ---- 4. the centre of rank i: table entry i, and code i for every weight from the first of its range up to
+            // the first of the next non-empty range
             if (live && sub == 0) {
-                lut[n * L + q4] = (uint16_t)f32_to_bf16((float)d);
-                fin[q4] = (rep && start < end) ? kv[pad16(start)].x : kPadKey;
+                lut[n * L + i] = (uint16_t)f32_to_bf16((float)d);
+                fin[i] = some ? kv[pad16(start)].x : kPadKey;
             }
             if (msteps && lane == 0) msteps[n] = done;
         }
