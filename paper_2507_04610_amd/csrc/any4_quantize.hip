@@ -78,6 +78,11 @@ __device__ __forceinline__ double row_shr_f64(double v) {
     return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x110 + D, 0xF, 0xF, false),
                             __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x110 + D, 0xF, 0xF, false));
 }
+// The double one lane down (0.0 in lane 0).
+__device__ __forceinline__ double wave_shr1_f64(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xF, 0xF, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xF, 0xF, false));
+}
 // Inclusive sum over the 64 lanes: along the rows of 16 by DPP moves, then the three row totals (scalars)
 // onto the rows after them.  A fixed order of additions, like every sum here.
 __device__ __forceinline__ double wave_inclusive_sum(double v, int lane) {
@@ -768,82 +773,126 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     double* cen = scan + 2 * W;                 // [L]
     double* cen0 = cen + L;                     // [L]
     uint32_t* fin = reinterpret_cast<uint32_t*>(cen0 + L);   // [L] smallest key of the cluster of rank i (none: kPadKey)
-    int* misc = reinterpret_cast<int*>(fin + L);// [0], [1] selected index (by turns); [2] method flag; [40] as below
+    int* misc = reinterpret_cast<int*>(fin + L);// [0], [1] selected index (by turns); [2] method flag; [3] a weight that is no number, crowded buckets; [40] as below
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t n = blockIdx.x;
+    if (tid == 0) misc[3] = 0;
     scale_row<BITS, T>(w + n * K64, n, G, symmetric, scale, offset, ws, alpha, beta);
-
-    auto sample_weight = [&](int j) -> float { return alpha[j >> 7] * (act ? act[j] : 1.0f); };
 
     // ---- 2. k-means++ with sample weights; thread t owns the chunk [t * C, (t + 1) * C), C <= 16, in registers:
     // the scaled weight, the sample weight s and the sampling mass.  The mass is s for the first centre and
     // s * (squared distance to the nearest centre chosen so far) afterwards; as s >= 0, multiplying by s and
     // rounding is monotone, so s * min(d_old, d_new) is min(s * d_old, s * d_new) bit for bit and the
-    // distances themselves need not be kept.
+    // distances themselves need not be kept.  Bound: vector issue, 2^n rounds of seven instructions per weight (ten with a
+    // comparison and two selects in place of v_min_f64 and copies of x and s): 6144 x 4096 any4 588 -> 535 us, 4096 x 14336
+    // 1698 -> 1502 us together with the sums of the wavefronts, read several at a time.
+    const float* const wrow = w + n * K64;
     const int C = (K + T - 1) / T;
     const int j0 = min(tid * C, K), cnt = min(j0 + C, K) - j0;
     float xv[16], sv[16];
     {
-        double mass[16];
+        const float* const ap = act ? act : wrow;                  // (no activations: any K numbers, not used)
+        bool odd = false;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const bool in = e < cnt;
-            xv[e] = in ? ws[j0 + e] : 0.0f;
-            sv[e] = in ? sample_weight(j0 + e) : 0.0f;            // outside the chunk: mass +0, which changes no sum
-            mass[e] = (double)sv[e];
+            const int j = min(j0 + e, K - 1);
+            const float x = ws[j], av = ap[j], sw = alpha[j >> 7] * (act ? av : 1.0f);
+            odd |= __builtin_amdgcn_classf(x, 0x207) | __builtin_amdgcn_classf(sw, 0x207);   // a NaN or an infinity
+            xv[e] = e < cnt ? x : 0.0f;
+            sv[e] = e < cnt ? sw : 0.0f;                           // outside the chunk: mass +0, which changes no sum
         }
-#pragma unroll 1
-        for (int q = 0; q < L; ++q) {
-            double part = 0.0;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) part += mass[e];
+        if (odd) misc[3] = 1;
+        __syncthreads();
+        const bool odd_row = misc[3] != 0;
+        // one draw: the threads' masses are summed and scanned, the thread whose chunk holds the draw walks it
+        auto draw = [&](int q, double part, auto&& walk) -> double {
             double inc = wave_inclusive_sum(part, lane);
-            if (lane == 63) scan[(q & 1) * W + wv] = inc;          // (two sets of partial sums and of the selected
-            if (tid == 0) misc[q & 1] = 0x7FFFFFFF;                // index, used by turns: one barrier less per centre)
+            if (lane == 63) scan[(q & 1) * W + wv] = inc;          // (two sets of partial sums and of the drawn
+            if (tid == 0) misc[q & 1] = 0x7FFFFFFF;                // sample, used by turns: one barrier less per centre)
             __syncthreads();
             double base = 0.0, total = 0.0;
-#pragma unroll 1
+#pragma unroll 4
             for (int i = 0; i < W; ++i) {
-                if (i == wv) base = total;
+                base = i == wv ? total : base;
                 total += scan[(q & 1) * W + i];
             }
             inc += base;
-            double before = shfl_up_f64(inc, 1);
+            double before = wave_shr1_f64(inc);
             if (lane == 0) before = base;
             if (total > 0.0) {
                 const double t = (double)u[n * L + q] * total;
-                if (before <= t && inc > t && cnt > 0) {
-                    double run = before;
-                    int pick = -1, lastpos = j0;
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        run += mass[e];
-                        if (e < cnt && pick < 0) {
-                            if (mass[e] > 0.0) lastpos = j0 + e;
-                            if (run > t) pick = j0 + e;
-                        }
-                    }
-                    atomicMin(&misc[q & 1], pick >= 0 ? pick : lastpos);
-                }
+                if (before <= t && inc > t && cnt > 0) atomicMin(&misc[q & 1], j0 + walk(before, t));
             } else if (tid == 0) {
-                int64_t j = (int64_t)((double)u[n * L + q] * (double)K);
+                const int64_t j = (int64_t)((double)u[n * L + q] * (double)K);
                 misc[q & 1] = (int)min(j, (int64_t)K - 1);
             }
             __syncthreads();
-            int sel = misc[q & 1];
-            if (sel >= K) sel = K - 1;            // not reachable with finite, non-negative masses
-            const double cq = (double)ws[sel];
+            const double cq = (double)ws[min(misc[q & 1], K - 1)];   // (nothing drawn: not reachable with finite, non-negative masses)
             if (tid == 0) { cen[q] = cq; cen0[q] = cq; }
-            // (the empty asm statements keep the fp32 -> fp64 conversions inside the loop over q: hoisted,
-            // they would hold 64 more registers for the whole start)
+            return cq;
+        };
+        double mass[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) mass[e] = (double)sv[e];
+#pragma unroll 1
+        for (int q = odd_row ? L : 0; q < L; ++q) {
+            double part = 0.0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) part += mass[e];
+            const double cq = draw(q, part, [&](double run, double t) -> int {
+                // the first weight at which the running mass exceeds t; if rounding leaves none, the last one
+                // with any mass (masses outside the chunk are 0)
+                int pick = 16, last = 0;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    run += mass[e];
+                    last = mass[e] > 0.0 ? e : last;
+                    pick = min(pick, run > t ? e : 16);
+                }
+                return pick == 16 ? last : pick;
+            });
+            if (q == 0) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) mass[e] = __hiloint2double(0x7FF00000, 0);
+            }
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                float xe = xv[e], se = sv[e];
-                asm volatile("" : "+v"(xe), "+v"(se));
-                const double d = (double)xe - cq;
-                const double sd = (double)se * (d * d);
-                if (q == 0 || sd < mass[e]) mass[e] = sd;
+                // (the empty asm statement keeps the conversions inside the loop over q: hoisted, they
+                // would hold 64 more registers for the whole start)
+                asm volatile("" : "+v"(xv[e]), "+v"(sv[e]));
+                const double d = (double)xv[e] - cq;
+                const double m = (double)sv[e] * (d * d);
+                asm("v_min_f64 %0, %1, %0" : "+v"(mass[e]) : "v"(m));   // (both are numbers)
+            }
+        }
+        if (odd_row) {
+            // a NaN or an infinity somewhere: a mass is replaced only by one that compares as smaller.  Nothing is kept
+            // between the centres.
+#pragma unroll 1
+            for (int q = 0; q < L; ++q) {
+                auto mass_of = [&](int j) -> double {
+                    const double s = (double)(alpha[j >> 7] * (act ? act[j] : 1.0f)), x = (double)ws[j];
+                    double m = s;
+                    for (int p = 0; p < q; ++p) {
+                        const double d = x - cen[p], sd = s * (d * d);
+                        if (p == 0 || sd < m) m = sd;
+                    }
+                    return m;
+                };
+                double part = 0.0;
+                for (int e = 0; e < cnt; ++e) part += mass_of(j0 + e);
+                draw(q, part, [&](double run, double t) -> int {
+                    int pick = -1, last = 0;
+                    for (int e = 0; e < cnt && pick < 0; ++e) {
+                        const double m = mass_of(j0 + e);
+                        run += m;
+                        if (m > 0.0) last = e;
+                        if (run > t) pick = e;
+                    }
+                    return pick < 0 ? last : pick;
+                });
+                __syncthreads();                                   // cen[q] is there
             }
         }
     }
@@ -1087,7 +1136,6 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
         uint32_t fk[L];
 #pragma unroll
         for (int i = 0; i < L; ++i) fk[i] = fin[i];
-        const float* wrow = w + n * K64;
         uint8_t* crow = codes_out + n * K64;
         for (int j = tid * 16; j < K; j += T * 16) {
             const float a = alpha[j >> 7], b = beta[j >> 7];
