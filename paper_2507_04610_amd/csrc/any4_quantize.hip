@@ -784,9 +784,9 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     // the scaled weight, the sample weight s and the sampling mass.  The mass is s for the first centre and
     // s * (squared distance to the nearest centre chosen so far) afterwards; as s >= 0, multiplying by s and
     // rounding is monotone, so s * min(d_old, d_new) is min(s * d_old, s * d_new) bit for bit and the
-    // distances themselves need not be kept.  Bound: vector issue, 2^n rounds of seven instructions per weight (ten with a
-    // comparison and two selects in place of v_min_f64 and copies of x and s): 6144 x 4096 any4 588 -> 535 us, 4096 x 14336
-    // 1698 -> 1502 us together with the sums of the wavefronts, read several at a time.
+    // distances themselves need not be kept.  Bound: vector issue, 2^n rounds of six instructions per weight (ten with a
+    // comparison and two selects in place of v_min_f64, x converted every time and copies of x and s): 6144 x 4096 any4
+    // 588 -> 519 us, 4096 x 14336 1698 -> 1479 us together with the sums of the wavefronts, read several at a time.
     const float* const wrow = w + n * K64;
     const int C = (K + T - 1) / T;
     const int j0 = min(tid * C, K), cnt = min(j0 + C, K) - j0;
@@ -832,9 +832,13 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
             if (tid == 0) { cen[q] = cq; cen0[q] = cq; }
             return cq;
         };
-        double mass[16];
+        double mass[16], xd[16];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) mass[e] = (double)sv[e];
+        for (int e = 0; e < 16; ++e) {
+            mass[e] = (double)sv[e];
+            xd[e] = (double)xv[e];
+            asm volatile("" : "+v"(xd[e]));
+        }
 #pragma unroll 1
         for (int q = odd_row ? L : 0; q < L; ++q) {
             double part = 0.0;
@@ -860,12 +864,14 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
             for (int e = 0; e < 16; ++e) {
                 // (the empty asm statement keeps the conversions inside the loop over q: hoisted, they
                 // would hold 64 more registers for the whole start)
-                asm volatile("" : "+v"(xv[e]), "+v"(sv[e]));
-                const double d = (double)xv[e] - cq;
+                asm volatile("" : "+v"(sv[e]));
+                const double d = xd[e] - cq;
                 const double m = (double)sv[e] * (d * d);
                 asm("v_min_f64 %0, %1, %0" : "+v"(mass[e]) : "v"(m));   // (both are numbers)
             }
         }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) xv[e] = (float)xd[e];         // exact
         if (odd_row) {
             // a NaN or an infinity somewhere: a mass is replaced only by one that compares as smaller.  Nothing is kept
             // between the centres.
