@@ -118,7 +118,7 @@ __device__ __forceinline__ float wave_minmax(float v) {
 template <int BITS, int T>
 __device__ __forceinline__ void scale_row(const float* __restrict__ wrow, int64_t n, int G, int symmetric,
                                           uint16_t* __restrict__ scale, uint16_t* __restrict__ offset,
-                                          float* ws, float* alpha, float* beta = nullptr) {
+                                          float* ws, float* alpha) {
     constexpr int L = 1 << BITS;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const float qrange = symmetric ? (float)((1 << (BITS - 1)) - 1) : (float)(L - 1);
@@ -136,7 +136,6 @@ __device__ __forceinline__ void scale_row(const float* __restrict__ wrow, int64_
             scale[n * G + g] = (uint16_t)ab;
             offset[n * G + g] = (uint16_t)bb;
             alpha[g] = a;
-            if (beta) beta[g] = b;
         }
         const float d0 = v.x - b, d1 = v.y - b;
         reinterpret_cast<float2*>(ws + g * kGroup)[lane] = make_float2(d0 / a, d1 / a);
@@ -454,14 +453,14 @@ __global__ __launch_bounds__(QT) void quantize_kernel(
 //   kv [PADW] u32 x 2   the row's scaled weights (fp32, row order, in the first 4 K bytes) until the sort; then
 //                       the elements (order-preserving integer image of w_S, sample weight s as fp32 bits),
 //                       ascending in w_S.  (The per-weight method keeps its codes behind the scaled weights.)
-//   alpha, beta [KP/128] f32 | pre_s, pre_sx [T + 1] f64 (running sums before every 16th sorted element; the total)
+//   alpha [KP/128] f32 | pre_s, pre_sx [T + 1] f64 (running sums before every 16th sorted element; the total)
 //   scan [2 W] f64 | cen [L] f64 | cen0 [L] f64 | fin [L] u32 | misc [64] i32
 //   (the per-weight method's partial sums red [W][2][L] f64 lie over pre_s: 2 W L <= 2 (T + 1))
 constexpr int kSortedMaxK = 16384;
 constexpr size_t sorted_padw(int T) { return (size_t)T * 17; }
 constexpr size_t sorted_lds_bytes(int T, int bits) {
     const size_t W = (size_t)T / kWave, L = (size_t)1 << bits;
-    return sorted_padw(T) * 8 + 2 * ((size_t)T / 8) * 4 + 2 * ((size_t)T + 1) * 8 + 2 * W * 8 + 2 * L * 8 + L * 4 + 64 * 4;
+    return sorted_padw(T) * 8 + ((size_t)T / 8) * 4 + 2 * ((size_t)T + 1) * 8 + 2 * W * 8 + 2 * L * 8 + L * 4 + 64 * 4;
 }
 
 __device__ __forceinline__ int pad16(int p) { return p + (p >> 4); }
@@ -613,14 +612,15 @@ __device__ __forceinline__ uint32_t wave_minmax_u32(uint32_t v) {
 // instructions per thread where the bitonic network of 16 T elements takes ~8 k (K <= 4096) to ~11 k.  The order among
 // the elements of a bucket is (key, sample weight): the sorted row does not depend on the order in which the counters
 // were bumped.  Bound: LDS latency and vector issue.  6144 x 4096 any4 836 -> 698 us for the whole kernel, of which
-// the sort is 78 now; 4096 x 14336 2704 -> 2070 us, the sort 275 of it.  False, and nothing sorted, where the buckets would not do: a bucket of more than kBucketMost elements
-// (few distinct values, outliers), all weights equal, or a weight that is not finite.
-// `key`, `sv`: the thread's cnt elements; `scan`: 4 W words of scratch; `flag`: one word.  LDS of kv is free on entry
-// once every thread has arrived.
+// the sort is 78 now; 4096 x 14336 2704 -> 2070 us, the sort 275 of it.  False, and nothing sorted, where the buckets
+// would not do: a bucket of more than kBucketMost elements (few distinct values, outliers), all weights equal, or a
+// weight that is not finite.
+// `key`, `sv`: the 16 elements of a thread that has any (`mine`); `scan`: 4 W words of scratch; `flag`: one word.  LDS of
+// kv is free on entry once every thread has arrived.
 constexpr int kBucketMost = 32;
 template <int T>
 __device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, int* flag, const uint32_t (&key)[16],
-                                                const float (&sv)[16], int cnt, int K) {
+                                                const float (&sv)[16], bool mine, int K) {
     constexpr int W = T / kWave;
     constexpr int NB = 32 * T;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -628,8 +628,9 @@ __device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, int* 
     asm volatile("" : "+v"(tid));
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
-    for (int e = 0; e < 16; ++e)
-        if (e < cnt) { lo = min(lo, key[e]); hi = max(hi, key[e]); }
+    for (int e = 0; e < 16; ++e) { lo = min(lo, key[e]); hi = max(hi, key[e]); }
+    lo = mine ? lo : 0xFFFFFFFFu;
+    hi = mine ? hi : 0u;
     lo = wave_minmax_u32<false>(lo);
     hi = wave_minmax_u32<true>(hi);
     if (lane == 0) { scan[2 * wv] = lo; scan[2 * wv + 1] = hi; }
@@ -647,20 +648,19 @@ __device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, int* 
     for (int i = 0; i < 4; ++i) reinterpret_cast<uint4*>(hist)[i * T + tid] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     // bucket (monotone in the weight: one subtraction, one product, both rounded monotonically) and place in it
-    uint32_t slot[16];
-    bool crowded = false;
+    uint32_t slot[16] = {};
+    if (mine) {
+        uint32_t rmax = 0;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const uint32_t b = min((uint32_t)((key_f32(key[e]) - mn) * inv), (uint32_t)(NB - 1));
-        uint32_t r = 0;
-        if (e < cnt) {
+        for (int e = 0; e < 16; ++e) {
+            const uint32_t b = (uint32_t)__builtin_amdgcn_fmed3f((key_f32(key[e]) - mn) * inv, 0.0f, (float)(NB - 1));
             const uint32_t old = atomicAdd(&hist[b >> 1], (b & 1) ? 0x10000u : 1u);
-            r = (b & 1) ? old >> 16 : old & 0xFFFFu;
+            const uint32_t r = (b & 1) ? old >> 16 : old & 0xFFFFu;
+            rmax = max(rmax, r);
+            slot[e] = b | (r << 16);
         }
-        crowded |= r >= (uint32_t)kBucketMost;
-        slot[e] = b | (min(r, 255u) << 16);
+        if (rmax >= (uint32_t)kBucketMost) *flag = 1;
     }
-    if (crowded) *flag = 1;
     __syncthreads();
     if (*flag != 0) return false;
     // counters -> first position of every bucket; a thread has 32 neighbouring ones
@@ -694,57 +694,61 @@ __device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, int* 
     // first position (low half) and size of the element's bucket
     const uint16_t* const first = reinterpret_cast<const uint16_t*>(hist);
     uint32_t most = 0;
+    if (mine) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const uint32_t b = slot[e] & 0xFFFFu, r = slot[e] >> 16;
-        const uint32_t f = first[b], size = first[b + 1] - f;
-        slot[e] = f | (size << 16) | (r << 24);
-        most = e < cnt ? max(most, size) : most;
+        for (int e = 0; e < 16; ++e) {
+            const uint32_t b = slot[e] & 0xFFFFu, r = slot[e] >> 16;
+            const uint32_t f = first[b], size = first[b + 1] - f;
+            slot[e] = f | (size << 16) | (r << 24);
+            most = max(most, size);
+        }
     }
     __syncthreads();
     // into the buckets (no spare elements yet), and what sorts last behind the row: a look beyond a bucket's end
     // finds larger keys only
+    if (mine) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e)
-        if (e < cnt) kv[(slot[e] & 0xFFFFu) + (slot[e] >> 24)] = make_uint2(key[e], __float_as_uint(sv[e]));
+        for (int e = 0; e < 16; ++e) kv[(slot[e] & 0xFFFFu) + (slot[e] >> 24)] = make_uint2(key[e], __float_as_uint(sv[e]));
+    }
     if (tid < 8) kv[K + tid] = make_uint2(kPadKey, 0u);
     __syncthreads();
     most = wave_minmax_u32<true>(most);
-    uint32_t less[16];
+    if (mine) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) less[e] = 0;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const uint32_t f = e < cnt ? slot[e] & 0xFFFFu : 0u, size = (slot[e] >> 16) & 0xFFu, r = slot[e] >> 24;
-        const unsigned long long me = ((unsigned long long)key[e] << 32) | __float_as_uint(sv[e]);
-        uint32_t same = 0;
-        auto look = [&](uint32_t i) {
-            const uint2 v = kv[f + i];
-            const unsigned long long o = ((unsigned long long)v.x << 32) | v.y;
-            less[e] += o < me ? 1u : 0u;
-            same += o == me ? 1u : 0u;
-        };
-#pragma unroll
-        for (uint32_t i = 0; i < 4; ++i) look(i);
-        if (most > 4) {
-#pragma unroll 1
-            for (uint32_t i = 4; i < size; i += 4) {               // (reads at most three past the bucket)
-#pragma unroll
-                for (uint32_t t = 0; t < 4; ++t) look(i + t);
-            }
-        }
-        if (same > 1) {                                            // equal pairs: in the order of their places
-#pragma unroll 1
-            for (uint32_t i = 0; i < r; ++i) {
+        for (int e = 0; e < 16; ++e) {
+            const uint32_t f = slot[e] & 0xFFFFu, size = (slot[e] >> 16) & 0xFFu, r = slot[e] >> 24;
+            const unsigned long long me = ((unsigned long long)key[e] << 32) | __float_as_uint(sv[e]);
+            uint32_t less = 0, same = 0;
+            auto look = [&](uint32_t i) {
                 const uint2 v = kv[f + i];
-                less[e] += (v.x == key[e] && v.y == __float_as_uint(sv[e])) ? 1u : 0u;
+                const unsigned long long o = ((unsigned long long)v.x << 32) | v.y;
+                less += o < me ? 1u : 0u;
+                same += o == me ? 1u : 0u;
+            };
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) look(i);
+            if (most > 4) {
+#pragma unroll 1
+                for (uint32_t i = 4; i < size; i += 4) {           // (reads at most three past the bucket)
+#pragma unroll
+                    for (uint32_t t = 0; t < 4; ++t) look(i + t);
+                }
             }
+            if (same > 1) {                                        // equal pairs: in the order of their places
+#pragma unroll 1
+                for (uint32_t i = 0; i < r; ++i) {
+                    const uint2 v = kv[f + i];
+                    less += (v.x == key[e] && v.y == __float_as_uint(sv[e])) ? 1u : 0u;
+                }
+            }
+            slot[e] = f + less;
         }
     }
     __syncthreads();
+    if (mine) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e)
-        if (e < cnt) kv[pad16((int)((slot[e] & 0xFFFFu) + less[e]))] = make_uint2(key[e], __float_as_uint(sv[e]));
+        for (int e = 0; e < 16; ++e) kv[pad16((int)slot[e])] = make_uint2(key[e], __float_as_uint(sv[e]));
+    }
     for (int p = K + tid; p < 16 * T; p += T) kv[pad16(p)] = make_uint2(kPadKey, 0u);
     __syncthreads();
     return true;
@@ -765,8 +769,7 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     uint2* kv = reinterpret_cast<uint2*>(smem);
     float* ws = reinterpret_cast<float*>(smem);
     float* alpha = reinterpret_cast<float*>(smem + sorted_padw(T) * 8);
-    float* beta = alpha + T / 8;
-    double* pre_s = reinterpret_cast<double*>(beta + T / 8);   // [T + 1]
+    double* pre_s = reinterpret_cast<double*>(alpha + T / 8);   // [T + 1]
     double* pre_sx = pre_s + T + 1;             // [T + 1]
     double* scan = pre_sx + T + 1;              // [2 W]
     double* red = pre_s;                        // [W][2][L], per-weight method only: it has no running sums
@@ -778,29 +781,39 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t n = blockIdx.x;
     if (tid == 0) misc[3] = 0;
-    scale_row<BITS, T>(w + n * K64, n, G, symmetric, scale, offset, ws, alpha, beta);
+    scale_row<BITS, T>(w + n * K64, n, G, symmetric, scale, offset, ws, alpha);
 
-    // ---- 2. k-means++ with sample weights; thread t owns the chunk [t * C, (t + 1) * C), C <= 16, in registers:
+    // ---- 2. k-means++ with sample weights; thread t owns the 16 weights from 16 t on, if the row has them, in registers:
     // the scaled weight, the sample weight s and the sampling mass.  The mass is s for the first centre and
     // s * (squared distance to the nearest centre chosen so far) afterwards; as s >= 0, multiplying by s and
     // rounding is monotone, so s * min(d_old, d_new) is min(s * d_old, s * d_new) bit for bit and the
     // distances themselves need not be kept.  Bound: vector issue, 2^n rounds of six instructions per weight (ten with a
     // comparison and two selects in place of v_min_f64, x converted every time and copies of x and s): 6144 x 4096 any4
     // 588 -> 519 us, 4096 x 14336 1698 -> 1479 us together with the sums of the wavefronts, read several at a time.
-    const float* const wrow = w + n * K64;
-    const int C = (K + T - 1) / T;
-    const int j0 = min(tid * C, K), cnt = min(j0 + C, K) - j0;
+    // Sixteen weights a thread for every K, so that whole wavefronts have none where the row is shorter than the block's
+    // 16 T and skip the phases: with the row spread evenly, all of them ran all phases with most lanes idle.  With the
+    // codes from the sort's keys (below): 11525 x 1024 any4 726 -> 579 us, 6144 x 4096 528 -> 500, 4096 x 14336 1522 -> 1447.
+    const bool mine = tid * 16 < K;                                // (K is a multiple of 128)
+    const int j0 = mine ? tid * 16 : 0;
     float xv[16], sv[16];
     {
-        const float* const ap = act ? act : wrow;                  // (no activations: any K numbers, not used)
         bool odd = false;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int j = min(j0 + e, K - 1);
-            const float x = ws[j], av = ap[j], sw = alpha[j >> 7] * (act ? av : 1.0f);
-            odd |= __builtin_amdgcn_classf(x, 0x207) | __builtin_amdgcn_classf(sw, 0x207);   // a NaN or an infinity
-            xv[e] = e < cnt ? x : 0.0f;
-            sv[e] = e < cnt ? sw : 0.0f;                           // outside the chunk: mass +0, which changes no sum
+        for (int e = 0; e < 16; ++e) { xv[e] = 0.0f; sv[e] = 0.0f; }
+        if (mine) {
+            const float a = alpha[j0 >> 7];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 x4 = reinterpret_cast<const float4*>(ws + j0)[g];
+                float4 s4 = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+                if (act) s4 = reinterpret_cast<const float4*>(act + j0)[g];   // (a call's pointers are 16-byte aligned)
+                const float x[4] = {x4.x, x4.y, x4.z, x4.w}, s[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { xv[4 * g + i] = x[i]; sv[4 * g + i] = a * s[i]; }
+            }
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                odd |= __builtin_amdgcn_classf(xv[e], 0x207) | __builtin_amdgcn_classf(sv[e], 0x207);   // a NaN or an infinity
         }
         if (odd) misc[3] = 1;
         __syncthreads();
@@ -822,7 +835,7 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
             if (lane == 0) before = base;
             if (total > 0.0) {
                 const double t = (double)u[n * L + q] * total;
-                if (before <= t && inc > t && cnt > 0) atomicMin(&misc[q & 1], j0 + walk(before, t));
+                if (mine && before <= t && inc > t) atomicMin(&misc[q & 1], j0 + walk(before, t));
             } else if (tid == 0) {
                 const int64_t j = (int64_t)((double)u[n * L + q] * (double)K);
                 misc[q & 1] = (int)min(j, (int64_t)K - 1);
@@ -842,11 +855,13 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
 #pragma unroll 1
         for (int q = odd_row ? L : 0; q < L; ++q) {
             double part = 0.0;
+            if (mine) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) part += mass[e];
+                for (int e = 0; e < 16; ++e) part += mass[e];
+            }
             const double cq = draw(q, part, [&](double run, double t) -> int {
                 // the first weight at which the running mass exceeds t; if rounding leaves none, the last one
-                // with any mass (masses outside the chunk are 0)
+                // with any mass
                 int pick = 16, last = 0;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
@@ -860,14 +875,16 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
 #pragma unroll
                 for (int e = 0; e < 16; ++e) mass[e] = __hiloint2double(0x7FF00000, 0);
             }
+            if (mine) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                // (the empty asm statement keeps the conversions inside the loop over q: hoisted, they
-                // would hold 64 more registers for the whole start)
-                asm volatile("" : "+v"(sv[e]));
-                const double d = xd[e] - cq;
-                const double m = (double)sv[e] * (d * d);
-                asm("v_min_f64 %0, %1, %0" : "+v"(mass[e]) : "v"(m));   // (both are numbers)
+                for (int e = 0; e < 16; ++e) {
+                    // (the empty asm statement keeps the conversions inside the loop over q: hoisted, they
+                    // would hold 64 more registers for the whole start)
+                    asm volatile("" : "+v"(sv[e]));
+                    const double d = xd[e] - cq;
+                    const double m = (double)sv[e] * (d * d);
+                    asm("v_min_f64 %0, %1, %0" : "+v"(mass[e]) : "v"(m));   // (both are numbers)
+                }
             }
         }
 #pragma unroll
@@ -887,10 +904,10 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
                     return m;
                 };
                 double part = 0.0;
-                for (int e = 0; e < cnt; ++e) part += mass_of(j0 + e);
+                for (int e = 0; e < (mine ? 16 : 0); ++e) part += mass_of(j0 + e);
                 draw(q, part, [&](double run, double t) -> int {
                     int pick = -1, last = 0;
-                    for (int e = 0; e < cnt && pick < 0; ++e) {
+                    for (int e = 0; e < 16 && pick < 0; ++e) {
                         const double m = mass_of(j0 + e);
                         run += m;
                         if (m > 0.0) last = e;
@@ -904,15 +921,15 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     }
 
     // ---- sort the row: elements (order-preserving image of w_S, sample weight), ascending; every thread
-    // brings the chunk it holds
+    // brings the chunk it holds, and keeps its keys for the codes
+    uint32_t key[16];
     {
-        uint32_t key[16];
 #pragma unroll
         for (int e = 0; e < 16; ++e) key[e] = f32_key(xv[e]);
-        if (!sort_by_buckets<T>(kv, reinterpret_cast<uint32_t*>(scan), misc + 3, key, sv, cnt, K)) {
+        if (!sort_by_buckets<T>(kv, reinterpret_cast<uint32_t*>(scan), misc + 3, key, sv, mine, K)) {
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-                kv[tid * 17 + e] = e < cnt ? make_uint2(key[e], __float_as_uint(sv[e])) : make_uint2(kPadKey, 0u);
+                kv[tid * 17 + e] = mine ? make_uint2(key[e], __float_as_uint(sv[e])) : make_uint2(kPadKey, 0u);
             __syncthreads();
             sort_first16<T>(kv);
             for (int m = 5; m <= LOGKP; ++m) {
@@ -1129,41 +1146,38 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     if (misc[2] != 0) {
         // two unequal centres too close for the sorted search: the row again, per weight, from its starting centres
         __syncthreads();
-        scale_row<BITS, T>(w + n * K64, n, G, symmetric, scale, offset, ws, alpha, beta);
+        scale_row<BITS, T>(w + n * K64, n, G, symmetric, scale, offset, ws, alpha);
         if (tid < L) cen[tid] = cen0[tid];
         __syncthreads();
         lloyd_per_weight_lean<BITS, T>(ws, smem + (size_t)K * 4, alpha, red, cen, misc, act, K64, iters, n, codes_out, lut,
                                        msteps);
         return;
     }
-    // the codes in row order: scale the row again (the same arithmetic as in step 1) and place every weight
-    // among the clusters' smallest members; a cluster never splits equal weights, so this is its range
-    {
+    // the codes in row order: every weight's place among the clusters' smallest members; a cluster never splits equal
+    // weights, so this is its range.  The smallest members ascend with the rank once an empty cluster takes that of the next
+    // one, so four comparisons and the selects of what to compare with do (15 comparisons and selects otherwise).  The keys
+    // are those of the sort: scaling the row once more cost a read and a division per weight.
+    if (mine) {
         uint32_t fk[L];
+        fk[L - 1] = fin[L - 1];
 #pragma unroll
-        for (int i = 0; i < L; ++i) fk[i] = fin[i];
-        uint8_t* crow = codes_out + n * K64;
-        for (int j = tid * 16; j < K; j += T * 16) {
-            const float a = alpha[j >> 7], b = beta[j >> 7];
-            uint32_t out[4];
+        for (int i = L - 2; i > 0; --i) fk[i] = min(fin[i], fk[i + 1]);
+        uint32_t out[4] = {};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float4 v = *reinterpret_cast<const float4*>(wrow + j + 4 * i);
-                const float f[4] = {v.x, v.y, v.z, v.w};
-                uint32_t o = 0;
+        for (int e = 0; e < 16; ++e) {
+            uint32_t f[L], code = 0;                               // f[i]: fk[i] among those still in question
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float dlt = f[t] - b;
-                    const uint32_t key = f32_key(dlt / a);
-                    uint32_t code = 0;
+            for (int i = 1; i < L; ++i) f[i] = fk[i];
 #pragma unroll
-                    for (int q = 1; q < L; ++q) code = key >= fk[q] ? q : code;
-                    o |= code << (8 * t);
-                }
-                out[i] = o;
+            for (int h = L / 2; h > 0; h >>= 1) {
+                const bool up = key[e] >= f[h];
+                code |= up ? (uint32_t)h << (8 * (e & 3)) : 0u;
+#pragma unroll
+                for (int i = 1; i < h; ++i) f[i] = up ? f[h + i] : f[i];
             }
-            *reinterpret_cast<uint4*>(crow + j) = make_uint4(out[0], out[1], out[2], out[3]);
+            out[e >> 2] |= code;
         }
+        *reinterpret_cast<uint4*>(codes_out + n * K64 + j0) = make_uint4(out[0], out[1], out[2], out[3]);
     }
 }
 

@@ -214,3 +214,12 @@ def test_quantize_rows_with_crowded_buckets(any4, qoracle, K, unit_act):
     w[7] = np.round(w[7] * 2000) / 2000                                      # few distinct values per group
     for symmetric in (False, True):
         run_and_compare(any4, qoracle, w, None if unit_act else qc.act, qc.u, 4, symmetric, 20, ("crowded", K, symmetric))
+
+
+@pytest.mark.parametrize("bits", (4, 3, 2))
+@pytest.mark.parametrize("K", (1024, 4224, 8064, 8320, 16256))
+def test_quantize_rows_that_leave_threads_idle(any4, qoracle, bits, K):
+    """A thread of the sorted-row kernel owns 16 weights: rows that end inside a wavefront, and rows that need little
+    more than a quarter or half of the block's threads, or all but a few."""
+    qc = inputs.make_quant_case(5, K, bits, seed=K + bits)
+    run_and_compare(any4, qoracle, qc.w, qc.act, qc.u, bits, False, 20, ("idle threads", K, bits))
