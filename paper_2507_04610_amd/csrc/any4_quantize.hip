@@ -19,8 +19,8 @@
 //        lower index) - and take every cluster's sums as differences of running sums: O(2^n log K)
 //        instead of O(K 2^n) per pass.  The E-step predicate is monotone along the sorted row as
 //        long as unequal centres are further apart than the rounding of the distances; a row in
-//        which two unequal centres come closer than `centre_gap * max|w_S|` is finished by the
-//        other method from its starting centres;
+//        which two unequal centres come closer than `centre_gap * max|w_S|`, and one with a NaN or an
+//        infinity, is finished by the other method from its starting centres;
 //      per weight (larger K, and the rows just named): one pass assigns every weight to its nearest
 //        centre and at the same time accumulates, per thread and per centre, sum(s * w_S) and
 //        sum(s); the partial sums are combined in a fixed order (lanes, then wavefronts);
@@ -776,11 +776,11 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     double* cen = scan + 2 * W;                 // [L]
     double* cen0 = cen + L;                     // [L]
     uint32_t* fin = reinterpret_cast<uint32_t*>(cen0 + L);   // [L] smallest key of the cluster of rank i (none: kPadKey)
-    int* misc = reinterpret_cast<int*>(fin + L);// [0], [1] selected index (by turns); [2] method flag; [3] a weight that is no number, crowded buckets; [40] as below
+    int* misc = reinterpret_cast<int*>(fin + L);// [0], [1] selected index (by turns); [2] method flag; [3] crowded buckets; [4] a weight that is not finite; [40] as below
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t n = blockIdx.x;
-    if (tid == 0) misc[3] = 0;
+    if (tid == 0) misc[4] = 0;
     scale_row<BITS, T>(w + n * K64, n, G, symmetric, scale, offset, ws, alpha);
 
     // ---- 2. k-means++ with sample weights; thread t owns the 16 weights from 16 t on, if the row has them, in registers:
@@ -815,9 +815,9 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
             for (int e = 0; e < 16; ++e)
                 odd |= __builtin_amdgcn_classf(xv[e], 0x207) | __builtin_amdgcn_classf(sv[e], 0x207);   // a NaN or an infinity
         }
-        if (odd) misc[3] = 1;
+        if (odd) misc[4] = 1;
         __syncthreads();
-        const bool odd_row = misc[3] != 0;
+        const bool odd_row = misc[4] != 0;
         // one draw: the threads' masses are summed and scanned, the thread whose chunk holds the draw walks it
         auto draw = [&](int q, double part, auto&& walk) -> double {
             double inc = wave_inclusive_sum(part, lane);
@@ -998,7 +998,7 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
         int prev_s = -2, prev_e = -2;
         int done = 0, chunk = 0;                                   // chunk: where the centre's lower boundary was last
         float last_mid = 0.0f, density = 0.0f;
-        bool fallback = false, some = false;
+        bool fallback = misc[4] != 0, some = false;                // (no order among weights that are no numbers)
         int start = 0;
         auto below_f64 = [](double v) { return row_shr_f64<1>(v); };
         auto below_i32 = [](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false); };
@@ -1018,7 +1018,7 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
             const unsigned long long m = __ballot(b) >> i;
             return __popc((unsigned)m & 0x00010001u) + __popc((unsigned)(m >> 32) & 0x00010001u);
         };
-        for (;;) {
+        while (!fallback) {
             // the centres in order of (value, index)?  Ranked anew, 2^n comparisons per centre, only where they are not
             // (the centres of a one-dimensional k-means hardly ever overtake each other)
             double dprev = below_f64(d);
@@ -1144,7 +1144,7 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     }
     __syncthreads();
     if (misc[2] != 0) {
-        // two unequal centres too close for the sorted search: the row again, per weight, from its starting centres
+        // two unequal centres too close for the sorted search, or a weight that is not finite: the row again, per weight, from its starting centres
         __syncthreads();
         scale_row<BITS, T>(w + n * K64, n, G, symmetric, scale, offset, ws, alpha);
         if (tid < L) cen[tid] = cen0[tid];

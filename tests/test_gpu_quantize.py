@@ -223,3 +223,26 @@ def test_quantize_rows_that_leave_threads_idle(any4, qoracle, bits, K):
     more than a quarter or half of the block's threads, or all but a few."""
     qc = inputs.make_quant_case(5, K, bits, seed=K + bits)
     run_and_compare(any4, qoracle, qc.w, qc.act, qc.u, bits, False, 20, ("idle threads", K, bits))
+
+
+@pytest.mark.parametrize("bits", (4, 2))
+@pytest.mark.parametrize("K", (384, 4096, 14336))
+def test_quantize_rows_that_are_not_finite(any4, bits, K):
+    """Rows with a NaN or an infinity have no sorted order: they get what the per-weight method gives them (tables up to the
+    sign and payload of NaNs)."""
+    qc = inputs.make_quant_case(6, K, bits, seed=K + bits)
+    w = qc.w.copy()
+    w[0, 5] = np.nan
+    w[1, 7] = np.inf
+    w[2, 9] = -np.inf
+    w[3, 200:230] = np.nan
+    w[4] = np.nan
+    w, u = torch.from_numpy(w).cuda(), torch.from_numpy(qc.u).cuda()
+    for symmetric in (False, True):
+        for act in (torch.from_numpy(qc.act).cuda(), None):
+            got = any4.any4_quantize(w, act, u, bits, symmetric, 20)
+            ref = any4.any4_quantize(w, act, u, bits, symmetric, 20, centre_gap=METHODS["per_weight"])
+            for k in ("codes_u8", "msteps"):
+                assert torch.equal(got[k], ref[k]), (k, symmetric, act is None)
+            for k in ("lut", "scale", "offset"):
+                assert torch.equal(got[k].float().nan_to_num(nan=1e30), ref[k].float().nan_to_num(nan=1e30)), (k, symmetric)
