@@ -762,8 +762,8 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     int32_t* __restrict__ msteps) {
     constexpr int L = 1 << BITS;
     constexpr int W = T / kWave;
-    constexpr int LOGKP = T == 256 ? 12 : T == 512 ? 13 : 14;
-    static_assert(T == 256 || T == 512 || T == 1024, "16 elements per thread, 4096 to 16384 per block");
+    constexpr int LOGKP = T == 64 ? 10 : T == 128 ? 11 : T == 256 ? 12 : T == 512 ? 13 : 14;
+    static_assert(16 * T == 1 << LOGKP, "16 elements per thread, 1024 to 16384 per block");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int K = (int)K64, G = K / kGroup;
     uint2* kv = reinterpret_cast<uint2*>(smem);
@@ -937,7 +937,7 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
                 if constexpr (LOGKP > 12) {
                     if (top >= 12) sort_round<T, 12, LOGKP - 12>(kv, m, top);
                 }
-                if (top >= 8) sort_round<T, 8, 4>(kv, m, min(top, 11));
+                if (top >= 8) sort_round<T, 8, LOGKP < 12 ? LOGKP - 8 : 4>(kv, m, min(top, 11));
                 if (top >= 4) sort_round<T, 4, 4>(kv, m, min(top, 7));
                 sort_round<T, 0, 4>(kv, m, min(top, 3));
             }
@@ -1199,9 +1199,15 @@ hipError_t launch_quantize(const float* w, const float* act, const float* u, int
         hipLaunchKernelGGL((quantize_sorted_kernel<B, T>), dim3((unsigned)N), dim3(T), sorted_lds_bytes(T, B), stream, w, \
                            act, u, K, symmetric, iters, centre_gap, codes, lut, scale, offset, msteps);           \
     } while (0)
+        // The smallest block that holds the row: a compute unit holds 16 wavefronts of this kernel, so a row of at most 1024
+        // weights in a block of one wavefront has 15 others beside it and in one of four only three.  any4 against four
+        // wavefronts: 11525 x 1024 584 -> 270 us, 11525 x 1152 645 -> 411 us, 28000 x 2048 1650 -> 1074 us; 512 x 1024,
+        // where the chip is nearly empty either way, 57 us both.
 #define ANY4_QUANT_ST(B)                                                                                          \
     do {                                                                                                          \
-        if (K <= 4096) ANY4_QUANT_S(B, 256);                                                                      \
+        if (K <= 1024) ANY4_QUANT_S(B, 64);                                                                       \
+        else if (K <= 2048) ANY4_QUANT_S(B, 128);                                                                 \
+        else if (K <= 4096) ANY4_QUANT_S(B, 256);                                                                      \
         else if (K <= 8192) ANY4_QUANT_S(B, 512);                                                                 \
         else ANY4_QUANT_S(B, 1024);                                                                               \
     } while (0)

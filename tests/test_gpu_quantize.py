@@ -197,7 +197,7 @@ def test_quantize_rejects_bad_arguments(any4):
 
 
 @pytest.mark.parametrize("unit_act", (False, True))
-@pytest.mark.parametrize("K", (640, 4096, 4224, 14336))
+@pytest.mark.parametrize("K", (640, 1024, 2048, 4096, 4224, 14336))
 def test_quantize_rows_with_crowded_buckets(any4, qoracle, K, unit_act):
     """The sort places a row's weights in buckets of equal width and hands rows with more than 32 in a bucket to
     the bitonic network: rows on both sides of that limit, rows with many equal weights (with unit activations also
@@ -246,3 +246,12 @@ def test_quantize_rows_that_are_not_finite(any4, bits, K):
                 assert torch.equal(got[k], ref[k]), (k, symmetric, act is None)
             for k in ("lut", "scale", "offset"):
                 assert torch.equal(got[k].float().nan_to_num(nan=1e30), ref[k].float().nan_to_num(nan=1e30)), (k, symmetric)
+
+
+@pytest.mark.parametrize("method", sorted(METHODS))
+@pytest.mark.parametrize("bits", (4, 3, 2))
+@pytest.mark.parametrize("K", (896, 1024, 1152, 2048, 2176))
+def test_quantize_short_rows(any4, qoracle, bits, K, method):
+    """Blocks of one, two and four wavefronts, on both sides of the row lengths at which the next larger one is taken."""
+    qc = inputs.make_quant_case(19, K, bits, seed=5 * K + bits)
+    run_and_compare(any4, qoracle, qc.w, qc.act, qc.u, bits, False, 20, (method, K, bits), centre_gap=METHODS[method])
