@@ -1207,7 +1207,7 @@ hipError_t launch_quantize(const float* w, const float* act, const float* u, int
     do {                                                                                                          \
         if (K <= 1024) ANY4_QUANT_S(B, 64);                                                                       \
         else if (K <= 2048) ANY4_QUANT_S(B, 128);                                                                 \
-        else if (K <= 4096) ANY4_QUANT_S(B, 256);                                                                      \
+        else if (K <= 4096) ANY4_QUANT_S(B, 256);                                                                 \
         else if (K <= 8192) ANY4_QUANT_S(B, 512);                                                                 \
         else ANY4_QUANT_S(B, 1024);                                                                               \
     } while (0)
