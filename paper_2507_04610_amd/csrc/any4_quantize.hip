@@ -1094,6 +1094,7 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
             const int c0 = max(chunk - 2, 0), c1 = min(chunk + 2, nch - 1);
             const uint32_t key0 = kv[c0 * 17].x, key1 = kv[c1 * 17].x;
             const double run_s = pre_s[chunk], run_sx = pre_sx[chunk];
+            const double next_s = pre_s[chunk + 1], next_sx = pre_sx[chunk + 1];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const double x = (double)key_f32(v[k].x), sw = (double)__uint_as_float(v[k].y);
@@ -1106,6 +1107,10 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
             start = seek ? chunk * 16 + before : 0;
             ss = rows_sum(ss) + run_s;
             sx = rows_sum(sx) + run_sx;
+            // (a boundary between two chunks, or at the row's end, always takes the running sums' own entry: the sums up to
+            // a position are then one number whichever chunk a search came from, and an empty cluster's mass is exactly 0)
+            ss = before == 16 ? next_s : ss;
+            sx = before == 16 ? next_sx : sx;
             last_mid = mid;                                        // chunks per unit of weight around it, for the next guess
             density = (float)(c1 - c0) * __builtin_amdgcn_rcpf(key_f32(key1) - key_f32(key0));
             // the range ends where the next run's begins

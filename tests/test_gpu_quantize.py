@@ -255,3 +255,24 @@ def test_quantize_short_rows(any4, qoracle, bits, K, method):
     """Blocks of one, two and four wavefronts, on both sides of the row lengths at which the next larger one is taken."""
     qc = inputs.make_quant_case(19, K, bits, seed=5 * K + bits)
     run_and_compare(any4, qoracle, qc.w, qc.act, qc.u, bits, False, 20, (method, K, bits), centre_gap=METHODS[method])
+
+
+@pytest.mark.parametrize("K", (384, 1024, 4096, 14336))
+def test_quantize_empty_clusters_keep_their_centres(any4, qoracle, K):
+    """Rows of 3 to 6 distinct values, most of whose centres win no weight, with centre_gap 0, which hands hardly any
+    row over: an empty cluster's mass is a difference of two running sums up to the same position and has to be exactly 0,
+    wherever that position lies (the row's end, between two of the sums' chunks).  The activations span 14 decades, so
+    that sums in another order differ.  A table entry is one of the row's values, give or take an fp64 rounding."""
+    rng = np.random.default_rng(K)
+    N = 400
+    w = np.empty((N, K), np.float32)
+    for i in range(N):
+        v = rng.standard_normal(rng.integers(3, 7)).astype(np.float32)
+        w[i] = np.concatenate([rng.permutation(np.resize(v, 128)) for _ in range(K // 128)])
+    act = (10.0 ** rng.uniform(-14, 0, K)).astype(np.float32)
+    u = rng.random((N, 16), dtype=np.float32)
+    ref = qoracle.quantize(w, act, u, 4, threads=8)
+    got = any4.any4_quantize(torch.from_numpy(w).cuda(), torch.from_numpy(act).cuda(), torch.from_numpy(u).cuda(), 4,
+                             centre_gap=0.0)
+    bad = np.argwhere((bits16(got["lut"]) != ref["lut"]).any(axis=1))[:, 0]
+    assert bad.size == 0, (K, len(bad), bad[:5].tolist())
