@@ -239,8 +239,9 @@ int any4_quantize(const float* w, const float* act, const float* u, int64_t N, i
  * apart than the rounding of a distance; a row in which two unequal centres come closer than
  * centre_gap * max|w_S| is done again from its starting centres by the plain method (every weight
  * against every centre in every pass), which is also the method of longer rows.
- *   centre_gap  >= 0: as described (any4_quantize passes 2^-40); a huge value sends every row with two
- *               unequal centres through the hand-over; < 0: the plain method for all rows.
+ *   centre_gap  >= 0: as described (any4_quantize passes 2^-40), values below 2^-49 as 2^-49, the least
+ *               distance at which that holds; a huge value sends every row with two unequal centres
+ *               through the hand-over; < 0: the plain method for all rows.
  * Both methods take every decision in fp64 on the same fp32 inputs and differ only in the
  * association of the fp64 sums.  All other arguments, errors and limits as any4_quantize; NaN for
  * centre_gap returns ANY4_ERR_SHAPE.

@@ -754,6 +754,13 @@ __device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, int* 
     return true;
 }
 
+// The least distance of unequal centres, in units of M = max|w_S|, at which the E-step's comparison of two of them is
+// monotone along the row whatever the caller's centre_gap.  With distances p, q of a weight to centres d apart and
+// u = 2^-53, the rounded squares differ from p^2, q^2 by at most 3 u of them: outside the two centres |p - q| = d, so the
+// comparison comes out right where d (p + q) > 3 u (p^2 + q^2), hence for d >= 12 u M; between them both rounded squares
+// are monotone in the weight.
+constexpr double kLeastGap = 0x1p-49;
+
 template <int BITS, int T>
 __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     const float* __restrict__ w, const float* __restrict__ act, const float* __restrict__ u,
@@ -994,7 +1001,8 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
         double d = live ? cen[i] : 0.0;
         int own = i;
         const double maxabs = fmax(fabs((double)key_f32(kv[0].x)), fabs((double)key_f32(kv[pad16(K - 1)].x)));
-        const double tol = centre_gap * maxabs;
+        const double tol = fmax(centre_gap, kLeastGap) * maxabs;
+        const double total_s = pre_s[nch], total_sx = pre_sx[nch];
         int prev_s = -2, prev_e = -2;
         int done = 0, chunk = 0;                                   // chunk: where the centre's lower boundary was last
         float last_mid = 0.0f, density = 0.0f;
@@ -1094,7 +1102,6 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
             const int c0 = max(chunk - 2, 0), c1 = min(chunk + 2, nch - 1);
             const uint32_t key0 = kv[c0 * 17].x, key1 = kv[c1 * 17].x;
             const double run_s = pre_s[chunk], run_sx = pre_sx[chunk];
-            const double next_s = pre_s[chunk + 1], next_sx = pre_sx[chunk + 1];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const double x = (double)key_f32(v[k].x), sw = (double)__uint_as_float(v[k].y);
@@ -1107,10 +1114,9 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
             start = seek ? chunk * 16 + before : 0;
             ss = rows_sum(ss) + run_s;
             sx = rows_sum(sx) + run_sx;
-            // (a boundary between two chunks, or at the row's end, always takes the running sums' own entry: the sums up to
-            // a position are then one number whichever chunk a search came from, and an empty cluster's mass is exactly 0)
-            ss = before == 16 ? next_s : ss;
-            sx = before == 16 ? next_sx : sx;
+            // (the row's end takes the running sums' own entry: the mass of an empty last cluster is exactly 0)
+            ss = start == K ? total_s : ss;
+            sx = start == K ? total_sx : sx;
             last_mid = mid;                                        // chunks per unit of weight around it, for the next guess
             density = (float)(c1 - c0) * __builtin_amdgcn_rcpf(key_f32(key1) - key_f32(key0));
             // the range ends where the next run's begins
@@ -1123,8 +1129,8 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
             }
             const int end = nxt < 0 ? K : s_nxt;
             bad = bad || (rep && end < start);
-            const double den = (nxt < 0 ? pre_s[nch] : e_ss) - ss;
-            const double num = (nxt < 0 ? pre_sx[nch] : e_sx) - sx;
+            const double den = (nxt < 0 ? total_s : e_ss) - ss;
+            const double num = (nxt < 0 ? total_sx : e_sx) - sx;
             // did any weight change its centre?  compare every centre's range with the previous pass
             some = rep && start < end;
             const int rs = some ? start : -1, re = some ? end : -1;

@@ -276,3 +276,25 @@ def test_quantize_empty_clusters_keep_their_centres(any4, qoracle, K):
                              centre_gap=0.0)
     bad = np.argwhere((bits16(got["lut"]) != ref["lut"]).any(axis=1))[:, 0]
     assert bad.size == 0, (K, len(bad), bad[:5].tolist())
+
+
+@pytest.mark.parametrize("gap", (0.0, 1e-18))
+@pytest.mark.parametrize("K", (128, 640))
+def test_quantize_centre_gaps_below_the_least(any4, qoracle, K, gap):
+    """Rows of 3 to 6 values of very different size: centres a rounding apart, whose comparison ties far away from them and
+    then goes by their index.  They have to be handed over however small the centre_gap."""
+    rng = np.random.default_rng(K)
+    N = 1000
+    w = np.empty((N, K), np.float32)
+    for i in range(N):
+        m = rng.integers(3, 7)
+        v = (10.0 ** -np.arange(m) * rng.uniform(1, 2, m)).astype(np.float32)
+        w[i] = np.concatenate([rng.permutation(np.resize(v, 128)) for _ in range(K // 128)])
+    act = (0.05 + np.abs(rng.standard_normal(K))).astype(np.float32)
+    u = rng.random((N, 16), dtype=np.float32)
+    run_and_compare(any4, qoracle, w, act, u, 4, False, 20, ("least gap", K, gap), centre_gap=gap, by_value=range(N))
+    ref = qoracle.quantize(w, act, u, 4, threads=8)
+    got = any4.any4_quantize(torch.from_numpy(w).cuda(), torch.from_numpy(act).cuda(), torch.from_numpy(u).cuda(), 4,
+                             centre_gap=gap)
+    bad = np.argwhere((bits16(got["lut"]) != ref["lut"]).any(axis=1))[:, 0]
+    assert bad.size == 0, (K, len(bad), bad[:5].tolist())
