@@ -606,23 +606,52 @@ __device__ __forceinline__ uint32_t wave_minmax_u32(uint32_t v) {
     return pick(pick(a, b), pick(c, d));
 }
 
+// `n`, and one more if element `o` comes before `me` in the order (key, sample weight, place in the bucket), where its place
+// less PLACE is `d` below that of `me`: one borrow carried through the three words, four instructions at full rate (a
+// comparison of 64-bit integers is not one).
+template <int PLACE>
+__device__ __forceinline__ uint32_t count_below(uint32_t n, uint2 o, uint2 me, int d) {
+    uint32_t t;
+    asm("v_cmp_lt_i32_e32 vcc, %6, %7\n\t"
+        "v_subb_co_u32_e32 %1, vcc, %2, %3, vcc\n\t"
+        "v_subb_co_u32_e32 %1, vcc, %4, %5, vcc\n\t"
+        "v_addc_co_u32_e32 %0, vcc, 0, %0, vcc"
+        : "+v"(n), "=&v"(t) : "v"(o.y), "v"(me.y), "v"(o.x), "v"(me.x), "n"(PLACE), "v"(d) : "vcc");
+    return n;
+}
+
 // Sort by distribution: 32 T buckets of equal width between the row's smallest and largest scaled weight, filled by a
 // counting sort (two 16-bit counters to a word of LDS); then every element counts the smaller ones of its bucket.
-// Group scaling spreads a row over a fixed range, so a bucket holds about one element, and the sort is ~1.5 k
+// Group scaling spreads a row over a fixed range, so most buckets hold about one element, and the sort is ~1.5 k
 // instructions per thread where the bitonic network of 16 T elements takes ~8 k (K <= 4096) to ~11 k.  The order among
 // the elements of a bucket is (key, sample weight): the sorted row does not depend on the order in which the counters
-// were bumped.  Bound: LDS latency and vector issue.  6144 x 4096 any4 836 -> 698 us for the whole kernel, of which
-// the sort is 78 now; 4096 x 14336 2704 -> 2070 us, the sort 275 of it.  False, and nothing sorted, where the buckets
-// would not do: a bucket of more than kBucketMost elements (few distinct values, outliers), all weights equal, or a
-// weight that is not finite.
-// `key`, `sv`: the 16 elements of a thread that has any (`mine`); `scan`: 4 W words of scratch; `flag`: one word.  LDS of
-// kv is free on entry once every thread has arrived.
-constexpr int kBucketMost = 32;
+// were bumped.  Bound: LDS latency and vector issue.  Against the network, fp32 weights: 6144 x 4096 any4 836 -> 698 us for
+// the whole kernel, of which the sort was 78 then; 4096 x 14336 2704 -> 2070 us, the sort 275 of it.
+// Equal weights crowd a bucket.  Weights that are bf16 numbers do so by nature: the offset is a group's smallest weight
+// itself, which scales to exactly 0, once a group at least (112 - 130 in a row of 14336), and pruned weights are equal
+// within a group.  The elements of a bucket of more than kBucketOwn go on a list and are ranked from there by four lanes
+// each: left with their owners, a few of them in a wavefront make all its lanes go round the bucket.  The list is as
+// large as the LDS that is free here, 4 T elements; a row with more takes it in several rounds.  bf16 weights, the network
+// (what they had when a bucket of more than 32 sent a row there) against the list: 4096 x 14336 2055 -> 1461 us (fp32 1386),
+// 4096 x 8192 904 -> 654, 6144 x 4096 591 -> 502; half of 4096 x 14336 pruned 2159 -> 1955.
+// False, and nothing sorted, where the buckets would not do: all weights equal, a weight that is not finite, a bucket of
+// more than kBucketMost (what a slot has bits for), or a list that costs more than the network.  Its cost is counted in
+// looks, the squares of the sizes of its buckets.  The network wins from 46 looks per weight of the row on where equal
+// weights are neighbours, whose threads look at the same elements, and from 25 on where they lie scattered over the row
+// (4096 x 14336; at K = 1024 .. 4096 from 35 - 44 and from 20 - 25).  Equal scaled weights are mostly of one group, and half of
+// the weights pruned make 32 - 44, so kBucketLooks is at the former; a row of 352 scattered values, 40 weights each, 39
+// looks per weight, pays for it (2286 us against 1775).  Sizes from 8 to 24 as kBucketOwn time alike.
+// `key`, `sv`: the 16 elements of a thread that has any (`mine`); scratch: `scan` 4 W words, `list` 4 T words, `flag` one and
+// `count` two.  LDS of kv is free on entry once every thread has arrived.
+constexpr uint32_t kBucketOwn = 16;
+constexpr uint32_t kBucketMost = 512;
+constexpr uint32_t kBucketLooks = 44;             // per weight of the row
 template <int T>
-__device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, int* flag, const uint32_t (&key)[16],
-                                                const float (&sv)[16], bool mine, int K) {
+__device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, uint32_t* list, int* flag, int* count,
+                                                const uint32_t (&key)[16], const float (&sv)[16], bool mine, int K) {
     constexpr int W = T / kWave;
-    constexpr int NB = 32 * T;
+    constexpr int NB = 32 * T, LIST = 4 * T;
+    static_assert(16 * T <= 1 << 14 && kBucketMost <= 512, "an element's slot: 14 bits of position, 9 of its bucket's size, 9 of its place");
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
@@ -634,7 +663,7 @@ __device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, int* 
     lo = wave_minmax_u32<false>(lo);
     hi = wave_minmax_u32<true>(hi);
     if (lane == 0) { scan[2 * wv] = lo; scan[2 * wv + 1] = hi; }
-    if (tid == 0) *flag = 0;
+    if (tid == 0) { *flag = 0; count[0] = count[1] = 0; }
     __syncthreads();                                               // every thread is done with what lay in kv
     uint32_t* const hist = reinterpret_cast<uint32_t*>(kv);        // [NB / 2] words, and one counter more
 #pragma unroll 1
@@ -648,9 +677,8 @@ __device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, int* 
     for (int i = 0; i < 4; ++i) reinterpret_cast<uint4*>(hist)[i * T + tid] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     // bucket (monotone in the weight: one subtraction, one product, both rounded monotonically) and place in it
-    uint32_t slot[16] = {};
+    uint32_t slot[16] = {}, rmax = 0;
     if (mine) {
-        uint32_t rmax = 0;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const uint32_t b = (uint32_t)__builtin_amdgcn_fmed3f((key_f32(key[e]) - mn) * inv, 0.0f, (float)(NB - 1));
@@ -659,10 +687,21 @@ __device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, int* 
             rmax = max(rmax, r);
             slot[e] = b | (r << 16);
         }
-        if (rmax >= (uint32_t)kBucketMost) *flag = 1;
+        if (rmax >= kBucketMost) *flag = 1;
+    }
+    if (__ballot(rmax >= kBucketOwn) != 0ull) {
+        // squares of the sizes of the buckets with more than kBucketOwn elements, by the places in them
+        uint32_t looks = 0;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const uint32_t r = slot[e] >> 16;
+            looks += r > kBucketOwn ? 2 * r + 1 : r == kBucketOwn ? (r + 1) * (r + 1) : 0u;
+        }
+        looks = wave_inclusive_sum_u32(looks, lane);
+        if (lane == 63) atomicAdd(count + 1, (int)looks);
     }
     __syncthreads();
-    if (*flag != 0) return false;
+    if (*flag != 0 || (uint32_t)count[1] > kBucketLooks * (uint32_t)K) return false;
     // counters -> first position of every bucket; a thread has 32 neighbouring ones
     {
         uint32_t c[16], sum = 0;
@@ -691,7 +730,7 @@ __device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, int* 
         if (tid == T - 1) hist[NB / 2] = run;                      // = K
     }
     __syncthreads();
-    // first position (low half) and size of the element's bucket
+    // first position, size less one of the element's bucket, and its place in it
     const uint16_t* const first = reinterpret_cast<const uint16_t*>(hist);
     uint32_t most = 0;
     if (mine) {
@@ -699,50 +738,100 @@ __device__ __forceinline__ bool sort_by_buckets(uint2* kv, uint32_t* scan, int* 
         for (int e = 0; e < 16; ++e) {
             const uint32_t b = slot[e] & 0xFFFFu, r = slot[e] >> 16;
             const uint32_t f = first[b], size = first[b + 1] - f;
-            slot[e] = f | (size << 16) | (r << 24);
+            slot[e] = f | ((size - 1) << 14) | (r << 23);
             most = max(most, size);
         }
     }
     __syncthreads();
     // into the buckets (no spare elements yet), and what sorts last behind the row: a look beyond a bucket's end
     // finds larger keys only
+    auto position = [](uint32_t s) { return s & 0x3FFFu; };
+    auto bucket_size = [](uint32_t s) { return ((s >> 14) & 0x1FFu) + 1; };
+    auto place = [](uint32_t s) { return s >> 23; };
     if (mine) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) kv[(slot[e] & 0xFFFFu) + (slot[e] >> 24)] = make_uint2(key[e], __float_as_uint(sv[e]));
+        for (int e = 0; e < 16; ++e) kv[position(slot[e]) + place(slot[e])] = make_uint2(key[e], __float_as_uint(sv[e]));
     }
-    if (tid < 8) kv[K + tid] = make_uint2(kPadKey, 0u);
-    __syncthreads();
+    if (tid < 16) kv[K + tid] = make_uint2(kPadKey, 0u);
     most = wave_minmax_u32<true>(most);
-    if (mine) {
+    uint32_t waiting = 0, listed = 0;                              // bit e: element e is to go on the list; is or was on it
+    auto put = [&]() {
+        const uint32_t n = (uint32_t)__popc(waiting), to = wave_inclusive_sum_u32(n, lane);
+        int at = 0;
+        if (lane == 63) at = atomicAdd(count, (int)to);
+        uint32_t i = (uint32_t)__builtin_amdgcn_readlane(at, 63) + to - n;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const uint32_t f = slot[e] & 0xFFFFu, size = (slot[e] >> 16) & 0xFFu, r = slot[e] >> 24;
-            const unsigned long long me = ((unsigned long long)key[e] << 32) | __float_as_uint(sv[e]);
-            uint32_t less = 0, same = 0;
-            auto look = [&](uint32_t i) {
-                const uint2 v = kv[f + i];
-                const unsigned long long o = ((unsigned long long)v.x << 32) | v.y;
-                less += o < me ? 1u : 0u;
-                same += o == me ? 1u : 0u;
-            };
+            if ((waiting >> e) & 1) {
+                if (i < (uint32_t)LIST) {
+                    list[i] = slot[e];
+                    slot[e] = i;
+                    listed |= 1u << e;
+                }
+                ++i;
+            }
+        }
+    };
+    if (most > kBucketOwn) {                                       // the same in all lanes
 #pragma unroll
-            for (uint32_t i = 0; i < 4; ++i) look(i);
+        for (int e = 0; e < 16; ++e) waiting |= bucket_size(slot[e]) > kBucketOwn ? 1u << e : 0u;
+        put();
+    }
+    __syncthreads();
+    const uint32_t some = (uint32_t)count[0];                      // on the list or waiting for it
+    for (uint32_t left = some; left != 0;) {
+        const uint32_t n = min(left, (uint32_t)LIST), sub = tid & 3;
+        left -= n;
+        // four lanes to an element, every fourth of its bucket's elements each
+#pragma unroll 1
+        for (uint32_t i = tid >> 2; i < n; i += T / 4) {
+            const uint32_t s = list[i], f = position(s), size = bucket_size(s), r = place(s);
+            const uint2 me = kv[f + r];
+            uint32_t less = 0;
+#pragma unroll 1
+            for (uint32_t j = sub; j < size; j += 16) {            // (reads at most fifteen past the bucket)
+                static_for<4>([&](auto t) { less = count_below<4 * t>(less, kv[f + j + 4 * t], me, (int)(r - j)); });
+            }
+            less += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)less, 0xB1, 0xF, 0xF, false);
+            less += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)less, 0x4E, 0xF, 0xF, false);
+            if (sub == 0) list[i] = f + less;
+        }
+        __syncthreads();
+        const uint32_t now = listed & waiting;
+        if (now != 0) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if ((now >> e) & 1) slot[e] = list[slot[e]];
+        }
+        waiting &= ~listed;
+        if (left != 0) {
+            if (tid == 0) count[0] = 0;                            // (everybody has read it)
+            __syncthreads();
+            if (__ballot(waiting != 0) != 0ull) put();
+            __syncthreads();
+        }
+    }
+    auto rank = [&](auto some_) {
+        constexpr bool SOME = decltype(some_)::value;              // is anything on the list?
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            if (SOME && ((listed >> e) & 1)) continue;
+            const uint32_t f = position(slot[e]), size = bucket_size(slot[e]), r = place(slot[e]);
+            const uint2 me = make_uint2(key[e], __float_as_uint(sv[e]));
+            uint32_t less = 0;
+            static_for<4>([&](auto t) { less = count_below<t>(less, kv[f + t], me, (int)r); });
             if (most > 4) {
 #pragma unroll 1
                 for (uint32_t i = 4; i < size; i += 4) {           // (reads at most three past the bucket)
-#pragma unroll
-                    for (uint32_t t = 0; t < 4; ++t) look(i + t);
-                }
-            }
-            if (same > 1) {                                        // equal pairs: in the order of their places
-#pragma unroll 1
-                for (uint32_t i = 0; i < r; ++i) {
-                    const uint2 v = kv[f + i];
-                    less += (v.x == key[e] && v.y == __float_as_uint(sv[e])) ? 1u : 0u;
+                    static_for<4>([&](auto t) { less = count_below<t>(less, kv[f + i + t], me, (int)(r - i)); });
                 }
             }
             slot[e] = f + less;
         }
+    };
+    if (mine) {
+        if (some != 0) rank(std::true_type{});
+        else rank(std::false_type{});
     }
     __syncthreads();
     if (mine) {
@@ -783,7 +872,7 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     double* cen = scan + 2 * W;                 // [L]
     double* cen0 = cen + L;                     // [L]
     uint32_t* fin = reinterpret_cast<uint32_t*>(cen0 + L);   // [L] smallest key of the cluster of rank i (none: kPadKey)
-    int* misc = reinterpret_cast<int*>(fin + L);// [0], [1] selected index (by turns); [2] method flag; [3] crowded buckets; [4] a weight that is not finite; [40] as below
+    int* misc = reinterpret_cast<int*>(fin + L);// [0], [1] selected index (by turns); [2] method flag; [3] .. [6] of the sort ([3] no buckets, [5] length of the list, [6] looks); [4] a weight that is not finite; [40] as below
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t n = blockIdx.x;
@@ -933,7 +1022,8 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     {
 #pragma unroll
         for (int e = 0; e < 16; ++e) key[e] = f32_key(xv[e]);
-        if (!sort_by_buckets<T>(kv, reinterpret_cast<uint32_t*>(scan), misc + 3, key, sv, mine, K)) {
+        if (!sort_by_buckets<T>(kv, reinterpret_cast<uint32_t*>(scan), reinterpret_cast<uint32_t*>(pre_s), misc + 3, misc + 5,
+                                key, sv, mine, K)) {
 #pragma unroll
             for (int e = 0; e < 16; ++e)
                 kv[tid * 17 + e] = mine ? make_uint2(key[e], __float_as_uint(sv[e])) : make_uint2(kPadKey, 0u);

@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 from paper_2507_04610_amd import inputs
+from tests import quant_buckets
 
 pytestmark = pytest.mark.gpu
 
@@ -199,15 +200,15 @@ def test_quantize_rejects_bad_arguments(any4):
 @pytest.mark.parametrize("unit_act", (False, True))
 @pytest.mark.parametrize("K", (640, 1024, 2048, 4096, 4224, 14336))
 def test_quantize_rows_with_crowded_buckets(any4, qoracle, K, unit_act):
-    """The sort places a row's weights in buckets of equal width and hands rows with more than 32 in a bucket to
-    the bitonic network: rows on both sides of that limit, rows with many equal weights (with unit activations also
-    equal sample weights), very small and very large weights."""
+    """Rows that crowd the buckets of the sort: bf16 weights (ties inside a group, the smallest of every group scaled to
+    exactly 0), many equal weights (with unit activations also equal sample weights), a constant group, few distinct values;
+    very small and very large weights."""
     qc = inputs.make_quant_case(8, K, 4, seed=3 * K)
     w = qc.w.copy()
     w[0] = inputs.bf16_bits_to_f32(inputs.f32_to_bf16_bits(w[0]))            # ties inside a group
-    w[1, 5:5 + 32] = w[1, 5]                                                 # a bucket of 32 at least
-    w[2, 256:256 + 31] = w[2, 300]                                           # ... with one more in its place
-    w[3, 128:128 + 33] = w[3, 140]                                           # more than a bucket takes
+    w[1, 5:5 + 32] = w[1, 5]
+    w[2, 256:256 + 31] = w[2, 300]
+    w[3, 128:128 + 33] = w[3, 140]
     w[4, 384:512] = 0.125                                                    # a constant group: 128 equal weights
     w[5] *= np.float32(1e-30)
     w[6] *= np.float32(1e30)
@@ -276,6 +277,45 @@ def test_quantize_empty_clusters_keep_their_centres(any4, qoracle, K):
                              centre_gap=0.0)
     bad = np.argwhere((bits16(got["lut"]) != ref["lut"]).any(axis=1))[:, 0]
     assert bad.size == 0, (K, len(bad), bad[:5].tolist())
+
+
+def crowded_row(K, size, buckets, rng):
+    """A row whose scaled weights are known on the host (every group spans 0 .. 15 / 1024: scale 2^-10, offset 0): `buckets`
+    buckets of the sort with `size` equal weights each, the groups' ends in the first and the last, all others alone in
+    theirs."""
+    nb = quant_buckets.count(K)
+    w = np.zeros(K, np.float64)
+    low, high = np.arange(0, K, 128), np.arange(1, K, 128)
+    free = rng.permutation(np.setdiff1d(np.arange(K), np.concatenate([low, high])))
+    at = rng.permutation(np.arange(1, nb - 1))[:buckets + len(free) - size * buckets]
+    w[free] = np.concatenate([np.repeat(at[:buckets], size), at[buckets:]]) + 0.5
+    w = (w * (15.0 / nb) / 1024.0).astype(np.float32)
+    w[high] = np.float32(15.0 / 1024.0)
+    return w
+
+
+@pytest.mark.parametrize("unit_act", (False, True))
+@pytest.mark.parametrize("K", (1024, 2048, 4096, 8192, 14336))
+def test_quantize_rows_with_equal_weights(any4, qoracle, K, unit_act):
+    """Buckets on both sides of the sizes at which their elements go on a list and at which the row goes to the bitonic
+    network, lists of one round and of several, more comparisons than the list may cost.  That a row is what it is meant to
+    be is checked against the kernel's own bucket formula."""
+    c = quant_buckets.constants()
+    lanes = quant_buckets.threads(K)
+    own, most = c["kBucketOwn"], c["kBucketMost"]
+    crowd = 4 * lanes // 32 + 1                                     # buckets of 32 that do not fit into one list
+    want = [(own, 1), (own + 1, 1), (33, 1), (112, 1), (300, 1), (most, 1), (most + 1, 1), (own + 1, 3), (32, crowd),
+            (32, 2 * crowd), (100, K // 200)]
+    rng = np.random.default_rng(K)
+    rows = [crowded_row(K, size, n, rng) for size, n in want]
+    for (size, n), row in zip(want, rows):
+        sizes = quant_buckets.sizes(qoracle.scale_row(row, None, 4)[2])
+        assert np.sum(sizes[1:-1] == size) == n and np.all((sizes[1:-1] == size) | (sizes[1:-1] <= 1)), (size, n)
+    accepted = [quant_buckets.accepted(qoracle.scale_row(row, None, 4)[2]) for row in rows]
+    assert accepted[:6] == [True] * 4 + [K > 1024 or 300 * 300 <= c["kBucketLooks"] * K, most * most <= c["kBucketLooks"] * K]
+    assert not accepted[6] and accepted[8] and not accepted[10]
+    qc = inputs.make_quant_case(len(rows), K, 4, seed=K)
+    run_and_compare(any4, qoracle, np.stack(rows), None if unit_act else qc.act, qc.u, 4, False, 20, ("equal", K, unit_act))
 
 
 @pytest.mark.parametrize("gap", (0.0, 1e-18))
