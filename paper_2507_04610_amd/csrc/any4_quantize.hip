@@ -221,18 +221,22 @@ __device__ __forceinline__ void lloyd_per_weight(const float* ws, unsigned char*
     emit_row_order<BITS, T>(codes, cen, misc, K, n, codes_out, lut);
 }
 
-// The same iterations for the rarely taken hand-over inside the sorted-row kernel, which has 128 registers
-// per lane: the E-step and the M-step are separate passes and the M-step takes four centres at a time.
-// Every accumulator still adds its weights in the same order, so the sums are the same bit for bit.
+// The same iterations for the rarely taken hand-over inside the sorted-row kernel, which has 128 registers per lane: the
+// E-step and the M-step are separate passes, so that the centres and the accumulators are never in registers together.
+// Every accumulator still adds its weights in the same order, so the sums are the same bit for bit.  A short row has one or
+// two wavefronts, and a chip with few rows nothing else to do meanwhile: what counts is latency, so the E-step carries
+// four weights at a time and the M-step loads two before it adds them, once for all centres.  All rows handed over, any4,
+// against one weight at a time and four centres per sweep: 512 x 1024 568 -> 281 us (in blocks of four wavefronts, as
+// for longer rows, 372 with the slower loops), 512 x 2048 678 -> 378, 6144 x 4096 5250 -> 3670, 256 x 14336 967 -> 738.
 template <int BITS, int T>
 __device__ __forceinline__ void lloyd_per_weight_lean(const float* ws, unsigned char* codes, const float* alpha, double* red,
-                                                   double* cen, int* misc, const float* __restrict__ act, int64_t K,
+                                                   double* cen, int* misc, const float* __restrict__ act, int K,
                                                    int iters, int64_t n, uint8_t* __restrict__ codes_out,
                                                    uint16_t* __restrict__ lut, int32_t* __restrict__ msteps) {
     constexpr int L = 1 << BITS;
     constexpr int W = T / kWave;
+    constexpr int E = 4, M = 2;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    auto sample_weight = [&](int j) -> float { return alpha[j >> 7] * (act ? act[j] : 1.0f); };
     for (int j = tid; j < K; j += T) codes[j] = 0xFF;
     __syncthreads();
     int done = 0;
@@ -240,51 +244,79 @@ __device__ __forceinline__ void lloyd_per_weight_lean(const float* ws, unsigned 
         int changed = 0;
         if (tid == 0) misc[40] = 0;                                // "some code changed in this pass"
         __syncthreads();
+        {
+            double c[L];
+#pragma unroll
+            for (int p = 0; p < L; ++p) c[p] = cen[p];
 #pragma unroll 1
-        for (int j = tid; j < K; j += T) {
-            const double x = (double)ws[j];
-            int best = 0;
-            double bd = (x - cen[0]) * (x - cen[0]);
-#pragma unroll 1
-            for (int p = 1; p < L; ++p) {
-                const double d = x - cen[p];
-                const double dd = d * d;
-                if (dd < bd) { bd = dd; best = p; }
+            for (int j = tid; j < K; j += E * T) {
+                double x[E], bd[E];
+                int best[E], was[E];
+#pragma unroll
+                for (int k = 0; k < E; ++k) {
+                    const int jk = min(j + k * T, K - 1);          // (past the row: nothing is stored)
+                    x[k] = (double)ws[jk];
+                    was[k] = codes[jk];
+                    bd[k] = (x[k] - c[0]) * (x[k] - c[0]);
+                    best[k] = 0;
+                }
+#pragma unroll
+                for (int p = 1; p < L; ++p) {
+#pragma unroll
+                    for (int k = 0; k < E; ++k) {
+                        const double d = x[k] - c[p];
+                        const double dd = d * d;
+                        if (dd < bd[k]) { bd[k] = dd; best[k] = p; }
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < E; ++k) {
+                    if (j + k * T < K) {
+                        changed |= was[k] != best[k];
+                        codes[j + k * T] = (unsigned char)best[k];
+                    }
+                }
             }
-            changed |= (codes[j] != (unsigned char)best);
-            codes[j] = (unsigned char)best;
         }
         if (changed) misc[40] = 1;
         __syncthreads();
         changed = misc[40];
         if ((done > 0 && !changed) || done >= iters) break;
-#pragma unroll 1
-        for (int p0 = 0; p0 < L; p0 += 4) {
-            double num[4] = {0.0, 0.0, 0.0, 0.0}, den[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-            for (int j = tid; j < K; j += T) {
-                const double x = (double)ws[j];
-                const int best = (int)codes[j] - p0;
-                const double s = (double)sample_weight(j);
-                const double sx = s * x;
+        {
+            double num[L], den[L];
 #pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    const double one = __hiloint2double(best == p ? 0x3FF00000 : 0, 0);
-                    num[p] = __builtin_fma(sx, one, num[p]);
-                    den[p] = __builtin_fma(s, one, den[p]);
+            for (int p = 0; p < L; ++p) { num[p] = 0.0; den[p] = 0.0; }
+#pragma unroll 1
+            for (int j = tid; j < K; j += M * T) {
+                float x[M], s[M];
+                int best[M];
+#pragma unroll
+                for (int k = 0; k < M; ++k) {
+                    const int jk = j + k * T;
+                    const bool in = jk < K;                        // (past the row: adds 0 * 0)
+                    x[k] = in ? ws[jk] : 0.0f;
+                    s[k] = in ? alpha[jk >> 7] * (act ? act[jk] : 1.0f) : 0.0f;
+                    best[k] = in ? (int)codes[jk] : 0;
+                }
+#pragma unroll
+                for (int k = 0; k < M; ++k) {
+                    const double sd = (double)s[k], sx = sd * (double)x[k];
+#pragma unroll
+                    for (int p = 0; p < L; ++p) {
+                        const double one = __hiloint2double(best[k] == p ? 0x3FF00000 : 0, 0);
+                        num[p] = __builtin_fma(sx, one, num[p]);
+                        den[p] = __builtin_fma(sd, one, den[p]);
+                    }
                 }
             }
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
+            for (int p = 0; p < L; ++p) {
 #pragma unroll
                 for (int m = 1; m < 64; m <<= 1) {
                     num[p] += shfl_xor_f64(num[p], m);
                     den[p] += shfl_xor_f64(den[p], m);
                 }
-            }
-            if (lane == 0) {
-#pragma unroll
-                for (int p = 0; p < 4; ++p) { red[(wv * 2 + 0) * L + p0 + p] = num[p]; red[(wv * 2 + 1) * L + p0 + p] = den[p]; }
+                if (lane == 0) { red[(wv * 2 + 0) * L + p] = num[p]; red[(wv * 2 + 1) * L + p] = den[p]; }
             }
         }
         __syncthreads();
@@ -1250,7 +1282,7 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
         scale_row<BITS, T>(w + n * K64, n, G, symmetric, scale, offset, ws, alpha);
         if (tid < L) cen[tid] = cen0[tid];
         __syncthreads();
-        lloyd_per_weight_lean<BITS, T>(ws, smem + (size_t)K * 4, alpha, red, cen, misc, act, K64, iters, n, codes_out, lut,
+        lloyd_per_weight_lean<BITS, T>(ws, smem + (size_t)K * 4, alpha, red, cen, misc, act, K, iters, n, codes_out, lut,
                                        msteps);
         return;
     }
