@@ -226,25 +226,50 @@ def test_quantize_rows_that_leave_threads_idle(any4, qoracle, bits, K):
     run_and_compare(any4, qoracle, qc.w, qc.act, qc.u, bits, False, 20, ("idle threads", K, bits))
 
 
+def not_finite(kind, qc):
+    """weights and activations with numbers that are none, or are infinite, in six rows or in all"""
+    w, act = qc.w.copy(), qc.act.copy()
+    K = len(act)
+    if kind == "weights":
+        w[0, 5] = np.nan
+        w[1, 7] = np.inf
+        w[2, 9] = -np.inf
+        w[3, 200:230] = np.nan
+        w[4] = np.nan
+    elif kind == "nan":
+        act[K // 3] = np.nan
+    elif kind == "inf":
+        act[K // 3] = np.inf
+    elif kind == "inf_last":                                       # where a total of infinity draws
+        act[K - 1] = np.inf
+    elif kind == "inf_equal":                                      # a distance of 0 to that weight, times infinity
+        act[K // 3] = np.inf
+        w[::2, K // 3:K // 3 + 2] = 0.0
+        w[::2, K - 128:] = 0.0
+    elif kind == "overflow":                                       # finite, but not times a group's scale
+        act[K // 3] = 3e38
+        w *= 1e4
+    else:
+        act[K // 3], act[K // 2] = np.nan, np.inf
+        w[0, 5], w[1, 7], w[2, K // 3] = np.nan, np.inf, np.nan
+    return w, act
+
+
+@pytest.mark.parametrize("kind", ("weights", "nan", "inf", "inf_last", "inf_equal", "overflow", "all"))
 @pytest.mark.parametrize("bits", (4, 2))
-@pytest.mark.parametrize("K", (384, 4096, 14336))
-def test_quantize_rows_that_are_not_finite(any4, bits, K):
-    """Rows with a NaN or an infinity have no sorted order: they get what the per-weight method gives them (tables up to the
-    sign and payload of NaNs)."""
+@pytest.mark.parametrize("K", (384, 2048, 4096, 14336))
+def test_quantize_rows_that_are_not_finite(any4, bits, K, kind):
+    """Rows with a NaN or an infinity among the weights or the sample weights have no sorted order, or no sums: they get
+    what the per-weight method gives them (tables up to the sign and payload of NaNs)."""
     qc = inputs.make_quant_case(6, K, bits, seed=K + bits)
-    w = qc.w.copy()
-    w[0, 5] = np.nan
-    w[1, 7] = np.inf
-    w[2, 9] = -np.inf
-    w[3, 200:230] = np.nan
-    w[4] = np.nan
-    w, u = torch.from_numpy(w).cuda(), torch.from_numpy(qc.u).cuda()
+    w, act = not_finite(kind, qc)
+    w, u, act = torch.from_numpy(w).cuda(), torch.from_numpy(qc.u).cuda(), torch.from_numpy(act).cuda()
     for symmetric in (False, True):
-        for act in (torch.from_numpy(qc.act).cuda(), None):
-            got = any4.any4_quantize(w, act, u, bits, symmetric, 20)
-            ref = any4.any4_quantize(w, act, u, bits, symmetric, 20, centre_gap=METHODS["per_weight"])
+        for a in (act, None):
+            got = any4.any4_quantize(w, a, u, bits, symmetric, 20)
+            ref = any4.any4_quantize(w, a, u, bits, symmetric, 20, centre_gap=METHODS["per_weight"])
             for k in ("codes_u8", "msteps"):
-                assert torch.equal(got[k], ref[k]), (k, symmetric, act is None)
+                assert torch.equal(got[k], ref[k]), (k, symmetric, a is None)
             for k in ("lut", "scale", "offset"):
                 assert torch.equal(got[k].float().nan_to_num(nan=1e30), ref[k].float().nan_to_num(nan=1e30)), (k, symmetric)
 
