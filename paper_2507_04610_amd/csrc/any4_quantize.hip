@@ -486,14 +486,19 @@ __global__ __launch_bounds__(QT) void quantize_kernel(
 //                       the elements (order-preserving integer image of w_S, sample weight s as fp32 bits),
 //                       ascending in w_S.  (The per-weight method keeps its codes behind the scaled weights.)
 //   alpha [KP/128] f32 | pre_s, pre_sx [T + 1] f64 (running sums before every 16th sorted element; the total)
-//   scan [2 W] f64 | cen [L] f64 | cen0 [L] f64 | fin [L] u32 | misc [64] i32
-//   (the per-weight method's partial sums red [W][2][L] f64 lie over pre_s: 2 W L <= 2 (T + 1))
+//   scan [2 W] f64 | cen [L] f64 | cen0 [L] f64 | misc [44] i32
+//   (the per-weight method's partial sums red [W][2][L] f64 lie over pre_s: 2 W L <= 2 (T + 1); the smallest key of the cluster
+//   of rank i, fin [L] u32, over cen, which the sorted row's passes read only once)
+// A compute unit holds 16 wavefronts of this kernel by their registers, and as many by its LDS: 16 blocks of one wavefront
+// have 10240 bytes each (with 10368, and fewer blocks, 11525 x 1024 any4 took 256 us; 243).
 constexpr int kSortedMaxK = 16384;
 constexpr size_t sorted_padw(int T) { return (size_t)T * 17; }
 constexpr size_t sorted_lds_bytes(int T, int bits) {
     const size_t W = (size_t)T / kWave, L = (size_t)1 << bits;
-    return sorted_padw(T) * 8 + ((size_t)T / 8) * 4 + 2 * ((size_t)T + 1) * 8 + 2 * W * 8 + 2 * L * 8 + L * 4 + 64 * 4;
+    return sorted_padw(T) * 8 + ((size_t)T / 8) * 4 + 2 * ((size_t)T + 1) * 8 + 2 * W * 8 + 2 * L * 8 + 44 * 4;
 }
+constexpr bool sorted_blocks_fit(int T) { return sorted_lds_bytes(T, 4) <= (size_t)160 * 1024 * T / (16 * kWave); }
+static_assert(sorted_blocks_fit(64) && sorted_blocks_fit(128) && sorted_blocks_fit(256) && sorted_blocks_fit(512) && sorted_blocks_fit(1024));
 
 __device__ __forceinline__ int pad16(int p) { return p + (p >> 4); }
 // fp32 -> u32 whose unsigned order is the order of the numbers (finite inputs), and back
@@ -903,8 +908,8 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     double* red = pre_s;                        // [W][2][L], per-weight method only: it has no running sums
     double* cen = scan + 2 * W;                 // [L]
     double* cen0 = cen + L;                     // [L]
-    uint32_t* fin = reinterpret_cast<uint32_t*>(cen0 + L);   // [L] smallest key of the cluster of rank i (none: kPadKey)
-    int* misc = reinterpret_cast<int*>(fin + L);// [0], [1] selected index (by turns); [2] method flag; [3] .. [6] of the sort ([3] no buckets, [5] length of the list, [6] looks); [4] a weight that is not finite; [40] as below
+    uint32_t* fin = reinterpret_cast<uint32_t*>(cen);   // [L] smallest key of the cluster of rank i (none: kPadKey), once cen has been read
+    int* misc = reinterpret_cast<int*>(cen0 + L);// [0], [1] selected index (by turns); [2] method flag; [3] .. [6] of the sort ([3] no buckets, [5] length of the list, [6] looks); [4] a weight that is not finite; [40] as below
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t n = blockIdx.x;
@@ -1317,7 +1322,7 @@ hipError_t launch_quantize(const float* w, const float* act, const float* u, int
     } while (0)
         // The smallest block that holds the row: a compute unit holds 16 wavefronts of this kernel, so a row of at most 1024
         // weights in a block of one wavefront has 15 others beside it and in one of four only three.  any4 against four
-        // wavefronts: 11525 x 1024 584 -> 270 us, 11525 x 1152 645 -> 411 us, 28000 x 2048 1650 -> 1074 us; 512 x 1024,
+        // wavefronts, when these were measured: 11525 x 1024 584 -> 270 us, 11525 x 1152 645 -> 411 us, 28000 x 2048 1650 -> 1074 us; 512 x 1024,
         // where the chip is nearly empty either way, 57 us both.
 #define ANY4_QUANT_ST(B)                                                                                          \
     do {                                                                                                          \
