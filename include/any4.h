@@ -233,12 +233,14 @@ int any4_quantize(const float* w, const float* act, const float* u, int64_t N, i
 
 /*
  * any4_quantize_with_gap - any4_quantize with its one tuning knob exposed.  Rows of K <= 16384 are
- * sorted once, after which a Lloyd pass (section 3.2, E-step and M-step) costs O(2^bits log K): the
- * clusters are runs of the sorted row, found by binary search with the E-step's own comparison, and
- * their sums are differences of running sums.  That search presumes that unequal centres are further
- * apart than the rounding of a distance; a row in which two unequal centres come closer than
- * centre_gap * max|w_S| is done again from its starting centres by the plain method (every weight
- * against every centre in every pass), which is also the method of longer rows.
+ * sorted once, after which a Lloyd pass (section 3.2, E-step and M-step) costs O(2^bits log K) at
+ * most: the clusters are runs of the sorted row, found with the E-step's own comparison by a search
+ * that starts where the last pass lets their bounds be expected, and their sums are differences of
+ * running sums.  That search presumes that unequal centres are further apart than the rounding of a
+ * distance; a row in which two unequal centres come closer than centre_gap * max|w_S| is done again
+ * from its starting centres by the plain method (every weight against every centre in every pass),
+ * which is also the method of longer rows and of rows with a NaN or an infinity among the weights or
+ * the sample weights.
  *   centre_gap  >= 0: as described (any4_quantize passes 2^-40), values below 2^-49 as 2^-49, the least
  *               distance at which that holds; a huge value sends every row with two unequal centres
  *               through the hand-over; < 0: the plain method for all rows.

@@ -10,17 +10,16 @@
 //      the drawn point walks it (the uniform draws are an input, one per centre);
 //   3. weighted Lloyd iterations in fp64 until a pass changes no code or `iters` centre updates
 //      were made, by one of two methods:
-//      sorted row (K <= 16384): the scaled row is sorted once (into buckets, which then order themselves; rows
-//        that crowd a bucket by a bitonic network, 16 elements per thread in registers, LDS between rounds)
-//        and running sums of s and s * w_S are kept per 16
-//        sorted elements.  A pass is then the work of 2^n lanes of one wavefront: order the centres,
-//        find for each neighbouring pair the first sorted position the upper one wins - a binary
-//        search that evaluates the very predicate of the E-step (squared fp64 distances, ties to the
-//        lower index) - and take every cluster's sums as differences of running sums: O(2^n log K)
-//        instead of O(K 2^n) per pass.  The E-step predicate is monotone along the sorted row as
-//        long as unequal centres are further apart than the rounding of the distances; a row in
-//        which two unequal centres come closer than `centre_gap * max|w_S|`, and one with a NaN or an
-//        infinity, is finished by the other method from its starting centres;
+//      sorted row (K <= 16384): the scaled row is sorted once (into buckets, whose elements then order themselves; rows
+//        that crowd the buckets too much by a bitonic network, 16 elements per thread in registers, LDS between
+//        rounds) and running sums of s and s * w_S are kept per 16 sorted elements, a chunk.  A pass is then the work
+//        of one wavefront, four lanes per centre: order the centres, find for each neighbouring pair the first sorted
+//        position the upper one wins - a search among the chunks' first elements, from where the last pass and the
+//        centres' moves let it be expected, that evaluates the very predicate of the E-step (squared fp64 distances,
+//        ties to the lower index), then that one chunk - and take every cluster's sums as differences of running sums.
+//        The E-step predicate is monotone along the sorted row as long as unequal centres are further apart than the
+//        rounding of the distances; a row in which two unequal centres come closer than `centre_gap * max|w_S|`, and
+//        one with a NaN or an infinity, is finished by the other method from its starting centres;
 //      per weight (larger K, and the rows just named): one pass assigns every weight to its nearest
 //        centre and at the same time accumulates, per thread and per centre, sum(s * w_S) and
 //        sum(s); the partial sums are combined in a fixed order (lanes, then wavefronts);
@@ -670,7 +669,7 @@ __device__ __forceinline__ uint32_t count_below(uint32_t n, uint2 o, uint2 me, i
 // each: left with their owners, a few of them in a wavefront make all its lanes go round the bucket.  The list is as
 // large as the LDS that is free here, 4 T elements; a row with more takes it in several rounds.  bf16 weights, the network
 // (what they had when a bucket of more than 32 sent a row there) against the list: 4096 x 14336 2055 -> 1461 us (fp32 1386),
-// 4096 x 8192 904 -> 654, 6144 x 4096 591 -> 502; half of 4096 x 14336 pruned 2159 -> 1955.
+// 4096 x 8192 904 -> 654, 6144 x 4096 591 -> 502; half of 4096 x 14336 pruned 2159 -> 1920.
 // False, and nothing sorted, where the buckets would not do: all weights equal, a weight that is not finite, a bucket of
 // more than kBucketMost (what a slot has bits for), or a list that costs more than the network.  Its cost is counted in
 // looks, the squares of the sizes of its buckets.  The network wins from 46 looks per weight of the row on where equal
@@ -1322,8 +1321,8 @@ hipError_t launch_quantize(const float* w, const float* act, const float* u, int
     } while (0)
         // The smallest block that holds the row: a compute unit holds 16 wavefronts of this kernel, so a row of at most 1024
         // weights in a block of one wavefront has 15 others beside it and in one of four only three.  any4 against four
-        // wavefronts, when these were measured: 11525 x 1024 584 -> 270 us, 11525 x 1152 645 -> 411 us, 28000 x 2048 1650 -> 1074 us; 512 x 1024,
-        // where the chip is nearly empty either way, 57 us both.
+        // wavefronts, when these were measured: 11525 x 1024 584 -> 270 us, 11525 x 1152 645 -> 411 us, 28000 x 2048 1650 ->
+        // 1074 us; 512 x 1024, where the chip is nearly empty either way, 57 us both.
 #define ANY4_QUANT_ST(B)                                                                                          \
     do {                                                                                                          \
         if (K <= 1024) ANY4_QUANT_S(B, 64);                                                                       \
