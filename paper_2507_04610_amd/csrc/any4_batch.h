@@ -33,6 +33,7 @@
 #pragma once
 #include "any4_device.h"
 #include "any4_internal.h"
+#include "any4_lds_copy.h"
 #include "any4_regtable.h"
 #include "any4_splitk.h"
 #include <type_traits>
@@ -95,24 +96,6 @@ struct Params {
     int sc_stride;                   // Shape::sc_stride of the largest slab
 };
 
-// waits for LDS, leaves global loads in flight
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-// at most LEFT of this wavefront's vector memory operations are outstanding
-template <int LEFT> __device__ __forceinline__ void loads_left() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LEFT) : "memory"); }
-
-// The copies to LDS are issued and waited for by hand: the compiler would wait for all of them in front of every LDS
-// read.  It does not see them, and loads return in order, so that its own waits (for codes) are for no less than
-// they need.
-// 64 lanes x 16 bytes straight from memory to LDS: lane l's piece goes to lds + 16 l.
-// (m0 is a reserved register: the compiler sets it in front of each use of its own and keeps no value of the
-// program in it, but merges equal settings where it sees no other.  The clobber shows it this one; that nothing is
-// saved and restored around the statement, which is what the warning says, is not needed.)
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void copy_to_lds(uint32_t lds, const void* base, uint32_t voff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "m0", "memory");
-}
-#pragma clang diagnostic pop
 template <int BITS, int MT, int WN, bool F16, bool FINE>
 __device__ __forceinline__ void batch_body(const Params& p) {
     using S = Shape<MT, WN>;

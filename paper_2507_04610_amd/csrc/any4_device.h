@@ -41,6 +41,14 @@ template <bool F16> __device__ __forceinline__ uint32_t f32_to_h16(float f) {
     else return f32_to_bf16(f);
 }
 
+// two at once, a in the low half (bf16: one instruction that rounds as f32_to_bf16 does)
+template <bool F16> __device__ __forceinline__ uint32_t f32x2_to_h16x2(float a, float b) {
+    if constexpr (F16) return f32_to_h16<true>(a) | (f32_to_h16<true>(b) << 16);
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+
 // words per packed row
 __host__ __device__ __forceinline__ int64_t row_words(int64_t K, int bits) { return K * bits / 32; }
 

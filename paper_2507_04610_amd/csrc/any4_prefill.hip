@@ -17,23 +17,27 @@
 // (relative error 2^-16), and whose right operand is the bf16 offset itself.
 //
 // Block tile 256 (m) x 128 (n), K step 64, eight wavefronts in a 4 x 2 arrangement, each owning a
-// 64 x 64 sub-tile as 2 x 2 v_mfma_f32_32x32x16_bf16 accumulators.  Two LDS buffers and one barrier
-// per K step.  A K step is written as ONE software-pipelined instruction stream whose order is
-// pinned (scheduling barriers): the 16 MFMAs of the step on buffer b are interleaved with
-// everything that prepares the next step in buffer b^1 - operand reads one 16-wide slice ahead,
-// the table lookups, packing and the LDS writes of the activation tile and of the looked-up tile,
-// the per-group scale fold - while the global loads of later steps are in flight.  Left to
-// itself the compiler emits "all MFMAs, then all staging", and the two wavefronts of a SIMD, which
-// the barrier keeps in step, then leave the matrix cores idle while both stage.
+// 64 x 64 sub-tile as 2 x 2 v_mfma_f32_32x32x16_bf16 accumulators.  x, codes and scales are copied straight to LDS, three
+// steps (groups) to a ring; a thread keeps to one weight row, whose table sits in its registers (any4_regtable.h), and
+// turns 16 codes of a step into a piece of the looked-up tile, two steps to a ring.
 //
-// What bounds a K step: no unit by itself.  At M = 2048, N = 28672, K = 4096 (590 us under the counters, 1.76 GHz) the matrix
-// cores are busy 45 % of the cycles, the LDS pipe 69 %, vector issue 45 % (two wavefronts per SIMD); with
-// the table in LDS they were 43, 88 and 40.  A staging thread
-// keeps to one weight row for the whole launch, so the row's table sits in its registers (any4_regtable.h): 46 vector
-// instructions for its 16 codes of a step where a table in LDS took 16 LDS reads and 40 (addresses and packs), and
-// nothing to fill before the first step.  The four linears of an 8B layer at M = 2048 / 512: 1139 / 358 -> 1101 / 350 us.
+// What bounds it.  Per wavefront and group of 128: 64 matrix instructions for a SIMD's two wavefronts take 2048 cycles, its
+// vector instructions (92 lookup, 64 scale fold, 4 others; a matrix instruction holds the issue port for two) 1800, the LDS pipe
+// 1400 + its share of the copies: all three are near their limits together, so the order of the instructions decides.
+//   - Operands are read half a step ahead, the barrier stands in the middle of a step, between matrix instructions that
+//     both have their operands: nothing waits behind it.
+//   - A tile's two instructions of a half step follow each other, so that a finished group's sums have six matrix
+//     instructions' time to be scaled before the next group writes their registers.
+//   - Lookups, reads, writes and copies are spread over the instructions of a step.  Four copies at once at its start
+//     held every wavefront until the address unit had taken them: 530 cycles a step.
+// The order is pinned by scheduling barriers; left to itself the compiler emits "all MFMAs, then all staging".  A K step takes 1520
+// cycles (1940 with x and codes through registers into padded LDS, operands read behind the barrier, and the fold at a
+// group's end), of which the matrix instructions are 1024; a loop of nothing but their mix of matrix, vector
+// and LDS instructions takes 1280.  The clock follows the load: 1.85 GHz here, 1.7 in that loop.  N = 28672, K = 4096 at M = 2048: 540 -> 475 us;
+// the four linears of an 8B layer at M = 2048 / 512: 1086 / 346 -> 955 / 306 us.
 #include "any4_device.h"
 #include "any4_internal.h"
+#include "any4_lds_copy.h"
 #include "any4_regtable.h"
 #include "any4_splitk.h"
 #include <type_traits>
@@ -44,17 +48,30 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) u32x4* lds_u4;
+typedef __attribute__((address_space(3))) u32x2* lds_u2;
+typedef __attribute__((address_space(3))) uint32_t* lds_u32;
 
 constexpr int PBM = 256, PBN = 128, PBK = 64;
 constexpr int PTHREADS = 512;
-constexpr int PLD = PBK + 8;          // LDS row stride in bf16 elements (144 B: keeps 16-byte reads spread over banks)
-constexpr uint32_t kXBuf = PBM * PLD * 2, kWBuf = PBN * PLD * 2;   // bytes of one activation / weight buffer
-constexpr uint32_t kLdsBytes = 2 * kXBuf + 2 * kWBuf;
+// LDS, bytes.  A tile is 64 rows of 64 values (one K step).  Its row r holds 16-byte chunk c at place c ^ place(r): the 16 lanes
+// that LDS serves together in a read, one chunk of 16 rows, find it in 16 different columns of 256 bytes, and the 8 lanes of a
+// write, the even or the odd chunks of two rows, in 8 different ones of 128.
+constexpr uint32_t kTile = 64 * PBK * 2;
+constexpr uint32_t kXSlots = 3, kWSlots = 2, kRing = 3;           // steps of x, steps of looked-up weights; groups of codes and scales
+constexpr uint32_t kWAt = (PBM / 64) * kXSlots * kTile;           // x: [rows / 64][slot], then looked-up weights: [rows / 64][slot]
+constexpr uint32_t kCAt = kWAt + (PBN / 64) * kWSlots * kTile;    // a group's codes of the block's 128 rows: [slot]
+constexpr uint32_t kCSlot = PBN * kGroup / 2;
+constexpr uint32_t kSAt = kCAt + kRing * kCSlot;                  // a group's scales of a wavefront's 64 columns, one a word: [slot][wavefront]
+constexpr uint32_t kSSlot = 8 * 256;
+constexpr uint32_t kLdsBytes = kSAt + kRing * kSSlot;
+static_assert(kLdsBytes <= 160 * 1024);
+__device__ __forceinline__ int place(int row) { return ((row >> 1) & 7) ^ (row & 1); }
+// longest rows whose offsets inside a wavefront (32 rows of x) are kept in 32 bits; WIDE kernels beyond.  They would fit up to
+// K = 2^26; the line lies where both sides can be tested.
+constexpr int64_t kNarrowK = 1 << 17;
 
-__device__ __forceinline__ void lds_barrier() {                 // outstanding global loads stay in flight
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
 #define ANY4_SB() __builtin_amdgcn_sched_barrier(0)
 
 // X[m][g] = sum of the 128 activations of group g, in fp32, stored as two bf16 (high part,
@@ -99,7 +116,7 @@ __global__ __launch_bounds__(256) void group_sums_kernel(const uint16_t* __restr
 // instructions for eight codes where the table takes 23 - and the surplus 136 * scale * X (X = the
 // group sum of the activations) is taken off in the offset phase by two more passes over the same
 // group sums whose right operands are the exact bf16 numbers -128 * scale and -8 * scale.
-template <int BITS, bool FINE, bool F16, bool NOLUT = false>
+template <int BITS, bool FINE, bool F16, bool NOLUT, bool WIDE>
 __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
     const uint16_t* __restrict__ x, const uint32_t* __restrict__ codes,
     const uint16_t* __restrict__ lut, const uint16_t* __restrict__ scale,
@@ -117,8 +134,8 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
     };
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1, r32 = lane & 31, h = lane >> 5;
     const int64_t G = K / kGroup, RW = row_words(K, BITS);
     // Blocks below tail_first own a whole output tile.  The tiles of the last, partly filled round
     // of blocks are cut along K into tail_s slices of whole groups, one block each, so that the
@@ -134,38 +151,71 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
         g_hi = (int)((slice + 1) * G / tail_s);
     }
     const int64_t m0 = (int64_t)(tile % gm) * PBM, n0 = (int64_t)(tile / gm) * PBN;   // m fastest: an XCD keeps its rows of x
-    const int S0 = 2 * g_lo, T = 2 * g_hi;                                // this block's K steps
+    const int T = 2 * g_hi;                                               // the block's K steps end here
+    const int64_t GS = FINE ? 2 * G : G >> lr;                            // scales / offsets per row
 
-    // ---- staging roles.  Weights: thread -> (row, 16-code quarter of the K step); rows past N are
-    //      clamped (computed, never stored).  Activations: thread -> 4 rows, one 16-byte piece each.
+    // ---- copies to LDS.  Rows past M or N are clamped (computed, never stored).  A lane's address is a base of its
+    //      wavefront and a 32-bit offset; WIDE: an offset holds (row << 10 | bytes in the row).
+    auto copy16 = [&](uint32_t lds, const void* base, uint32_t off, int64_t stride) {
+        if constexpr (!WIDE) copy_to_lds(lds, base, off);
+        else {
+            asm volatile("" : "+v"(off));                      // (64-bit addresses are not kept in registers)
+            copy_to_lds_from(lds, static_cast<const char*>(base) + (int64_t)(off >> 10) * stride + (off & 1023));
+        }
+    };
+    auto offset_of = [&](int64_t row, int64_t stride, int bytes) -> uint32_t {
+        return WIDE ? (uint32_t)(row << 10) + (uint32_t)bytes : (uint32_t)(row * stride) + (uint32_t)bytes;
+    };
+    // x: a wavefront moves 32 rows of a step, 8 to a copy
+    const int64_t xrow = min(m0 + wave * 32, M - 1);
+    const char* const xbase = reinterpret_cast<const char*>(x + xrow * K);
+    uint32_t xoff[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        xoff[i] = offset_of(min(m0 + wave * 32 + i * 8 + (lane >> 3), M - 1) - xrow, 2 * K, ((lane & 7) ^ place(i * 8 + (lane >> 3))) * 16);
+    auto fetch_x = [&](int step, uint32_t slot, int i) {
+        copy16((wave >> 1) * (kXSlots * kTile) + slot * kTile + ((wave & 1) * 4 + i) * 1024, xbase + (int64_t)min(step, T - 1) * (PBK * 2), xoff[i], 2 * K);
+    };
+    // codes: pieces of 16 bytes, BITS to a row and group, one behind the other (re-laid-out: as they lie in units of
+    // 16 rows); with less than 4 bits the last wavefronts repeat what the first ones copy
+    const int cwave = wave % (2 * BITS), cpiece = cwave * 64 + lane, ufirst = cwave * 64 / (16 * BITS), rfirst = cwave * 64 / BITS;
+    const int64_t units = (N + 15) >> 4;
+    const int64_t crow = repacked ? min((n0 >> 4) + ufirst, units - 1) : min(n0 + rfirst, N - 1);
+    const int64_t cstride = repacked ? G * (256 * BITS) : RW * 4;         // bytes from a unit / row to the next
+    const char* const cbase = reinterpret_cast<const char*>(codes) + crow * cstride;
+    const uint32_t coff = repacked ? offset_of(min((n0 >> 4) + cpiece / (16 * BITS), units - 1) - crow, cstride, cpiece % (16 * BITS) * 16)
+                                   : offset_of(min(n0 + cpiece / BITS, N - 1) - crow, cstride, cpiece % BITS * 16);
+    auto fetch_codes = [&](int g, uint32_t slot) {
+        copy16(kCAt + slot * kCSlot + cwave * 1024, cbase + (int64_t)min(g, g_hi - 1) * (repacked ? 256 * BITS : 16 * BITS), coff, cstride);
+    };
+    // scales of the wavefront's columns (FINE: the pair of the group's halves, 4 bytes: rows are a whole number of pairs)
+    const int64_t srow = min(n0 + wn * 64, N - 1);
+    const uint16_t* const sbase = scale + srow * GS;
+    const uint32_t soff = (uint32_t)((min(n0 + wn * 64 + lane, N - 1) - srow) * GS * 2);
+    auto fetch_scales = [&](int g, uint32_t slot) {
+        const int gg = min(g, g_hi - 1);
+        copy_values_to_lds<FINE>(kSAt + slot * kSSlot + wave * 256, sbase + (FINE ? 2 * gg : gg >> lr), soff);
+    };
+
+    // ---- where this lane reads and writes LDS (the kernel has no static LDS: dynamic LDS starts at 0)
+    uint32_t ard[4], brd[4];                                              // operand kk of a step; + slot, + 32-row tile
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        const uint32_t at = r32 * (PBK * 2) + (((2 * kk + h) ^ place(r32)) << 4);
+        ard[kk] = wm * (kXSlots * kTile) + at;
+        brd[kk] = kWAt + wn * (kWSlots * kTile) + at;
+    }
+    // looking up: thread -> (weight row, 16-code quarter of the K step)
     const int wrow = tid >> 2, wq = tid & 3;
     const int64_t wn_glob = min(n0 + wrow, N - 1);
-    // word offset / bit shift of the thread's 16 codes inside the K step's (2 * BITS)-word chunk
-    const int qword = BITS == 4 ? 2 * wq : (BITS == 2 ? wq : (6 * wq) >> 2);
-    const int qshift = BITS == 3 ? ((6 * wq) & 3) * 8 : 0;
-    // plain layout: the K step's codes start at word tile * 2 * BITS of the row.  Tile-major layout
-    // (any4_repack): the step is half of group tile / 2; the thread's 16 codes are one half of
-    // piece 16 * q + n, q = 2 * (tile % 2) + wq / 2, of unit (row / 16, group): the word offset of
-    // step `tile` is (tile / 2) * 64 * BITS + (tile % 2) * 32 * BITS past the thread's base.
-    const int hword = (BITS == 4 ? 2 : 1) * (wq & 1);                     // first word of the thread's half inside its piece
-    const uint32_t* const wsrc = repacked
-        ? codes + (((wn_glob >> 4) * G * 64 + (wq >> 1) * 16 + (wn_glob & 15)) * BITS + hword)
-        : codes + wn_glob * RW + qword;
-    const int64_t qstep_even = repacked ? 64 * BITS : 4 * BITS, qstep_odd = repacked ? 32 * BITS : 2 * BITS;
-    const int xr_row = tid >> 3, xc8 = tid & 7;
-    const uint16_t* xsrc[4];                                              // rows past M are clamped, never stored
-#pragma unroll
-    for (int p = 0; p < 4; ++p) xsrc[p] = x + min(m0 + p * 64 + xr_row, M - 1) * K + xc8 * 8;
-    // the two output columns this lane owns (one per 32-wide n tile of its wavefront)
-    const uint16_t* scol[2];
-    const int64_t GS = FINE ? 2 * G : G >> lr;                            // scales / offsets per row
-#pragma unroll
-    for (int j = 0; j < 2; ++j) scol[j] = scale + min(n0 + wn * 64 + j * 32 + (lane & 31), N - 1) * GS;
-    // LDS byte addresses (the kernel has no static LDS: dynamic LDS starts at 0)
-    const uint32_t xwr = (uint32_t)(xr_row * PLD + xc8 * 8) * 2u;                         // + buf * kXBuf + p * 64 rows
-    const uint32_t wwr = 2 * kXBuf + (uint32_t)(wrow * PLD + wq * 16) * 2u;               // + buf * kWBuf + chunk * 16
-    const uint32_t ard = (uint32_t)((wm * 64 + (lane & 31)) * PLD + (lane >> 5) * 8) * 2u;
-    const uint32_t brd = 2 * kXBuf + (uint32_t)((wn * 64 + (lane & 31)) * PLD + (lane >> 5) * 8) * 2u;
+    const uint32_t wwr = kWAt + (wrow >> 6) * (kWSlots * kTile) + (wrow & 63) * (PBK * 2);
+    const uint32_t wwr0 = wwr + (((2 * wq) ^ place(wrow)) << 4), wwr1 = wwr + (((2 * wq + 1) ^ place(wrow)) << 4);
+    // The thread's 16 codes inside a group: plain layout, word (2 * BITS) * (step % 2) + qword of the row (any3: from
+    // bit qshift of it).  Tile-major layout (any4_repack): one half of piece 16 * q + n, q = 2 * (step % 2) + wq / 2, n = row % 16.
+    const int qword = BITS == 4 ? 2 * wq : (BITS == 2 ? wq : (6 * wq) >> 2), qshift = BITS == 3 ? ((6 * wq) & 3) * 8 : 0;
+    const uint32_t crd0 = kCAt + 4 * (repacked ? (wrow >> 4) * 64 * BITS + ((wq >> 1) * 16 + (wrow & 15)) * BITS + (BITS == 4 ? 2 : 1) * (wq & 1)
+                                               : wrow * 4 * BITS + qword);
+    const uint32_t crd1 = crd0 + 4 * (repacked ? 32 * BITS : 2 * BITS);
 
     f32x16 acc[2][2], part[2][2];
     f32x16 zero;
@@ -176,291 +226,379 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
 #pragma unroll
         for (int j = 0; j < 2; ++j) { acc[i][j] = zero; part[i][j] = zero; }
 
-    // ---- global fetches (tile indices are clamped by the callers: the loads are unconditional so
-    //      that the compiler waits for them by count, not with vmcnt(0))
-    u32x4 xr[4];
-    auto fetch_x = [&](int tile) {
-#pragma unroll
-        for (int p = 0; p < 4; ++p) xr[p] = *reinterpret_cast<const u32x4*>(xsrc[p] + (int64_t)tile * PBK);
-    };
-    auto fetch_q = [&](uint32_t (&q)[2], int tile) {
-        const int64_t wbase = (int64_t)(tile >> 1) * qstep_even + (tile & 1) * qstep_odd;
-        q[0] = wsrc[wbase];
-        q[1] = BITS == 2 ? 0u : wsrc[wbase + 1];
-    };
     // NOLUT: codes 2p, 2p + 1 of a word of eight as the bf16 pair (128 + c, 128 + c')
     auto grid_pair = [&](uint32_t w, int pi) -> uint32_t {
         const uint32_t t = w >> (8 * pi);
         return (t & 0xFu) | ((t << 12) & 0xF0000u) | 0x43004300u;
     };
-    // values of codes 8 c + 4 h .. + 3 of the thread's 16 (lo, hi: their bits in order)
     RowTable<BITS> table;
-    auto lookup = [&](uint32_t lo, uint32_t hi, int c, int h, uint32_t& d0, uint32_t& d1) {
+    struct Words { uint32_t lo, hi; };                                    // a thread's 16 codes of a step
+    auto read_codes = [&](uint32_t slot, int odd) -> Words {
+        const uint32_t at = (odd ? crd1 : crd0) + slot * kCSlot;
+        if constexpr (BITS == 4) {
+            const u32x2 v = *reinterpret_cast<lds_u2>(at);
+            return {v[0], v[1]};
+        } else if constexpr (BITS == 3) {
+            return {*reinterpret_cast<lds_u32>(at), *reinterpret_cast<lds_u32>(at + 4)};
+        } else return {*reinterpret_cast<lds_u32>(at), 0u};
+    };
+    auto aligned = [&](const Words& q) -> Words {
+        if constexpr (BITS != 3) return q;
+        const unsigned long long v = (((unsigned long long)q.hi << 32) | q.lo) >> qshift;
+        return {(uint32_t)v, (uint32_t)(v >> 32)};
+    };
+    // values of codes 8 c + 4 s .. + 3 of the thread's 16
+    auto lookup = [&](const Words& q, int c, int s, uint32_t (&d)[4]) {
         if constexpr (NOLUT) {
-            d0 = grid_pair(c ? hi : lo, 2 * h);
-            d1 = grid_pair(c ? hi : lo, 2 * h + 1);
+            d[2 * s] = grid_pair(c ? q.hi : q.lo, 2 * s);
+            d[2 * s + 1] = grid_pair(c ? q.hi : q.lo, 2 * s + 1);
         } else {
-            const uint32_t w[2] = {lo, hi};
-            table.half(w, c, h, d0, d1);
+            const uint32_t w[2] = {q.lo, q.hi};
+            table.half(w, c, s, d[2 * s], d[2 * s + 1]);
         }
     };
-    auto code_words = [&](const uint32_t (&q)[2], uint32_t& lo, uint32_t& hi) {
-        lo = q[0]; hi = q[1];
-        if constexpr (BITS == 3) {
-            const unsigned long long v = (((unsigned long long)hi << 32) | lo) >> qshift;
-            lo = (uint32_t)v; hi = (uint32_t)(v >> 32);
-        }
+    auto write_chunk = [&](uint32_t slot, int c, const uint32_t (&d)[4]) {
+        *reinterpret_cast<lds_u4>((c ? wwr1 : wwr0) + slot * kTile) = u32x4{d[0], d[1], d[2], d[3]};
     };
 
-    // ---- one K step: matrix cores on buffer BUF, staging of the next step into buffer BUF ^ 1.
-    //      FIRST: the step starts a group (its first MFMAs take a zero accumulator); FOLD: it ends
-    //      one (acc += scale * part).  q: the codes of the step being staged; qn / tile_q: the set
-    //      freed by this step's staging is refilled with the codes of step tile_q.
-    auto step = [&](auto buf_, auto first_, auto fold_, uint32_t (&q)[2], int tile_q, int tile_x, uint32_t sraw0, uint32_t sraw1) {
-        constexpr int BUF = decltype(buf_)::value;
-        constexpr bool FIRST = decltype(first_)::value, FOLD = decltype(fold_)::value;
-        op16x8 a[2][2], b[2][2];
-        uint32_t wpk[4];
-        uint32_t lo, hi;
-        auto read_ops = [&](int set, int kk) {
+    // ---- first loads: the thread's table row and its first offsets, the first group sums, the codes of two groups and x
+    //      of the first step; then what is waited for later
+    const uint16_t* const trow = lut + (one_table ? 0 : wn_glob * L);     // (rows past N are clamped: they are never stored)
+    uint32_t td[L / 2];
+    if (!NOLUT && lut) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                a[set][i] = __builtin_bit_cast(op16x8, *reinterpret_cast<lds_u4>(ard + BUF * kXBuf + i * (32 * PLD * 2) + kk * 32));
-                b[set][i] = __builtin_bit_cast(op16x8, *reinterpret_cast<lds_u4>(brd + BUF * kWBuf + i * (32 * PLD * 2) + kk * 32));
-            }
-        };
-        auto w_stage = [&](int c, int h) {                      // look up half of chunk c; then the 16-byte write
-            lookup(lo, hi, c, h, wpk[2 * h], wpk[2 * h + 1]);
-            if (h == 1)
-                *reinterpret_cast<lds_u4>(wwr + (BUF ^ 1) * kWBuf + c * 16) = u32x4{wpk[0], wpk[1], wpk[2], wpk[3]};
-        };
-        auto x_write = [&](int p) {
-            *reinterpret_cast<lds_u4>(xwr + (BUF ^ 1) * kXBuf + p * (64 * PLD * 2)) = xr[p];
-        };
-        float s0 = 0.f, s1 = 0.f;
-        auto fold = [&](int t) {
-            const int i = t >> 1, j = t & 1;
-            const float s = j ? s1 : s0;
+        for (int i = 0; i < L / 4; ++i) { const u32x2 v = reinterpret_cast<const u32x2*>(trow)[i]; td[2 * i] = v[0]; td[2 * i + 1] = v[1]; }
+    }
+    const int og_lo = FINE ? 2 * g_lo : g_lo, og_hi = FINE ? 2 * g_hi : g_hi;      // this block's groups, in the units of xsums
+    const bool by16 = (GS & 7) == 0 && (FINE || lr == 0);      // a thread's 8 offsets are one aligned piece
+    const int64_t orow = wn_glob * GS;
+    auto fetch8 = [&](const uint16_t* from, int g0) -> u32x4 { // groups g0 .. g0 + 7 of the thread's row (past the last: masked below)
+        u32x4 v = {0, 0, 0, 0};
+        if (by16) {
+            v = *reinterpret_cast<const u32x4*>(from + orow + (g0 < og_hi ? g0 : 0));
+        } else {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = __builtin_fmaf(part[i][j][v], s, acc[i][j][v]);
-        };
-
-        read_ops(0, 0);
-        code_words(q, lo, hi);
-        ANY4_SB();
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const int cur = kk & 1;
-            if (kk < 3) read_ops(cur ^ 1, kk + 1);
-            ANY4_SB();
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int i = t >> 1, j = t & 1;
-                part[i][j] = mma(a[cur][i], b[cur][j], (FIRST && kk == 0) ? zero : part[i][j]);
-                if (kk == 0) {
-                    if (t & 1) w_stage(0, t >> 1);
-                } else if (kk == 1) {
-                    if (t & 1) w_stage(1, t >> 1);
-                    if (t == 3) fetch_q(q, tile_q);             // the set is free: its codes are in lo / hi and used up
-                } else if (kk == 2) {
-                    x_write(t);
-                    if (t == 3) fetch_x(tile_x);                // the registers are free again: a full K step of lead
-                } else if (FOLD) {
-                    // the scales were fetched two K steps ago; widening them here, not earlier,
-                    // keeps the wait for that fetch away from the start of the group
-                    if (t == 1) { s0 = h16_to_f32<F16>(sraw0); s1 = h16_to_f32<F16>(sraw1); }
-                    if (t >= 2) fold(t - 2);
-                }
-                ANY4_SB();
+            for (int e = 0; e < 8; ++e) {
+                const int gg = min(g0 + e, og_hi - 1);
+                v[e >> 1] |= (uint32_t)from[orow + (FINE ? gg : gg >> lr)] << (16 * (e & 1));
             }
         }
-        if constexpr (FOLD) { fold(2); fold(3); }
+        return v;
     };
-    // matrix cores on buffer 0, accumulating straight into acc (the offset steps: nothing to scale)
-    auto mma_plain = [&]() {
+    auto fetch_sums = [&](int c0) {                            // 64 columns of the group sums of 32 rows of x
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            op16x8 a[2], b[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                a[i] = __builtin_bit_cast(op16x8, *reinterpret_cast<lds_u4>(ard + i * (32 * PLD * 2) + kk * 32));
-                b[i] = __builtin_bit_cast(op16x8, *reinterpret_cast<lds_u4>(brd + i * (32 * PLD * 2) + kk * 32));
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = mma(a[i], b[j], acc[i][j]);
+        for (int i = 0; i < 4; ++i) {
+            const int64_t m = min(m0 + wave * 32 + i * 8 + (lane >> 3), M - 1);
+            const int col = 2 * c0 + 8 * ((lane & 7) ^ place(i * 8 + (lane >> 3)));
+            copy_to_lds_from((wave >> 1) * (kXSlots * kTile) + 2 * kTile + ((wave & 1) * 4 + i) * 1024, xsums + m * KP + (col < KP ? col : 0));
         }
     };
-    using B0 = std::integral_constant<int, 0>;
-    using B1 = std::integral_constant<int, 1>;
-    using Yes = std::true_type;
-    using No = std::false_type;
-
-    uint32_t q0[2], q1[2];
-    fetch_x(S0);                                               // in flight while the row's table is loaded
-    fetch_q(q0, S0);
-    fetch_q(q1, S0 + 1);
-    // the table of the thread's weight row (rows past N are clamped: they are never stored)
+    const int oc_lo = og_lo / 32 * 32;
+    u32x4 vo = fetch8(offset, oc_lo + 8 * wq), vs = {0, 0, 0, 0};
+    if constexpr (NOLUT) vs = fetch8(scale, oc_lo + 8 * wq);
+    fetch_sums(oc_lo);
+    fetch_codes(g_lo, 0);
+    fetch_codes(g_lo + 1, 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fetch_x(2 * g_lo, 0, i);
+    fetch_scales(g_lo, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fetch_x(2 * g_lo + 1, 1, i);
+    fetch_codes(g_lo + 2, 2);
+    fetch_scales(g_lo + 1, 1);
+    constexpr int kLater = 7;
     if constexpr (!NOLUT) {
-        uint32_t d[L / 2];
-        if (lut) {
-            const uint2* const src = reinterpret_cast<const uint2*>(lut + (one_table ? 0 : wn_glob * L));
-#pragma unroll
-            for (int i = 0; i < L / 4; ++i) { const uint2 v = src[i]; d[2 * i] = v.x; d[2 * i + 1] = v.y; }
-        } else {
+        if (!lut) {
 #pragma unroll
             for (int i = 0; i < L / 2; ++i)                    // no table: the integer grid
-                d[i] = f32_to_h16<F16>((float)(2 * i - L / 2)) | (f32_to_h16<F16>((float)(2 * i + 1 - L / 2)) << 16);
+                td[i] = f32_to_h16<F16>((float)(2 * i - L / 2)) | (f32_to_h16<F16>((float)(2 * i + 1 - L / 2)) << 16);
         }
-        table.load(d);
+        table.load(td);
     }
-    // K step 0 goes to buffer 0 with nothing to overlap with
-    {
-#pragma unroll
-        for (int p = 0; p < 4; ++p) *reinterpret_cast<lds_u4>(xwr + p * (64 * PLD * 2)) = xr[p];
-        uint32_t lo, hi;
-        code_words(q0, lo, hi);
+    op16x8 a[2][2][2], b[2][2][2];                             // [set][operand][32-row tile]
+    // operands kk = 2 * half + k of a step, n: 0 .. 7 in the order of their use
+    auto read_op = [&](int set, uint32_t xslot, uint32_t wslot, int half, int n) {
+        const int k = n < 4 ? n >> 1 : n & 1, i = n >> 2, kk = 2 * half + k;
+        if (n < 4 ? !(n & 1) : n >= 6) a[set][k][i] = __builtin_bit_cast(op16x8, *reinterpret_cast<lds_u4>(ard[kk] + xslot * kTile + i * (kTile / 2)));
+        else b[set][k][i] = __builtin_bit_cast(op16x8, *reinterpret_cast<lds_u4>(brd[kk] + wslot * kTile + i * (kTile / 2)));
+    };
+    // ---- offset term, while the first copies are on their way: K steps over the group dimension (activation group sums
+    //      split into bf16 hi + lo in columns 2g, 2g + 1; both columns meet offset[n][g]); unscaled
+    // NOLUT: three products over the group sums - right operand offset, then -128 * scale and -8 * scale (the
+    // bf16 scale with 7 / 3 added to its exponent and the sign flipped: exact)
+    constexpr int kKinds = NOLUT ? 3 : 1;
+    auto look_up_step = [&](int odd) {                         // the weights of one of the first two steps
+        const Words q = aligned(read_codes(0, odd));
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             uint32_t v[4];
-            lookup(lo, hi, c, 0, v[0], v[1]);
-            lookup(lo, hi, c, 1, v[2], v[3]);
-            *reinterpret_cast<lds_u4>(wwr + c * 16) = u32x4{v[0], v[1], v[2], v[3]};
+            lookup(q, c, 0, v);
+            lookup(q, c, 1, v);
+            write_chunk(odd, c, v);
         }
-        fetch_q(q0, min(S0 + 2, T - 1));
-        fetch_x(S0 + 1);
+    };
+    for (int c0 = oc_lo;;) {
+#pragma unroll
+        for (int kind = 0; kind < kKinds; ++kind) {
+            uint32_t d[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int gg = c0 + 8 * wq + e;
+                uint32_t t = ((kind == 0 ? vo : vs)[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
+                if (kind > 0) t = (t + (kind == 1 ? 0x0380u : 0x0180u)) ^ 0x8000u;
+                d[e] = gg >= og_lo && gg < og_hi ? (t & 0xFFFFu) | (t << 16) : 0u;
+            }
+            *reinterpret_cast<lds_u4>(wwr0 + kTile) = u32x4{d[0], d[1], d[2], d[3]};
+            *reinterpret_cast<lds_u4>(wwr1 + kTile) = u32x4{d[4], d[5], d[6], d[7]};
+            if (c0 == oc_lo) loads_left<kLater>();
+            else loads_left<0>();
+            lds_barrier();
+            if (kind == 0 && c0 == oc_lo) look_up_step(0);
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+#pragma unroll
+                for (int n = 0; n < 8; ++n) read_op(0, 2, 1, half, n);
+#pragma unroll
+                for (int n = 0; n < 8; ++n) {
+                    const int k = n >> 2, i = (n >> 1) & 1, j = n & 1;
+                    acc[i][j] = mma(a[0][k][i], b[0][k][j], acc[i][j]);
+                }
+            }
+            lds_barrier();
+        }
+        c0 += 32;
+        if (c0 >= og_hi) break;
+        vo = fetch8(offset, c0 + 8 * wq);
+        if constexpr (NOLUT) vs = fetch8(scale, c0 + 8 * wq);
+        fetch_sums(c0);
     }
-    lds_barrier();
+    fetch_x(2 * g_lo + 2, 2, 0);
+    fetch_x(2 * g_lo + 2, 2, 1);
+    look_up_step(1);                                           // (read behind the first barrier of the main loop)
 
-    // ---- main loop, one group of 128 (two K steps) per iteration.  Step s works on buffer s % 2 and
-    //      stages step s + 1: activations fetched during step s - 1 (right after that step's LDS
-    //      writes freed the registers), codes from set (s + 1) % 2, which it then refills with the
-    //      codes of step s + 3.  The last step stages a repeat of step T - 1 into a buffer that is
-    //      not read again.
-    // FINE: both scales of a chunk in one aligned 4-byte load per column, fetched one chunk ahead (the
-    // first fold comes three quarters of a K step after the top of the iteration: a load issued
-    // there would be waited for together with everything issued since)
-    uint32_t pn0 = 0, pn1 = 0;
-    if constexpr (FINE) { pn0 = reinterpret_cast<const uint32_t*>(scol[0])[g_lo]; pn1 = reinterpret_cast<const uint32_t*>(scol[1])[g_lo]; }
-    for (int g = g_lo; g < g_hi; ++g) {
-        const int s = 2 * g;
-        if constexpr (FINE) {
-            const uint32_t p0 = pn0, p1 = pn1;
-            const int gn = min(g + 1, g_hi - 1);
-            pn0 = reinterpret_cast<const uint32_t*>(scol[0])[gn];
-            pn1 = reinterpret_cast<const uint32_t*>(scol[1])[gn];
-            step(B0{}, Yes{}, Yes{}, q1, min(s + 3, T - 1), min(s + 2, T - 1), p0 & 0xFFFFu, p1 & 0xFFFFu);
-            lds_barrier();
-            step(B1{}, Yes{}, Yes{}, q0, min(s + 4, T - 1), min(s + 3, T - 1), p0 >> 16, p1 >> 16);
-            lds_barrier();
-        } else {
-            const uint32_t sraw0 = scol[0][g >> lr], sraw1 = scol[1][g >> lr];
-            step(B0{}, Yes{}, No{}, q1, min(s + 3, T - 1), min(s + 2, T - 1), 0u, 0u);
-            lds_barrier();
-            step(B1{}, No{}, Yes{}, q0, min(s + 4, T - 1), min(s + 3, T - 1), sraw0, sraw1);
-            lds_barrier();
+    // ---- main loop.  Operands are read half a K step (32 values) ahead of the matrix instructions, into two sets of
+    //      registers; a barrier stands between the instructions of a step's first half and those of its second.
+    // One half of a step: eight matrix instructions, each tile's two one after the other, and what `between` puts
+    // behind each of them
+    auto half_step = [&](auto set_, auto first_, auto between) {
+        constexpr int SET = decltype(set_)::value;
+        constexpr bool FIRST = decltype(first_)::value;
+#pragma unroll
+        for (int n = 0; n < 8; ++n) {
+            const int i = n >> 2, j = (n >> 1) & 1, k = n & 1;
+            // the wavefront that is behind in the phase goes first: both of a SIMD reach the barrier together
+            if constexpr (SET == 1) {
+                if (n == 0) __builtin_amdgcn_s_setprio(3);
+                if (n == 4) __builtin_amdgcn_s_setprio(2);
+            } else {
+                if (n == 0) __builtin_amdgcn_s_setprio(1);
+                if (n == 4) __builtin_amdgcn_s_setprio(0);
+            }
+            part[i][j] = mma(a[SET][k][i], b[SET][k][j], FIRST && k == 0 ? zero : part[i][j]);
+            between(n);
+            if (n & 1) ANY4_SB();
         }
+    };
+    // elements lo .. hi - 1 of the 64 sums of a finished group enter the result
+    float s0 = 0.f, s1 = 0.f;
+    uint32_t sraw0 = 0, sraw1 = 0;
+    auto fold = [&](int lo, int hi) {
+#pragma unroll
+        for (int e = lo; e < hi; ++e) {
+            const int i = e >> 5, j = (e >> 4) & 1, v = e & 15;
+            acc[i][j][v] = __builtin_fmaf(part[i][j][v], j ? s1 : s0, acc[i][j][v]);
+        }
+    };
+    auto read_scales = [&](uint32_t slot) {
+        const uint32_t at = kSAt + slot * kSSlot + wave * 256 + r32 * 4;
+        sraw0 = *reinterpret_cast<lds_u32>(at);
+        sraw1 = *reinterpret_cast<lds_u32>(at + 128);
+    };
+    auto widen_scales = [&](int odd) {
+        s0 = h16_to_f32<F16>(FINE && odd ? sraw0 >> 16 : sraw0 & 0xFFFFu);
+        s1 = h16_to_f32<F16>(FINE && odd ? sraw1 >> 16 : sraw1 & 0xFFFFu);
+    };
+    // the sums are folded between the last instructions on them (n >= 4 of the old half) and the next on the same registers
+    auto pin = [&]() {                                         // (or the additions move to where their results are used)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(acc[i][j]));
+    };
+    auto fold_old = [&](int n) { if (n >= 4) fold((n - 4) * 26 / 4, (n - 3) * 26 / 4); };
+    auto fold_new = [&](int n) { if (n < 6) fold(26 + n * 38 / 6, 26 + (n + 1) * 38 / 6); };
+    // end of a phase: the copies of x and codes issued before this phase have landed (six younger ones may be on their way)
+    auto next_phase = [&]() {
+        loads_left<6>();
+        lds_barrier();
+    };
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, 1>;
+    using C2 = std::integral_constant<int, 2>;
+    using Yes = std::true_type;
+    using No = std::false_type;
+    uint32_t wpk[4], held[4];
+    // a group, steps 2g and 2g + 1; U: its place in the rings of three
+    auto group = [&](auto u_, int g) {
+        constexpr uint32_t U = decltype(u_)::value, X0 = 2 * U % 3, X1 = (2 * U + 1) % 3, X2 = (2 * U + 2) % 3, NEXT = (U + 1) % 3, AFTER = (U + 2) % 3;
+        Words q, qn;
+        // first half of step 2g
+        half_step(C0{}, Yes{}, [&](int n) {
+            read_op(1, X0, 0, 1, n);
+            if (n == 4) q = read_codes(NEXT, 0);
+            if ((n & 3) == 1) fetch_x(2 * g + 2, X2, 2 + (n >> 2));
+            fold_new(n);
+        });
+        pin();
+        next_phase();
+        // second half of step 2g; the first half of the weights of step 2g + 2
+        q = aligned(q);
+        half_step(C1{}, No{}, [&](int n) {
+            read_op(0, X1, 1, 0, n);
+            if (FINE && n == 0) read_scales(U);
+            if (FINE && n == 4) widen_scales(0);
+            if (FINE) fold_old(n);
+            if (n == 1) lookup(q, 0, 0, wpk);
+            if (n == 3) { lookup(q, 0, 1, wpk); write_chunk(0, 0, wpk); }
+            if (n == 5) qn = read_codes(NEXT, 1);
+            if ((n & 3) == 1) fetch_x(2 * g + 3, X0, n >> 2);
+        });
+        // first half of step 2g + 1; the second half of the weights of step 2g + 2, the first of those of 2g + 3
+        half_step(C0{}, std::integral_constant<bool, FINE>{}, [&](int n) {
+            read_op(1, X1, 1, 1, n);
+            if (FINE) fold_new(n);
+            if (n == 1) lookup(q, 1, 0, wpk);
+            if (n == 3) { lookup(q, 1, 1, wpk); write_chunk(0, 1, wpk); }
+            if (n == 5) { qn = aligned(qn); lookup(qn, 0, 0, held); }
+            if (n == 7) lookup(qn, 0, 1, held);
+            if ((n & 3) == 1) fetch_x(2 * g + 3, X0, 2 + (n >> 2));
+            if (n == 6) fetch_codes(g + 3, U);
+            if (n == 7) fetch_scales(g + 2, AFTER);
+        });
+        next_phase();
+        // second half of step 2g + 1
+        half_step(C1{}, No{}, [&](int n) {
+            read_op(0, X2, 0, 0, n);
+            if (n == 0) { write_chunk(1, 0, held); if (!FINE) read_scales(U); }
+            if (n == 1) lookup(qn, 1, 0, wpk);
+            if (n == 3) { lookup(qn, 1, 1, wpk); write_chunk(1, 1, wpk); }
+            if (n == 4) widen_scales(1);
+            if ((n & 3) == 1) fetch_x(2 * g + 4, X1, n >> 2);
+            fold_old(n);
+        });
+        pin();
+    };
+#pragma unroll
+    for (int n = 0; n < 8; ++n) read_op(0, 0, 0, 0, n);
+    for (int g = g_lo;;) {
+        group(C0{}, g);
+        if (++g == g_hi) break;
+        group(C1{}, g);
+        if (++g == g_hi) break;
+        group(C2{}, g);
+        if (++g == g_hi) break;
     }
+    fold(26, 64);
+    loads_left<0>();                                           // (what was copied past the last step)
 
-    // ---- offset term: a few more K steps over the group dimension (activation group sums split into
-    //      bf16 hi + lo in columns 2g, 2g+1; both columns meet offset[n][g]); unscaled
-    const int og_lo = FINE ? 2 * g_lo : g_lo, og_hi = FINE ? 2 * g_hi : g_hi;      // this block's groups, in the units of xsums
-    // NOLUT: three passes over the group sums - right operand offset, then -128 * scale and -8 * scale (the
-    // bf16 scale with 7 / 3 added to its exponent and the sign flipped: exact)
-    constexpr int kKinds = NOLUT ? 3 : 1;
-#pragma unroll
-    for (int kind = 0; kind < kKinds; ++kind)
-    for (int k0 = 2 * og_lo / PBK * PBK; k0 < 2 * og_hi; k0 += PBK) {
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const uint16_t* src = xsums + min(m0 + p * 64 + xr_row, M - 1) * KP + xc8 * 8 + k0;
-            xr[p] = k0 + xc8 * 8 < KP ? *reinterpret_cast<const u32x4*>(src) : u32x4{0, 0, 0, 0};
-        }
-        uint32_t pk[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int gg = (k0 + wq * 16 + 2 * j) >> 1;
-            const bool in = gg >= og_lo && gg < og_hi;
-            uint32_t b = in ? (kind == 0 ? offset : scale)[wn_glob * GS + (FINE ? gg : gg >> lr)] : 0u;
-            if (kind == 1) b = in ? (b + 0x0380u) ^ 0x8000u : 0u;
-            if (kind == 2) b = in ? (b + 0x0180u) ^ 0x8000u : 0u;
-            pk[j] = b | (b << 16);
-        }
-#pragma unroll
-        for (int p = 0; p < 4; ++p) *reinterpret_cast<lds_u4>(xwr + p * (64 * PLD * 2)) = xr[p];
-        *reinterpret_cast<lds_u4>(wwr) = u32x4{pk[0], pk[1], pk[2], pk[3]};
-        *reinterpret_cast<lds_u4>(wwr + 16) = u32x4{pk[4], pk[5], pk[6], pk[7]};
-        lds_barrier();
-        mma_plain();
-        lds_barrier();
-    }
+    lds_barrier();                                             // LDS is free: the whole block's copies have landed, its operands have been read
 
     // ---- store (accumulator element v of a lane is row 8*(v/4) + 4*(lane/32) + v%4, column lane%32 of its
     //      32 x 32 tile)
+    // Rows of y that are whole 16-byte pieces take 8 stores of 16 bytes per lane through LDS: 64 stores of 2 bytes took a block
+    // 10 000 cycles, 8 % of its time at K = 4096, in which nothing else runs on the compute unit.
+    const bool by8 = (N & 7) == 0;
+    constexpr uint32_t kRow = 64 * 2 + 16, kWaveOut = 64 * kRow;          // a wavefront's 64 x 64 outputs, rows spread over the banks
+    auto put_tile = [&](int i, int j, const f32x16& r) {
+        // two rows (v, v + 1) of one column -> two columns of one row: even lanes keep row v, odd ones row v + 1
+        const uint32_t sel = lane & 1 ? 0x03020706u : 0x05040100u;
+        const uint32_t at = wave * kWaveOut + (i * 32 + 4 * h + (lane & 1)) * kRow + j * 64 + (r32 >> 1) * 4;
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) {
+            const uint32_t own = f32x2_to_h16x2<F16>(r[v], r[v + 1]);
+            const uint32_t other = __builtin_amdgcn_update_dpp(0, own, 0xB1 /*quad_perm 1 0 3 2*/, 0xF, 0xF, false);
+            *reinterpret_cast<lds_u32>(at + ((v >> 2) * 8 + (v & 3)) * kRow) = vperm(other, own, sel);
+        }
+    };
+    auto store_rows = [&]() {                                  // (the wavefront's own part of LDS)
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            const int row = p * 8 + (lane >> 3);
+            const u32x4 v = *reinterpret_cast<lds_u4>(wave * kWaveOut + row * kRow + (lane & 7) * 16);
+            const int64_t m = m0 + wm * 64 + row, n = n0 + wn * 64 + (lane & 7) * 8;
+            if (m < M && n < N) *reinterpret_cast<u32x4*>(y + m * N + n) = v;
+        }
+    };
     auto store_tile = [&](int i, int j, const f32x16& r) {
-        const int64_t n = n0 + wn * 64 + j * 32 + (lane & 31);
+        const int64_t n = n0 + wn * 64 + j * 32 + r32;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const int64_t m = m0 + wm * 64 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
+            const int64_t m = m0 + wm * 64 + i * 32 + (v >> 2) * 8 + h * 4 + (v & 3);
             if (m < M && n < N) y[m * N + n] = (uint16_t)f32_to_h16<F16>(r[v]);
         }
+    };
+    auto finish = [&](int i, int j, const f32x16& r) {
+        if (by8) put_tile(i, j, r);
+        else store_tile(i, j, r);
     };
     if (slice < 0) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) store_tile(i, j, acc[i][j]);
+            for (int j = 0; j < 2; ++j) finish(i, j, acc[i][j]);
+        if (by8) store_rows();
         return;
     }
     // ---- a K slice: its fp32 sums go to the workspace; the last slice of the tile to arrive adds them all
-    float* mine = partial + ((int64_t)(tile - tail_first) * tail_s + slice) * (PBM * PBN);
-    auto elem = [&](int i, int j, int v) -> int {
-        return (wm * 64 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3)) * PBN + wn * 64 + j * 32 + (lane & 31);
-    };
+    //      (16 bytes per lane: four accumulator elements)
+    float* const all = partial + (int64_t)(tile - tail_first) * tail_s * (PBM * PBN);
+    const __amdgpu_buffer_rsrc_t ares = __builtin_amdgcn_make_buffer_rsrc(all, 0, tail_s * (PBM * PBN) * 4, 0x00020000);
+    auto quad = [&](int i, int j, int v4) -> uint32_t { return (uint32_t)(((((i * 2 + j) * 4 + v4) * 8 + wave) * 64 + lane) * 16); };
+    constexpr int kAgent = 16;                                 // cache policy: coherent over the whole device
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                // through an opaque copy: with the accumulator vector itself as the source of the atomic
+            for (int v4 = 0; v4 < 4; ++v4) {
+                // through an opaque copy: with the accumulator vector itself as the source of the
                 // stores the compiler copies all 64 accumulators inside the main loop on every iteration
-                float t = acc[i][j][v];
-                asm volatile("" : "+v"(t));
-                splitk_store(mine + elem(i, j, v), t);
+                u32x4 q = {__float_as_uint(acc[i][j][4 * v4]), __float_as_uint(acc[i][j][4 * v4 + 1]), __float_as_uint(acc[i][j][4 * v4 + 2]), __float_as_uint(acc[i][j][4 * v4 + 3])};
+                asm volatile("" : "+v"(q));
+                __builtin_amdgcn_raw_buffer_store_b128(q, ares, quad(i, j, v4), slice * (PBM * PBN) * 4, kAgent);
             }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this thread's sums are out
     lds_barrier();                                             // ... and so are the whole block's
-    int* flag = reinterpret_cast<int*>(smem);
-    if (tid == 0) *flag = arrive_one(counters + (tile - tail_first), tail_s) ? 1 : 0;
+    if (tid == 0) *reinterpret_cast<lds_u32>(0u) = arrive_one(counters + (tile - tail_first), tail_s) ? 1u : 0u;
     lds_barrier();
-    if (*flag == 0) return;
-    const float* all = partial + (int64_t)(tile - tail_first) * tail_s * (PBM * PBN);
+    const uint32_t last = *reinterpret_cast<lds_u32>(0u);
+    lds_barrier();                                             // (the outputs go over it)
+    if (last == 0u) return;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            f32x16 sum;
+            f32x16 sum = zero;
+            constexpr int FLIGHT = 4;                          // slices whose loads are in flight together
+            for (int sl = 0; sl < tail_s; sl += FLIGHT) {
+                u32x4 q[FLIGHT][4];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) sum[v] = 0.f;
-            for (int sl = 0; sl < tail_s; sl += 2) {           // two slices' worth of loads in flight
-                float a[16], b[16];
-                const int sl1 = min(sl + 1, tail_s - 1);
+                for (int u = 0; u < FLIGHT; ++u)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    a[v] = splitk_load(all + (int64_t)sl * (PBM * PBN) + elem(i, j, v));
-                    b[v] = splitk_load(all + (int64_t)sl1 * (PBM * PBN) + elem(i, j, v));
-                }
+                    for (int v4 = 0; v4 < 4; ++v4) q[u][v4] = __builtin_amdgcn_raw_buffer_load_b128(ares, quad(i, j, v4), min(sl + u, tail_s - 1) * (PBM * PBN) * 4, kAgent);
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    sum[v] += a[v];
-                    if (sl + 1 < tail_s) sum[v] += b[v];
-                }
+                for (int u = 0; u < FLIGHT; ++u)               // (otherwise each load is put in front of its addition)
+#pragma unroll
+                    for (int v4 = 0; v4 < 4; ++v4) asm volatile("" : "+v"(q[u][v4]));
+#pragma unroll
+                for (int u = 0; u < FLIGHT; ++u)
+                    if (sl + u < tail_s)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) sum[v] += __uint_as_float(q[u][v >> 2][v & 3]);
             }
-            store_tile(i, j, sum);
+            finish(i, j, sum);
         }
+    if (by8) store_rows();
 }
 
 // Work split: whole tiles, and K slices for the tiles of a last round that would leave more than
@@ -504,23 +642,28 @@ hipError_t launch_prefill(const uint16_t* x, const uint32_t* codes, const uint16
     const int gm = (int)pp.gm, tail_first = (int)(pp.tiles - pp.tail_tiles), tail_s = pp.tail_s;
     // the LDS limit first: whatever can be refused is refused before anything is enqueued
     hipError_t e = hipSuccess;
-#define ANY4_PREFILL_F(B, F, H, NL)                                                                                 \
+#define ANY4_PREFILL_F(B, F, H, NL, W)                                                                              \
     do {                                                                                                          \
-        e = ensure_lds<prefill_kernel<B, F, H, NL>>((int)kLdsBytes);                                       \
+        e = ensure_lds<prefill_kernel<B, F, H, NL, W>>((int)kLdsBytes);                                    \
         if (e != hipSuccess) return e;                                                                            \
         if (f16) hipLaunchKernelGGL(group_sums_kernel<true>, dim3((unsigned)sblocks), dim3(256), 0, stream, x, M, K, KP, 0, xsums); \
         else hipLaunchKernelGGL(group_sums_kernel<false>, dim3((unsigned)sblocks), dim3(256), 0, stream, x, M, K, KP, fine ? 1 : 0, xsums); \
         e = hipGetLastError();                                                                                    \
         if (e != hipSuccess) return e;                                                                            \
-        hipLaunchKernelGGL((prefill_kernel<B, F, H, NL>), grid, block, kLdsBytes, stream, x, codes, lut, scale, \
+        hipLaunchKernelGGL((prefill_kernel<B, F, H, NL, W>), grid, block, kLdsBytes, stream, x, codes, lut, scale, \
                            offset, xsums, KP, M, N, K, F ? 0 : lr, (repacked ? 1 : 0) | (one_table ? 2 : 0), gm, tail_first, tail_s, counters, partial, y); \
+    } while (0)
+#define ANY4_PREFILL_W(B, W)                                                                                      \
+    do {                                                                                                          \
+        if (B == 4 && !lut && !f16 && !fine && lr == 0) ANY4_PREFILL_F(4, false, false, true, W);                 \
+        else if (f16) ANY4_PREFILL_F(B, false, true, false, W);                                                   \
+        else if (fine) ANY4_PREFILL_F(B, true, false, false, W);                                                  \
+        else ANY4_PREFILL_F(B, false, false, false, W);                                                           \
     } while (0)
 #define ANY4_PREFILL(B)                                                                                           \
     do {                                                                                                          \
-        if (B == 4 && !lut && !f16 && !fine && lr == 0) ANY4_PREFILL_F(4, false, false, true);                    \
-        else if (f16) ANY4_PREFILL_F(B, false, true, false);                                                             \
-        else if (fine) ANY4_PREFILL_F(B, true, false, false);                                                            \
-        else ANY4_PREFILL_F(B, false, false, false);                                                                     \
+        if (K > kNarrowK) ANY4_PREFILL_W(B, true);                                                                \
+        else ANY4_PREFILL_W(B, false);                                                                            \
     } while (0)
     switch (bits) {
         case 4: ANY4_PREFILL(4); break;
@@ -528,6 +671,7 @@ hipError_t launch_prefill(const uint16_t* x, const uint32_t* codes, const uint16
         default: ANY4_PREFILL(2); break;
     }
 #undef ANY4_PREFILL_F
+#undef ANY4_PREFILL_W
 #undef ANY4_PREFILL
     return hipGetLastError();
 }

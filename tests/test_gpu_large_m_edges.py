@@ -1,0 +1,88 @@
+"""The matrix-core kernel (more than 128 rows of x) at the edges of its tiles (256 rows of x, 128 rows of weights, 64 values
+along K): one group, group counts that leave its rings of three part-filled, offsets in and out of 16-byte pieces, rows of y
+that are and are not whole 16-byte pieces, K slices, rows so long that addresses take 64 bits.  Against the oracle; bar as in
+test_gpu_parity.py."""
+import numpy as np
+import pytest
+
+from paper_2507_04610_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = [(129, 1, 1), (256, 128, 2), (257, 264, 3), (130, 127, 33), (385, 520, 40), (512, 136, 72), (777, 129, 23)]
+LONG = [(129, 24, 1026)]          # K = 131328: beyond the 32-bit offsets
+
+
+def dev16(a, f16=False):
+    t = torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).cuda()
+    return t.view(torch.float16 if f16 else torch.bfloat16)
+
+
+@pytest.mark.parametrize("bits", (4, 3, 2))
+@pytest.mark.parametrize("variant", ("plain", "repack", "f16", "g64", "g256", "one_table", "int4"))
+def test_tile_edges(oracle, bits, variant):
+    import paper_2507_04610_amd as any4
+    any4.load_library()
+    if variant == "int4" and bits != 4:
+        pytest.skip("the table-free format has 4 bits")
+    f16, group = variant == "f16", {"g64": 64, "g256": 256}.get(variant, 128)
+    for M, N, G in SHAPES + LONG:
+        if group == 256 and G % 2:
+            G += 1
+        K = 128 * G
+        cs = inputs.make_case(M, N, K, bits, seed=M + G, f16=f16)
+        lut, sc, of = cs.lut, cs.scale, cs.offset
+        if variant == "int4":
+            lut = np.tile(inputs.f32_to_bf16_bits(np.arange(-8, 8, dtype=np.float32)), (N, 1))
+        if variant == "one_table":
+            lut = np.ascontiguousarray(np.tile(cs.lut[:1], (N, 1)))
+        if group == 64:
+            other = inputs.make_case(1, N, K, bits, seed=M + G + 7)
+            sc = np.ascontiguousarray(np.stack([sc, other.scale], axis=2).reshape(N, -1))
+            of = np.ascontiguousarray(np.stack([of, other.offset], axis=2).reshape(N, -1))
+        elif group == 256:
+            sc, of = np.ascontiguousarray(sc[:, ::2]), np.ascontiguousarray(of[:, ::2])
+        packed = oracle.pack(cs.codes_u8, bits)
+        y64 = oracle.gemm(cs.x, packed, lut, sc, of, K, bits, threads=8, group=group, f16=f16)
+        codes = torch.from_numpy(packed.view(np.int32)).cuda()
+        x, s, o = dev16(cs.x, f16), dev16(sc, f16), dev16(of, f16)
+        print((bits, variant, M, N, K), flush=True)
+        ws = torch.full((max(16, any4.any4_gemm_workspace_bytes(M, N, K, bits)),), 0xA5, dtype=torch.uint8, device="cuda")
+
+        def run():
+            if variant == "repack":
+                return any4.any4_gemm_repacked(x, any4.any4_repack(codes, bits), dev16(lut, f16), s, o, bits, workspace=ws)
+            t = None if variant == "int4" else dev16(lut[:1] if variant == "one_table" and N > 1 else lut, f16)
+            return any4.any4_gemm(x, codes, t, s, o, bits, group=group, workspace=ws)
+        y = run()
+        got = y.float().cpu().numpy().astype(np.float64)
+        tol = 1e-2 * oracle.rms(y64) + np.abs(y64) * (2.0 ** -11 if f16 else 2.0 ** -8)
+        assert np.all(np.abs(got - y64) <= tol), (M, N, K, float((np.abs(got - y64) - tol).max()))
+        assert torch.equal(y.view(torch.int16), run().view(torch.int16))     # the workspace is left clean
+
+
+@pytest.mark.parametrize("N", (136, 131))
+def test_outputs_round_to_nearest_even(oracle, N):
+    """One activation per row of x, no offsets: an output is the product of three bf16 numbers, exact in fp32 while it is a
+    normal number, so that only its rounding to bf16 is left.  With results from sub-normal to beyond bf16's range."""
+    import paper_2507_04610_amd as any4
+    any4.load_library()
+    M, K, bits = 300, 256, 4
+    rng = np.random.default_rng(N)
+    cs = inputs.make_case(M, N, K, bits, seed=N)
+    at = rng.integers(0, K, M)
+    value = inputs.f32_to_bf16_bits((rng.standard_normal(M) * 2.0 ** rng.integers(-70, 66, M)).astype(np.float32))
+    x = np.zeros((M, K), np.uint16)
+    x[np.arange(M), at] = value
+    scale = inputs.f32_to_bf16_bits((rng.uniform(1, 2, cs.scale.shape) * 2.0 ** rng.integers(-72, 72, cs.scale.shape)).astype(np.float32))
+    y = any4.any4_gemm(dev16(x), any4.any4_pack(torch.from_numpy(cs.codes_u8).cuda(), bits), dev16(cs.lut), dev16(scale),
+                       dev16(np.zeros_like(cs.offset)), bits)
+    f64 = lambda a: inputs.bf16_bits_to_f32(a).astype(np.float64)
+    w = np.take_along_axis(f64(cs.lut), cs.codes_u8.astype(np.int64), axis=1) * np.repeat(f64(scale), 128, axis=1)
+    exact = f64(value)[:, None] * w[:, at].T
+    with np.errstate(over="ignore"):
+        want = torch.from_numpy(exact.astype(np.float32)).to(torch.bfloat16).float().numpy()
+    assert np.isinf(want).any() and (np.abs(want[want != 0]) < 2.0 ** -126).any()
+    assert np.array_equal(y.float().cpu().numpy(), want)
