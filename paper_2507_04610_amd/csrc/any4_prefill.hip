@@ -29,12 +29,14 @@
 //   - A tile's two instructions of a half step follow each other, so that a finished group's sums have six matrix
 //     instructions' time to be scaled before the next group writes their registers.
 //   - Lookups, reads, writes and copies are spread over the instructions of a step.  Four copies at once at its start
-//     held every wavefront until the address unit had taken them: 530 cycles a step.
-// The order is pinned by scheduling barriers; left to itself the compiler emits "all MFMAs, then all staging".  A K step takes 1520
+//     held every wavefront until the address unit had taken them: 530 cycles a step.  The reads of a half step that ends at the
+//     barrier come in its first four instructions: read one by one, the last held everybody there (1 %).
+// The order is pinned by scheduling barriers, one per four matrix instructions (one per two: 1 % slower; none, and the
+// compiler emits "all MFMAs, then all staging").  A K step takes 1500
 // cycles (1940 with x and codes through registers into padded LDS, operands read behind the barrier, and the fold at a
 // group's end), of which the matrix instructions are 1024; a loop of nothing but their mix of matrix, vector
-// and LDS instructions takes 1280.  The clock follows the load: 1.85 GHz here, 1.7 in that loop.  N = 28672, K = 4096 at M = 2048: 540 -> 475 us;
-// the four linears of an 8B layer at M = 2048 / 512: 1086 / 346 -> 955 / 306 us.
+// and LDS instructions takes 1280.  Power holds the clock: 1.84 GHz before, 1.65 now.  N = 28672, K = 4096 at M = 2048: 540 -> 470 us;
+// the four linears of an 8B layer at M = 2048 / 512: 1035 / 337 -> 908 / 296 us.
 #include "any4_device.h"
 #include "any4_internal.h"
 #include "any4_lds_copy.h"
@@ -396,7 +398,7 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
             }
             part[i][j] = mma(a[SET][k][i], b[SET][k][j], FIRST && k == 0 ? zero : part[i][j]);
             between(n);
-            if (n & 1) ANY4_SB();
+            if ((n & 3) == 3) ANY4_SB();
         }
     };
     // elements lo .. hi - 1 of the 64 sums of a finished group enter the result
@@ -444,7 +446,7 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
         Words q, qn;
         // first half of step 2g
         half_step(C0{}, Yes{}, [&](int n) {
-            read_op(1, X0, 0, 1, n);
+            if (n < 4) { read_op(1, X0, 0, 1, 2 * n); read_op(1, X0, 0, 1, 2 * n + 1); }
             if (n == 4) q = read_codes(NEXT, 0);
             if ((n & 3) == 1) fetch_x(2 * g + 2, X2, 2 + (n >> 2));
             fold_new(n);
@@ -465,7 +467,7 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
         });
         // first half of step 2g + 1; the second half of the weights of step 2g + 2, the first of those of 2g + 3
         half_step(C0{}, std::integral_constant<bool, FINE>{}, [&](int n) {
-            read_op(1, X1, 1, 1, n);
+            if (n < 4) { read_op(1, X1, 1, 1, 2 * n); read_op(1, X1, 1, 1, 2 * n + 1); }
             if (FINE) fold_new(n);
             if (n == 1) lookup(q, 1, 0, wpk);
             if (n == 3) { lookup(q, 1, 1, wpk); write_chunk(0, 1, wpk); }
