@@ -919,9 +919,10 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     // the scaled weight, the sample weight s and the sampling mass.  The mass is s for the first centre and
     // s * (squared distance to the nearest centre chosen so far) afterwards; as s >= 0, multiplying by s and
     // rounding is monotone, so s * min(d_old, d_new) is min(s * d_old, s * d_new) bit for bit and the
-    // distances themselves need not be kept.  Bound: vector issue, 2^n rounds of six instructions per weight (ten with a
+    // distances themselves need not be kept.  Bound: vector issue, 2^n rounds of five instructions per weight (ten with a
     // comparison and two selects in place of v_min_f64, x converted every time and copies of x and s): 6144 x 4096 any4
-    // 588 -> 519 us, 4096 x 14336 1698 -> 1479 us together with the sums of the wavefronts, read several at a time.
+    // 588 -> 519 us, 4096 x 14336 1698 -> 1479 us together with the sums of the wavefronts, read several at a time.  The sample weights
+    // are held in fp64 too: their conversion takes as long as two of the others; 493 -> 485 and 1427 -> 1410 us.
     // Sixteen weights a thread for every K, so that whole wavefronts have none where the row is shorter than the block's
     // 16 T and skip the phases: with the row spread evenly, all of them ran all phases with most lanes idle.  With the
     // codes from the sort's keys (below): 11525 x 1024 any4 726 -> 579 us, 6144 x 4096 528 -> 500, 4096 x 14336 1522 -> 1447.
@@ -977,12 +978,13 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
             if (tid == 0) { cen[q] = cq; cen0[q] = cq; }
             return cq;
         };
-        double mass[16], xd[16];
+        double mass[16], xd[16], sd[16];
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            mass[e] = (double)sv[e];
+            sd[e] = (double)sv[e];
             xd[e] = (double)xv[e];
-            asm volatile("" : "+v"(xd[e]));
+            asm volatile("" : "+v"(xd[e]), "+v"(sd[e]));
+            mass[e] = sd[e];
         }
         // With a NaN or an infinity in the row a mass is replaced only by one that compares as smaller: one that is no number
         // from the first centre on stays so, and with it the total (`none`, whatever v_min_f64 makes of the mass); one that
@@ -1005,6 +1007,7 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
                     run += mass[e];
                     last = mass[e] > 0.0 ? e : last;
                     pick = min(pick, run > t ? e : 16);
+                    asm volatile("" : "+v"(run), "+v"(pick), "+v"(last));      // (one after the other: sixteen sums at a time hold 32 registers)
                 }
                 return pick == 16 ? last : pick;
             });
@@ -1022,17 +1025,15 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
             if (mine) {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    // (the empty asm statement keeps the conversions inside the loop over q: hoisted, they
-                    // would hold 32 more registers for the whole start)
-                    asm volatile("" : "+v"(sv[e]));
                     const double d = xd[e] - cq;
-                    const double m = (double)sv[e] * (d * d);
+                    const double m = sd[e] * (d * d);
                     asm("v_min_f64 %0, %1, %0" : "+v"(mass[e]) : "v"(m));
+                    if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);         // (more of them at a time do not fit the registers)
                 }
             }
         }
 #pragma unroll
-        for (int e = 0; e < 16; ++e) xv[e] = (float)xd[e];         // exact
+        for (int e = 0; e < 16; ++e) { xv[e] = (float)xd[e]; sv[e] = (float)sd[e]; }        // exact
     }
 
     // ---- sort the row: elements (order-preserving image of w_S, sample weight), ascending; every thread
