@@ -79,9 +79,14 @@ constexpr int64_t kNarrowK = 1 << 17;
 // X[m][g] = sum of the 128 activations of group g, in fp32, stored as two bf16 (high part,
 // remainder) at xs[m][2g], xs[m][2g+1]; columns 2G .. KP-1 are zero.  16 lanes per (m, g).
 // `fine`: groups of 64 activations, 8 lanes each.
+// Also sets the words that count the arrivals of K slices to 0, so that those find no earlier call's leftovers: claiming
+// such words by compare-and-swap, as the other kernels do, has every part of every slice of a tile queue up at one word (four
+// linears at M = 512, scratch allocated by the call: 314 us against 295).
 template <bool F16>
 __global__ __launch_bounds__(256) void group_sums_kernel(const uint16_t* __restrict__ x, int64_t M,
-                                                         int64_t K, int KP, int fine, uint16_t* __restrict__ xs) {
+                                                         int64_t K, int KP, int fine, uint16_t* __restrict__ xs,
+                                                         unsigned long long* __restrict__ counters, int ncounters) {
+    for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < ncounters; c += (int64_t)gridDim.x * 256) counters[c] = 0ull;
     const int lanes = fine ? 8 : 16;
     const int64_t G = K / (8 * lanes);
     const int64_t unit = ((int64_t)blockIdx.x * 256 + threadIdx.x) / lanes;  // (m, g), g fastest
@@ -142,7 +147,7 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
     // Blocks below tail_first own a whole output tile.  The tiles of the last, partly filled round
     // of blocks are cut along K into tail_s slices of whole groups, one block each, so that the
     // round keeps every compute unit busy for 1 / tail_s of a tile's time; the slices' fp32 results
-    // meet in the workspace and the block that arrives last adds them in slice order.
+    // meet in the workspace and are added in slice order.
     int tile = blockIdx.x, slice = -1;
     int g_lo = 0, g_hi = (int)G;
     if (tile >= tail_first) {
@@ -171,12 +176,20 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
     // x: a wavefront moves 32 rows of a step, 8 to a copy
     const int64_t xrow = min(m0 + wave * 32, M - 1);
     const char* const xbase = reinterpret_cast<const char*>(x + xrow * K);
+    auto x_offset = [&](int i, int l) -> uint32_t {
+        return offset_of(min(m0 + wave * 32 + i * 8 + (l >> 3), M - 1) - xrow, 2 * K, ((l & 7) ^ place(i * 8 + (l >> 3))) * 16);
+    };
     uint32_t xoff[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        xoff[i] = offset_of(min(m0 + wave * 32 + i * 8 + (lane >> 3), M - 1) - xrow, 2 * K, ((lane & 7) ^ place(i * 8 + (lane >> 3))) * 16);
+    for (int i = 0; i < 4; ++i) xoff[i] = x_offset(i, lane);
     auto fetch_x = [&](int step, uint32_t slot, int i) {
-        copy16((wave >> 1) * (kXSlots * kTile) + slot * kTile + ((wave & 1) * 4 + i) * 1024, xbase + (int64_t)min(step, T - 1) * (PBK * 2), xoff[i], 2 * K);
+        uint32_t off = xoff[i];
+        if constexpr (WIDE) {                                  // (four registers less to keep)
+            int l = lane;
+            asm volatile("" : "+v"(l));
+            off = x_offset(i, l);
+        }
+        copy16((wave >> 1) * (kXSlots * kTile) + slot * kTile + ((wave & 1) * 4 + i) * 1024, xbase + (int64_t)min(step, T - 1) * (PBK * 2), off, 2 * K);
     };
     // codes: pieces of 16 bytes, BITS to a row and group, one behind the other (re-laid-out: as they lie in units of
     // 16 rows); with less than 4 bits the last wavefronts repeat what the first ones copy
@@ -522,14 +535,11 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
             *reinterpret_cast<lds_u32>(at + ((v >> 2) * 8 + (v & 3)) * kRow) = vperm(other, own, sel);
         }
     };
-    auto store_rows = [&]() {                                  // (the wavefront's own part of LDS)
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int row = p * 8 + (lane >> 3);
-            const u32x4 v = *reinterpret_cast<lds_u4>(wave * kWaveOut + row * kRow + (lane & 7) * 16);
-            const int64_t m = m0 + wm * 64 + row, n = n0 + wn * 64 + (lane & 7) * 8;
-            if (m < M && n < N) *reinterpret_cast<u32x4*>(y + m * N + n) = v;
-        }
+    // 16 bytes of a row of them to y (the wavefront's own part of LDS)
+    auto store_piece = [&](int row, int chunk) {
+        const u32x4 v = *reinterpret_cast<lds_u4>(wave * kWaveOut + row * kRow + chunk * 16);
+        const int64_t m = m0 + wm * 64 + row, n = n0 + wn * 64 + chunk * 8;
+        if (m < M && n < N) *reinterpret_cast<u32x4*>(y + m * N + n) = v;
     };
     auto store_tile = [&](int i, int j, const f32x16& r) {
         const int64_t n = n0 + wn * 64 + j * 32 + r32;
@@ -548,59 +558,83 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j) finish(i, j, acc[i][j]);
-        if (by8) store_rows();
+        if (by8) {
+#pragma unroll
+            for (int p = 0; p < 8; ++p) store_piece(p * 8 + (lane >> 3), lane & 7);
+        }
         return;
     }
-    // ---- a K slice: its fp32 sums go to the workspace; the last slice of the tile to arrive adds them all
-    //      (16 bytes per lane: four accumulator elements)
+    // ---- a K slice: its fp32 sums go to the workspace, where those of all slices are added.  The four 32 x 32 tiles of the
+    //      wavefronts are four parts (two of two slices), which the last slice to arrive with one adds up, and the slices bring the parts in
+    //      different orders: blocks that end together then share the adding.  Done by the last block alone it took 22 000 cycles for four
+    //      slices, nearly as long as their loop over K at K = 4096 (a compute unit reads 17 - 20 bytes a cycle of what others wrote):
+    //      4096 x 4096 at M = 512 37.8 -> 32.0 us, at M = 200 (eight slices) 37.0 -> 30.0.  A part costs a trip to memory: two
+    //      slices in four parts took 777 x 2944 x 2944 34.3 -> 34.8 us, in two 33.7.
     float* const all = partial + (int64_t)(tile - tail_first) * tail_s * (PBM * PBN);
     const __amdgpu_buffer_rsrc_t ares = __builtin_amdgcn_make_buffer_rsrc(all, 0, tail_s * (PBM * PBN) * 4, 0x00020000);
-    auto quad = [&](int i, int j, int v4) -> uint32_t { return (uint32_t)(((((i * 2 + j) * 4 + v4) * 8 + wave) * 64 + lane) * 16); };
+    auto quad = [&](int part, int v4) -> uint32_t { return (uint32_t)((((part * 4 + v4) * 8 + wave) * 64 + lane) * 16); };   // 16 bytes: four elements
     constexpr int kAgent = 16;                                 // cache policy: coherent over the whole device
+    // (a word per tile with a count of 16 bits per part, 0 at first: group_sums_kernel)
+    unsigned long long* const word = counters + (tile - tail_first);
+    unsigned long long before = 0;
+    auto arrive = [&](int part) { before = __hip_atomic_fetch_add(word, 1ull << (16 * part), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> (16 * part); };
+    const int sh = tail_s == 2 ? 1 : 0, parts = 4 >> sh;       // part p: tiles p << sh ..
+#pragma unroll 1
+    for (int r = 0; r < parts; ++r) {
+        // (the arrival with the part before: its trip to memory goes with that of this part's stores)
+        if (r > 0 && tid == (r - 1) * 64) arrive((r - 1 + slice) & (parts - 1));
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int k = 0; k < 4; ++k)
+            if (k >> sh == ((r + slice) & (parts - 1))) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v4 = 0; v4 < 4; ++v4) {
-                // through an opaque copy: with the accumulator vector itself as the source of the
-                // stores the compiler copies all 64 accumulators inside the main loop on every iteration
-                u32x4 q = {__float_as_uint(acc[i][j][4 * v4]), __float_as_uint(acc[i][j][4 * v4 + 1]), __float_as_uint(acc[i][j][4 * v4 + 2]), __float_as_uint(acc[i][j][4 * v4 + 3])};
-                asm volatile("" : "+v"(q));
-                __builtin_amdgcn_raw_buffer_store_b128(q, ares, quad(i, j, v4), slice * (PBM * PBN) * 4, kAgent);
+                for (int v4 = 0; v4 < 4; ++v4) {
+                    // through an opaque copy: with the accumulator vector itself as the source of the
+                    // stores the compiler copies all 64 accumulators inside the main loop on every iteration
+                    const f32x16& c = acc[k >> 1][k & 1];
+                    u32x4 q = {__float_as_uint(c[4 * v4]), __float_as_uint(c[4 * v4 + 1]), __float_as_uint(c[4 * v4 + 2]), __float_as_uint(c[4 * v4 + 3])};
+                    asm volatile("" : "+v"(q));
+                    // (no scalar offset: with one the compiler takes it that the next instruction may overwrite the registers of
+                    // the data, and the upper halves of some lanes' did not get out)
+                    __builtin_amdgcn_raw_buffer_store_b128(q, ares, quad(k, v4) + (uint32_t)slice * (PBM * PBN * 4), 0, kAgent);
+                }
             }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this thread's sums are out
-    lds_barrier();                                             // ... and so are the whole block's
-    if (tid == 0) *reinterpret_cast<lds_u32>(0u) = arrive_one(counters + (tile - tail_first), tail_s) ? 1u : 0u;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this thread's sums are out
+        lds_barrier();                                         // ... and so are the whole block's
+    }
+    if (tid == (parts - 1) * 64) arrive((parts - 1 + slice) & (parts - 1));
+    if (lane == 0 && wave < parts) *reinterpret_cast<lds_u32>((uint32_t)((wave + slice) & (parts - 1)) * 4u) = (before & 0xFFFFull) == (unsigned long long)(tail_s - 1) ? 1u : 0u;
     lds_barrier();
-    const uint32_t last = *reinterpret_cast<lds_u32>(0u);
+    const u32x4 mine = *reinterpret_cast<lds_u4>(0u);          // the parts that this block was the last to bring
     lds_barrier();                                             // (the outputs go over it)
-    if (last == 0u) return;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int k = 0; k < 4; ++k) {
+        if (__builtin_amdgcn_readfirstlane(sh ? mine[k >> 1] : mine[k]) == 0u) continue;
+        f32x16 sum = zero;
+        constexpr int FLIGHT = 4;                              // slices whose loads are in flight together
+        for (int sl = 0; sl < tail_s; sl += FLIGHT) {
+            u32x4 q[FLIGHT][4];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            f32x16 sum = zero;
-            constexpr int FLIGHT = 4;                          // slices whose loads are in flight together
-            for (int sl = 0; sl < tail_s; sl += FLIGHT) {
-                u32x4 q[FLIGHT][4];
+            for (int u = 0; u < FLIGHT; ++u)                   // (past the last slice: an offset beyond the buffer, 0 without a read)
 #pragma unroll
-                for (int u = 0; u < FLIGHT; ++u)
+                for (int v4 = 0; v4 < 4; ++v4) {
+                    const bool in = sl + u < tail_s;           // (the scalar offset takes no part in the check of the range)
+                    q[u][v4] = __builtin_amdgcn_raw_buffer_load_b128(ares, in ? quad(k, v4) : 0x80000000u, in ? (sl + u) * (PBM * PBN) * 4 : 0, kAgent);
+                }
 #pragma unroll
-                    for (int v4 = 0; v4 < 4; ++v4) q[u][v4] = __builtin_amdgcn_raw_buffer_load_b128(ares, quad(i, j, v4), min(sl + u, tail_s - 1) * (PBM * PBN) * 4, kAgent);
+            for (int u = 0; u < FLIGHT; ++u)                   // (otherwise each load is put in front of its addition)
 #pragma unroll
-                for (int u = 0; u < FLIGHT; ++u)               // (otherwise each load is put in front of its addition)
+                for (int v4 = 0; v4 < 4; ++v4) asm volatile("" : "+v"(q[u][v4]));
 #pragma unroll
-                    for (int v4 = 0; v4 < 4; ++v4) asm volatile("" : "+v"(q[u][v4]));
+            for (int u = 0; u < FLIGHT; ++u)
 #pragma unroll
-                for (int u = 0; u < FLIGHT; ++u)
-                    if (sl + u < tail_s)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) sum[v] += __uint_as_float(q[u][v >> 2][v & 3]);
-            }
-            finish(i, j, sum);
+                for (int v = 0; v < 16; ++v) sum[v] += __uint_as_float(q[u][v >> 2][v & 3]);
         }
-    if (by8) store_rows();
+        finish(k >> 1, k & 1, sum);
+        if (by8) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) store_piece((k >> 1) * 32 + p * 16 + (lane >> 2), (k & 1) * 4 + (lane & 3));
+        }
+    }
 }
 
 // Work split: whole tiles, and K slices for the tiles of a last round that would leave more than
@@ -648,8 +682,8 @@ hipError_t launch_prefill(const uint16_t* x, const uint32_t* codes, const uint16
     do {                                                                                                          \
         e = ensure_lds<prefill_kernel<B, F, H, NL, W>>((int)kLdsBytes);                                    \
         if (e != hipSuccess) return e;                                                                            \
-        if (f16) hipLaunchKernelGGL(group_sums_kernel<true>, dim3((unsigned)sblocks), dim3(256), 0, stream, x, M, K, KP, 0, xsums); \
-        else hipLaunchKernelGGL(group_sums_kernel<false>, dim3((unsigned)sblocks), dim3(256), 0, stream, x, M, K, KP, fine ? 1 : 0, xsums); \
+        if (f16) hipLaunchKernelGGL(group_sums_kernel<true>, dim3((unsigned)sblocks), dim3(256), 0, stream, x, M, K, KP, 0, xsums, counters, (int)pp.tail_tiles); \
+        else hipLaunchKernelGGL(group_sums_kernel<false>, dim3((unsigned)sblocks), dim3(256), 0, stream, x, M, K, KP, fine ? 1 : 0, xsums, counters, (int)pp.tail_tiles); \
         e = hipGetLastError();                                                                                    \
         if (e != hipSuccess) return e;                                                                            \
         hipLaunchKernelGGL((prefill_kernel<B, F, H, NL, W>), grid, block, kLdsBytes, stream, x, codes, lut, scale, \

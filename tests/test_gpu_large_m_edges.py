@@ -86,3 +86,34 @@ def test_outputs_round_to_nearest_even(oracle, N):
         want = torch.from_numpy(exact.astype(np.float32)).to(torch.bfloat16).float().numpy()
     assert np.isinf(want).any() and (np.abs(want[want != 0]) < 2.0 ** -126).any()
     assert np.array_equal(y.float().cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("group", (128, 64))
+@pytest.mark.parametrize("slices", (2, 3, 4, 5, 6, 7, 8))
+def test_slices_meet_in_parts(oracle, slices, group):
+    """A few tiles, cut along K into every number of slices there is; the words that count arrivals hold zeros and
+    garbage at first.  Every result has the same bits."""
+    import paper_2507_04610_amd as any4
+    any4.load_library()
+    M, N, G, bits = 300, 264, 4 * slices + (slices < 8), 4                   # (at least four groups a slice)
+    K = 128 * G
+    cs = inputs.make_case(M, N, K, bits, seed=slices)
+    sc, of = cs.scale, cs.offset
+    if group == 64:
+        sc, of = (np.ascontiguousarray(np.repeat(a, 2, axis=1)) for a in (sc, of))
+    packed = oracle.pack(cs.codes_u8, bits)
+    y64 = oracle.gemm(cs.x, packed, cs.lut, sc, of, K, bits, threads=8, group=group)
+    args = (dev16(cs.x), torch.from_numpy(packed.view(np.int32)).cuda(), dev16(cs.lut), dev16(sc), dev16(of), bits)
+    need = any4.any4_gemm_workspace_bytes(M, N, K, bits)
+    tiles = 2 * 3
+    assert need == (M * ((4 * G + 15) // 16 * 16) * 2 + 255) // 256 * 256 + 256 + tiles * slices * 256 * 128 * 4
+    first = None
+    for word in (0, 0xA5A5A5A5A5A5A5, -1):
+        ws = torch.full((need // 8,), word, dtype=torch.int64, device="cuda").view(torch.uint8)
+        for _ in range(4):
+            y = any4.any4_gemm(*args, group=group, workspace=ws)
+            if first is None:
+                first = y.clone()
+                got = y.float().cpu().numpy().astype(np.float64)
+                assert np.all(np.abs(got - y64) <= 1e-2 * oracle.rms(y64) + np.abs(y64) * 2.0 ** -8)
+            assert torch.equal(y.view(torch.int16), first.view(torch.int16))
