@@ -415,7 +415,9 @@ __device__ __forceinline__ void batch_body(const Params& p) {
 #pragma unroll
             for (int v4 = 0; v4 < 4; ++v4) {
                 const u32x4 q = {__float_as_uint(acc[i][4 * v4]), __float_as_uint(acc[i][4 * v4 + 1]), __float_as_uint(acc[i][4 * v4 + 2]), __float_as_uint(acc[i][4 * v4 + 3])};
-                __builtin_amdgcn_raw_buffer_store_b128(q, ares, quad(i, v4), slab * (ROWS * BN) * 4, kAgent);
+                // (no scalar offset: with one the compiler takes it that the next instruction may overwrite the registers of the
+                // data, which in the large-M kernel sent other values out)
+                __builtin_amdgcn_raw_buffer_store_b128(q, ares, quad(i, v4) + (uint32_t)slab * (ROWS * BN * 4), 0, kAgent);
             }
         }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
