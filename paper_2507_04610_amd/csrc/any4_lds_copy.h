@@ -31,6 +31,11 @@ template <bool WORDS> __device__ __forceinline__ void copy_values_to_lds(uint32_
     if constexpr (WORDS) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "m0", "memory");
     else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_ushort %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "m0", "memory");
 }
+// the same from an address of the lane's own
+template <bool WORDS> __device__ __forceinline__ void copy_values_to_lds_from(uint32_t lds, const void* from) {
+    if constexpr (WORDS) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(from) : "m0", "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_ushort %1, off" ::"s"(lds), "v"(from) : "m0", "memory");
+}
 #pragma clang diagnostic pop
 
 }  // namespace any4

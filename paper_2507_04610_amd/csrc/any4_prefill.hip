@@ -206,10 +206,18 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
     // scales of the wavefront's columns (FINE: the pair of the group's halves, 4 bytes: rows are a whole number of pairs)
     const int64_t srow = min(n0 + wn * 64, N - 1);
     const uint16_t* const sbase = scale + srow * GS;
-    const uint32_t soff = (uint32_t)((min(n0 + wn * 64 + lane, N - 1) - srow) * GS * 2);
+    uint32_t soff = (uint32_t)(min(n0 + wn * 64 + lane, N - 1) - srow);   // WIDE: the row alone
+    if constexpr (!WIDE) soff *= (uint32_t)GS * 2;
     auto fetch_scales = [&](int g, uint32_t slot) {
         const int gg = min(g, g_hi - 1);
-        copy_values_to_lds<FINE>(kSAt + slot * kSSlot + wave * 256, sbase + (FINE ? 2 * gg : gg >> lr), soff);
+        const uint32_t lds = kSAt + slot * kSSlot + wave * 256;
+        const uint16_t* const from = sbase + (FINE ? 2 * gg : gg >> lr);
+        if constexpr (!WIDE) copy_values_to_lds<FINE>(lds, from, soff);
+        else {
+            uint32_t row = soff;
+            asm volatile("" : "+v"(row));
+            copy_values_to_lds_from<FINE>(lds, from + (int64_t)row * GS);
+        }
     };
 
     // ---- where this lane reads and writes LDS (the kernel has no static LDS: dynamic LDS starts at 0)
