@@ -70,9 +70,13 @@ constexpr uint32_t kSSlot = 8 * 256;
 constexpr uint32_t kLdsBytes = kSAt + kRing * kSSlot;
 static_assert(kLdsBytes <= 160 * 1024);
 __device__ __forceinline__ int place(int row) { return ((row >> 1) & 7) ^ (row & 1); }
-// longest rows whose offsets inside a wavefront (32 rows of x) are kept in 32 bits; WIDE kernels beyond.  They would fit up to
-// K = 2^26; the line lies where both sides can be tested.
-constexpr int64_t kNarrowK = 1 << 17;
+// Longest rows whose offsets inside a wavefront are kept in 32 bits (31 rows of x, the furthest apart, stay below 2^31 bytes); WIDE
+// kernels beyond, which form a 64-bit address at every copy and take longer for it: 300 x 2048, K = 132096 303 us, by a WIDE kernel 349.
+// (With the line at 2^17 calls beyond were 1 - 3 % slower than with x and codes through registers, now 4 - 25 % faster on both sides.
+// WIDE launches without K slices take 80 GB of operands at least.)
+constexpr int64_t kNarrowK = 1 << 25;
+constexpr int64_t furthest(int64_t K) { return 31 * 2 * K + PBK * 2; }
+static_assert(furthest(kNarrowK) < ((int64_t)1 << 31) && furthest(2 * kNarrowK) > ((int64_t)1 << 31), "a power of two, as large as it goes");
 
 #define ANY4_SB() __builtin_amdgcn_sched_barrier(0)
 

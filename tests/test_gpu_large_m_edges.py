@@ -1,7 +1,7 @@
 """The matrix-core kernel (more than 128 rows of x) at the edges of its tiles (256 rows of x, 128 rows of weights, 64 values
 along K): one group, group counts that leave its rings of three part-filled, offsets in and out of 16-byte pieces, rows of y
-that are and are not whole 16-byte pieces, K slices, rows so long that addresses take 64 bits.  Against the oracle; bar as in
-test_gpu_parity.py."""
+that are and are not whole 16-byte pieces, K slices, rows so long that addresses take 64 bits, and the
+longest before that.  Against the oracle; bar as in test_gpu_parity.py."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 SHAPES = [(129, 1, 1), (256, 128, 2), (257, 264, 3), (130, 127, 33), (385, 520, 40), (512, 136, 72), (777, 129, 23)]
-LONG = [(129, 24, 1026)]          # K = 131328: beyond the 32-bit offsets
+LONG = [(129, 24, 1026)]          # K = 131328
 
 
 def dev16(a, f16=False):
@@ -61,6 +61,58 @@ def test_tile_edges(oracle, bits, variant):
         tol = 1e-2 * oracle.rms(y64) + np.abs(y64) * (2.0 ** -11 if f16 else 2.0 ** -8)
         assert np.all(np.abs(got - y64) <= tol), (M, N, K, float((np.abs(got - y64) - tol).max()))
         assert torch.equal(y.view(torch.int16), run().view(torch.int16))     # the workspace is left clean
+
+
+# The longest rows of the kernels with 32-bit offsets, and just beyond (64-bit addresses).  Two blocks of rows of x and of weights.
+LONGEST = 1 << 25
+LONG_M, LONG_N = 257, 136
+
+
+@pytest.fixture(scope="module")
+def long_x():
+    t = torch.zeros(LONG_M * (LONGEST + 128), dtype=torch.int16, device="cuda")
+    yield t
+    del t
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("K", (LONGEST, LONGEST + 128))
+@pytest.mark.parametrize("variant,bits", (("plain", 4), ("plain", 3), ("plain", 2), ("repack", 4), ("repack", 3), ("f16", 4), ("g64", 4), ("g64", 2), ("int4", 4)))
+def test_longest_rows(oracle, long_x, variant, bits, K):
+    """All activations are 0 but those of some groups (the first, the last, both sides of the K slices' ends, others),
+    so that the oracle needs these groups only; the others add exactly 0."""
+    import paper_2507_04610_amd as any4
+    any4.load_library()
+    M, N, G, f16, per = LONG_M, LONG_N, K // 128, variant == "f16", 2 if variant == "g64" else 1
+    rng = np.random.default_rng(bits)
+    ends = np.array([s * G // 8 for s in range(1, 8)])
+    at = np.unique(np.concatenate(([0, 1, G - 2, G - 1], ends - 1, ends, rng.integers(0, G, 20))))
+    cs = inputs.make_case(M, N, 128 * len(at), bits, seed=bits, f16=f16)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(bits)
+    codes = torch.empty((N, K * bits // 32), dtype=torch.int32, device="cuda").random_(-2 ** 31, 2 ** 31 - 1, generator=gen)
+    dt = torch.float16 if f16 else torch.bfloat16
+    scale = torch.empty((N, per * G), device="cuda").uniform_(0.005, 0.02, generator=gen).to(dt)
+    offset = torch.empty((N, per * G), device="cuda").normal_(0, 0.002, generator=gen).to(dt)
+    lut = cs.lut
+    if variant == "int4":
+        lut = np.tile(inputs.f32_to_bf16_bits(np.arange(-8, 8, dtype=np.float32)), (N, 1))
+    groups = torch.from_numpy(at).cuda()
+    x = long_x[:M * K].view(M, G, 128)
+    x[:, groups] = torch.from_numpy(cs.x.view(np.int16)).cuda().view(M, -1, 128)
+    words = lambda t: np.ascontiguousarray(t.view(N, G, -1)[:, groups].cpu().view(torch.int16 if t.dtype == dt else torch.int32).numpy()).reshape(N, -1)
+    y64 = oracle.gemm(cs.x, words(codes).view(np.uint32), lut, words(scale).view(np.uint16), words(offset).view(np.uint16), 128 * len(at), bits,
+                      threads=8, group=128 // per, f16=f16)
+    print((variant, bits, M, N, K), flush=True)
+    xs = x.view(M, K).view(dt)
+    if variant == "repack":
+        y = any4.any4_gemm_repacked(xs, any4.any4_repack(codes, bits), dev16(lut), scale, offset, bits)
+    else:
+        y = any4.any4_gemm(xs, codes, None if variant == "int4" else dev16(lut, f16), scale, offset, bits, group=128 // per)
+    x[:, groups] = 0
+    got = y.float().cpu().numpy().astype(np.float64)
+    tol = 1e-2 * oracle.rms(y64) + np.abs(y64) * (2.0 ** -11 if f16 else 2.0 ** -8)
+    assert np.all(np.abs(got - y64) <= tol), float((np.abs(got - y64) - tol).max())
 
 
 @pytest.mark.parametrize("N", (136, 131))
