@@ -77,7 +77,6 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
             if (!p.bp.ok || !p.bp_fine.ok) {                   // the other kind of groups goes to the matrix-core kernel
                 const size_t wm = pp.xsums_bytes + pp.counter_bytes + pp.partial_bytes;
                 if (wm > p.workspace) p.workspace = wm;
-                if (!p.bp.ok) { p.counter_offset = pp.xsums_bytes; p.counter_bytes = pp.counter_bytes; }
             }
             if (p.bp.ok) p.counter_bytes = p.bp.counter_bytes;
             if (p.bp.ok && M <= kTwoLaunchMaxM) {
@@ -112,8 +111,6 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
     else {
         const PrefillPlan pp = plan_prefill(M, N, K, cus);
         p.workspace = pp.xsums_bytes + pp.counter_bytes + pp.partial_bytes;
-        p.counter_offset = pp.xsums_bytes;
-        p.counter_bytes = pp.counter_bytes;
     }
     return p;
 }

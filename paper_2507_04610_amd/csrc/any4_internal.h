@@ -76,7 +76,7 @@ struct GemmPlan {
     BatchPlan bp_fine;    // the same for groups of 64 weights (twice the scales to keep in LDS)
     int ksplit;           // number of K slices whose fp32 partials are reduced in a 2nd pass
     size_t workspace;     // bytes of scratch: K-slice partials (decode) or group sums of x (matrix-core path)
-    size_t counter_offset, counter_bytes;   // where in the workspace the arrival counters sit (groups of 128)
+    size_t counter_bytes; // arrival counters at the start of the workspace (groups of 128; the matrix-core path sets its own in every call)
 };
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits);
 // Validation, kernel choice and launches behind every any4_gemm* entry point; returns an ANY4_* code.

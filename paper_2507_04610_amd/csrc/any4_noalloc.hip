@@ -35,9 +35,10 @@ static hipError_t scratch_of_current_device(void** out) {
 }
 
 // The array keeps whatever the previous call left.  Partial sums and group sums are always written
-// before they are read; the arrival counters are the one thing that must start clean, and the
-// words a call uses as counters may have held another call's partial sums, so they are reset to
-// zero arrivals here (a fill kernel, not a memset: callers may be capturing a graph).
+// before they are read, and the matrix-core path sets the words that count its slices' arrivals in every
+// call.  The counters of K slabs (streaming kernel, kernel for a few dozen rows) are the one thing that must
+// start clean, and the words a call uses for them may have held another call's partial sums, so they are reset
+// to zero arrivals here (a fill kernel, not a memset: callers may be capturing a graph).
 __global__ void clear_words_kernel(unsigned long long* p, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0ull;
@@ -67,9 +68,8 @@ extern "C" int any4_gemm_noalloc(const uint16_t* x, const uint32_t* codes, const
     if (scratch_of_current_device(&ws) != hipSuccess) return ANY4_ERR_HIP;
     if (plan.counter_bytes > 0) {
         const int64_t nclear = (int64_t)(plan.counter_bytes / 8);
-        unsigned long long* base = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + plan.counter_offset);
         hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)((nclear + 255) / 256)), dim3(256), 0,
-                           static_cast<hipStream_t>(stream), base, nclear);
+                           static_cast<hipStream_t>(stream), static_cast<unsigned long long*>(ws), nclear);
         if (hipGetLastError() != hipSuccess) return ANY4_ERR_HIP;
     }
     return gemm_dispatch(x, codes, false, lut, scale, offset, M, N, K, bits, ANY4_GROUP, y, ws, kScratchBytes, stream, false, false);

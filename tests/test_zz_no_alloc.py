@@ -105,3 +105,34 @@ def test_noalloc_rejects_what_its_scratch_cannot_hold(lib):
     assert lib.any4_gemm_noalloc(A, A, A, A, A, M, N, K, 4, A, None) == -5
     torch.cuda.synchronize()
     assert torch.all(y == 7.0)
+
+
+def test_large_m_launches_no_more_than_gemm(lib, oracle):
+    """K slices of the matrix-core kernel: the words that count their arrivals are set by the group sums' kernel, nothing
+    else clears them"""
+    t = problem(oracle, 300, 384, 4096, 4, seed=73)
+    ref, need = call_workspace(lib, t)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    y = torch.empty_like(ref)
+    call_noalloc(lib, t)
+    args = [t[k].data_ptr() for k in ("x", "codes", "lut", "scale", "offset")] + [t[k] for k in ("M", "N", "K", "bits")] + [y.data_ptr()]
+    nodes = []
+    for call in (lambda s: lib.any4_gemm(*args, ws.data_ptr(), need, s), lambda s: lib.any4_gemm_noalloc(*args, s)):
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph):
+            rc = call(torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        count = ctypes.c_size_t()
+        get = lib.hipGraphGetNodes
+        get.argtypes, get.restype = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)], ctypes.c_int
+        assert get(graph.raw_cuda_graph(), None, ctypes.byref(count)) == 0
+        nodes.append(count.value)
+        graph.instantiate()
+        for word in (-1, 0, 0xA4C0DE5EED1703):                  # (replays over what the words may hold)
+            ws.view(torch.int64).fill_(word)
+            y.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(y.view(torch.int16), ref.view(torch.int16))
+    assert nodes == [2, 2]
