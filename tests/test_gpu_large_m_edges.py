@@ -169,3 +169,40 @@ def test_slices_meet_in_parts(oracle, slices, group):
                 got = y.float().cpu().numpy().astype(np.float64)
                 assert np.all(np.abs(got - y64) <= 1e-2 * oracle.rms(y64) + np.abs(y64) * 2.0 ** -8)
             assert torch.equal(y.view(torch.int16), first.view(torch.int16))
+
+
+@pytest.mark.parametrize("K", (384, 1152))                                   # whole tiles, two slices
+@pytest.mark.parametrize("variant,bits,N", (("plain", 4, 136), ("plain", 3, 131), ("g64", 4, 131), ("f16", 4, 136), ("int4", 4, 131), ("repack", 2, 136)))
+def test_not_finite(variant, bits, N, K):
+    """A NaN or an infinity in a row of x makes that row of y NaN (the group sum's low part is none), one among the scales or
+    offsets of a row of weights leaves that column of y without a finite number; every other output has the bits that it
+    has without them.  In first, inner and last groups, in the last rows (which stand in for those past the end)."""
+    import paper_2507_04610_amd as any4
+    any4.load_library()
+    M, f16, group = 300, variant == "f16", 64 if variant == "g64" else 128
+    cs = inputs.make_case(M, N, K, bits, seed=K + N, f16=f16)
+    sc, of = (np.ascontiguousarray(np.repeat(a, 128 // group, axis=1)) for a in (cs.scale, cs.offset))
+    codes = any4.any4_pack(torch.from_numpy(cs.codes_u8).cuda(), bits)
+    lut = None if variant == "int4" else dev16(cs.lut, f16)
+
+    def gemm(x, s, o):
+        if variant == "repack":
+            return any4.any4_gemm_repacked(dev16(x), any4.any4_repack(codes, bits), lut, dev16(s), dev16(o), bits)
+        return any4.any4_gemm(dev16(x, f16), codes, lut, dev16(s, f16), dev16(o, f16), bits, group=group)
+    clean = gemm(cs.x, sc, of)
+    inf = 0x7C00 if f16 else 0x7F80
+    nan, ninf = inf | 0x40, inf | 0x8000
+    x = cs.x.copy()
+    rows = {3: (0, nan), 64: (K - 1, inf), 200: (K // 2 + 5, ninf), 255: (130, nan), M - 1: (K - 130, inf)}
+    for m, (k, v) in rows.items():
+        x[m, k] = v
+    s, o = sc.copy(), of.copy()
+    s[5, 0], s[70, -1], s[N - 1, 1] = nan, inf, nan
+    o[9, -1], o[40, 0], o[129, 2] = nan, inf, ninf
+    y = gemm(x, s, o)
+    bad = torch.zeros((M, N), dtype=torch.bool, device="cuda")
+    bad[:, [5, 9, 40, 70, 129, N - 1]] = True
+    bad[list(rows)] = True
+    assert torch.equal(~torch.isfinite(y), bad)
+    assert torch.isnan(y[list(rows)]).all() and torch.isnan(y[:, [5, 9, N - 1]]).all()
+    assert torch.equal(y[~bad].view(torch.int16), clean[~bad].view(torch.int16))
