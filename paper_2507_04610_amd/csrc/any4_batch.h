@@ -28,8 +28,8 @@
 // wavefront issues 317 vector instructions (20 of them matrix) and 24 LDS instructions a step; vector issue is
 // busy 53 % of the time, the matrix cores of the SIMDs that hold a block 27 %, the LDS pipe 20 %, and wavefronts wait 35 % of
 // theirs.  A step takes 1.8 us, the first four 0.9 (their loads are issued together).  The rest of a launch is fixed: 6 - 12 us for start and end of a block (32 .. 128 rows of x),
-// and where slabs meet 2 - 11 us for their sums (any4_batch.hip has the constants).  The four linears of an 8B layer at M = 24 / 64 / 128: 81 / 103 / 183 us,
-// where the kernels for fewer and for more rows took 94 / 197 / 229.
+// and where slabs meet 2 - 11 us for their sums (any4_batch.hip has the constants).  The four linears of an 8B layer at M = 24 / 64 / 128:
+// 84 / 107 / 191 us; the kernel for more rows takes 209, however few they are.
 #pragma once
 #include "any4_device.h"
 #include "any4_internal.h"

@@ -21,9 +21,10 @@
 // steps (groups) to a ring; a thread keeps to one weight row, whose table sits in its registers (any4_regtable.h), and
 // turns 16 codes of a step into a piece of the looked-up tile, two steps to a ring.
 //
-// What bounds it.  Per wavefront and group of 128: 64 matrix instructions for a SIMD's two wavefronts take 2048 cycles, its
-// vector instructions (92 lookup, 64 scale fold, 4 others; a matrix instruction holds the issue port for two) 1800, the LDS pipe
-// 1400 + its share of the copies: all three are near their limits together, so the order of the instructions decides.
+// What bounds it: no unit by itself.  A K step takes a block 1500 cycles, of which the matrix cores are busy 1024, vector issue 900
+// (a SIMD's two wavefronts: 46 lookup, 32 scale fold and 2 other instructions of 4 cycles each, and 16 matrix instructions, which
+// hold the issue port for 8) and the LDS pipe about 1000 (700 for operands, codes and looked-up weights, the rest the copies): two
+// thirds each, so the order of the instructions decides.
 //   - Operands are read half a step ahead, the barrier stands in the middle of a step, between matrix instructions that
 //     both have their operands: nothing waits behind it.
 //   - A tile's two instructions of a half step follow each other, so that a finished group's sums have six matrix
@@ -32,10 +33,9 @@
 //     held every wavefront until the address unit had taken them: 530 cycles a step.  The reads of a half step that ends at the
 //     barrier come in its first four instructions: read one by one, the last held everybody there (1 %).
 // The order is pinned by scheduling barriers, one per four matrix instructions (one per two: 1 % slower; none, and the
-// compiler emits "all MFMAs, then all staging").  A K step takes 1500
-// cycles (1940 with x and codes through registers into padded LDS, operands read behind the barrier, and the fold at a
-// group's end), of which the matrix instructions are 1024; a loop of nothing but their mix of matrix, vector
-// and LDS instructions takes 1280.  Power holds the clock: 1.84 GHz before, 1.65 now.  N = 28672, K = 4096 at M = 2048: 540 -> 470 us;
+// compiler emits "all MFMAs, then all staging").  With x and codes through registers into padded LDS, operands read behind the
+// barrier, and the fold at a group's end a step took 1940 cycles; a loop of nothing but this mix of matrix, vector and LDS
+// instructions takes 1280.  The clock was 1.84 GHz then and is 1.5 - 1.65 now, by box.  N = 28672, K = 4096 at M = 2048: 540 -> 470 us;
 // the four linears of an 8B layer at M = 2048 / 512: 1035 / 337 -> 908 / 296 us.
 #include "any4_device.h"
 #include "any4_internal.h"

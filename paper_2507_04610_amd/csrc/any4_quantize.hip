@@ -919,10 +919,12 @@ __global__ __launch_bounds__(T, 4) void quantize_sorted_kernel(
     // the scaled weight, the sample weight s and the sampling mass.  The mass is s for the first centre and
     // s * (squared distance to the nearest centre chosen so far) afterwards; as s >= 0, multiplying by s and
     // rounding is monotone, so s * min(d_old, d_new) is min(s * d_old, s * d_new) bit for bit and the
-    // distances themselves need not be kept.  Bound: vector issue, 2^n rounds of five instructions per weight (ten with a
-    // comparison and two selects in place of v_min_f64, x converted every time and copies of x and s): 6144 x 4096 any4
-    // 588 -> 519 us, 4096 x 14336 1698 -> 1479 us together with the sums of the wavefronts, read several at a time.  The sample weights
-    // are held in fp64 too: their conversion takes as long as two of the others; 493 -> 485 and 1427 -> 1410 us.
+    // distances themselves need not be kept.  Bound: 2^n rounds of five instructions per weight, a third of the time (6144 x 4096: 60 of
+    // 180 us), and in every round a chain of sums over the wavefronts, sixteen additions in the thread that holds the draw and two
+    // barriers.  (Ten instructions with a comparison and two selects in place of v_min_f64, x converted every time and copies of x and
+    // s: 6144 x 4096 any4 588 -> 519 us, 4096 x 14336 1698 -> 1479 us together with the sums of the wavefronts, read several at a time.
+    // The sample weights are held in fp64 too: their conversion takes as long as two of the others; 6144 x 4096 493 -> 485 us,
+    // 4096 x 14336 1427 -> 1410, no more than runs differ.)
     // Sixteen weights a thread for every K, so that whole wavefronts have none where the row is shorter than the block's
     // 16 T and skip the phases: with the row spread evenly, all of them ran all phases with most lanes idle.  With the
     // codes from the sort's keys (below): 11525 x 1024 any4 726 -> 579 us, 6144 x 4096 528 -> 500, 4096 x 14336 1522 -> 1447.
