@@ -86,13 +86,12 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
             if (p.bp.ok) p.counter_bytes = p.bp.counter_bytes;
             if (p.bp.ok && M <= kTwoLaunchMaxM) {
                 // Where the streaming kernel has one tile per block and the whole of K in it (4096 x 4096 and below, K a multiple
-                // of 512: with other K its wavefronts read their scales one by one, 3 us more for the two), two
-                // launches of it, 16 rows of x and at most 8, can beat one that adds up slabs: 4096 x 4096 at M = 17 / 24
+                // of 512: 2048 x 2944 at M = 17 12.7 us, the other kernel 12.3), two launches of it, 16 rows of x and at most 8, can beat one that adds up slabs: 4096 x 4096 at M = 17 / 24
                 // 13.0 / 13.8 us, the other 14.6 / 14.7.  A launch: a fixed part, the larger of the time of a tile and
                 // that of the codes, a share per row of x (constants measured, 10 % rms).
                 p.sp = plan_stream(kStreamMaxM, N, K, cus);
                 const double tile = 0.68 + 0.025 * p.sp.slab_groups, codes = (double)N * (double)K * bits / 8 / 4.74e6;
-                if (p.sp.gw > 0 && p.sp.aux && p.sp.slabs == 1 && p.sp.tiles <= p.sp.blocks_per_slab)
+                if (p.sp.gw > 0 && K % 512 == 0 && p.sp.slabs == 1 && p.sp.tiles <= p.sp.blocks_per_slab)
                     p.two_launches = 2 * (3.6 + (tile > codes ? tile : codes)) + 0.15 * (double)M;
             }
             return p;

@@ -44,9 +44,11 @@
 //
 // Small per-tile inputs (the rows' tables, scales and offsets: 2.5 KB per tile against 4 KB of
 // codes per wavefront) are not read by every wavefront: for tile t one wavefront, taking turns,
-// loads them four tiles ahead with five instructions and passes them on through LDS (AUX mode;
-// it needs K/128 to be a multiple of 4 for the 8-byte alignment of its loads, otherwise every
-// wavefront reads what it needs itself).
+// loads them four tiles ahead with five instructions and passes them on through LDS (AUX mode,
+// four groups and more).  Where K/128 is no multiple of 4 its 8-byte loads are aligned to 2 bytes only, and the last
+// one of a row starts early, so that it ends with the row, and is moved down in registers: 5003 x 2944 at M = 1 / 8 / 16 takes
+// 7.3 / 8.2 / 9.7 us, with every wavefront reading its own scales one by one 9.7 / 10.3 / 11.2; 28672 x 4224 at M = 1 26.6, 33.4.
+// (The moving costs rows that need none 0 - 0.1 us a launch.)
 //
 // 3- and 2-bit codes (the "anyn" variants of section 4.1) use the same kernel.  A lane's quarter of a
 // group is 12 or 8 bytes instead of 16.  any3: a pair of codes is a 6-bit field of the lane's 96-bit
@@ -133,7 +135,7 @@ __device__ __forceinline__ float sum8(const uint4& v) {
 // BITS    code width: 4, 3 or 2
 // GW      groups (of 128 weights) a wavefront owns: 1, 2 or 4
 // AUX     tables, scales and offsets of a tile are loaded by one wavefront and shared through LDS;
-//         requires K/128 and the slab size to be multiples of 4 (8-byte aligned loads)
+//         requires K/128 >= 4 and slabs (except the last) of a multiple of 4 groups
 // NOLUT   4-bit codes on the uniform grid (value = code - 8, the int4 format): no table at all.
 //         A code c becomes the bf16 number 128 + c by OR-ing it into the mantissa of 128.0
 //         (0x4300 | c), and the surplus 136 * scale * (group sum of x) is taken off again by two more
@@ -310,47 +312,56 @@ __global__ __launch_bounds__(kWaves * 64, 1) void decode_stream_kernel(const Par
     //      (lane (n, j): scale / offset groups 4j .. 4j+3 and 16 + 4j .. 16 + 4j+3 of the slab; the
     //      row's table by lanes j < 2 (any4, 16 bytes each) or j = 0 (any3: 16 bytes, any2: 8)) and
     //      written to an LDS slot two tiles later.  Table rows keep a 32-byte stride in the slot.
-    uint2 axs[2], axo[2];
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 axs[2], axo[2];
     // FINE: twice the entries.  (Plain vector variables, not arrays of HIP's uint4: those the compiler
     // kept in scratch memory across the tile loop, with a store - and a full wait - right after each load.)
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     u32x4 fxs0 = {0, 0, 0, 0}, fxs1 = {0, 0, 0, 0}, fxo0 = {0, 0, 0, 0}, fxo1 = {0, 0, 0, 0};
     uint4 axl;
+    // A lane's four groups are those from aux_chunk(c) of the slab on.  Lanes past the slab's groups repeat its last
+    // four, so that all loads are unconditional.  What it loads starts at group aux_first[c] of the row: the same one unless
+    // K / 128 is no multiple of 4 and the row has fewer than four left; its last four are then loaded and moved down when the slot is
+    // written, zeros in the place of groups that are not there.
+    auto aux_chunk = [&](int c) -> int { return min((c * 4 + q) * 4, (sg - 1) & ~3); };
+    const int aux_first[2] = {min(gs0 + aux_chunk(0), G - 4), min(gs0 + aux_chunk(1), G - 4)};
+    const int aux_by[2] = {gs0 + aux_chunk(0) - aux_first[0], gs0 + aux_chunk(1) - aux_first[1]};    // 0 .. 3 groups
     auto aux_load = [&](int t) {
         if constexpr (FINE) {
             // two entries per chunk of 128: lane (n, j) loads those of chunks 4j .. 4j+3 and 16 + 4j .. + 3
-            const int64_t tile_off = (int64_t)t * (kTile * 2) * GS + gs0 * 4;
+            typedef u32x4 u32x4_at4 __attribute__((aligned(4)));
+            const int64_t tile_off = (int64_t)t * (kTile * 2) * GS;
             const uint32_t vs = t == last_tile ? vs_last : vs_norm;
-            const uint32_t go0 = (uint32_t)min(q * 4, max(sg, 4) - 4) * 4u, go1 = (uint32_t)min((4 + q) * 4, max(sg, 4) - 4) * 4u;
-            fxs0 = *reinterpret_cast<const u32x4*>(scale_b + tile_off + vs + go0);
-            fxo0 = *reinterpret_cast<const u32x4*>(offset_b + tile_off + vs + go0);
-            fxs1 = *reinterpret_cast<const u32x4*>(scale_b + tile_off + vs + go1);
-            fxo1 = *reinterpret_cast<const u32x4*>(offset_b + tile_off + vs + go1);
+            const uint32_t go0 = (uint32_t)aux_first[0] * 4u, go1 = (uint32_t)aux_first[1] * 4u;
+            fxs0 = *reinterpret_cast<const u32x4_at4*>(scale_b + tile_off + vs + go0);
+            fxo0 = *reinterpret_cast<const u32x4_at4*>(offset_b + tile_off + vs + go0);
+            fxs1 = *reinterpret_cast<const u32x4_at4*>(scale_b + tile_off + vs + go1);
+            fxo1 = *reinterpret_cast<const u32x4_at4*>(offset_b + tile_off + vs + go1);
         } else if constexpr (!COARSE) {
-            // lanes past the slab's groups repeat its last four: the loads are unconditional
-            const int64_t tile_off = (int64_t)t * (kTile * 2) * G + gs0 * 2;
+            typedef u32x2 u32x2_at2 __attribute__((aligned(2)));
+            const int64_t tile_off = (int64_t)t * (kTile * 2) * G;
             const uint32_t vs = t == last_tile ? vs_last : vs_norm;
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
-                const uint32_t go = (uint32_t)min((c * 4 + q) * 4, max(sg, 4) - 4) * 2u;
-                axs[c] = *reinterpret_cast<const uint2*>(scale_b + tile_off + vs + go);
-                axo[c] = *reinterpret_cast<const uint2*>(offset_b + tile_off + vs + go);
+                const uint32_t go = (uint32_t)aux_first[c] * 2u;
+                axs[c] = *reinterpret_cast<const u32x2_at2*>(scale_b + tile_off + vs + go);
+                axo[c] = *reinterpret_cast<const u32x2_at2*>(offset_b + tile_off + vs + go);
             }
         } else {
             // groups of 256 weights and more: chunks 4j, 4j + 1 share a scale and so do 4j + 2, 4j + 3
-            // (4j is a multiple of 4), so two 2-byte loads give the four entries the slot expects.
-            // Lanes past the slab's groups repeat its last four chunks: all loads are unconditional.
+            // (4j is a multiple of 4), so two 2-byte loads give the four entries the slot expects
+            // (chunks past the row's repeat its last value).
             const int64_t tile_off = (int64_t)t * (kTile * 2) * GS;
             const uint32_t v = t == last_tile ? vs_last : vs_norm;
             // The registers keep the bare values; they are doubled up when the slot is written.
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
-                const int g0 = gs0 + min((c * 4 + q) * 4, max(sg, 4) - 4);
-                const uint32_t i0 = (uint32_t)(g0 >> lr) * 2u, i1 = (uint32_t)((g0 + 2) >> lr) * 2u;
-                axs[c].x = *reinterpret_cast<const uint16_t*>(scale_b + tile_off + v + i0);
-                axs[c].y = *reinterpret_cast<const uint16_t*>(scale_b + tile_off + v + i1);
-                axo[c].x = *reinterpret_cast<const uint16_t*>(offset_b + tile_off + v + i0);
-                axo[c].y = *reinterpret_cast<const uint16_t*>(offset_b + tile_off + v + i1);
+                const int g0 = gs0 + aux_chunk(c);
+                const uint32_t i0 = (uint32_t)(g0 >> lr) * 2u, i1 = (uint32_t)min((g0 + 2) >> lr, GS - 1) * 2u;
+                axs[c][0] = *reinterpret_cast<const uint16_t*>(scale_b + tile_off + v + i0);
+                axs[c][1] = *reinterpret_cast<const uint16_t*>(scale_b + tile_off + v + i1);
+                axo[c][0] = *reinterpret_cast<const uint16_t*>(offset_b + tile_off + v + i0);
+                axo[c][1] = *reinterpret_cast<const uint16_t*>(offset_b + tile_off + v + i1);
             }
         }
         const char* lrow = lut_b + (int64_t)t * lut_tile_bytes + (t == last_tile ? vl_last : vl_norm);
@@ -366,20 +377,27 @@ __global__ __launch_bounds__(kWaves * 64, 1) void decode_stream_kernel(const Par
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             const bool in_slab = (c * 4 + q) * 4 < sg;
+            const int by = aux_by[c];
             if constexpr (FINE) {
+                auto down = [&](u32x4 v) -> u32x4 {
+                    if (by & 1) v = u32x4{v[1], v[2], v[3], 0u};
+                    if (by & 2) v = u32x4{v[2], v[3], 0u, 0u};
+                    return v;
+                };
                 if (in_slab) {
-                    *reinterpret_cast<u32x4*>(s + kAuxScale + n * kAuxRow + (c * 4 + q) * 16) = c ? fxs1 : fxs0;
-                    *reinterpret_cast<u32x4*>(s + kAuxOffset + n * kAuxRow + (c * 4 + q) * 16) = c ? fxo1 : fxo0;
+                    *reinterpret_cast<u32x4*>(s + kAuxScale + n * kAuxRow + (c * 4 + q) * 16) = down(c ? fxs1 : fxs0);
+                    *reinterpret_cast<u32x4*>(s + kAuxOffset + n * kAuxRow + (c * 4 + q) * 16) = down(c ? fxo1 : fxo0);
                 }
             } else {
-                uint2 sv = axs[c], ov = axo[c];
-                if constexpr (COARSE) {
-                    sv = make_uint2(sv.x | (sv.x << 16), sv.y | (sv.y << 16));
-                    ov = make_uint2(ov.x | (ov.x << 16), ov.y | (ov.y << 16));
-                }
+                auto four = [&](const u32x2& v) -> unsigned long long {
+                    if constexpr (COARSE) {
+                        const bool both = gs0 + aux_chunk(c) + 2 < G;
+                        return (v[0] | (v[0] << 16)) | (both ? (unsigned long long)(v[1] | (v[1] << 16)) << 32 : 0ull);
+                    } else return __builtin_bit_cast(unsigned long long, v) >> (16 * by);
+                };
                 if (in_slab) {
-                    *reinterpret_cast<uint2*>(s + kAuxScale + n * kAuxRow + (c * 4 + q) * 8) = sv;
-                    *reinterpret_cast<uint2*>(s + kAuxOffset + n * kAuxRow + (c * 4 + q) * 8) = ov;
+                    *reinterpret_cast<unsigned long long*>(s + kAuxScale + n * kAuxRow + (c * 4 + q) * 8) = four(axs[c]);
+                    *reinterpret_cast<unsigned long long*>(s + kAuxOffset + n * kAuxRow + (c * 4 + q) * 8) = four(axo[c]);
                 }
             }
         }
@@ -872,7 +890,7 @@ StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, int cus) {
     const int64_t tiles = (N + stream::kTile - 1) / stream::kTile;
     if (M > stream::kTile || tiles > 0x7FFFFFFF) return best;
     double best_cost = 1e300;
-    const bool aux = G % 4 == 0;
+    const bool aux = G >= 4;
     for (int gw : {4, 2, 1}) {
         const int slab_max = stream::kWaves * gw;
         int slabs = (G + slab_max - 1) / slab_max;
@@ -915,17 +933,31 @@ static hipError_t launch_stream_t(const Params& p, int grid, hipStream_t stream)
     return hipGetLastError();
 }
 
-template <int BITS, bool REPACK>
-static hipError_t launch_stream_b(const Params& p, const StreamPlan& sp, int grid, hipStream_t stream) {
-#define ANY4_STREAM(GW)                                                                    \
-    (sp.aux ? launch_stream_t<BITS, GW, true, false, REPACK>(p, grid, stream)              \
-            : launch_stream_t<BITS, GW, false, false, REPACK>(p, grid, stream))
-    switch (sp.gw) {
-        case 4: return ANY4_STREAM(4);
-        case 2: return ANY4_STREAM(2);
-        default: return ANY4_STREAM(1);
+// the variants of one kind by groups per wavefront.  Without shared small inputs: rows of fewer than four groups, which
+// plan_stream gives wavefronts of one or two, and any2 with groups of 64.
+template <int BITS, bool NOLUT, bool REPACK, bool COARSE, bool FINE, bool F16>
+static hipError_t launch_stream_gw(const Params& p, const StreamPlan& sp, int grid, hipStream_t stream) {
+    constexpr bool SHARE = !(FINE && BITS == 2);
+    if constexpr (SHARE) {
+        if (sp.aux) {
+            switch (sp.gw) {
+                case 4: return launch_stream_t<BITS, 4, true, NOLUT, REPACK, COARSE, FINE, F16>(p, grid, stream);
+                case 2: return launch_stream_t<BITS, 2, true, NOLUT, REPACK, COARSE, FINE, F16>(p, grid, stream);
+                default: return launch_stream_t<BITS, 1, true, NOLUT, REPACK, COARSE, FINE, F16>(p, grid, stream);
+            }
+        }
+        if (sp.gw > 2) return hipErrorInvalidValue;
+    } else {
+        if (sp.gw == 4) return launch_stream_t<BITS, 4, false, NOLUT, REPACK, COARSE, FINE, F16>(p, grid, stream);
     }
-#undef ANY4_STREAM
+    if (sp.gw == 2) return launch_stream_t<BITS, 2, false, NOLUT, REPACK, COARSE, FINE, F16>(p, grid, stream);
+    return launch_stream_t<BITS, 1, false, NOLUT, REPACK, COARSE, FINE, F16>(p, grid, stream);
+}
+template <bool REPACK, bool COARSE, bool FINE, bool F16>
+static hipError_t launch_stream_bits(int bits, const Params& p, const StreamPlan& sp, int grid, hipStream_t stream) {
+    if (bits == 4) return launch_stream_gw<4, false, REPACK, COARSE, FINE, F16>(p, sp, grid, stream);
+    if (bits == 3) return launch_stream_gw<3, false, REPACK, COARSE, FINE, F16>(p, sp, grid, stream);
+    return launch_stream_gw<2, false, REPACK, COARSE, FINE, F16>(p, sp, grid, stream);
 }
 
 hipError_t launch_decode_stream(const uint16_t* x, const uint32_t* codes, const uint16_t* lut,
@@ -948,77 +980,25 @@ hipError_t launch_decode_stream(const uint16_t* x, const uint32_t* codes, const 
     if (f16) {
         // fp16: the table-based kernels on the plain layout with groups of 128
         if (lut == nullptr || repacked || lr != 0) return hipErrorInvalidValue;
-#define ANY4_STREAM_H(B, GW)                                                               \
-        return sp.aux ? launch_stream_t<B, GW, true, false, false, false, false, true>(p, grid, stream)   \
-                      : launch_stream_t<B, GW, false, false, false, false, false, true>(p, grid, stream)
-#define ANY4_STREAM_HB(B)                                                                  \
-        switch (sp.gw) {                                                                   \
-            case 4: ANY4_STREAM_H(B, 4);                                                   \
-            case 2: ANY4_STREAM_H(B, 2);                                                   \
-            default: ANY4_STREAM_H(B, 1);                                                  \
-        }
-        if (bits == 4) { ANY4_STREAM_HB(4) }
-        if (bits == 3) { ANY4_STREAM_HB(3) }
-        ANY4_STREAM_HB(2)
-#undef ANY4_STREAM_HB
-#undef ANY4_STREAM_H
+        return launch_stream_bits<false, false, false, true>(bits, p, sp, grid, stream);
     }
     if (bits == 4 && lut == nullptr) {                     // the integer grid: no table
         if (repacked || lr != 0) return hipErrorInvalidValue;
-#define ANY4_STREAM_NL(GW)                                                                 \
-    (sp.aux ? launch_stream_t<4, GW, true, true>(p, grid, stream) : launch_stream_t<4, GW, false, true>(p, grid, stream))
-        switch (sp.gw) {
-            case 4: return ANY4_STREAM_NL(4);
-            case 2: return ANY4_STREAM_NL(2);
-            default: return ANY4_STREAM_NL(1);
-        }
-#undef ANY4_STREAM_NL
+        return launch_stream_gw<4, true, false, false, false, false>(p, sp, grid, stream);
     }
     if (lr < 0) {
-        // groups of 64 weights: at most 8 rows a launch
+        // groups of 64 weights: at most 8 rows a launch (any2: every wavefront reads its own scales - no room for
+        // the shared slots beside its tables)
         if (repacked || lr != -1 || M > stream::kTile / 2) return hipErrorInvalidValue;
-        // (any2: every wavefront reads its own scales - no room for the shared slots beside its tables)
-#define ANY4_STREAM_F(B, GW, SHARE)                                                        \
-        return sp.aux && SHARE ? launch_stream_t<B, GW, SHARE, false, false, false, true>(p, grid, stream)   \
-                               : launch_stream_t<B, GW, false, false, false, false, true>(p, grid, stream)
-#define ANY4_STREAM_FB(B, SHARE)                                                           \
-        switch (sp.gw) {                                                                   \
-            case 4: ANY4_STREAM_F(B, 4, SHARE);                                            \
-            case 2: ANY4_STREAM_F(B, 2, SHARE);                                            \
-            default: ANY4_STREAM_F(B, 1, SHARE);                                           \
-        }
-        if (bits == 4) { ANY4_STREAM_FB(4, true) }
-        if (bits == 3) { ANY4_STREAM_FB(3, true) }
-        ANY4_STREAM_FB(2, false)
-#undef ANY4_STREAM_FB
-#undef ANY4_STREAM_F
+        return launch_stream_bits<false, false, true, false>(bits, p, sp, grid, stream);
     }
     if (lr > 0) {
         // groups of 256 weights and more: the variants that read one scale per group
         if (repacked) return hipErrorInvalidValue;
-#define ANY4_STREAM_C(B, GW)                                                               \
-        return sp.aux ? launch_stream_t<B, GW, true, false, false, true>(p, grid, stream)  \
-                      : launch_stream_t<B, GW, false, false, false, true>(p, grid, stream)
-#define ANY4_STREAM_CB(B)                                                                  \
-        switch (sp.gw) {                                                                   \
-            case 4: ANY4_STREAM_C(B, 4);                                                   \
-            case 2: ANY4_STREAM_C(B, 2);                                                   \
-            default: ANY4_STREAM_C(B, 1);                                                  \
-        }
-        if (bits == 4) { ANY4_STREAM_CB(4) }
-        if (bits == 3) { ANY4_STREAM_CB(3) }
-        ANY4_STREAM_CB(2)
-#undef ANY4_STREAM_CB
-#undef ANY4_STREAM_C
+        return launch_stream_bits<false, true, false, false>(bits, p, sp, grid, stream);
     }
-    if (repacked) {
-        if (bits == 4) return launch_stream_b<4, true>(p, sp, grid, stream);
-        if (bits == 3) return launch_stream_b<3, true>(p, sp, grid, stream);
-        return launch_stream_b<2, true>(p, sp, grid, stream);
-    }
-    if (bits == 4) return launch_stream_b<4, false>(p, sp, grid, stream);
-    if (bits == 3) return launch_stream_b<3, false>(p, sp, grid, stream);
-    return launch_stream_b<2, false>(p, sp, grid, stream);
+    if (repacked) return launch_stream_bits<true, false, false, false>(bits, p, sp, grid, stream);
+    return launch_stream_bits<false, false, false, false>(bits, p, sp, grid, stream);
 }
 
 }  // namespace any4
