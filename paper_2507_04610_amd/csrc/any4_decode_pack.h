@@ -66,9 +66,9 @@ constexpr int table_bytes(int bits) { return bits == 4 ? 256 * 256 : (bits == 3 
 constexpr int red_bytes(int mp) { return 2 * kWaves * mp * 16 * 4; }
 // A operands of the offset MFMAs: [kWaves][NOF][MP rows][4 quarters] of 16 bytes
 constexpr int xo_bytes(int mp, int passes) { return kWaves * ((4 * passes + 15) / 16) * mp * 4 * 16; }
-// one slot: scales [16 rows][G bf16 + 8 bytes of padding against bank conflicts], offsets the same, tables
-// [16 rows][32 bytes]
-constexpr int aux_row_bytes(int G) { return G * 2 + 8; }
+// one slot: scales [16 rows][G bf16, rounded up to whole pieces of 8, + 8 bytes of padding against bank conflicts], offsets
+// the same, tables [16 rows][32 bytes]
+constexpr int aux_row_bytes(int G) { return (G + 7) / 8 * 16 + 8; }
 constexpr int slot_bytes(int G) { return 2 * kTile * aux_row_bytes(G) + kTile * 32; }
 constexpr int lds_bytes(int bits, int mp, int passes, int G) {
     return table_bytes(bits) + red_bytes(mp) + xo_bytes(mp, passes) + kSlots * slot_bytes(G);
@@ -90,7 +90,7 @@ struct Params {
     const uint16_t* offset;
     uint16_t* y;
     int64_t N, K;
-    int M, G;                        // G = K / 128, a multiple of 8
+    int M, G;                        // G = K / 128, at least 8
     int tiles;                       // 16-row tiles
     int nblocks;                     // grid size
     int tpb, trem;                   // tiles = nblocks * tpb + trem: the first trem blocks get tpb + 1 tiles
@@ -125,7 +125,9 @@ __device__ __forceinline__ uint32_t bf16_rne_finite(float f) {
 // MP      rows of x rounded up to a power of two: 1, 2 or 4
 // PASSES  units of 4 groups a wavefront processes per tile: 8 wavefronts x 4 x PASSES groups cover K
 // REPACK  codes in the tile-major layout of any4_repack
-template <int BITS, int MP, int PASSES, bool REPACK>
+// ANY     a number of groups that is no multiple of 8: rows of scales and offsets start at any 2 bytes, and the row's last
+//         unit of groups, and piece of scales, may be there in part
+template <int BITS, int MP, int PASSES, bool REPACK, bool ANY>
 __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void decode_pack_kernel(const Params p) {
     static_assert(BITS == 4 || BITS == 3 || BITS == 2, "code width");
     static_assert(MP == 1 || MP == 2 || MP == 4, "rows of x, rounded up");
@@ -162,10 +164,9 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
     const int M = p.M, G = p.G;
     const int64_t N = p.N, K = p.K;
     const int aux_row = aux_row_bytes(G), slot_size = slot_bytes(G);
-    // groups of this wavefront: G is a multiple of 4, so a unit of 4 groups exists entirely or not at all.
-    // A wavefront (or unit) without groups reads the codes of a group that exists and multiplies them by
-    // zero activations: every load stays unconditional and inside the arrays.
-    const int ngw = max(0, min(GPW, G - w * GPW));
+    // groups of this wavefront.  In a unit of 4 groups that it has in part the row's last group stands in for those it
+    // does not have, which meet zero activations, scales and offsets.
+    const int ngw = max(0, min(GPW, G - w * GPW)), ngw4 = max(ANY ? (ngw + 3) & ~3 : ngw, 4);
     const int gbase = ngw > 0 ? w * GPW : 0;
     const int gmaxl = max(ngw, 1) - 1;
 
@@ -186,20 +187,20 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
     // ---- codes: a ring of two units; one lane holds the QW words of its quarter of each of the unit's 4 groups
     struct Quarter { uint32_t w[QW]; };
     Quarter cw[2][4];
-    // (A unit of 4 groups exists entirely or not at all.  The scalar offset names the tile and the unit, the
-    // group inside the unit is a constant that the load instruction carries itself.  A load that is not
-    // wanted - a unit the wavefront does not have, a tile past the block's last - gets a lane offset
+    // (The scalar offset names the tile and the unit, the group inside the unit is a constant that the load
+    // instruction carries itself; the range check would not see an offset past the row's end.  A load that is not wanted - a unit the wavefront does not have, a tile past the block's last - gets a lane offset
     // beyond the end of the descriptor: the hardware's range check then returns zeros without touching
     // memory, and the instruction stream stays free of branches.)
     constexpr uint32_t kGroupStride = REPACK ? 64 * QB : GB;
     constexpr uint32_t kOutOfRange = 0x80000000u;        // every array is shorter than this
-    const int nunits = ngw / 4;
+    const int nunits = (ANY ? ngw + 3 : ngw) / 4;
     auto load_codes = [&](Quarter& c, int li, int pp, int gi) {
         const int t = tile_of(li);
         const bool wanted = pp < nunits && li < ntiles;
-        const uint32_t so = (uint32_t)t * tile_code_bytes + (uint32_t)(gbase + 4 * pp) * kGroupStride;
+        const int g = ANY ? min(4 * pp + gi, gmaxl) : 4 * pp;    // ANY: the group, else the unit (the load carries the rest)
+        const uint32_t so = (uint32_t)t * tile_code_bytes + (uint32_t)(gbase + g) * kGroupStride;
         const uint32_t lane_off = REPACK ? (uint32_t)lane * QB : row_in(t) * row_bytes + (uint32_t)q * QB;
-        const uint32_t vo = (wanted ? lane_off : kOutOfRange) + (uint32_t)gi * kGroupStride;
+        const uint32_t vo = (wanted ? lane_off : kOutOfRange) + (ANY ? 0u : (uint32_t)gi * kGroupStride);
         // the re-laid-out codes are read exactly once and whole cache lines per instruction: nontemporal
         constexpr int aux = REPACK ? 2 : 0;
         if constexpr (BITS == 4) {
@@ -219,8 +220,12 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
     //      16 rows' scales, lane (n, sub) piece 4 j + sub of row n;  PASSES <= j < 2 PASSES the same of
     //      the offsets;  j = 2 PASSES the rows' tables (any4: lane (n, half) with half < 2; any3: 16 bytes
     //      a row; any2: the aligned 16 bytes that hold the row's 8).  A wavefront whose turn it is not, and
-    //      lanes without a piece, issue the load with an out-of-range offset and write nothing.
+    //      lanes without a piece, issue the load with an out-of-range offset and write nothing.  (ANY: rows start at any
+    //      2 bytes, which loads through a buffer descriptor do not take; the first bytes of an array stand in for what is not wanted.)
+    //      A row's last piece, where it has fewer than 8 groups, is loaded early, so that it ends with the row, and moved down when
+    //      it is written, zeros behind it.
     struct Stage { u32x4 v[KI]; };
+    const int pieces = (ANY ? G + 7 : G) / 8;
     auto stage_load = [&](Stage& s, int li) {
         const int t = tile_of(li);
         const int r = (w - li) & (kWaves - 1);
@@ -230,20 +235,31 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
             const int j = min(jr, NI - 1);
             const bool is_lut = j == 2 * PASSES;
             const bool is_off = !is_lut && j >= PASSES;
-            const uint16_t* base = is_lut ? p.lut : (is_off ? p.offset : p.scale);
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0,
-                                                                                is_lut ? p.lut_bytes : p.so_bytes, kRsrcFlags);
             const uint32_t row = (uint32_t)t * kTile + row_in(t);
-            const uint32_t piece = (uint32_t)((j - (is_off ? PASSES : 0)) * 4 + q);
-            uint32_t vo = row * (uint32_t)(G * 2) + piece * 16u;
-            bool wanted = jr < NI && li < ntiles && piece < (uint32_t)(G / 8);
+            const int piece = (j - (is_off ? PASSES : 0)) * 4 + q;
+            uint32_t vo = row * (uint32_t)(G * 2) + (uint32_t)(ANY ? min(piece * 8, G - 8) : piece * 8) * 2u;
+            bool wanted = jr < NI && li < ntiles && piece < pieces;
             if (is_lut) {
                 wanted = jr < NI && li < ntiles && q < (BITS == 4 ? 2 : 1) && !p.one_table;
                 if constexpr (BITS == 4) vo = row * 32u + (uint32_t)(q & 1) * 16u;
                 else if constexpr (BITS == 3) vo = row * 16u;
                 else vo = min((row * 8u) & ~15u, (uint32_t)p.lut_bytes - 16u);
             }
-            s.v[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, wanted ? vo : kOutOfRange, 0, 0);
+            if constexpr (ANY) {
+                // (opaque copies: a choice between members of `p` is else compiled as a load from a chosen address, for which
+                // all of `p` goes to scratch memory)
+                typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
+                typedef const __attribute__((address_space(1))) char* gptr;
+                auto scales = (gptr)p.scale, offsets = (gptr)p.offset, tables = (gptr)p.lut;
+                asm("" : "+s"(scales), "+s"(offsets), "+s"(tables));
+                const gptr base = is_lut && !p.one_table ? tables : (is_off ? offsets : scales);
+                s.v[k] = *(const __attribute__((address_space(1))) u32x4_at2*)(base + (wanted ? vo : 0u));
+            } else {
+                const uint16_t* base = is_lut ? p.lut : (is_off ? p.offset : p.scale);
+                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0,
+                                                                                    is_lut ? p.lut_bytes : p.so_bytes, kRsrcFlags);
+                s.v[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, wanted ? vo : kOutOfRange, 0, 0);
+            }
         }
     };
     auto stage_write = [&](const Stage& s, int li, int slot) {
@@ -251,30 +267,38 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
         const int t = tile_of(li);
         const int r = (w - li) & (kWaves - 1);
         unsigned char* const sb = slots + slot * slot_size;
-#pragma unroll
-        for (int k = 0; k < KI; ++k) {
+        static_for<KI>([&](auto k_) {
+            constexpr int k = decltype(k_)::value;
             const int j = r + kWaves * k;
-            if (j >= NI) continue;
+            u32x4 v = s.v[k];
+            if (j >= NI) return;
             if (j == 2 * PASSES) {
                 unsigned char* dst = sb + 2 * kTile * aux_row + n * 32;
-                if constexpr (BITS == 4) { if (q < 2) *reinterpret_cast<u32x4*>(dst + q * 16) = s.v[k]; }
-                else if constexpr (BITS == 3) { if (q < 1) *reinterpret_cast<u32x4*>(dst) = s.v[k]; }
+                if constexpr (BITS == 4) { if (q < 2) *reinterpret_cast<u32x4*>(dst + q * 16) = v; }
+                else if constexpr (BITS == 3) { if (q < 1) *reinterpret_cast<u32x4*>(dst) = v; }
                 else {
                     // the row's 8 bytes are the lower or the upper half of the 16 that were fetched
                     const uint32_t rowb = ((uint32_t)t * kTile + row_in(t)) * 8u;
                     const bool upper = rowb - min(rowb & ~15u, (uint32_t)p.lut_bytes - 16u) != 0u;
-                    if (q < 1) *reinterpret_cast<uint2*>(dst) = upper ? make_uint2(s.v[k][2], s.v[k][3]) : make_uint2(s.v[k][0], s.v[k][1]);
+                    if (q < 1) *reinterpret_cast<uint2*>(dst) = upper ? make_uint2(v[2], v[3]) : make_uint2(v[0], v[1]);
                 }
             } else {
                 const int jb = j >= PASSES ? j - PASSES : j;
                 const int piece = jb * 4 + q;
                 unsigned char* dst = sb + (j >= PASSES ? kTile * aux_row : 0) + n * aux_row + piece * 16;
-                if (piece < G / 8) {                                // (rows are 8-byte aligned in the slot)
-                    reinterpret_cast<uint2*>(dst)[0] = make_uint2(s.v[k][0], s.v[k][1]);
-                    reinterpret_cast<uint2*>(dst)[1] = make_uint2(s.v[k][2], s.v[k][3]);
+                if constexpr (ANY) {                                // down by 0 .. 7 groups
+                    const int by = max(piece * 8 - (G - 8), 0);
+                    asm volatile("" : "+v"(v));                     // (else done, and waited for, by wavefronts whose turn it is not)
+                    if (by & 2) v = u32x4{v[1], v[2], v[3], 0u};
+                    if (by & 4) v = u32x4{v[2], v[3], 0u, 0u};
+                    if (by & 1) v = u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
+                }
+                if (piece < pieces) {                               // (rows are 8-byte aligned in the slot)
+                    reinterpret_cast<uint2*>(dst)[0] = make_uint2(v[0], v[1]);
+                    reinterpret_cast<uint2*>(dst)[1] = make_uint2(v[2], v[3]);
                 }
             }
-        }
+        });
     };
 
     // ---- table source of a tile.  The entries of a row are written by its 32 threads (w, q):
@@ -363,7 +387,7 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
         const unsigned char* row = slots + slot * slot_size + n * aux_row;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            const uint32_t gl = min((uint32_t)(c * P) + sc_lane, (uint32_t)(max(ngw, 4) - NSC));
+            const uint32_t gl = min((uint32_t)(c * P) + sc_lane, (uint32_t)(ngw4 - NSC));
             const unsigned char* a = row + ((uint32_t)gbase + gl) * 2u;
             if constexpr (NSC == 4) {
                 const uint2 v = *reinterpret_cast<const uint2*>(a);
@@ -381,7 +405,7 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
     //      groups the wavefront has (a clamped offset meets a zero group sum)
     auto read_offsets = [&](int c, int slot) -> uint4 {
         const unsigned char* row = slots + slot * slot_size + kTile * aux_row + n * aux_row;
-        const uint32_t hi_grp = (uint32_t)(max(ngw, 4) - 4);
+        const uint32_t hi_grp = (uint32_t)(ngw4 - 4);
         const uint32_t g0 = min((uint32_t)(c * 16) + (uint32_t)(q & 1) * 8u, hi_grp);
         const uint32_t g1 = min((uint32_t)(c * 16) + (uint32_t)(q & 1) * 8u + 4u, hi_grp);
         const uint2 a = *reinterpret_cast<const uint2*>(row + ((uint32_t)gbase + g0) * 2u);
@@ -635,9 +659,9 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
 
 }  // namespace pack
 
-template <int BITS, int MP, int PASSES, bool REPACK>
+template <int BITS, int MP, int PASSES, bool REPACK, bool ANY>
 inline hipError_t launch_pack_t(const pack::Params& p, hipStream_t stream) {
-    constexpr auto kern = pack::decode_pack_kernel<BITS, MP, PASSES, REPACK>;
+    constexpr auto kern = pack::decode_pack_kernel<BITS, MP, PASSES, REPACK, ANY>;
     // (the limit is raised once to all of a compute unit's LDS; what a launch asks for depends on K)
     const int lds = pack::lds_bytes(BITS, MP, PASSES, p.G);
     if (hipError_t e = ensure_lds<kern>(pack::kLdsPerCu); e != hipSuccess) return e;
@@ -647,7 +671,7 @@ inline hipError_t launch_pack_t(const pack::Params& p, hipStream_t stream) {
 
 template <int BITS, bool REPACK>
 inline hipError_t launch_pack_b(const pack::Params& p, const PackPlan& pl, hipStream_t stream) {
-#define ANY4_PACK(MP, PS) if (pl.mp == MP && pl.passes == PS) return launch_pack_t<BITS, MP, PS, REPACK>(p, stream)
+#define ANY4_PACK(MP, PS) if (pl.mp == MP && pl.passes == PS) return (p.G & 7) ? launch_pack_t<BITS, MP, PS, REPACK, true>(p, stream) : launch_pack_t<BITS, MP, PS, REPACK, false>(p, stream)
     ANY4_PACK(1, 2); ANY4_PACK(1, 3); ANY4_PACK(1, 4);
     ANY4_PACK(1, 5); ANY4_PACK(1, 6); ANY4_PACK(1, 7); ANY4_PACK(1, 8);
     ANY4_PACK(2, 2); ANY4_PACK(2, 3); ANY4_PACK(2, 4);

@@ -26,7 +26,7 @@ def test_numbers_of_groups(oracle, bits, variant):
     f16, group = variant == "f16", {"g64": 64, "g256": 256}.get(variant, 128)
     # (33 .. 35 groups of 33 rows: five slabs, the last of one to three groups; 20500 rows: six tiles a block)
     for M, N, G in ((1, 17, 1), (2, 33, 2), (4, 16, 3), (1, 33, 5), (16, 100, 6), (3, 31, 7), (7, 4200, 9), (2, 20500, 5), (9, 48, 11),
-                    (1, 33, 33), (16, 33, 34), (5, 33, 35), (4, 40, 66), (6, 5003, 22)):
+                    (1, 33, 33), (16, 33, 34), (5, 33, 35), (4, 40, 66), (6, 5003, 22), (2, 50, 37), (1, 17, 70)):
         if group == 256 and G % 2:
             G += 1
         K = 128 * G

@@ -1,8 +1,8 @@
 """The kernel for one to four rows of x that walks the whole K axis inside one block (packed
 activation operands, no K slabs): every shape class it distinguishes, against the oracle.
-K = 128 * G with G a multiple of 8 and K >= 8192 goes to it: 2 .. 8 units per wavefront (odd and even:
+K = 128 * G with G > 32 goes to it: 2 .. 8 units per wavefront (odd and even:
 the ring of code registers then does / does not depend on the tile's parity), wavefronts with fewer
-groups than the others or none, one tile, fewer tiles than blocks, a few more tiles than blocks,
+groups than the others or none, units and 16-byte pieces of scales that are there in part, one tile, fewer tiles than blocks, a few more tiles than blocks,
 ragged last tile, all three code widths, both code layouts.  Bar as in test_gpu_parity.py."""
 import numpy as np
 import pytest
@@ -53,6 +53,15 @@ def run(any4, oracle, M, N, K, bits, seed):
 def test_one_row_every_unit_count(any4, oracle, bits, G):
     """M = 1: 2 .. 8 units per wavefront; G = 72, 104, 112, 200: the last wavefronts own fewer groups or none"""
     run(any4, oracle, 1, 333, 128 * G, bits, seed=inputs.case_seed(71, bits, G % 10))
+
+
+@pytest.mark.parametrize("bits", (4, 3, 2))
+@pytest.mark.parametrize("M,N,G", [(1, 333, 33), (1, 17, 34), (1, 40, 35), (2, 100, 36), (4, 333, 37), (3, 33, 38), (1, 8500, 39), (2, 50, 61),
+                                   (4, 16, 63), (1, 1, 65), (2, 70, 94), (1, 333, 97), (2, 9000, 33), (1, 48, 113), (2, 333, 127), (1, 100, 131),
+                                   (1, 47, 163), (1, 333, 193), (1, 20, 221), (1, 64, 255)])
+def test_any_number_of_groups(any4, oracle, bits, M, N, G):
+    """every remainder of G by 4 and by 8, every unit count, the last wavefront with 1 .. 31 groups"""
+    run(any4, oracle, M, N, 128 * G, bits, seed=inputs.case_seed(73, bits, G % 10))
 
 
 @pytest.mark.parametrize("bits", (4, 3, 2))
