@@ -87,14 +87,64 @@ struct Params {
     const uint16_t* offset;
     uint16_t* y;
     float* partial;                  // [tiles][slabs][ROWS * BN] fp32, slabs > 1 only
-    unsigned long long* counters;    // [tiles], slabs > 1 only
+    unsigned long long* words;       // a meeting word every word_step words per tile, slabs > 1 only
+    int word_step;
     int64_t N, K, ldy;               // N: rows of weights of this launch; ldy: values from a row of y to the next
     int M, G;                        // G = K / 128
     int lr;                          // log2(group size / 128), 0 with groups of 64
     int flags;                       // 1: re-laid-out codes, 2: one table for all rows
     int slabs, tiles_n;              // grid = (tiles_n * slabs, blocks of ROWS rows of x)
+    int parts;                       // in how many parts the sums of a tile's slabs are added: 1, or one for each of up to 8 slabs
     int sc_stride;                   // Shape::sc_stride of the largest slab
 };
+
+// Slabs of a tile meet at a word: arrivals (8 bits), the parts whose owners have left (8 bits), a bit that every completed
+// meeting turns over, a tag.  The sums of a tile are `parts` parts; part k belongs to slab k.  A slab that has brought its sums waits a
+// while for the others; if all have come it adds its part of all slabs, otherwise it leaves, and the last slab to come adds the parts
+// of those that have left.  So blocks that end together share the adding, and nobody depends on anybody who may not be running.  Returns
+// the parts (bits) that the block is to add.  By one thread, after the block's sums are out.
+//
+// The last to arrive puts the word back for the next meeting; the bit then tells those who still look at it.  A word that is not
+// of this kind (memory used for the first time, or for something else) counts as no arrivals, as in any4_splitk.h.  (One that a launch
+// which never finished has left with parts marked only has a part added twice.)
+//
+// One block adding all the sums of a tile took 8 - 12 000 cycles (a compute unit reads 20 - 26 bytes a cycle of what others wrote; 256 KB of
+// eight slabs at 64 rows of x, 1 MB at 128): 4096 x 4096 at M = 64 / 128 18.5 / 34.2 -> 16.4 / 24.3 us, 4096 x 14336 29.0 / 54.2 -> 26.5 / 39.2.
+// (the words of blocks that look at them lie in cache lines of their own: packed, a sum took up to 11 000 cycles more to get out, and
+// an arrival as many, however seldom the blocks looked)
+constexpr int kWordBytes = 64;
+constexpr int kMaxParts = 8, kLooks = 10;                      // looks: about 0.4 us each
+__device__ __forceinline__ uint32_t meet(unsigned long long* word, int slabs, int parts, int slab) {
+    constexpr unsigned long long kTag = 0x24B47C5EED17ull << 17, kTurn = 1ull << 16, kCount = 0xFFull;
+    const unsigned long long all = (unsigned long long)slabs;
+    auto own = [&](unsigned long long v) -> bool { return (v >> 17) == (kTag >> 17) && (v & kCount) < all; };
+    unsigned long long old = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!own(old)) {
+        // the add above went into a foreign word and is dropped with it
+        unsigned long long seen = old + 1ull;
+        for (;;) {
+            old = own(seen) ? seen : kTag;
+            if (__hip_atomic_compare_exchange_strong(word, &seen, old + 1ull, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+        }
+    }
+    const uint32_t bit = slab < parts ? 1u << slab : 0u;       // this slab's part
+    if ((old & kCount) + 1ull == all) {
+        __hip_atomic_store(word, kTag | (~old & kTurn), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return parts == 1 ? 1u : bit | ((uint32_t)(old >> 8) & 0xFFu);
+    }
+    if (parts == 1 || bit == 0u) return 0u;
+    auto complete = [&](unsigned long long v) -> bool { return ((v ^ old) & kTurn) != 0ull || (v & kCount) == all; };
+    for (int look = 0; look < kLooks; ++look) {
+        if (complete(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) return bit;
+        __builtin_amdgcn_s_sleep(8);
+    }
+    const unsigned long long mark = (unsigned long long)bit << 8;
+    const unsigned long long left = __hip_atomic_fetch_or(word, mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!complete(left)) return 0u;
+    // the last came in between and counts on this slab; its mark comes off the word where it went into the next meeting's
+    if ((left ^ old) & kTurn) __hip_atomic_fetch_and(word, ~mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return bit;
+}
 
 template <int BITS, int MT, int WN, bool F16, bool FINE>
 __device__ __forceinline__ void batch_body(const Params& p) {
@@ -422,32 +472,66 @@ __device__ __forceinline__ void batch_body(const Params& p) {
         }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
-    if (threadIdx.x == 0) *reinterpret_cast<lds_u32>(0u) = arrive_one(p.counters + btile, p.slabs) ? 1u : 0u;
+    if (threadIdx.x == 0) *reinterpret_cast<lds_u32>(0u) = meet(p.words + btile * p.word_step, p.slabs, p.parts, slab);
     lds_barrier();
-    if (*reinterpret_cast<lds_u32>(0u) == 0u) return;
+    const uint32_t mine = __builtin_amdgcn_readfirstlane(*reinterpret_cast<lds_u32>(0u));
+    // A unit is 1 KB, one wavefront's quads, numbered as they lie; part k has units k U / parts ..  UNITS of them at a time
+    // are added over all slabs and stored.
+    constexpr int U = MT * WN * 4;
+    auto add_units = [&](auto units_, auto flight_, const int (&unit)[4]) {
+        constexpr int UNITS = decltype(units_)::value, FLIGHT = decltype(flight_)::value;      // slabs whose loads are in flight together
+        float sum[UNITS][4];
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
-        if (wk == i % WK) {
-            f32x16 sum = zero;
-            constexpr int FLIGHT = 8;                             // slabs whose loads are in flight together
-            for (int sl = 0; sl < p.slabs; sl += FLIGHT) {
-                u32x4 a[FLIGHT][4];
+        for (int k = 0; k < UNITS; ++k)
 #pragma unroll
-                for (int u = 0; u < FLIGHT; ++u)
+            for (int e = 0; e < 4; ++e) sum[k][e] = 0.f;
+        for (int sl = 0; sl < p.slabs; sl += FLIGHT) {
+            u32x4 q[FLIGHT][UNITS];
 #pragma unroll
-                    for (int v4 = 0; v4 < 4; ++v4) a[u][v4] = __builtin_amdgcn_raw_buffer_load_b128(ares, quad(i, v4), min(sl + u, p.slabs - 1) * (ROWS * BN) * 4, kAgent);
+            for (int f = 0; f < FLIGHT; ++f)
 #pragma unroll
-                for (int u = 0; u < FLIGHT; ++u)                  // (otherwise each load is put in front of its addition)
+                for (int k = 0; k < UNITS; ++k)                // (not there: an offset beyond the buffer, 0 without a read)
+                    q[f][k] = __builtin_amdgcn_raw_buffer_load_b128(ares, sl + f < p.slabs && unit[k] < U ? (uint32_t)((sl + f) * (ROWS * BN * 4) + unit[k] * 1024 + lane * 16) : 0x80000000u, 0, kAgent);
 #pragma unroll
-                    for (int v4 = 0; v4 < 4; ++v4) asm volatile("" : "+v"(a[u][v4]));
+            for (int f = 0; f < FLIGHT; ++f)                   // (otherwise each load is put in front of its addition)
 #pragma unroll
-                for (int u = 0; u < FLIGHT; ++u)
-                    if (sl + u < p.slabs)
+                for (int k = 0; k < UNITS; ++k) asm volatile("" : "+v"(q[f][k]));
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) sum[v] += __uint_as_float(a[u][v >> 2][v & 3]);
-            }
-            store_tile(i, sum);
+            for (int f = 0; f < FLIGHT; ++f)
+                if (sl + f < p.slabs)
+#pragma unroll
+                    for (int k = 0; k < UNITS; ++k)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sum[k][e] += __uint_as_float(q[f][k][e]);
         }
+#pragma unroll
+        for (int k = 0; k < UNITS; ++k) {
+            if (unit[k] >= U) break;
+            const int64_t col = n0 + (unit[k] >> 2) % WN * 32 + r32;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t m = m0 + (unit[k] >> 2) / WN * 32 + (unit[k] & 3) * 8 + h * 4 + e;
+                if (m < p.M && col < p.N) p.y[m * p.ldy + col] = (uint16_t)f32_to_h16<F16>(sum[k][e]);
+            }
+        }
+    };
+    int at = wave - kWaves;
+    auto next_unit = [&]() -> int {
+        do at += kWaves; while (at < U && !(mine >> (at * p.parts / U) & 1u));
+        return at;
+    };
+    for (;;) {
+        const int first = next_unit();
+        if (first >= U) break;
+        const int second = next_unit();
+        if (second >= U) {
+            add_units(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{}, {first, U, U, U});
+            break;
+        }
+        const int third = next_unit(), fourth = next_unit();
+        if (p.slabs <= 2) add_units(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{}, {first, second, third, fourth});
+        else add_units(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{}, {first, second, third, fourth});
+    }
 }
 
 template <int BITS, int MT, int WN, bool F16, bool FINE>

@@ -54,6 +54,10 @@ BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
     const int G = (int)(K / kGroup), tiles = (int)((N + bn - 1) / bn), most = kMaxSlabValues[mt - 1];   // values per row in LDS
     const int first = (G + most - 1) / most, first_fine = (2 * G + most / 2 * 2 - 1) / (most / 2 * 2);
     const size_t tile_bytes = (size_t)rows * bn * sizeof(float);
+    // The blocks of a tile share the adding where all blocks of a launch run at once and there is room for its words.
+    auto share = [&](int part, int s) -> bool {
+        return (int64_t)part * s <= cus && splitk_counter_bytes(part) + (size_t)part * (s + 1) * tile_bytes <= (size_t)ANY4_NOALLOC_SCRATCH_BYTES;
+    };
     auto take = [&](BatchPlan& pl, int part, int s, double us) {
         if (pl.ok && us >= pl.us) return;
         pl = BatchPlan{};
@@ -90,8 +94,14 @@ BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
             }
         }
         if (pl.slabs > 1) {
-            pl.counter_bytes = splitk_counter_bytes(pl.tiles_n);
-            pl.workspace = pl.counter_bytes + (size_t)pl.tiles_n * pl.slabs * tile_bytes;
+            const size_t sums = (size_t)pl.tiles_n * pl.slabs * tile_bytes;
+            pl.counter_bytes = pl.sums_at = splitk_counter_bytes(pl.tiles_n);
+            pl.shared = share(pl.tiles_n, pl.slabs);
+            if (pl.shared) {                                   // words in lines of their own, in the room of one more slab
+                pl.counter_bytes = ((size_t)pl.tiles_n * batch::kWordBytes + 255) / 256 * 256;
+                pl.sums_at += (size_t)pl.tiles_n * tile_bytes;
+            }
+            pl.workspace = pl.sums_at + sums;
         }
     }
     return both;
@@ -104,8 +114,10 @@ hipError_t launch_batch(const uint16_t* x, const uint32_t* codes, const uint16_t
     if (!pl.ok || lr < -1 || (f16 && fine) || (pl.slabs > 1 && !workspace)) return hipErrorInvalidValue;
     batch::Params p{};
     p.x = x;
-    p.counters = static_cast<unsigned long long*>(workspace);
-    p.partial = pl.slabs > 1 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + pl.counter_bytes) : nullptr;
+    p.words = static_cast<unsigned long long*>(workspace);
+    p.word_step = pl.shared ? batch::kWordBytes / 8 : 1;
+    p.parts = pl.shared ? (pl.slabs < batch::kMaxParts ? pl.slabs : batch::kMaxParts) : 1;
+    p.partial = pl.slabs > 1 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + pl.sums_at) : nullptr;
     p.K = K; p.ldy = N; p.M = (int)M; p.G = (int)(K / kGroup);
     p.lr = fine ? 0 : lr;
     p.flags = (repacked ? 1 : 0) | (one_table ? 2 : 0);

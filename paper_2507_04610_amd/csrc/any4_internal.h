@@ -55,7 +55,8 @@ struct BatchPlan {
     bool ok;              // the kernel takes this problem
     int mt, rows;         // 32-row tiles of x per block, 32 * mt
     int tiles_n, slabs;   // blocks along n of one launch (the last may have fewer), K slabs
-    size_t counter_bytes, workspace;      // arrival counters, and with them the fp32 partial sums (several slabs only)
+    bool shared;          // the blocks of a tile share the adding of its slabs' sums
+    size_t counter_bytes, sums_at, workspace;      // meeting words; where the fp32 partial sums begin, where they end (several slabs only)
     double us;            // the time it is expected to take
 };
 struct BatchPlans { BatchPlan plain, fine; };             // groups of 128 and more, groups of 64
