@@ -156,8 +156,9 @@ __device__ __forceinline__ void batch_body(const Params& p) {
     };
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wn = wave % WN, wk = wave / WN, r32 = lane & 31, h = lane >> 5;
-    const int slab = blockIdx.x % p.slabs, tile = blockIdx.x / p.slabs;
-    const int G = p.G, g_lo = (int)((int64_t)slab * G / p.slabs), g_hi = (int)((int64_t)(slab + 1) * G / p.slabs);
+    // (32-bit divisions: G < 2^17, at most 64 slabs)
+    const int tile = (int)(blockIdx.x / (unsigned)p.slabs), slab = (int)blockIdx.x - tile * p.slabs;
+    const int G = p.G, g_lo = (int)((unsigned)(slab * G) / (unsigned)p.slabs), g_hi = (int)((unsigned)((slab + 1) * G) / (unsigned)p.slabs);
     const int T = (g_hi - g_lo + WK - 1) / WK;                    // steps
     // A block starts at a step of its own and wraps around: rows lie powers of two apart, and blocks that
     // walked along K together would all ask the same few memory channels at a time.
@@ -214,10 +215,9 @@ __device__ __forceinline__ void batch_body(const Params& p) {
     // Scales and offsets of the slab are staged in LDS once, with loads as wide as their alignment allows: a
     // load of one value from each of 32 rows costs the memory pipeline as much as one of their codes.
     const int s_lo = FINE ? 2 * g_lo : g_lo >> p.lr, s_n = (FINE ? 2 * g_hi : ((g_hi - 1) >> p.lr) + 1) - s_lo;
-    auto stage_scales = [&](auto unit) {
+    auto stage_pieces = [&](auto unit, auto flight_, int chunks, int total) {
         using V = decltype(unit);
-        constexpr int PER = sizeof(V) / 2, FLIGHT = 4;
-        const int chunks = (s_n + PER - 1) / PER, total = BN * chunks;
+        constexpr int PER = sizeof(V) / 2, FLIGHT = decltype(flight_)::value;
         for (int base = threadIdx.x; base < total; base += kThreads * FLIGHT) {
             V v[2][FLIGHT];
             uint32_t to[FLIGHT];
@@ -241,6 +241,13 @@ __device__ __forceinline__ void batch_body(const Params& p) {
                 }
         }
     };
+    auto stage_scales = [&](auto unit) {
+        constexpr int PER = sizeof(unit) / 2;
+        const int chunks = (s_n + PER - 1) / PER, total = BN * chunks;
+        if (total <= kThreads) stage_pieces(unit, std::integral_constant<int, 1>{}, chunks, total);
+        else if (total <= 2 * kThreads) stage_pieces(unit, std::integral_constant<int, 2>{}, chunks, total);
+        else stage_pieces(unit, std::integral_constant<int, 4>{}, chunks, total);
+    };
 
     // the row's table and the codes of the first steps
     using table_words = std::conditional_t<BITS == 2, u32x2, u32x4>;
@@ -250,15 +257,21 @@ __device__ __forceinline__ void batch_body(const Params& p) {
         tw[0] = src[0];
         if constexpr (BITS == 4) tw[1] = src[1];
     }
+    // (Loads are taken only as fast as earlier ones are served - the first 160 KB of a block took 10 - 14 000 cycles to be taken - so
+    // what the first step does not need is asked for behind what it waits for: two steps, the scales, a third step, and the rest
+    // after the wait.  6144 / 4096 / 28672 x 4096 at M = 64 17.9 / 16.5 / 40.1 -> 17.0 / 15.7 / 38.5 us; without the third step before the wait 17.5 /
+    // 16.4 / 39.3.)
     Codes cq[CD];
 #pragma unroll
-    for (int t = 0; t < CD; ++t) fetch_codes(cq[t], min(t, T - 1));
-#pragma unroll
-    for (int t = 0; t < D; ++t)
+    for (int t = 0; t < 2; ++t) {
+        fetch_codes(cq[t], min(t, T - 1));
         if (t < T) fetch_x(t);
+    }
     if (((GS | s_lo | s_n) & 7) == 0) stage_scales(u32x4{});
     else if (((GS | s_lo) & 1) == 0) stage_scales(uint32_t{});
     else stage_scales(uint16_t{});
+    fetch_codes(cq[2], min(2, T - 1));
+    if (2 < T) fetch_x(2);
     for (uint32_t a = threadIdx.x * 16; a < 2 * S::XS_SET; a += kThreads * 16) *reinterpret_cast<lds_u4>(S::XS + a) = u32x4{0, 0, 0, 0};
     const uint32_t srow = (uint32_t)(S::SC + (wn * 32 + r32) * p.sc_stride);   // this lane's staged scales; offsets BN rows on
     auto staged = [&](uint32_t at, int g) -> uint32_t {           // FINE: the pair of the group's halves
@@ -383,9 +396,9 @@ __device__ __forceinline__ void batch_body(const Params& p) {
         lds_barrier();
     };
     static_assert(D == 3, "the waits");
-    loads_left<0>();
-#pragma unroll
-    for (int t = 0; t < CD; ++t) landed(cq[t]);
+    if (2 < T) loads_left<kLoads>(); else loads_left<2>();
+    landed(cq[0]);
+    landed(cq[1]);
     {
         constexpr int L = 1 << BITS, W = BITS == 2 ? 2 : 4;       // entries; dwords per load
         uint32_t d[L / 2];
@@ -400,6 +413,10 @@ __device__ __forceinline__ void batch_body(const Params& p) {
         table.load(d);
     }
     lds_barrier();
+#pragma unroll
+    for (int t = 3; t < CD; ++t) {
+        fetch_codes(cq[t], min(t, T - 1));
+    }
     prepare(cq[0], xbase(0), 0);
     // (whole turns: a step past the last does nothing.  With a way out in the middle of a turn, or loads left out, the
     // compiler's wait at the top of the loop would be for all the codes in flight)
