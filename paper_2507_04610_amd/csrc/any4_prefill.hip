@@ -89,8 +89,8 @@ static_assert(furthest(kNarrowK) < ((int64_t)1 << 31) && furthest(2 * kNarrowK) 
 template <bool F16>
 __global__ __launch_bounds__(256) void group_sums_kernel(const uint16_t* __restrict__ x, int64_t M,
                                                          int64_t K, int KP, int fine, uint16_t* __restrict__ xs,
-                                                         unsigned long long* __restrict__ counters, int ncounters) {
-    for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < ncounters; c += (int64_t)gridDim.x * 256) counters[c] = 0ull;
+                                                         unsigned long long* __restrict__ counters, int ncounters, int word_step) {
+    for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < ncounters; c += (int64_t)gridDim.x * 256) counters[c * word_step] = 0ull;
     const int lanes = fine ? 8 : 16;
     const int64_t G = K / (8 * lanes);
     const int64_t unit = ((int64_t)blockIdx.x * 256 + threadIdx.x) / lanes;  // (m, g), g fastest
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
     const uint16_t* __restrict__ x, const uint32_t* __restrict__ codes,
     const uint16_t* __restrict__ lut, const uint16_t* __restrict__ scale,
     const uint16_t* __restrict__ offset, const uint16_t* __restrict__ xsums, int KP,
-    int64_t M, int64_t N, int64_t K, int lr, int flags, int gm, int tail_first, int tail_s,
+    int64_t M, int64_t N, int64_t K, int lr, int flags, int gm, int tail_first, int tail_s, int word_step,
     unsigned long long* __restrict__ counters, float* __restrict__ partial, uint16_t* __restrict__ y) {
     constexpr int L = 1 << BITS;
     const bool repacked = flags & 1, one_table = flags & 2;     // re-laid-out codes / one table for all rows
@@ -586,8 +586,8 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
     const __amdgpu_buffer_rsrc_t ares = __builtin_amdgcn_make_buffer_rsrc(all, 0, tail_s * (PBM * PBN) * 4, 0x00020000);
     auto quad = [&](int part, int v4) -> uint32_t { return (uint32_t)((((part * 4 + v4) * 8 + wave) * 64 + lane) * 16); };   // 16 bytes: four elements
     constexpr int kAgent = 16;                                 // cache policy: coherent over the whole device
-    // (a word per tile with a count of 16 bits per part, 0 at first: group_sums_kernel)
-    unsigned long long* const word = counters + (tile - tail_first);
+    // (a word per tile, word_step words apart, with a count of 16 bits per part, 0 at first: group_sums_kernel)
+    unsigned long long* const word = counters + (tile - tail_first) * word_step;
     unsigned long long before = 0;
     auto arrive = [&](int part) { before = __hip_atomic_fetch_add(word, 1ull << (16 * part), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> (16 * part); };
     const int sh = tail_s == 2 ? 1 : 0, parts = 4 >> sh;       // part p: tiles p << sh ..
@@ -667,8 +667,8 @@ PrefillPlan plan_prefill(int64_t M, int64_t N, int64_t K, int cus) {
     }
     // (sized for groups of 64, the largest case: the workspace does not depend on the group size)
     p.xsums_bytes = ((size_t)M * (size_t)prefill_kp(K, true) * sizeof(uint16_t) + 255) / 256 * 256;
-    p.counter_bytes = p.tail_tiles ? splitk_counter_bytes(p.tail_tiles) : 0;
     p.partial_bytes = (size_t)p.tail_tiles * (size_t)p.tail_s * (PBM * PBN) * sizeof(float);
+    p.counter_bytes = p.tail_tiles ? splitk_counter_bytes(p.tail_tiles) : 0;
     return p;
 }
 
@@ -686,6 +686,15 @@ hipError_t launch_prefill(const uint16_t* x, const uint32_t* codes, const uint16
     uint16_t* xsums = static_cast<uint16_t*>(workspace);
     unsigned long long* counters = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + pp.xsums_bytes);
     float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + pp.xsums_bytes + pp.counter_bytes);
+    // A cache line of 64 bytes to a tile's word where the group sums leave room for it (they are half as many with groups of 128 and
+    // more): with eight tiles' words in one, all of whose slices come at once, 4096 x 4096 at M = 200 took 34.0 us, 31.2 so; 6144 x 4096
+    // at M = 512 49.2, 48.7.
+    int word_step = 1;
+    const size_t sums = ((size_t)M * KP * sizeof(uint16_t) + 255) / 256 * 256;
+    if (sums + (size_t)pp.tail_tiles * 64 <= pp.xsums_bytes) {
+        word_step = 8;
+        counters = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + sums);
+    }
     const dim3 grid((unsigned)nblocks), block(PTHREADS);
     const int gm = (int)pp.gm, tail_first = (int)(pp.tiles - pp.tail_tiles), tail_s = pp.tail_s;
     // the LDS limit first: whatever can be refused is refused before anything is enqueued
@@ -694,12 +703,12 @@ hipError_t launch_prefill(const uint16_t* x, const uint32_t* codes, const uint16
     do {                                                                                                          \
         e = ensure_lds<prefill_kernel<B, F, H, NL, W>>((int)kLdsBytes);                                    \
         if (e != hipSuccess) return e;                                                                            \
-        if (f16) hipLaunchKernelGGL(group_sums_kernel<true>, dim3((unsigned)sblocks), dim3(256), 0, stream, x, M, K, KP, 0, xsums, counters, (int)pp.tail_tiles); \
-        else hipLaunchKernelGGL(group_sums_kernel<false>, dim3((unsigned)sblocks), dim3(256), 0, stream, x, M, K, KP, fine ? 1 : 0, xsums, counters, (int)pp.tail_tiles); \
+        if (f16) hipLaunchKernelGGL(group_sums_kernel<true>, dim3((unsigned)sblocks), dim3(256), 0, stream, x, M, K, KP, 0, xsums, counters, (int)pp.tail_tiles, word_step); \
+        else hipLaunchKernelGGL(group_sums_kernel<false>, dim3((unsigned)sblocks), dim3(256), 0, stream, x, M, K, KP, fine ? 1 : 0, xsums, counters, (int)pp.tail_tiles, word_step); \
         e = hipGetLastError();                                                                                    \
         if (e != hipSuccess) return e;                                                                            \
         hipLaunchKernelGGL((prefill_kernel<B, F, H, NL, W>), grid, block, kLdsBytes, stream, x, codes, lut, scale, \
-                           offset, xsums, KP, M, N, K, F ? 0 : lr, (repacked ? 1 : 0) | (one_table ? 2 : 0), gm, tail_first, tail_s, counters, partial, y); \
+                           offset, xsums, KP, M, N, K, F ? 0 : lr, (repacked ? 1 : 0) | (one_table ? 2 : 0), gm, tail_first, tail_s, word_step, counters, partial, y); \
     } while (0)
 #define ANY4_PREFILL_W(B, W)                                                                                      \
     do {                                                                                                          \
