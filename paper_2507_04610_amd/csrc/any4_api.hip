@@ -35,21 +35,16 @@ int device_compute_units() {
     return n;
 }
 
-// Time in us of the matrix-core kernel at M <= 256 and of the group sums in front of it: per round of blocks 8 us and
-// K / 64 steps of 0.95 us (few blocks in flight) .. 1.3 us (every compute unit busy), the last round divided by its
-// number of K slices, plus 3 + 2 * slices us for adding them up.
-// The constants are those of the kernel before it copied straight to LDS and shared the adding among a tile's blocks (10 % rms
-// then).  Against the kernel as it is (150 random matrices of 512 .. 40000 rows, K = 1024 .. 20480, M = 200) the sum is 17 % too
-// large on average, from 14 % too small to 60 % too large, the most with 7 or 8 slices; groups of 64: 13 % on average.  So the line
-// errs towards the kernel for fewer rows: up to 96 rows of x that takes 0.79 of this kernel's time on average and is slower in 7 of 600
-// calls (8 % at most), at 97 .. 128 rows 0.98 on average, in two calls of five slower (up to 1.3x).
+// Time in us of the matrix-core kernel at M <= 256 and of the group sums in front of it, groups of 64: per round of blocks a fixed part
+// and K / 64 steps, which take longer with every compute unit busy, the last round divided by its number of K slices, plus the
+// adding of slices.  Constants fitted to 1100 matrices of 512 .. 60000 rows, K = 1024 .. 28672: 7 % rms.
 static double prefill_us(const PrefillPlan& pp, int64_t K, int cus) {
     const double steps = (double)(K / 64);
     const int64_t last = pp.tiles % cus;
-    double t = 2.0 + (double)(pp.tiles / cus) * (8.0 + 1.3 * steps);
+    double t = 2.30 + (double)(pp.tiles / cus) * (8.75 + 1.113 * steps);
     if (last > 0) {
         const double busy = (double)(last * pp.tail_s) / cus;
-        t += 8.0 + (0.95 + 0.35 * (busy < 1.0 ? busy : 1.0)) * steps / pp.tail_s + (pp.tail_s > 1 ? 3.0 + 2.0 * pp.tail_s : 0.0);
+        t += 7.58 + (0.542 + 0.675 * (busy < 1.0 ? busy : 1.0)) * steps / pp.tail_s + (pp.tail_s > 1 ? 8.34 + 0.73 * pp.tail_s : 0.0);
     }
     return t;
 }
@@ -69,14 +64,16 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
     }
     if (M > kStreamMaxM && M <= kBatchMaxM) {
         // A few dozen rows of x fill a fraction of one 256-row tile of the matrix-core kernel, whose time does
-        // not depend on M below 256.
+        // not depend on M below 256.  It is slower than the kernel for a few dozen rows wherever that takes the call, with groups of 128 and
+        // more at 128 rows for 2089 of 2100 matrices (0.75 of its time where the line was drawn the other way before slabs shared their
+        // adding).  Groups of 64 at more than 64 rows of x, where LDS holds scales for 11 .. 29 groups of 128 weights a slab: the faster
+        // by the two models, 0.2 % slower than the better of the two on average (this kernel takes 4 % longer than modelled there); calls
+        // that need no workspace stay here.
         const BatchPlans both = plan_batch(M, N, K, cus);
         p.bp = both.plain;
         p.bp_fine = both.fine;
         const PrefillPlan pp = plan_prefill(M, N, K, cus);
-        const double matrix = 0.92 * prefill_us(pp, K, cus) + 2.5;   // (where both say the same, this side of 30 us the other one was faster, beyond it this one)
-        if (p.bp.us > matrix) p.bp = BatchPlan{};
-        if (p.bp_fine.us > matrix) p.bp_fine = BatchPlan{};
+        if (M > 64 && p.bp_fine.workspace > 0 && 1.04 * p.bp_fine.us > prefill_us(pp, K, cus)) p.bp_fine = BatchPlan{};
         if (p.bp.ok || p.bp_fine.ok) {
             p.workspace = p.bp.workspace > p.bp_fine.workspace ? p.bp.workspace : p.bp_fine.workspace;
             if (!p.bp.ok || !p.bp_fine.ok) {                   // the other kind of groups goes to the matrix-core kernel
@@ -90,6 +87,8 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
                 // 13.0 / 13.8 us, the other 14.6 / 14.7.  A launch: a fixed part, the larger of the time of a tile and
                 // that of the codes, a share per row of x (constants measured, 10 % rms).
                 p.sp = plan_stream(kStreamMaxM, N, K, cus);
+                // (Taken up to 1.17 of the other's expected time: a call of these sizes keeps the bits that its first 16 rows of x
+                // and the rest have as calls of their own.)
                 const double tile = 0.68 + 0.025 * p.sp.slab_groups, codes = (double)N * (double)K * bits / 8 / 4.74e6;
                 if (p.sp.gw > 0 && K % 512 == 0 && p.sp.slabs == 1 && p.sp.tiles <= p.sp.blocks_per_slab)
                     p.two_launches = 2 * (3.6 + (tile > codes ? tile : codes)) + 0.15 * (double)M;
@@ -151,7 +150,7 @@ int gemm_dispatch(const uint16_t* x, const uint32_t* codes, bool repacked, const
     const PackPlan pk = (M <= 4 && lut && lr == 0 && !f16) ? plan_pack(M, N, K, bits, one_table, plan.cus) : PackPlan{};
     if (pk.ok) {
         e = launch_decode_pack(x, codes, lut, scale, offset, M, N, K, bits, repacked, one_table, pk, y, s);
-    } else if (plan.two_launches > 0 && lut && lr >= 0 && plan.two_launches + (f16 ? 1.4 : 0.0) < plan.bp.us) {
+    } else if (plan.two_launches > 0 && lut && lr >= 0 && plan.two_launches + (f16 ? 1.4 : 0.0) < 1.17 * plan.bp.us) {
         // (fp16 takes it 0.7 us more per launch.  Not without a table: the streaming kernel takes the integer grid as 128 + code and off again, whose rounding
         // the kernel for more rows does not have)
         e = launch_decode_stream(x, codes, lut, scale, offset, kStreamMaxM, N, K, bits, lr, repacked, f16, one_table, plan.sp, y, workspace, s);

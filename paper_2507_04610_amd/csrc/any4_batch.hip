@@ -14,20 +14,24 @@ template <int MT> constexpr int max_slab_values() {
 constexpr int kMaxSlabValues[4] = {max_slab_values<1>(), max_slab_values<2>(), max_slab_values<3>(), max_slab_values<4>()};
 
 // Time in us of a launch of t tiles with s slabs of G groups.  Per round of blocks: their start and end (more with the
-// chip full: `crowd`), four steps whose loads are all issued at the start, and the rest, which take longer from a quarter of the chip
-// on; a round that fills the chip to the last compute unit took longer by `even`.  Where slabs meet: a wait for their sums, eight slabs at a time
-// (seven or eight take longer by `full`), and the traffic of all sums.  Constants fitted to 1700 problems of 128 .. 128256
-// rows of weights, K = 128 .. 28672, each with up to 16 slab counts: times within 7 % rms, the count taken on average 0.8 %
-// slower than the best, 11 % at worst.
+// chip full: `crowd`), four steps whose loads come with the start, and the rest, which take longer from a quarter of the chip
+// on; a round that fills the chip to the last compute unit took longer by `even`.  Where slabs meet and share the adding: a meeting, more
+// beyond eight slabs (whose parts the first eight add), and the traffic of all sums; where the last adds alone: four slabs at a time, and
+// the traffic.  Constants fitted to 44 000 times of 2100 matrices of 512 .. 60000 rows of weights, K = 1024 .. 28672, at 32, 64, 96
+// and 128 rows of x: 4 - 5 % rms; the count taken is on average 0.4 / 0.6 / 0.7 / 0.8 % slower than the best of those timed (by the constants
+// from before the sharing 1.4 / 3.8 / 8.1 / 11.7 %), 4 / 6 / 7 / 11 % at the 99th of a hundred.
 struct Cost {
-    double block, crowd, first, rest, rest_busy, even, flight, more, full, per_mb;   // (more: flights after the first)
+    double block, crowd, first, rest, rest_busy, even;
+    double meeting, more, per_mb;          // the adding is shared
+    double more_alone, per_mb_alone;       // it is not
 };
-constexpr Cost kCost[4] = {{6.3, 3.0, 1.02, 1.33, 1.38, 0, 2.6, 1.15, 0.46, 0.16}, {8.5, 0.95, 0.91, 1.75, 1.83, 0, 2.85, 2.6, 0.31, 0.54},
-                           {9.2, 0, 1.32, 1.32, 2.0, 3, 7.7, 9.5, 0.95, 0.36}, {9.9, 0.66, 1.67, 1.34, 2.51, 4, 11.2, 9.6, 1.33, 0.19}};
-static double meet_us(int mt, int t, int s) {
+constexpr Cost kCost[4] = {{4.94, 0.49, 1.45, 1.24, 1.38, 0.11, 2.08, 0.93, 0.43, 0.66, 0.79}, {5.78, 0.27, 1.70, 1.47, 1.75, 0.19, 2.55, 0.86, 0.29, 0.97, 0.64},
+                           {6.94, 0.41, 1.98, 1.54, 1.82, 1.99, 3.10, 1.20, 0.19, 1.23, 0.59}, {6.79, 3.99, 2.38, 1.82, 2.06, 1.38, 3.46, 1.09, 0.09, 1.63, 0.39}};
+static double meet_us(int mt, int t, int s, int cus) {
     const Cost& c = kCost[mt - 1];
-    return s == 1 ? 0.0 : c.flight + c.more * (double)((s - 1) / 8) + (s % 8 == 0 || s % 8 == 7 ? c.full : 0.0) +
-                          c.per_mb * ((double)t * s * (32 * mt) * (32 * batch::wn_of(mt))) * 4e-6;
+    const double mb = ((double)t * s * (32 * mt) * (32 * batch::wn_of(mt))) * 4e-6;
+    if (s == 1) return 0.0;
+    return (int64_t)t * s <= cus ? c.meeting + c.more * (double)((s - 1) / 8) + c.per_mb * mb : c.more_alone * (double)((s - 1) / 4) + c.per_mb_alone * mb;
 }
 static double launch_us(int mt, int t, int s, int G, int cus) {
     const Cost& c = kCost[mt - 1];
@@ -35,7 +39,7 @@ static double launch_us(int mt, int t, int s, int G, int cus) {
     const double busy = blocks < cus ? (double)blocks / cus : 1.0, quarter = busy < 0.25 ? 4 * busy : 1.0;
     const int first = steps < 4 ? steps : 4;
     return (double)rounds * (c.block + c.crowd * busy + c.first * first + (c.rest + (c.rest_busy - c.rest) * quarter) * (steps - first)) +
-           (blocks % cus == 0 ? c.even : 0.0) + meet_us(mt, t, s);
+           (blocks % cus == 0 ? c.even : 0.0) + meet_us(mt, t, s, cus);
 }
 
 // Work split for groups of 128 and more and for groups of 64 (twice the scales to keep in LDS); a pure function of its arguments.
@@ -58,8 +62,10 @@ BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
     auto share = [&](int part, int s) -> bool {
         return (int64_t)part * s <= cus && splitk_counter_bytes(part) + (size_t)part * (s + 1) * tile_bytes <= (size_t)ANY4_NOALLOC_SCRATCH_BYTES;
     };
+    // (above 64 rows of x a matrix of up to 1024 x 1024 is not cut, so that its calls go on needing no workspace: 23 us at 128 rows, cut 14)
+    const bool no_workspace = mt > 2 && N <= 1024 && K <= 1024;
     auto take = [&](BatchPlan& pl, int part, int s, double us) {
-        if (pl.ok && us >= pl.us) return;
+        if (pl.ok && (no_workspace || us >= pl.us)) return;
         pl = BatchPlan{};
         pl.ok = true;
         pl.mt = mt; pl.rows = rows;
@@ -67,9 +73,9 @@ BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
         pl.us = us;
     };
     for (int s = first; s <= 64 && s <= (G + wk - 1) / wk; ++s) {
-        // no slab count from here on can be better once its sums and as many rounds of blocks take too long
+        // no slab count from here on can be better once as many rounds of blocks take too long
         const double rounds = (double)tiles * s / cus;
-        if (both.fine.ok && meet_us(mt, tiles, s) + kCost[mt - 1].block * (rounds > 1.0 ? rounds : 1.0) > (both.fine.us > both.plain.us ? both.fine.us : both.plain.us)) break;
+        if (both.fine.ok && kCost[mt - 1].block * (rounds > 1.0 ? rounds : 1.0) > (both.fine.us > both.plain.us ? both.fine.us : both.plain.us)) break;
         int part = tiles;
         if (s > 1 && (size_t)tiles * (s * tile_bytes + 8) + 256 > (size_t)ANY4_NOALLOC_SCRATCH_BYTES) {
             const int fit = (int)((ANY4_NOALLOC_SCRATCH_BYTES - 256) / (s * tile_bytes + 8)), full = fit * s / cus * cus;
