@@ -19,7 +19,7 @@
 // K; its 8 wavefronts are WN along n and WK = 8 / WN along k (alternate groups).  A step is one group per k part.
 // x of the coming steps is copied straight into a ring of LDS buffers, three steps ahead, and the codes are loaded into
 // registers, four steps ahead; a step waits for what step t + 2 needs, so the first operand of the next step can be
-// prepared before the barrier.  The parts meet in LDS, slabs of K in the workspace (fp32, added in slab order by the last to arrive).
+// prepared before the barrier.  The parts meet in LDS, slabs of K in the workspace (fp32, added in slab order by the blocks of the tile, see meet).
 //
 // Order of the sums.  A block starts at a step of its own along K (see `rot`), so the last bit of an output can depend on
 // the place of its row of weights in the matrix.
@@ -27,9 +27,9 @@
 // What bounds it: no unit by itself.  28672 x 4096 at M = 64 (16 steps, 224 blocks, 40 us under the counters, 1.94 GHz): a
 // wavefront issues 317 vector instructions (20 of them matrix) and 24 LDS instructions a step; vector issue is
 // busy 53 % of the time, the matrix cores of the SIMDs that hold a block 27 %, the LDS pipe 20 %, and wavefronts wait 35 % of
-// theirs.  A step takes 1.8 us, the first four 0.9 (their loads are issued together).  The rest of a launch is fixed: 6 - 12 us for start and end of a block (32 .. 128 rows of x),
-// and where slabs meet 2 - 11 us for their sums (any4_batch.hip has the constants).  The four linears of an 8B layer at M = 24 / 64 / 128:
-// 84 / 107 / 191 us; the kernel for more rows takes 209, however few they are.
+// theirs.  A step takes 1.8 us.  The rest of a launch is fixed: 5 - 11 us for start and end of a block (32 .. 128 rows of x),
+// and where slabs meet 3 - 6 us for their sums (any4_batch.hip has the constants).  The four linears of an 8B layer at M = 24 / 64 / 128:
+// 80 / 97 / 151 us; with one block adding all the sums of a tile and all first loads at once 84 / 106 / 183.
 #pragma once
 #include "any4_device.h"
 #include "any4_internal.h"
