@@ -98,54 +98,6 @@ struct Params {
     int sc_stride;                   // Shape::sc_stride of the largest slab
 };
 
-// Slabs of a tile meet at a word: arrivals (8 bits), the parts whose owners have left (8 bits), a bit that every completed
-// meeting turns over, a tag.  The sums of a tile are `parts` parts; part k belongs to slab k.  A slab that has brought its sums waits a
-// while for the others; if all have come it adds its part of all slabs, otherwise it leaves, and the last slab to come adds the parts
-// of those that have left.  So blocks that end together share the adding, and nobody depends on anybody who may not be running.  Returns
-// the parts (bits) that the block is to add.  By one thread, after the block's sums are out.
-//
-// The last to arrive puts the word back for the next meeting; the bit then tells those who still look at it.  A word that is not
-// of this kind (memory used for the first time, or for something else) counts as no arrivals, as in any4_splitk.h.  (One that a launch
-// which never finished has left with parts marked only has a part added twice.)
-//
-// One block adding all the sums of a tile took 8 - 12 000 cycles (a compute unit reads 20 - 26 bytes a cycle of what others wrote; 256 KB of
-// eight slabs at 64 rows of x, 1 MB at 128): 4096 x 4096 at M = 64 / 128 18.5 / 34.2 -> 16.4 / 24.3 us, 4096 x 14336 29.0 / 54.2 -> 26.5 / 39.2.
-// (the words of blocks that look at them lie in cache lines of their own: packed, a sum took up to 11 000 cycles more to get out, and
-// an arrival as many, however seldom the blocks looked)
-constexpr int kWordBytes = 64;
-constexpr int kMaxParts = 8, kLooks = 10;                      // looks: about 0.4 us each
-__device__ __forceinline__ uint32_t meet(unsigned long long* word, int slabs, int parts, int slab) {
-    constexpr unsigned long long kTag = 0x24B47C5EED17ull << 17, kTurn = 1ull << 16, kCount = 0xFFull;
-    const unsigned long long all = (unsigned long long)slabs;
-    auto own = [&](unsigned long long v) -> bool { return (v >> 17) == (kTag >> 17) && (v & kCount) < all; };
-    unsigned long long old = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (!own(old)) {
-        // the add above went into a foreign word and is dropped with it
-        unsigned long long seen = old + 1ull;
-        for (;;) {
-            old = own(seen) ? seen : kTag;
-            if (__hip_atomic_compare_exchange_strong(word, &seen, old + 1ull, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-        }
-    }
-    const uint32_t bit = slab < parts ? 1u << slab : 0u;       // this slab's part
-    if ((old & kCount) + 1ull == all) {
-        __hip_atomic_store(word, kTag | (~old & kTurn), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return parts == 1 ? 1u : bit | ((uint32_t)(old >> 8) & 0xFFu);
-    }
-    if (parts == 1 || bit == 0u) return 0u;
-    auto complete = [&](unsigned long long v) -> bool { return ((v ^ old) & kTurn) != 0ull || (v & kCount) == all; };
-    for (int look = 0; look < kLooks; ++look) {
-        if (complete(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) return bit;
-        __builtin_amdgcn_s_sleep(8);
-    }
-    const unsigned long long mark = (unsigned long long)bit << 8;
-    const unsigned long long left = __hip_atomic_fetch_or(word, mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (!complete(left)) return 0u;
-    // the last came in between and counts on this slab; its mark comes off the word where it went into the next meeting's
-    if ((left ^ old) & kTurn) __hip_atomic_fetch_and(word, ~mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return bit;
-}
-
 template <int BITS, int MT, int WN, bool F16, bool FINE>
 __device__ __forceinline__ void batch_body(const Params& p) {
     using S = Shape<MT, WN>;

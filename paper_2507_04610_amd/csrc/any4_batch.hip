@@ -104,7 +104,7 @@ BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
             pl.counter_bytes = pl.sums_at = splitk_counter_bytes(pl.tiles_n);
             pl.shared = share(pl.tiles_n, pl.slabs);
             if (pl.shared) {                                   // words in lines of their own, in the room of one more slab
-                pl.counter_bytes = ((size_t)pl.tiles_n * batch::kWordBytes + 255) / 256 * 256;
+                pl.counter_bytes = ((size_t)pl.tiles_n * kWordBytes + 255) / 256 * 256;
                 pl.sums_at += (size_t)pl.tiles_n * tile_bytes;
             }
             pl.workspace = pl.sums_at + sums;
@@ -121,8 +121,8 @@ hipError_t launch_batch(const uint16_t* x, const uint32_t* codes, const uint16_t
     batch::Params p{};
     p.x = x;
     p.words = static_cast<unsigned long long*>(workspace);
-    p.word_step = pl.shared ? batch::kWordBytes / 8 : 1;
-    p.parts = pl.shared ? (pl.slabs < batch::kMaxParts ? pl.slabs : batch::kMaxParts) : 1;
+    p.word_step = pl.shared ? kWordBytes / 8 : 1;
+    p.parts = pl.shared ? (pl.slabs < kMaxParts ? pl.slabs : kMaxParts) : 1;
     p.partial = pl.slabs > 1 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + pl.sums_at) : nullptr;
     p.K = K; p.ldy = N; p.M = (int)M; p.G = (int)(K / kGroup);
     p.lr = fine ? 0 : lr;

@@ -90,7 +90,7 @@ template <bool F16>
 __global__ __launch_bounds__(256) void group_sums_kernel(const uint16_t* __restrict__ x, int64_t M,
                                                          int64_t K, int KP, int fine, uint16_t* __restrict__ xs,
                                                          unsigned long long* __restrict__ counters, int ncounters, int word_step) {
-    for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < ncounters; c += (int64_t)gridDim.x * 256) counters[c * word_step] = 0ull;
+    for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < ncounters; c += (int64_t)gridDim.x * 256) counters[c * word_step] = word_step > 1 ? kMeetTag : 0ull;
     const int lanes = fine ? 8 : 16;
     const int64_t G = K / (8 * lanes);
     const int64_t unit = ((int64_t)blockIdx.x * 256 + threadIdx.x) / lanes;  // (m, g), g fastest
@@ -576,21 +576,23 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
         }
         return;
     }
-    // ---- a K slice: its fp32 sums go to the workspace, where those of all slices are added.  The four 32 x 32 tiles of the
-    //      wavefronts are four parts (two of two slices), which the last slice to arrive with one adds up, and the slices bring the parts in
-    //      different orders: blocks that end together then share the adding.  Done by the last block alone it took 22 000 cycles for four
-    //      slices, nearly as long as their loop over K at K = 4096 (a compute unit reads 17 - 20 bytes a cycle of what others wrote):
-    //      4096 x 4096 at M = 512 37.8 -> 32.0 us, at M = 200 (eight slices) 37.0 -> 30.0.  A part costs a trip to memory: two
-    //      slices in four parts took 777 x 2944 x 2944 34.3 -> 34.8 us, in two 33.7.
+    // ---- a K slice: its fp32 sums go to the workspace, where those of all slices are added.  Done by the last block alone that took
+    //      22 000 cycles for four slices, nearly as long as their loop over K at K = 4096 (a compute unit reads 17 - 20 bytes a cycle of
+    //      what others wrote).  Where the words have cache lines of their own (not with groups of 64) the slices meet and share the adding (any4_splitk.h).
+    //      Otherwise the four 32 x 32 tiles of the wavefronts are four parts (two of two slices), which the last slice to arrive with one adds up, and
+    //      the slices bring the parts in different orders, so that blocks that end together share the adding too; a part costs a trip to memory.
+    //      Parts by the last to bring them -> a meeting, us: 4096 x 4096 at M = 200 (eight slices) 30.1 -> 28.0, at M = 512 (four) 38.7 -> 38.0, 6144 x 4096
+    //      at M = 512 (two) 48.7 -> 47.2, 1000 x 4096 at M = 777 35.6 -> 29.7.
     float* const all = partial + (int64_t)(tile - tail_first) * tail_s * (PBM * PBN);
     const __amdgpu_buffer_rsrc_t ares = __builtin_amdgcn_make_buffer_rsrc(all, 0, tail_s * (PBM * PBN) * 4, 0x00020000);
     auto quad = [&](int part, int v4) -> uint32_t { return (uint32_t)((((part * 4 + v4) * 8 + wave) * 64 + lane) * 16); };   // 16 bytes: four elements
     constexpr int kAgent = 16;                                 // cache policy: coherent over the whole device
-    // (a word per tile, word_step words apart, with a count of 16 bits per part, 0 at first: group_sums_kernel)
+    // (a word per tile, word_step words apart, set by group_sums_kernel; without a meeting a count of 16 bits per part)
     unsigned long long* const word = counters + (tile - tail_first) * word_step;
     unsigned long long before = 0;
     auto arrive = [&](int part) { before = __hip_atomic_fetch_add(word, 1ull << (16 * part), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> (16 * part); };
-    const int sh = tail_s == 2 ? 1 : 0, parts = 4 >> sh;       // part p: tiles p << sh ..
+    const bool shared = word_step > 1;
+    const int sh = shared ? 2 : tail_s == 2 ? 1 : 0, parts = 4 >> sh;    // part p: tiles p << sh ..
 #pragma unroll 1
     for (int r = 0; r < parts; ++r) {
         // (the arrival with the part before: its trip to memory goes with that of this part's stores)
@@ -613,14 +615,26 @@ __global__ __launch_bounds__(PTHREADS, 1) void prefill_kernel(
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this thread's sums are out
         lds_barrier();                                         // ... and so are the whole block's
     }
-    if (tid == (parts - 1) * 64) arrive((parts - 1 + slice) & (parts - 1));
-    if (lane == 0 && wave < parts) *reinterpret_cast<lds_u32>((uint32_t)((wave + slice) & (parts - 1)) * 4u) = (before & 0xFFFFull) == (unsigned long long)(tail_s - 1) ? 1u : 0u;
-    lds_barrier();
-    const u32x4 mine = *reinterpret_cast<lds_u4>(0u);          // the parts that this block was the last to bring
+    uint32_t todo = 0;                                         // the wavefront's 32 x 32 tiles (bits) that it is to add up
+    if (shared) {
+        // the tiles of all wavefronts, numbered wavefront by wavefront, are as many parts as there are slices
+        if (tid == 0) *reinterpret_cast<lds_u32>(0u) = meet(word, tail_s, tail_s, slice);
+        lds_barrier();
+        const uint32_t mine = __builtin_amdgcn_readfirstlane(*reinterpret_cast<lds_u32>(0u));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) todo |= (mine >> (((k * 8 + wave) * tail_s) >> 5) & 1u) << k;
+    } else {
+        if (tid == (parts - 1) * 64) arrive((parts - 1 + slice) & (parts - 1));
+        if (lane == 0 && wave < parts) *reinterpret_cast<lds_u32>((uint32_t)((wave + slice) & (parts - 1)) * 4u) = (before & 0xFFFFull) == (unsigned long long)(tail_s - 1) ? 1u : 0u;
+        lds_barrier();
+        const u32x4 mine = *reinterpret_cast<lds_u4>(0u);      // the parts that this block was the last to bring
+#pragma unroll
+        for (int k = 0; k < 4; ++k) todo |= __builtin_amdgcn_readfirstlane(sh ? mine[k >> 1] : mine[k]) << k;
+    }
     lds_barrier();                                             // (the outputs go over it)
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        if (__builtin_amdgcn_readfirstlane(sh ? mine[k >> 1] : mine[k]) == 0u) continue;
+        if (!(todo >> k & 1u)) continue;
         f32x16 sum = zero;
         constexpr int FLIGHT = 4;                              // slices whose loads are in flight together
         for (int sl = 0; sl < tail_s; sl += FLIGHT) {

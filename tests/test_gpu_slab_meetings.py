@@ -1,4 +1,4 @@
-"""Where the K slabs of 17 .. 128 rows of x meet: the blocks of a tile share the adding, wait for each other for a while
+"""Where the K slabs of 17 .. 128 rows of x, and the K slices of more, meet: the blocks of a tile share the adding, wait for each other for a while
 and otherwise leave their part to the last.  Two to more than eight slabs, parts of unequal size, every tile height, whatever
 the workspace held, with another stream's work on the GPU that keeps some blocks from running at the same time: the bits of
 the first call every time, and the oracle's values."""
@@ -11,9 +11,10 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-TAG = 0x24B47C5EED17 << 17          # csrc/any4_batch.h
+TAG = 0x24B47C5EED17 << 17          # csrc/any4_splitk.h
 CASES = ((17, 200, 2048), (32, 1100, 4096), (48, 4096, 4096), (64, 6144, 4096), (64, 5003, 8192), (40, 300, 14336), (90, 700, 2944),
-         (96, 4096, 14336), (65, 2000, 5120), (128, 3000, 4096), (128, 6144, 4096), (113, 257, 8192))
+         (96, 4096, 14336), (65, 2000, 5120), (128, 3000, 4096), (128, 6144, 4096), (113, 257, 8192),
+         (129, 512, 4096), (200, 4096, 4096), (300, 1000, 2944), (512, 6144, 4096), (777, 2900, 2944), (1030, 700, 2048))
 
 
 def dev_bf16(a_u16):
@@ -27,7 +28,7 @@ def test_meetings(oracle, M, N, K):
     cs = inputs.make_case(M, N, K, 4, seed=M + N % 89)
     packed = oracle.pack(cs.codes_u8, 4)
     need = any4.any4_gemm_workspace_bytes(M, N, K, 4)
-    rows, bn = (M + 31) // 32 * 32, 128 if M <= 64 else 256
+    rows, bn = ((M + 31) // 32 * 32, 128 if M <= 64 else 256) if M <= 128 else (256, 128)
     assert need > rows * bn * 4 * 2, "these problems are cut along K"
     x, codes = dev_bf16(cs.x), torch.from_numpy(packed.view(np.int32)).cuda()
     lut, sc, of = dev_bf16(cs.lut), dev_bf16(cs.scale), dev_bf16(cs.offset)
