@@ -890,12 +890,12 @@ StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, int cus) {
     const int64_t tiles = (N + stream::kTile - 1) / stream::kTile;
     if (M > stream::kTile || tiles > 0x7FFFFFFF) return best;
     double best_cost = 1e300;
-    const bool aux = G >= 4;
     for (int gw : {4, 2, 1}) {
         const int slab_max = stream::kWaves * gw;
         int slabs = (G + slab_max - 1) / slab_max;
-        // equal slabs, each a multiple of gw groups (of 4 groups in AUX mode), except possibly the last
-        const int unit = aux ? 4 : gw;
+        // equal slabs, each a multiple of gw groups (of 4 where K / 128 is one), except possibly the last.  (Whole fours for any
+        // K / 128 had K = 640 .. 1792 done by wavefronts of four groups, half of them or fewer with any: 20685 x 640, any3, at M = 8 14.5 us, so 7.7.)
+        const int unit = G % 4 == 0 ? 4 : gw;
         const int sgroups = ((G + slabs - 1) / slabs + unit - 1) / unit * unit;
         if (sgroups > slab_max) continue;
         slabs = (G + sgroups - 1) / sgroups;
@@ -905,8 +905,10 @@ StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, int cus) {
         if (bps > tiles) bps = (int)tiles;
         const int64_t tpb = (tiles + bps - 1) / bps;
         // microseconds: streaming of the block's bytes at ~22 GB/s per compute unit, per-tile
-        // table build and barrier, and the end-of-kernel combination of slabs
-        const double cost = (double)tpb * sgroups * 0.047 + (double)tpb * 0.15 + (slabs > 1 ? 3.0 : 0.0);
+        // table build and barrier, and the end-of-kernel combination of slabs (K / 128 no multiple of 4: more for
+        // each beyond three; without that wavefronts of two groups were taken for four, 19417 x 12544 at M = 12 in 7 slabs 54 us, in 4 40)
+        double cost = (double)tpb * sgroups * 0.047 + (double)tpb * 0.15 + (slabs > 1 ? 3.0 : 0.0);
+        if (G % 4 != 0 && slabs > 3) cost += 0.3 * (slabs - 3);
         if (cost < best_cost) {
             best_cost = cost;
             best.gw = gw;
@@ -914,9 +916,14 @@ StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, int cus) {
             best.slab_groups = sgroups;
             best.blocks_per_slab = bps;
             best.tiles = tiles;
-            best.aux = aux;
+            // K / 128 no multiple of 4: wavefronts of one or two groups read their own few scales faster than one of them brings
+            // all and moves them down, once the block's start no longer counts.  Shared, time by tiles of a block: two groups 0.93
+            // (one or two tiles), 0.96 (three, four), 0.98 - 1.15 (five .. 25); one group 0.98 (one tile), 1.00 - 1.07; four 0.74 - 0.94 always.
+            best.aux = G % 4 == 0 || (G > 4 && (gw == 4 || tpb <= (gw == 2 ? 4 : 1)));
         }
     }
+    // (shared, slabs begin at a multiple of four groups; there are as many as before, 8 gw being one)
+    if (best.aux && best.slabs > 1) best.slab_groups = (best.slab_groups + 3) & ~3;
     best.workspace = best.slabs > 1
         ? splitk_counter_bytes(best.tiles) + (size_t)best.slabs * (size_t)M * (size_t)N * sizeof(float) : 0;
     return best;

@@ -14,7 +14,7 @@ struct StreamPlan {
     int slab_groups;      // groups per slab
     int blocks_per_slab;
     int64_t tiles;        // 16-row tiles
-    bool aux;             // tables, scales and offsets are shared through LDS (four groups and more)
+    bool aux;             // tables, scales and offsets are shared through LDS (not for fewer than four groups)
     size_t workspace;     // bytes: tile counters + fp32 partial sums (several slabs only)
 };
 StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, int cus);

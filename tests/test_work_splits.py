@@ -1,0 +1,47 @@
+"""Which split of the work the host code picks, where a wrong one costs time without making a result wrong.  The plans are pure
+functions of the problem and of the number of compute units."""
+import ctypes
+
+import pytest
+
+from paper_2507_04610_amd import binding
+
+CUS = 256
+
+
+class StreamPlan(ctypes.Structure):          # csrc/any4_internal.h
+    _fields_ = [("gw", ctypes.c_int), ("slabs", ctypes.c_int), ("slab_groups", ctypes.c_int), ("blocks_per_slab", ctypes.c_int),
+                ("tiles", ctypes.c_int64), ("aux", ctypes.c_bool), ("workspace", ctypes.c_size_t)]
+
+
+def plan_stream(M, N, K):
+    f = binding.load_library()._ZN4any411plan_streamEllli          # any4::plan_stream(int64_t, int64_t, int64_t, int)
+    f.restype, f.argtypes = StreamPlan, [ctypes.c_int64] * 3 + [ctypes.c_int]
+    return f(M, N, K, CUS)
+
+
+@pytest.mark.parametrize("M", (1, 8, 16))
+@pytest.mark.parametrize("N", (40, 1000, 4096, 20685, 40000))
+def test_no_wavefront_goes_through_groups_that_the_row_does_not_have(M, N):
+    """up to 4096 weights a row the eight wavefronts have all of it between them, and a block goes through the row's groups rounded up to
+    those of a wavefront of one, two or four, whichever is least (K = 640: five, not eight)"""
+    for G in range(1, 33):
+        p = plan_stream(M, N, 128 * G)
+        least = min(-(-G // gw) * gw for gw in (1, 2, 4) if 8 * gw >= G)
+        assert p.slabs == 1 and 8 * p.gw >= G
+        assert p.slab_groups == least and p.slab_groups - G < p.gw, (G, p.gw, p.slab_groups)
+
+
+@pytest.mark.parametrize("G", (5, 6, 7, 9, 10, 13, 14, 33, 34, 41, 42, 98, 101))
+def test_who_loads_the_small_inputs(G):
+    """shared: always for wavefronts of four groups, for others only while a block has few tiles; slabs then begin at whole fours"""
+    for N in (16, 600, 2000, 4096, 4112, 9000, 16384, 16400, 31443):
+        p = plan_stream(8, N, 128 * G)
+        tpb = -(-p.tiles // p.blocks_per_slab)
+        assert p.aux == (p.gw == 4 or tpb <= {1: 1, 2: 4}[p.gw]), (N, p.gw, tpb)
+        if p.aux and p.slabs > 1:
+            assert p.slab_groups % 4 == 0 and p.slab_groups <= 8 * p.gw
+        assert (p.slabs - 1) * p.slab_groups < G <= p.slabs * p.slab_groups
+    for rest in (1, 2, 3):
+        assert not plan_stream(8, 600, 128 * rest).aux
+    assert all(plan_stream(8, n, 128 * g).aux for n in (16, 40000) for g in (4, 8, 20, 32, 36, 100))
