@@ -48,7 +48,7 @@
 // four groups and more).  Where K/128 is no multiple of 4 its 8-byte loads are aligned to 2 bytes only, and the last
 // one of a row starts early, so that it ends with the row, and is moved down in registers: 5003 x 2944 at M = 1 / 8 / 16 takes
 // 7.3 / 8.2 / 9.7 us, with every wavefront reading its own scales one by one 9.7 / 10.3 / 11.2; 28672 x 4224 at M = 1 26.6, 33.4.
-// (The moving costs rows that need none 0 - 0.1 us a launch.)
+// Rows that need no moving have variants without it (it cost them 0.03 us a launch, 0.3 - 0.5 %).
 //
 // 3- and 2-bit codes (the "anyn" variants of section 4.1) use the same kernel.  A lane's quarter of a
 // group is 12 or 8 bytes instead of 16.  any3: a pair of codes is a 6-bit field of the lane's 96-bit
@@ -153,7 +153,8 @@ __device__ __forceinline__ float sum8(const uint4& v) {
 //         when the wavefronts' partial sums are.
 // F16     activations, table, scales, offsets and output are fp16 instead of bf16 (the f16 matrix
 //         instruction; everything else moves 16-bit patterns and does not care)
-template <int BITS, int GW, bool AUX, bool NOLUT, bool REPACK, bool COARSE, bool FINE, bool F16>
+// MOVE    AUX with K/128 no multiple of 4: the last loads of a row start early and are moved down
+template <int BITS, int GW, bool AUX, bool NOLUT, bool REPACK, bool COARSE, bool FINE, bool F16, bool MOVE>
 __global__ __launch_bounds__(kWaves * 64, 1) void decode_stream_kernel(const Params p) {
     static_assert(!F16 || (!NOLUT && !REPACK && !COARSE && !FINE), "fp16: table-based, plain layout, groups of 128");
     static_assert(!COARSE || (!NOLUT && !REPACK), "groups above 128 weights: table-based, plain layout");
@@ -320,32 +321,35 @@ __global__ __launch_bounds__(kWaves * 64, 1) void decode_stream_kernel(const Par
     u32x4 fxs0 = {0, 0, 0, 0}, fxs1 = {0, 0, 0, 0}, fxo0 = {0, 0, 0, 0}, fxo1 = {0, 0, 0, 0};
     uint4 axl;
     // A lane's four groups are those from aux_chunk(c) of the slab on.  Lanes past the slab's groups repeat its last
-    // four, so that all loads are unconditional.  What it loads starts at group aux_first[c] of the row: the same one unless
-    // K / 128 is no multiple of 4 and the row has fewer than four left; its last four are then loaded and moved down when the slot is
-    // written, zeros in the place of groups that are not there.
-    auto aux_chunk = [&](int c) -> int { return min((c * 4 + q) * 4, (sg - 1) & ~3); };
-    const int aux_first[2] = {min(gs0 + aux_chunk(0), G - 4), min(gs0 + aux_chunk(1), G - 4)};
-    const int aux_by[2] = {gs0 + aux_chunk(0) - aux_first[0], gs0 + aux_chunk(1) - aux_first[1]};    // 0 .. 3 groups
+    // four, so that all loads are unconditional.  MOVE: what a lane loads starts at group aux_first(c) of the row, the same one unless the
+    // row has fewer than four left; its last four are then loaded and moved down when the slot is written, zeros in the place of
+    // groups that are not there.  (Without MOVE aux_first counts from the slab's first group.)
+    auto aux_chunk = [&](int c) -> int { return min((c * 4 + q) * 4, MOVE ? (sg - 1) & ~3 : max(sg, 4) - 4); };
+    auto aux_first = [&](int c) -> int { return MOVE ? min(gs0 + aux_chunk(c), G - 4) : aux_chunk(c); };
+    const int aux_by[2] = {MOVE ? gs0 + aux_chunk(0) - aux_first(0) : 0, MOVE ? gs0 + aux_chunk(1) - aux_first(1) : 0};    // 0 .. 3 groups
+    const int aux_from = MOVE ? 0 : gs0;
     auto aux_load = [&](int t) {
         if constexpr (FINE) {
             // two entries per chunk of 128: lane (n, j) loads those of chunks 4j .. 4j+3 and 16 + 4j .. + 3
-            typedef u32x4 u32x4_at4 __attribute__((aligned(4)));
-            const int64_t tile_off = (int64_t)t * (kTile * 2) * GS;
+            typedef u32x4 at4 __attribute__((aligned(4)));
+            using entries4 = std::conditional_t<MOVE, at4, u32x4>;
+            const int64_t tile_off = (int64_t)t * (kTile * 2) * GS + aux_from * 4;
             const uint32_t vs = t == last_tile ? vs_last : vs_norm;
-            const uint32_t go0 = (uint32_t)aux_first[0] * 4u, go1 = (uint32_t)aux_first[1] * 4u;
-            fxs0 = *reinterpret_cast<const u32x4_at4*>(scale_b + tile_off + vs + go0);
-            fxo0 = *reinterpret_cast<const u32x4_at4*>(offset_b + tile_off + vs + go0);
-            fxs1 = *reinterpret_cast<const u32x4_at4*>(scale_b + tile_off + vs + go1);
-            fxo1 = *reinterpret_cast<const u32x4_at4*>(offset_b + tile_off + vs + go1);
+            const uint32_t go0 = (uint32_t)aux_first(0) * 4u, go1 = (uint32_t)aux_first(1) * 4u;
+            fxs0 = *reinterpret_cast<const entries4*>(scale_b + tile_off + vs + go0);
+            fxo0 = *reinterpret_cast<const entries4*>(offset_b + tile_off + vs + go0);
+            fxs1 = *reinterpret_cast<const entries4*>(scale_b + tile_off + vs + go1);
+            fxo1 = *reinterpret_cast<const entries4*>(offset_b + tile_off + vs + go1);
         } else if constexpr (!COARSE) {
-            typedef u32x2 u32x2_at2 __attribute__((aligned(2)));
-            const int64_t tile_off = (int64_t)t * (kTile * 2) * G;
+            typedef u32x2 at2 __attribute__((aligned(2)));
+            using entries2 = std::conditional_t<MOVE, at2, u32x2>;
+            const int64_t tile_off = (int64_t)t * (kTile * 2) * G + aux_from * 2;
             const uint32_t vs = t == last_tile ? vs_last : vs_norm;
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
-                const uint32_t go = (uint32_t)aux_first[c] * 2u;
-                axs[c] = *reinterpret_cast<const u32x2_at2*>(scale_b + tile_off + vs + go);
-                axo[c] = *reinterpret_cast<const u32x2_at2*>(offset_b + tile_off + vs + go);
+                const uint32_t go = (uint32_t)aux_first(c) * 2u;
+                axs[c] = *reinterpret_cast<const entries2*>(scale_b + tile_off + vs + go);
+                axo[c] = *reinterpret_cast<const entries2*>(offset_b + tile_off + vs + go);
             }
         } else {
             // groups of 256 weights and more: chunks 4j, 4j + 1 share a scale and so do 4j + 2, 4j + 3
@@ -357,7 +361,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void decode_stream_kernel(const Par
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
                 const int g0 = gs0 + aux_chunk(c);
-                const uint32_t i0 = (uint32_t)(g0 >> lr) * 2u, i1 = (uint32_t)min((g0 + 2) >> lr, GS - 1) * 2u;
+                const uint32_t i0 = (uint32_t)(g0 >> lr) * 2u, i1 = (uint32_t)(MOVE ? min((g0 + 2) >> lr, GS - 1) : (g0 + 2) >> lr) * 2u;
                 axs[c][0] = *reinterpret_cast<const uint16_t*>(scale_b + tile_off + v + i0);
                 axs[c][1] = *reinterpret_cast<const uint16_t*>(scale_b + tile_off + v + i1);
                 axo[c][0] = *reinterpret_cast<const uint16_t*>(offset_b + tile_off + v + i0);
@@ -380,6 +384,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void decode_stream_kernel(const Par
             const int by = aux_by[c];
             if constexpr (FINE) {
                 auto down = [&](u32x4 v) -> u32x4 {
+                    if constexpr (!MOVE) return v;
                     if (by & 1) v = u32x4{v[1], v[2], v[3], 0u};
                     if (by & 2) v = u32x4{v[2], v[3], 0u, 0u};
                     return v;
@@ -391,9 +396,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void decode_stream_kernel(const Par
             } else {
                 auto four = [&](const u32x2& v) -> unsigned long long {
                     if constexpr (COARSE) {
-                        const bool both = gs0 + aux_chunk(c) + 2 < G;
+                        const bool both = !MOVE || gs0 + aux_chunk(c) + 2 < G;
                         return (v[0] | (v[0] << 16)) | (both ? (unsigned long long)(v[1] | (v[1] << 16)) << 32 : 0ull);
-                    } else return __builtin_bit_cast(unsigned long long, v) >> (16 * by);
+                    } else return __builtin_bit_cast(unsigned long long, v) >> (MOVE ? 16 * by : 0);
                 };
                 if (in_slab) {
                     *reinterpret_cast<unsigned long long*>(s + kAuxScale + n * kAuxRow + (c * 4 + q) * 8) = four(axs[c]);
@@ -930,9 +935,9 @@ StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, int cus) {
 }
 
 template <int BITS, int GW, bool AUX, bool NOLUT = false, bool REPACK = false, bool COARSE = false, bool FINE = false,
-          bool F16 = false>
+          bool F16 = false, bool MOVE = false>
 static hipError_t launch_stream_t(const Params& p, int grid, hipStream_t stream) {
-    constexpr auto kern = stream::decode_stream_kernel<BITS, GW, AUX, NOLUT, REPACK, COARSE, FINE, F16>;
+    constexpr auto kern = stream::decode_stream_kernel<BITS, GW, AUX, NOLUT, REPACK, COARSE, FINE, F16, MOVE>;
     constexpr int lds = stream::lds_bytes(BITS, FINE && AUX);
     if (hipError_t e = ensure_lds<kern>(lds); e != hipSuccess) return e;
     if (grid != p.blocks_per_slab * p.slabs) return hipErrorInvalidValue;
@@ -945,20 +950,24 @@ static hipError_t launch_stream_t(const Params& p, int grid, hipStream_t stream)
 template <int BITS, bool NOLUT, bool REPACK, bool COARSE, bool FINE, bool F16>
 static hipError_t launch_stream_gw(const Params& p, const StreamPlan& sp, int grid, hipStream_t stream) {
     constexpr bool SHARE = !(FINE && BITS == 2);
+    auto go = [&](auto gw, auto share, auto move) -> hipError_t {
+        return launch_stream_t<BITS, decltype(gw)::value, decltype(share)::value, NOLUT, REPACK, COARSE, FINE, F16, decltype(move)::value>(p, grid, stream);
+    };
+    constexpr std::integral_constant<int, 4> four{};
+    constexpr std::integral_constant<int, 2> two{};
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
     if constexpr (SHARE) {
         if (sp.aux) {
-            switch (sp.gw) {
-                case 4: return launch_stream_t<BITS, 4, true, NOLUT, REPACK, COARSE, FINE, F16>(p, grid, stream);
-                case 2: return launch_stream_t<BITS, 2, true, NOLUT, REPACK, COARSE, FINE, F16>(p, grid, stream);
-                default: return launch_stream_t<BITS, 1, true, NOLUT, REPACK, COARSE, FINE, F16>(p, grid, stream);
-            }
+            if (p.G % 4 == 0) return sp.gw == 4 ? go(four, yes, no) : sp.gw == 2 ? go(two, yes, no) : go(one, yes, no);
+            return sp.gw == 4 ? go(four, yes, yes) : sp.gw == 2 ? go(two, yes, yes) : go(one, yes, yes);
         }
         if (sp.gw > 2) return hipErrorInvalidValue;
     } else {
-        if (sp.gw == 4) return launch_stream_t<BITS, 4, false, NOLUT, REPACK, COARSE, FINE, F16>(p, grid, stream);
+        if (sp.gw == 4) return go(four, no, no);
     }
-    if (sp.gw == 2) return launch_stream_t<BITS, 2, false, NOLUT, REPACK, COARSE, FINE, F16>(p, grid, stream);
-    return launch_stream_t<BITS, 1, false, NOLUT, REPACK, COARSE, FINE, F16>(p, grid, stream);
+    return sp.gw == 2 ? go(two, no, no) : go(one, no, no);
 }
 template <bool REPACK, bool COARSE, bool FINE, bool F16>
 static hipError_t launch_stream_bits(int bits, const Params& p, const StreamPlan& sp, int grid, hipStream_t stream) {

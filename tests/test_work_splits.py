@@ -1,6 +1,7 @@
 """Which split of the work the host code picks, where a wrong one costs time without making a result wrong.  The plans are pure
 functions of the problem and of the number of compute units."""
 import ctypes
+import re
 
 import pytest
 
@@ -45,3 +46,11 @@ def test_who_loads_the_small_inputs(G):
     for rest in (1, 2, 3):
         assert not plan_stream(8, 600, 128 * rest).aux
     assert all(plan_stream(8, n, 128 * g).aux for n in (16, 40000) for g in (4, 8, 20, 32, 36, 100))
+
+
+def test_rows_that_need_no_moving_have_kernels_without_it():
+    """every variant that moves the last small inputs of a row down has one that does not, for K / 128 a multiple of 4"""
+    names = {tuple(m) for m in re.findall(rb"decode_stream_kernelILi(\d)ELi(\d)ELb(\d)((?:ELb\d){5})ELb(\d)EEE", open(binding.LIB_PATH, "rb").read())}
+    moving = {n for n in names if n[4] == b"1"}
+    assert moving and all(n[2] == b"1" for n in moving)            # only where one wavefront loads for all
+    assert {n[:4] + (b"0",) for n in moving} <= names
