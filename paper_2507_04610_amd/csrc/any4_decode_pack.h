@@ -127,6 +127,8 @@ __device__ __forceinline__ uint32_t bf16_rne_finite(float f) {
 // REPACK  codes in the tile-major layout of any4_repack
 // ANY     a number of groups that is no multiple of 8: rows of scales and offsets start at any 2 bytes, and the row's last
 //         unit of groups, and piece of scales, may be there in part
+//         (what it needs stays out of the others: written so that both used one expression for row length, piece and loop, multiples of 8 took
+//         0.03 - 0.08 us longer a launch)
 template <int BITS, int MP, int PASSES, bool REPACK, bool ANY>
 __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void decode_pack_kernel(const Params p) {
     static_assert(BITS == 4 || BITS == 3 || BITS == 2, "code width");
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
 
     const int M = p.M, G = p.G;
     const int64_t N = p.N, K = p.K;
-    const int aux_row = aux_row_bytes(G), slot_size = slot_bytes(G);
+    const int aux_row = ANY ? aux_row_bytes(G) : G * 2 + 8, slot_size = 2 * kTile * aux_row + kTile * 32;
     // groups of this wavefront.  In a unit of 4 groups that it has in part the row's last group stands in for those it
     // does not have, which meet zero activations, scales and offsets.
     const int ngw = max(0, min(GPW, G - w * GPW)), ngw4 = max(ANY ? (ngw + 3) & ~3 : ngw, 4);
@@ -188,9 +190,9 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
     struct Quarter { uint32_t w[QW]; };
     Quarter cw[2][4];
     // (The scalar offset names the tile and the unit, the group inside the unit is a constant that the load
-    // instruction carries itself; the range check would not see an offset past the row's end.  A load that is not wanted - a unit the wavefront does not have, a tile past the block's last - gets a lane offset
-    // beyond the end of the descriptor: the hardware's range check then returns zeros without touching
-    // memory, and the instruction stream stays free of branches.)
+    // instruction carries itself; the range check would not see an offset past the row's end.  A load that is not wanted -
+    // a unit the wavefront does not have, a tile past the block's last - gets a lane offset beyond the end of the descriptor:
+    // the hardware's range check then returns zeros without touching memory, and the instruction stream stays free of branches.)
     constexpr uint32_t kGroupStride = REPACK ? 64 * QB : GB;
     constexpr uint32_t kOutOfRange = 0x80000000u;        // every array is shorter than this
     const int nunits = (ANY ? ngw + 3 : ngw) / 4;
@@ -225,7 +227,6 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
     //      A row's last piece, where it has fewer than 8 groups, is loaded early, so that it ends with the row, and moved down when
     //      it is written, zeros behind it.
     struct Stage { u32x4 v[KI]; };
-    const int pieces = (ANY ? G + 7 : G) / 8;
     auto stage_load = [&](Stage& s, int li) {
         const int t = tile_of(li);
         const int r = (w - li) & (kWaves - 1);
@@ -235,10 +236,13 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
             const int j = min(jr, NI - 1);
             const bool is_lut = j == 2 * PASSES;
             const bool is_off = !is_lut && j >= PASSES;
+            const uint16_t* base = is_lut ? p.lut : (is_off ? p.offset : p.scale);
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0,
+                                                                                is_lut ? p.lut_bytes : p.so_bytes, kRsrcFlags);
             const uint32_t row = (uint32_t)t * kTile + row_in(t);
-            const int piece = (j - (is_off ? PASSES : 0)) * 4 + q;
-            uint32_t vo = row * (uint32_t)(G * 2) + (uint32_t)(ANY ? min(piece * 8, G - 8) : piece * 8) * 2u;
-            bool wanted = jr < NI && li < ntiles && piece < pieces;
+            const uint32_t piece = (uint32_t)((j - (is_off ? PASSES : 0)) * 4 + q);
+            uint32_t vo = row * (uint32_t)(G * 2) + (ANY ? (uint32_t)min((int)piece * 8, G - 8) * 2u : piece * 16u);
+            bool wanted = jr < NI && li < ntiles && piece < (uint32_t)((ANY ? G + 7 : G) / 8);
             if (is_lut) {
                 wanted = jr < NI && li < ntiles && q < (BITS == 4 ? 2 : 1) && !p.one_table;
                 if constexpr (BITS == 4) vo = row * 32u + (uint32_t)(q & 1) * 16u;
@@ -252,14 +256,9 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
                 typedef const __attribute__((address_space(1))) char* gptr;
                 auto scales = (gptr)p.scale, offsets = (gptr)p.offset, tables = (gptr)p.lut;
                 asm("" : "+s"(scales), "+s"(offsets), "+s"(tables));
-                const gptr base = is_lut && !p.one_table ? tables : (is_off ? offsets : scales);
-                s.v[k] = *(const __attribute__((address_space(1))) u32x4_at2*)(base + (wanted ? vo : 0u));
-            } else {
-                const uint16_t* base = is_lut ? p.lut : (is_off ? p.offset : p.scale);
-                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0,
-                                                                                    is_lut ? p.lut_bytes : p.so_bytes, kRsrcFlags);
-                s.v[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, wanted ? vo : kOutOfRange, 0, 0);
-            }
+                const gptr from = is_lut && !p.one_table ? tables : (is_off ? offsets : scales);
+                s.v[k] = *(const __attribute__((address_space(1))) u32x4_at2*)(from + (wanted ? vo : 0u));
+            } else s.v[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, wanted ? vo : kOutOfRange, 0, 0);
         }
     };
     auto stage_write = [&](const Stage& s, int li, int slot) {
@@ -267,11 +266,11 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
         const int t = tile_of(li);
         const int r = (w - li) & (kWaves - 1);
         unsigned char* const sb = slots + slot * slot_size;
-        static_for<KI>([&](auto k_) {
-            constexpr int k = decltype(k_)::value;
+#pragma unroll
+        for (int k = 0; k < KI; ++k) {
             const int j = r + kWaves * k;
+            if (j >= NI) continue;
             u32x4 v = s.v[k];
-            if (j >= NI) return;
             if (j == 2 * PASSES) {
                 unsigned char* dst = sb + 2 * kTile * aux_row + n * 32;
                 if constexpr (BITS == 4) { if (q < 2) *reinterpret_cast<u32x4*>(dst + q * 16) = v; }
@@ -293,12 +292,12 @@ __global__ __launch_bounds__(kThreads, waves_per_eu(BITS, MP, PASSES)) void deco
                     if (by & 4) v = u32x4{v[2], v[3], 0u, 0u};
                     if (by & 1) v = u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
                 }
-                if (piece < pieces) {                               // (rows are 8-byte aligned in the slot)
+                if (piece < (ANY ? G + 7 : G) / 8) {                // (rows are 8-byte aligned in the slot)
                     reinterpret_cast<uint2*>(dst)[0] = make_uint2(v[0], v[1]);
                     reinterpret_cast<uint2*>(dst)[1] = make_uint2(v[2], v[3]);
                 }
             }
-        });
+        }
     };
 
     // ---- table source of a tile.  The entries of a row are written by its 32 threads (w, q):
