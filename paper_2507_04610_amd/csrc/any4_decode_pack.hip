@@ -16,9 +16,20 @@ PackPlan plan_pack(int64_t M, int64_t N, int64_t K, int bits, bool one_table, in
     const int mp = M == 1 ? 1 : (M == 2 ? 2 : 4);
     const int passes = (int)((G + 4 * pack::kWaves - 1) / (4 * pack::kWaves));
     // K <= 4096 (one unit per wavefront and tile): nothing to gain over the streaming kernel, which needs no K
-    // slabs there either and is 5 - 10 % faster on such shapes.  Beyond it this kernel is faster from the first group on: 4096 x 4224
-    // at M = 1 6.7 us, by the streaming kernel 9.7, 28672 x 4224 19.9 and 26.6, 4096 x 14464 9.8 and 12.6.
+    // slabs there either and is 5 - 10 % faster on such shapes
     if (passes < 2) return pl;
+    // K no multiple of 1024.  One block has all of a tile's K, so with few tiles most of the chip idles through it, where the streaming
+    // kernel spreads its slabs: 195 x 28160 at M = 1 13.0 us, by the streaming kernel 8.3, 39 x 13952 at M = 2 9.4 and 6.8, 39 x 7424 at M = 4
+    // 7.2 and 6.1; but 4096 x 4224 at M = 1 6.7 and 9.1, 28672 x 4224 19.9 and 26.6, 4096 x 14464 9.8 and 12.6.  The line lies where the two met
+    // for each number of register sets (11 000 matrices of 16 .. 20000 rows, 0.4 % from the better of the two on average); any2, whose
+    // tables cost the streaming kernel more, stays longer.  Long rows whose second round of tiles is nearly empty are not taken either
+    // (4578 x 24064 22.9, 19.4).
+    if (G % 8 != 0) {
+        const int few = bits == 2 ? (mp == 1 ? (passes <= 4 ? 0 : cus * 3 / 16) : mp == 2 && passes > 2 ? cus / 4 : 0)
+                      : mp == 1 ? (passes == 2 ? 0 : passes <= 4 ? cus / 4 : cus / 2)
+                      : mp == 2 ? (passes == 2 ? cus / 16 : cus * 3 / 8) : cus / 4;
+        if (tiles <= few || (bits != 2 && passes >= 5 && tiles > cus && tiles <= cus * 5 / 4)) return pl;
+    }
     // the activations of a wavefront's groups must fit two register sets
     if (passes > 8 / mp) return pl;
     pl.mp = mp;

@@ -54,3 +54,34 @@ def test_rows_that_need_no_moving_have_kernels_without_it():
     moving = {n for n in names if n[4] == b"1"}
     assert moving and all(n[2] == b"1" for n in moving)            # only where one wavefront loads for all
     assert {n[:4] + (b"0",) for n in moving} <= names
+
+
+class PackPlan(ctypes.Structure):
+    _fields_ = [("ok", ctypes.c_bool), ("mp", ctypes.c_int), ("passes", ctypes.c_int), ("tiles", ctypes.c_int64), ("nblocks", ctypes.c_int)]
+
+
+def whole_k(M, N, K, bits):
+    f = binding.load_library()._ZN4any49plan_packElllibi            # any4::plan_pack(int64_t, int64_t, int64_t, int, bool, int)
+    f.restype, f.argtypes = PackPlan, [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.c_bool, ctypes.c_int]
+    return f(M, N, K, bits, False, CUS).ok
+
+
+@pytest.mark.parametrize("M,K,bits,tiles", ((1, 8320, 4, 64), (1, 16256, 3, 64), (1, 16512, 4, 128), (1, 28160, 4, 128), (2, 8064, 4, 16), (2, 13952, 3, 96),
+                                            (3, 7680, 4, 64), (4, 4224, 3, 64), (1, 16512, 2, 48), (2, 13952, 2, 64)))
+def test_few_tiles_are_not_given_a_whole_row_each(M, K, bits, tiles):
+    """K no multiple of 1024: with that many tiles of 16 rows the blocks of the whole-K kernel leave most of the chip idle"""
+    assert not whole_k(M, 16, K, bits) and not whole_k(M, 16 * tiles, K, bits)
+    assert whole_k(M, 16 * tiles + 1, K, bits) and whole_k(M, 4096, K, bits)
+    up = (K + 1023) // 1024 * 1024
+    assert whole_k(M, 16, up, bits) == whole_k(M, 4096, up, bits)  # (whole kilos as they were: whatever the number of tiles)
+
+
+@pytest.mark.parametrize("M,K,bits", ((1, 4224, 4), (1, 8064, 3), (1, 14464, 2), (2, 4224, 2), (4, 7680, 2)))
+def test_short_rows_have_one_block_each_from_the_first_tile_on(M, K, bits):
+    assert whole_k(M, 16, K, bits) and whole_k(M, 40000, K, bits)
+
+
+def test_a_second_round_that_is_nearly_empty():
+    """rows of more than 16384 weights and 257 .. 320 tiles: four compute units in five would wait for the others' second tile"""
+    assert not whole_k(1, 4578, 24064, 4) and not whole_k(1, 5120, 16512, 3)
+    assert whole_k(1, 4096, 24064, 4) and whole_k(1, 5121, 24064, 4) and whole_k(1, 4578, 12416, 4)
