@@ -13,6 +13,12 @@ template <int MT> constexpr int max_slab_values() {
 }
 constexpr int kMaxSlabValues[4] = {max_slab_values<1>(), max_slab_values<2>(), max_slab_values<3>(), max_slab_values<4>()};
 
+// The blocks of a tile share the adding of their slabs' sums where all blocks of a launch run at once and there is room for its words.
+static size_t tile_sum_bytes(int mt) { return (size_t)(32 * mt) * (32 * batch::wn_of(mt)) * sizeof(float); }
+static bool shares(int mt, int t, int s, int cus) {
+    return (int64_t)t * s <= cus && splitk_counter_bytes(t) + (size_t)t * (s + 1) * tile_sum_bytes(mt) <= (size_t)ANY4_NOALLOC_SCRATCH_BYTES;
+}
+
 // Time in us of a launch of t tiles with s slabs of G groups.  Per round of blocks: their start and end (more with the
 // chip full: `crowd`), four steps whose loads come with the start, and the rest, which take longer from a quarter of the chip
 // on; a round that fills the chip to the last compute unit took longer by `even`.  Where slabs meet and share the adding: a meeting, more
@@ -29,9 +35,9 @@ constexpr Cost kCost[4] = {{4.94, 0.49, 1.45, 1.24, 1.38, 0.11, 2.08, 0.93, 0.43
                            {6.94, 0.41, 1.98, 1.54, 1.82, 1.99, 3.10, 1.20, 0.19, 1.23, 0.59}, {6.79, 3.99, 2.38, 1.82, 2.06, 1.38, 3.46, 1.09, 0.09, 1.63, 0.39}};
 static double meet_us(int mt, int t, int s, int cus) {
     const Cost& c = kCost[mt - 1];
-    const double mb = ((double)t * s * (32 * mt) * (32 * batch::wn_of(mt))) * 4e-6;
+    const double mb = (double)t * s * (double)tile_sum_bytes(mt) * 1e-6;
     if (s == 1) return 0.0;
-    return (int64_t)t * s <= cus ? c.meeting + c.more * (double)((s - 1) / 8) + c.per_mb * mb : c.more_alone * (double)((s - 1) / 4) + c.per_mb_alone * mb;
+    return shares(mt, t, s, cus) ? c.meeting + c.more * (double)((s - 1) / 8) + c.per_mb * mb : c.more_alone * (double)((s - 1) / 4) + c.per_mb_alone * mb;
 }
 static double launch_us(int mt, int t, int s, int G, int cus) {
     const Cost& c = kCost[mt - 1];
@@ -57,11 +63,7 @@ BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
     if (K * bn >= ((int64_t)1 << 31) || K * 2 * rows >= ((int64_t)1 << 31) || (N + bn - 1) / bn > ((int64_t)1 << 24)) return both;
     const int G = (int)(K / kGroup), tiles = (int)((N + bn - 1) / bn), most = kMaxSlabValues[mt - 1];   // values per row in LDS
     const int first = (G + most - 1) / most, first_fine = (2 * G + most / 2 * 2 - 1) / (most / 2 * 2);
-    const size_t tile_bytes = (size_t)rows * bn * sizeof(float);
-    // The blocks of a tile share the adding where all blocks of a launch run at once and there is room for its words.
-    auto share = [&](int part, int s) -> bool {
-        return (int64_t)part * s <= cus && splitk_counter_bytes(part) + (size_t)part * (s + 1) * tile_bytes <= (size_t)ANY4_NOALLOC_SCRATCH_BYTES;
-    };
+    const size_t tile_bytes = tile_sum_bytes(mt);
     // (above 64 rows of x a matrix of up to 1024 x 1024 is not cut, so that its calls go on needing no workspace: 23 us at 128 rows, cut 14)
     const bool no_workspace = mt > 2 && N <= 1024 && K <= 1024;
     auto take = [&](BatchPlan& pl, int part, int s, double us) {
@@ -102,8 +104,9 @@ BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
         if (pl.slabs > 1) {
             const size_t sums = (size_t)pl.tiles_n * pl.slabs * tile_bytes;
             pl.counter_bytes = pl.sums_at = splitk_counter_bytes(pl.tiles_n);
-            pl.shared = share(pl.tiles_n, pl.slabs);
+            pl.shared = shares(mt, pl.tiles_n, pl.slabs, cus);
             if (pl.shared) {                                   // words in lines of their own, in the room of one more slab
+                // (64 bytes a tile would do; so the size stays one counter and whole slabs of sums per tile, as it has always been)
                 pl.counter_bytes = ((size_t)pl.tiles_n * kWordBytes + 255) / 256 * 256;
                 pl.sums_at += (size_t)pl.tiles_n * tile_bytes;
             }

@@ -85,3 +85,27 @@ def test_a_second_round_that_is_nearly_empty():
     """rows of more than 16384 weights and 257 .. 320 tiles: four compute units in five would wait for the others' second tile"""
     assert not whole_k(1, 4578, 24064, 4) and not whole_k(1, 5120, 16512, 3)
     assert whole_k(1, 4096, 24064, 4) and whole_k(1, 5121, 24064, 4) and whole_k(1, 4578, 12416, 4)
+
+
+class BatchPlan(ctypes.Structure):
+    _fields_ = [("ok", ctypes.c_bool), ("mt", ctypes.c_int), ("rows", ctypes.c_int), ("tiles_n", ctypes.c_int), ("slabs", ctypes.c_int),
+                ("shared", ctypes.c_bool), ("counter_bytes", ctypes.c_size_t), ("sums_at", ctypes.c_size_t), ("workspace", ctypes.c_size_t),
+                ("us", ctypes.c_double)]
+
+
+class BatchPlans(ctypes.Structure):
+    _fields_ = [("plain", BatchPlan), ("fine", BatchPlan)]
+
+
+def plan_batch(M, N, K):
+    f = binding.load_library()._ZN4any410plan_batchEllli            # any4::plan_batch(int64_t, int64_t, int64_t, int)
+    f.restype, f.argtypes = BatchPlans, [ctypes.c_int64] * 3 + [ctypes.c_int]
+    return f(M, N, K, CUS)
+
+
+def test_adding_that_is_not_shared_is_not_priced_as_shared():
+    """128 rows of x and K = 4096 in two slabs: 127 tiles of sums leave room for the words that slabs meet at, 128 do not, and one block adds all
+    (0.3 - 0.4 us per MB of 33 instead of a meeting and 0.1)"""
+    shared, alone = plan_batch(128, 127 * 256, 4096).plain, plan_batch(128, 128 * 256, 4096).plain
+    assert (shared.slabs, shared.shared, shared.tiles_n) == (2, True, 127) and (alone.slabs, alone.shared, alone.tiles_n) == (2, False, 128)
+    assert alone.us > shared.us + 2.0, (alone.us, shared.us)
