@@ -23,16 +23,17 @@ static bool shares(int mt, int t, int s, int cus) {
 // chip full: `crowd`), four steps whose loads come with the start, and the rest, which take longer from a quarter of the chip
 // on; a round that fills the chip to the last compute unit took longer by `even`.  Where slabs meet and share the adding: a meeting, more
 // beyond eight slabs (whose parts the first eight add), and the traffic of all sums; where the last adds alone: four slabs at a time, and
-// the traffic.  Constants fitted to 44 000 times of 2100 matrices of 512 .. 60000 rows of weights, K = 1024 .. 28672, at 32, 64, 96
-// and 128 rows of x: 4 - 5 % rms; the count taken is on average 0.4 / 0.6 / 0.7 / 0.8 % slower than the best of those timed (by the constants
-// from before the sharing 1.4 / 3.8 / 8.1 / 11.7 %), 4 / 6 / 7 / 11 % at the 99th of a hundred.
+// the traffic.  Up to 32 rows of x: constants fitted to times of 2100 matrices of 512 .. 60000 rows of weights, K = 1024 .. 28672.  The others:
+// to 44 000 times of 10 000 matrices of 16 .. 60000 rows, K = 128 .. 28672, 6 - 7 % rms; the count taken is on average
+// 0.4 (64 rows), 0.8 (96) and 1.2 % (128) slower than the best of those timed, below K = 1024 0.7 at most.  (Constants from K = 1024 on had
+// shorter rows cut where they are faster in one piece: 9954 x 640 at M = 75 19.9 us for 15.5.)
 struct Cost {
     double block, crowd, first, rest, rest_busy, even;
     double meeting, more, per_mb;          // the adding is shared
     double more_alone, per_mb_alone;       // it is not
 };
-constexpr Cost kCost[4] = {{4.94, 0.49, 1.45, 1.24, 1.38, 0.11, 2.08, 0.93, 0.43, 0.66, 0.79}, {5.78, 0.27, 1.70, 1.47, 1.75, 0.19, 2.55, 0.86, 0.29, 0.97, 0.64},
-                           {6.94, 0.41, 1.98, 1.54, 1.82, 1.99, 3.10, 1.20, 0.19, 1.23, 0.59}, {6.79, 3.99, 2.38, 1.82, 2.06, 1.38, 3.46, 1.09, 0.09, 1.63, 0.39}};
+constexpr Cost kCost[4] = {{4.94, 0.49, 1.45, 1.24, 1.38, 0.11, 2.08, 0.93, 0.43, 0.66, 0.79}, {5.23, 2.05, 1.49, 1.53, 1.77, 0.12, 2.59, 0.59, 0.30, 1.07, 0.47},
+                           {6.80, 5.47, 1.54, 1.62, 1.80, 0.14, 3.40, 1.34, 0.15, 3.63, 0.36}, {7.46, 6.63, 1.85, 1.78, 2.05, 0.83, 3.46, 1.51, 0.12, 1.55, 0.34}};
 static double meet_us(int mt, int t, int s, int cus) {
     const Cost& c = kCost[mt - 1];
     const double mb = (double)t * s * (double)tile_sum_bytes(mt) * 1e-6;
@@ -64,10 +65,12 @@ BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
     const int G = (int)(K / kGroup), tiles = (int)((N + bn - 1) / bn), most = kMaxSlabValues[mt - 1];   // values per row in LDS
     const int first = (G + most - 1) / most, first_fine = (2 * G + most / 2 * 2 - 1) / (most / 2 * 2);
     const size_t tile_bytes = tile_sum_bytes(mt);
-    // (above 64 rows of x a matrix of up to 1024 x 1024 is not cut, so that its calls go on needing no workspace: 23 us at 128 rows, cut 14)
-    const bool no_workspace = mt > 2 && N <= 1024 && K <= 1024;
+    // Rows of up to 384 weights are faster in one piece whatever their number (measured 0.96 .. 1.00 of the best cut, 24 x 384 at M = 100 10.5 us and
+    // 12.8).  Above 96 rows of x a matrix of up to 1024 x 1024 is not cut so that its calls go on needing no workspace, at the price of speed (23 us at 128
+    // rows; in eight slabs 14).
+    const bool whole_k = G <= 3 || (mt > 3 && N <= 1024 && K <= 1024);
     auto take = [&](BatchPlan& pl, int part, int s, double us) {
-        if (pl.ok && (no_workspace || us >= pl.us)) return;
+        if (pl.ok && (whole_k || us >= pl.us)) return;
         pl = BatchPlan{};
         pl.ok = true;
         pl.mt = mt; pl.rows = rows;
