@@ -910,10 +910,11 @@ StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, int cus) {
         if (bps > tiles) bps = (int)tiles;
         const int64_t tpb = (tiles + bps - 1) / bps;
         // microseconds: streaming of the block's bytes at ~22 GB/s per compute unit, per-tile
-        // table build and barrier, and the end-of-kernel combination of slabs (K / 128 no multiple of 4: more for
-        // each beyond three; without that wavefronts of two groups were taken for four, 19417 x 12544 at M = 12 in 7 slabs 54 us, in 4 40)
+        // table build and barrier, and the end-of-kernel combination of slabs (K / 128 no multiple of 4 and more than two tiles a block:
+        // more for each slab beyond three; without that wavefronts of two groups were taken for four, 19417 x 12544 at M = 12 in 7 slabs
+        // 54 us, in 4 40, while few tiles want as many slabs as there are, 92 x 8832, any3, at M = 16 in 9 8.4 us, in 3 11.2)
         double cost = (double)tpb * sgroups * 0.047 + (double)tpb * 0.15 + (slabs > 1 ? 3.0 : 0.0);
-        if (G % 4 != 0 && slabs > 3) cost += 0.3 * (slabs - 3);
+        if (G % 4 != 0 && slabs > 3 && tpb > 2) cost += 0.3 * (slabs - 3);
         if (cost < best_cost) {
             best_cost = cost;
             best.gw = gw;

@@ -48,6 +48,11 @@ def test_who_loads_the_small_inputs(G):
     assert all(plan_stream(8, n, 128 * g).aux for n in (16, 40000) for g in (4, 8, 20, 32, 36, 100))
 
 
+@pytest.mark.parametrize("N,K,slabs", ((92, 8832, 9), (34, 10112, 10), (66, 8448, 9), (36, 14080, 14), (32, 11520, 12), (19417, 12544, 4), (6668, 12544, 4)))
+def test_few_tiles_are_spread_over_slabs_and_many_are_not(N, K, slabs):
+    assert plan_stream(12, N, K).slabs == slabs
+
+
 def test_rows_that_need_no_moving_have_kernels_without_it():
     """every variant that moves the last small inputs of a row down has one that does not, for K / 128 a multiple of 4"""
     names = {tuple(m) for m in re.findall(rb"decode_stream_kernelILi(\d)ELi(\d)ELb(\d)((?:ELb\d){5})ELb(\d)EEE", open(binding.LIB_PATH, "rb").read())}
