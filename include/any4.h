@@ -92,8 +92,8 @@ int any4_dequant(const uint32_t* codes, const uint16_t* lut, const uint16_t* sca
  * order may depend on M, N and the place of a row of weights in the matrix: equal rows, or
  * the same rows in a matrix cut along N, can differ in the last bit of y.
  * Small M (<= 16, token generation) takes a memory-bound kernel, 17 <= M <= 128 a kernel
- * for a few dozen rows of x (where that is expected to be faster, the memory-bound kernel in
- * two launches, M <= 24, or the matrix-core kernel), larger M a matrix-core kernel; the choice
+ * for a few dozen rows of x (near 4096 x 4096 and M <= 24 the memory-bound kernel in two
+ * launches, where that is expected to be faster the matrix-core kernel), larger M a matrix-core kernel; the choice
  * depends only on (M, N, K, bits), the format and the number of compute units of the device.
  *   x          in   bf16 [M][K]
  *   lut        as for any4_dequant, including NULL = int4 grid for bits = 4

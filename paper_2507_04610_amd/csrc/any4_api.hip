@@ -23,7 +23,8 @@ static bool group_shift(int64_t K, int group, int* lr) {
 constexpr int kDecodeMaxM = 16;
 constexpr int kStreamMaxM = 16;
 constexpr int kFineRows = 8;           // groups of 64 weights: rows of x per launch of the streaming kernel
-constexpr int kTwoLaunchMaxM = 24;     // rows of x that two launches of the streaming kernel are considered for
+constexpr int kTwoLaunchMaxM = 24;     // rows of x that two launches of the streaming kernel may serve
+constexpr int64_t kStreamWholeK = 4096;      // longest K that it has in one block
 
 // Compute units of the current device (256 on MI355X); only shapes the work split, never results.
 // Asked of the runtime on every call (the current device may differ from call to call).
@@ -81,17 +82,13 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
                 if (wm > p.workspace) p.workspace = wm;
             }
             if (p.bp.ok) p.counter_bytes = p.bp.counter_bytes;
-            if (p.bp.ok && M <= kTwoLaunchMaxM) {
-                // Where the streaming kernel has one tile per block and the whole of K in it (4096 x 4096 and below, K a multiple
-                // of 512: 2048 x 2944 at M = 17 12.7 us, the other kernel 12.3), two launches of it, 16 rows of x and at most 8, can beat one that adds up slabs: 4096 x 4096 at M = 17 / 24
-                // 13.0 / 13.8 us, the other 14.6 / 14.7.  A launch: a fixed part, the larger of the time of a tile and
-                // that of the codes, a share per row of x (constants measured, 10 % rms).
+            if (p.bp.ok && M <= kTwoLaunchMaxM && K == kStreamWholeK) {
+                // Two launches of the streaming kernel, 16 rows of x and at most 8, where it has all of the longest K that it does not cut in a block and
+                // one tile for nearly each compute unit: such a call keeps the bits that its first 16 rows of x and the rest have as calls of
+                // their own.  That is all it keeps: since slabs share their adding the other kernel is the faster one there too (4000 x 4096 at
+                // M = 17 .. 24 by 3 - 12 %, any3 14 - 25 %), and everywhere else by more (6200 problems of up to 4096 x 4096: 1.31 on average, 0.99 at best).
                 p.sp = plan_stream(kStreamMaxM, N, K, cus);
-                // (Taken up to 1.17 of the other's expected time: a call of these sizes keeps the bits that its first 16 rows of x
-                // and the rest have as calls of their own.)
-                const double tile = 0.68 + 0.025 * p.sp.slab_groups, codes = (double)N * (double)K * bits / 8 / 4.74e6;
-                if (p.sp.gw > 0 && K % 512 == 0 && p.sp.slabs == 1 && p.sp.tiles <= p.sp.blocks_per_slab)
-                    p.two_launches = 2 * (3.6 + (tile > codes ? tile : codes)) + 0.15 * (double)M;
+                p.two_launches = p.sp.gw > 0 && p.sp.slabs == 1 && p.sp.tiles <= p.sp.blocks_per_slab && 16 * p.sp.tiles >= 15 * (int64_t)cus;
             }
             return p;
         }
@@ -150,9 +147,9 @@ int gemm_dispatch(const uint16_t* x, const uint32_t* codes, bool repacked, const
     const PackPlan pk = (M <= 4 && lut && lr == 0 && !f16) ? plan_pack(M, N, K, bits, one_table, plan.cus) : PackPlan{};
     if (pk.ok) {
         e = launch_decode_pack(x, codes, lut, scale, offset, M, N, K, bits, repacked, one_table, pk, y, s);
-    } else if (plan.two_launches > 0 && lut && lr >= 0 && plan.two_launches + (f16 ? 1.4 : 0.0) < 1.17 * plan.bp.us) {
-        // (fp16 takes it 0.7 us more per launch.  Not without a table: the streaming kernel takes the integer grid as 128 + code and off again, whose rounding
-        // the kernel for more rows does not have)
+    } else if (plan.two_launches && lut && lr >= 0 && !f16) {
+        // (not without a table: the streaming kernel takes the integer grid as 128 + code and off again, whose rounding the
+        // kernel for more rows does not have)
         e = launch_decode_stream(x, codes, lut, scale, offset, kStreamMaxM, N, K, bits, lr, repacked, f16, one_table, plan.sp, y, workspace, s);
         if (e == hipSuccess)
             e = launch_decode_stream(x + kStreamMaxM * K, codes, lut, scale, offset, M - kStreamMaxM, N, K, bits, lr, repacked, f16, one_table,

@@ -73,7 +73,7 @@ struct GemmPlan {
     bool stream;          // decode only: persistent streaming kernel; false: one wavefront per (row, K slice)
     StreamPlan sp;
     BatchPlan bp;         // M just above the small-M range
-    double two_launches;  // expected time of two launches of the streaming kernel instead; 0: not considered
+    bool two_launches;    // two launches of the streaming kernel instead, where the call's format is one that they serve
     BatchPlan bp_fine;    // the same for groups of 64 weights (twice the scales to keep in LDS)
     int ksplit;           // number of K slices whose fp32 partials are reduced in a 2nd pass
     size_t workspace;     // bytes of scratch: K-slice partials (decode) or group sums of x (matrix-core path)

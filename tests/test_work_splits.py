@@ -126,3 +126,27 @@ def test_short_rows_that_are_faster_in_one_piece_are_not_cut(M, N, K):
 @pytest.mark.parametrize("M,N,K", ((95, 42, 1024), (66, 30, 1024), (128, 4096, 1024), (64, 512, 1024), (64, 4096, 4096), (128, 6144, 4096)))
 def test_rows_that_are_faster_cut_are_cut(M, N, K):
     assert plan_batch(M, N, K).plain.slabs > 1
+
+
+class GemmPlan(ctypes.Structure):
+    _fields_ = [("cus", ctypes.c_int), ("decode", ctypes.c_bool), ("stream", ctypes.c_bool), ("sp", StreamPlan), ("bp", BatchPlan),
+                ("two_launches", ctypes.c_bool), ("bp_fine", BatchPlan), ("ksplit", ctypes.c_int), ("workspace", ctypes.c_size_t),
+                ("counter_bytes", ctypes.c_size_t)]
+
+
+def plan_gemm(M, N, K, bits=4):
+    f = binding.load_library()._ZN4any49plan_gemmEllli              # any4::plan_gemm(int64_t, int64_t, int64_t, int)
+    f.restype, f.argtypes = GemmPlan, [ctypes.c_int64] * 3 + [ctypes.c_int]
+    return f(M, N, K, bits)
+
+
+@pytest.mark.parametrize("bits", (4, 3, 2))
+def test_two_launches_are_not_taken_where_one_is_faster(bits):
+    """17 .. 24 rows of x: one launch of the kernel for a few dozen is faster (21 x 2736 x 2560 any3 re-laid-out 10.4 us, two launches 15.0) up to the
+    sizes whose calls keep the bits of their two parts"""
+    for M in range(17, 25):
+        for N, K in ((1312, 2560), (2736, 2560), (3013, 2560), (1500, 3072), (2048, 4096), (3824, 4096), (4096, 3584), (4097, 4096), (4096, 4224)):
+            p = plan_gemm(M, N, K, bits)
+            assert p.bp.ok and not p.two_launches, (M, N, K)
+        assert plan_gemm(M, 4000, 4096, bits).two_launches and plan_gemm(M, 4096, 4096, bits).two_launches
+    assert not plan_gemm(25, 4000, 4096, bits).two_launches and not plan_gemm(16, 4000, 4096, bits).two_launches
