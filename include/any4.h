@@ -99,7 +99,9 @@ int any4_dequant(const uint32_t* codes, const uint16_t* lut, const uint16_t* sca
  *   lut        as for any4_dequant, including NULL = int4 grid for bits = 4
  *   y          out  bf16 [M][N], fully overwritten
  *   workspace  scratch of at least any4_gemm_workspace_bytes(M, N, K, bits) bytes,
- *              16-byte aligned; may be NULL when that size is 0.  Contents on entry
+ *              16-byte aligned; may be NULL when that size is 0.  (17 <= M <= 128: calls
+ *              that an earlier version asked no workspace for are still served without one, as
+ *              fast as they were then.)  Contents on entry
  *              are ignored (no initialisation is needed), contents on exit are unspecified.
  *              A workspace must not serve two calls that overlap in time, and after a
  *              launch that did not run to its end (a device reset, an aborted process

@@ -136,10 +136,15 @@ int gemm_dispatch(const uint16_t* x, const uint32_t* codes, bool repacked, const
     if (!aligned16(x) || !aligned16(codes) || !aligned16(lut) || !aligned16(scale) ||
         !aligned16(offset) || !aligned16(y) || !aligned16(workspace))
         return ANY4_ERR_ALIGN;
-    const GemmPlan plan = plan_gemm(M, N, K, bits);
+    GemmPlan plan = plan_gemm(M, N, K, bits);
     // K beyond the streaming kernel's range: only the plain layout with groups of 128
     if ((repacked || lr != 0 || f16) && plan.decode && !plan.stream) return ANY4_ERR_SHAPE;
-    if (plan.workspace > 0 && (!workspace || workspace_bytes < plan.workspace)) return ANY4_ERR_WORKSPACE;
+    if (plan.workspace > 0 && (!workspace || workspace_bytes < plan.workspace)) {
+        if (!batch_goes_without(M, N, K)) return ANY4_ERR_WORKSPACE;
+        const BatchPlans whole = plan_batch_whole(M, N, K, plan.cus);
+        plan.bp = whole.plain;
+        plan.bp_fine = whole.fine;
+    }
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e;
     // one to four rows of x, a table, groups of 128, bf16: the packed-activation kernel (whole K in one

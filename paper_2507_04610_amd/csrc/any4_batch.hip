@@ -56,7 +56,7 @@ static double launch_us(int mt, int t, int s, int G, int cus) {
 // The sums of slabs stay within what any4_gemm_noalloc has, so that it takes every call.  Where those of the whole
 // matrix do not fit, the rows of weights are cut into launches that follow each other in the same workspace, each as many
 // whole rounds of blocks as fit.
-BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
+static BatchPlans plan(int64_t M, int64_t N, int64_t K, int cus, bool whole) {
     BatchPlans both{};
     if (M < 1 || M > kBatchMaxM || cus < 1) return both;
     const int mt = (int)((M + 31) / 32), rows = 32 * mt, wn = batch::wn_of(mt), wk = batch::kWaves / wn, bn = 32 * wn;
@@ -68,7 +68,7 @@ BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
     // Rows of up to 384 weights are faster in one piece whatever their number (measured 0.96 .. 1.00 of the best cut, 24 x 384 at M = 100 10.5 us and
     // 12.8).  Above 96 rows of x a matrix of up to 1024 x 1024 is not cut so that its calls go on needing no workspace, at the price of speed (23 us at 128
     // rows; in eight slabs 14).
-    const bool whole_k = G <= 3 || (mt > 3 && N <= 1024 && K <= 1024);
+    const bool whole_k = whole || G <= 3 || (mt > 3 && N <= 1024 && K <= 1024);
     auto take = [&](BatchPlan& pl, int part, int s, double us) {
         if (pl.ok && (whole_k || us >= pl.us)) return;
         pl = BatchPlan{};
@@ -117,6 +117,38 @@ BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) {
         }
     }
     return both;
+}
+BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus) { return plan(M, N, K, cus, false); }
+
+// Calls without a workspace.  Until slabs shared their adding, rows of up to 18 groups were cut along K for few tiles only, or not at all: from how many
+// tiles on they went without, for each number of groups (0: never; two gaps at 128 rows of x).  Longer rows did where they fit one piece and there
+// are many tiles (not all of them; they may now).  Cutting is the faster way for some of them since, up to 1.7x, and any4_gemm_workspace_bytes
+// asks for what that takes; a caller who brings none is served in one piece, in the time that it took then.
+static int whole_mt(int64_t M, int G) {                          // height of the blocks, 0: no block holds the scales of a row
+    const int mt = (int)((M + 31) / 32);
+    return 2 * G <= kMaxSlabValues[mt - 1] / 2 * 2 ? mt : mt == 2 && 2 * G <= kMaxSlabValues[0] ? 1 : 0;
+}
+bool batch_goes_without(int64_t M, int64_t N, int64_t K) {
+    constexpr unsigned char kFrom[4][18] = {{1, 1, 1, 1, 1, 1, 11, 11, 31, 31, 71, 71, 91, 91, 129, 129, 129, 129},
+                                            {1, 1, 1, 1, 1, 1, 1, 1, 16, 16, 43, 43, 68, 68, 115, 115, 115, 115},
+                                            {1, 1, 1, 1, 1, 1, 1, 3, 13, 26, 49, 79, 79, 90, 90, 118, 118, 128},
+                                            {1, 1, 1, 1, 1, 1, 1, 1, 1, 8, 80, 0, 0, 0, 0, 0, 0, 0}};
+    if (M <= 16 || M > kBatchMaxM || K > 128 * kGroup) return false;
+    const int G = (int)(K / kGroup), mt = (int)((M + 31) / 32);
+    const int64_t bn = 32 * batch::wn_of(mt), tiles = (N + bn - 1) / bn;
+    if (G > 18) return tiles > 128 && whole_mt(M, G) > 0;
+    if (mt == 4 && (G == 9 || G == 10) && tiles > (G == 9 ? 55 : 36) && tiles <= 64) return false;
+    const int from = kFrom[mt - 1][G - 1];
+    return from > 0 && tiles >= from;
+}
+BatchPlans plan_batch_whole(int64_t M, int64_t N, int64_t K, int cus) {
+    BatchPlans p = plan(M, N, K, cus, true);
+    const int mt = whole_mt(M, (int)(K / kGroup));
+    if (p.plain.ok && mt > 0 && mt < p.plain.mt) {               // blocks of 32 rows of x for up to 64
+        p.plain = plan(32, N, K, cus, true).plain;
+        p.fine = p.plain;
+    }
+    return p;
 }
 
 hipError_t launch_batch(const uint16_t* x, const uint32_t* codes, const uint16_t* lut, const uint16_t* scale,

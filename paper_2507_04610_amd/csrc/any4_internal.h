@@ -61,6 +61,9 @@ struct BatchPlan {
 };
 struct BatchPlans { BatchPlan plain, fine; };             // groups of 128 and more, groups of 64
 BatchPlans plan_batch(int64_t M, int64_t N, int64_t K, int cus);
+// calls that have always gone without a workspace, whether or not their plan has a use for one, and the plan of one that gets none
+bool batch_goes_without(int64_t M, int64_t N, int64_t K);
+BatchPlans plan_batch_whole(int64_t M, int64_t N, int64_t K, int cus);
 hipError_t launch_batch(const uint16_t* x, const uint32_t* codes, const uint16_t* lut, const uint16_t* scale,
                         const uint16_t* offset, int64_t M, int64_t N, int64_t K, int bits, int lr, bool repacked, bool f16,
                         bool one_table, const BatchPlan& pl, uint16_t* y, void* workspace, hipStream_t stream);
