@@ -72,8 +72,9 @@ __device__ __forceinline__ bool arrive_one(unsigned long long* c, int ksplit) {
 // the parts (bits) that the block is to add.  By one thread, after the block's sums are out.
 //
 // The last to arrive puts the word back for the next meeting; the bit then tells those who still look at it.  A word that is not
-// of this kind (memory used for the first time, or for something else) counts as no arrivals, as above.  (One that a launch
-// which never finished has left with parts marked only has a part added twice.)
+// of this kind (memory used for the first time, or for something else) counts as no arrivals, as above.  (Marks that
+// a launch which never finished has left only have a part added twice.  Arrivals that it has left, fewer than `slabs`, count for the
+// next meeting, which then ends before all sums are there: a workspace is cleared or replaced after such a launch.)
 //
 // One block adding all the sums of a tile took 8 - 12 000 cycles (a compute unit reads 20 - 26 bytes a cycle of what others wrote; 256 KB of
 // eight slabs at 64 rows of x, 1 MB at 128): 4096 x 4096 at M = 64 / 128 18.5 / 34.2 -> 16.4 / 24.3 us, 4096 x 14336 29.0 / 54.2 -> 26.5 / 39.2.
@@ -82,7 +83,7 @@ __device__ __forceinline__ bool arrive_one(unsigned long long* c, int ksplit) {
 constexpr int kWordBytes = 64;
 constexpr unsigned long long kMeetTag = 0x24B47C5EED17ull << 17;
 constexpr int kMaxParts = 8, kLooks = 10;                      // looks: about 0.4 us each
-__device__ __forceinline__ uint32_t meet(unsigned long long* word, int slabs, int parts, int slab) {
+__device__ __forceinline__ uint32_t meet(unsigned long long* word, int slabs, int parts, int slab, int looks = kLooks) {
     constexpr unsigned long long kTag = kMeetTag, kTurn = 1ull << 16, kCount = 0xFFull;
     const unsigned long long all = (unsigned long long)slabs;
     auto own = [&](unsigned long long v) -> bool { return (v >> 17) == (kTag >> 17) && (v & kCount) < all; };
@@ -102,7 +103,7 @@ __device__ __forceinline__ uint32_t meet(unsigned long long* word, int slabs, in
     }
     if (parts == 1 || bit == 0u) return 0u;
     auto complete = [&](unsigned long long v) -> bool { return ((v ^ old) & kTurn) != 0ull || (v & kCount) == all; };
-    for (int look = 0; look < kLooks; ++look) {
+    for (int look = 0; look < looks; ++look) {
         if (complete(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) return bit;
         __builtin_amdgcn_s_sleep(8);
     }
