@@ -38,7 +38,8 @@ int device_compute_units() {
 
 // Time in us of the matrix-core kernel at M <= 256 and of the group sums in front of it, groups of 64: per round of blocks a fixed part
 // and K / 64 steps, which take longer with every compute unit busy, the last round divided by its number of K slices, plus the
-// adding of slices.  Constants fitted to 1100 matrices of 512 .. 60000 rows, K = 1024 .. 28672: 7 % rms.
+// adding of slices.  Constants fitted to 1100 matrices of 512 .. 60000 rows, K = 1024 .. 28672: 7 % rms (8 % against 2600 others now; groups
+// of 128 take 13 % less).
 static double prefill_us(const PrefillPlan& pp, int64_t K, int cus) {
     const double steps = (double)(K / 64);
     const int64_t last = pp.tiles % cus;
@@ -65,16 +66,16 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits) {
     }
     if (M > kStreamMaxM && M <= kBatchMaxM) {
         // A few dozen rows of x fill a fraction of one 256-row tile of the matrix-core kernel, whose time does
-        // not depend on M below 256.  It is slower than the kernel for a few dozen rows wherever that takes the call, with groups of 128 and
-        // more at 128 rows for 2089 of 2100 matrices (0.75 of its time where the line was drawn the other way before slabs shared their
-        // adding).  Groups of 64 at more than 64 rows of x, where LDS holds scales for 11 .. 29 groups of 128 weights a slab: the faster
-        // by the two models, 0.2 % slower than the better of the two on average (this kernel takes 4 % longer than modelled there); calls
-        // that need no workspace stay here.
+        // not depend on M below 256.  It is slower than the kernel for a few dozen rows nearly wherever that takes the call: with groups of 128 and
+        // more, K = 1024 .. 28672, faster for 38 of 1301 random matrices at 128 rows (more than 3 % for 17) and 28 of 1386 at 97 .. 112, and the call that stays here
+        // regardless takes 0.2 % more than the better of the two on average.  Groups of 64, where LDS holds scales for 11 .. 29 groups of 128 weights a slab:
+        // for 3 of 1315 matrices up to 96 rows, 114 of 1300 beyond.  The faster by the two models is taken there, 0.4 % slower than the better of the
+        // two on average (this kernel takes 8 - 9 % longer than modelled, the other 1 % less; the factor with the least loss); calls that need no workspace stay here.
         const BatchPlans both = plan_batch(M, N, K, cus);
         p.bp = both.plain;
         p.bp_fine = both.fine;
         const PrefillPlan pp = plan_prefill(M, N, K, cus);
-        if (M > 64 && p.bp_fine.workspace > 0 && 1.04 * p.bp_fine.us > prefill_us(pp, K, cus)) p.bp_fine = BatchPlan{};
+        if (M > 64 && p.bp_fine.workspace > 0 && 1.12 * p.bp_fine.us > prefill_us(pp, K, cus)) p.bp_fine = BatchPlan{};
         if (p.bp.ok || p.bp_fine.ok) {
             p.workspace = p.bp.workspace > p.bp_fine.workspace ? p.bp.workspace : p.bp_fine.workspace;
             if (!p.bp.ok || !p.bp_fine.ok) {                   // the other kind of groups goes to the matrix-core kernel
