@@ -24,12 +24,12 @@
 // Order of the sums.  A block starts at a step of its own along K (see `rot`), so the last bit of an output can depend on
 // the place of its row of weights in the matrix.
 //
-// What bounds it: no unit by itself.  28672 x 4096 at M = 64 (16 steps, 224 blocks, 40 us under the counters, 1.94 GHz): a
-// wavefront issues 317 vector instructions (20 of them matrix) and 24 LDS instructions a step; vector issue is
-// busy 53 % of the time, the matrix cores of the SIMDs that hold a block 27 %, the LDS pipe 20 %, and wavefronts wait 35 % of
-// theirs.  A step takes 1.8 us.  The rest of a launch is fixed: 5 - 11 us for start and end of a block (32 .. 128 rows of x),
+// What bounds it: no unit by itself.  28672 x 4096 at M = 64 (16 steps, 224 blocks, 38 us under the counters, 1.93 GHz): a
+// wavefront issues 310 vector instructions (20 of them matrix) and 24 LDS instructions a step; vector issue is
+// busy 54 % of the time, the matrix cores of the SIMDs that hold a block 28 %, the LDS pipe 18 %, and wavefronts wait 39 % of
+// theirs.  A step takes 1.8 us.  The rest of a launch is fixed: 5 - 14 us for start and end of a block (32 .. 128 rows of x),
 // and where slabs meet 3 - 6 us for their sums (any4_batch.hip has the constants).  The four linears of an 8B layer at M = 24 / 64 / 128:
-// 80 / 97 / 151 us; with one block adding all the sums of a tile and all first loads at once 84 / 106 / 183.
+// 81 / 96 / 147 us; with one block adding all the sums of a tile and all first loads at once 84 / 106 / 183.
 #pragma once
 #include "any4_device.h"
 #include "any4_internal.h"
@@ -421,7 +421,8 @@ __device__ __forceinline__ void batch_body(const Params& p) {
             if (wk == i % WK) store_tile(i, acc[i]);
         return;
     }
-    // ---- K slabs: fp32 sums to the workspace; the last slab of the tile to arrive adds them in slab order
+    // ---- K slabs: fp32 sums to the workspace, where the tile's blocks meet and add them in slab order, each its part (one of them all, where
+    //      they do not share the adding)
     const int64_t btile = (int64_t)blockIdx.y * p.tiles_n + tile;
     // (16 bytes per lane: four accumulator elements)
     float* const all = p.partial + btile * p.slabs * (ROWS * BN);

@@ -44,8 +44,8 @@
 //
 // Small per-tile inputs (the rows' tables, scales and offsets: 2.5 KB per tile against 4 KB of
 // codes per wavefront) are not read by every wavefront: for tile t one wavefront, taking turns,
-// loads them four tiles ahead with five instructions and passes them on through LDS (AUX mode,
-// four groups and more).  Where K/128 is no multiple of 4 its 8-byte loads are aligned to 2 bytes only, and the last
+// loads them four tiles ahead with five instructions and passes them on through LDS (AUX mode; not
+// for fewer than four groups, nor always where K/128 is no multiple of 4: plan_stream).  Where K/128 is no multiple of 4 its 8-byte loads are aligned to 2 bytes only, and the last
 // one of a row starts early, so that it ends with the row, and is moved down in registers: 5003 x 2944 at M = 1 / 8 / 16 takes
 // 7.3 / 8.2 / 9.7 us, with every wavefront reading its own scales one by one 9.7 / 10.3 / 11.2; 28672 x 4224 at M = 1 26.6, 33.4.
 // Rows that need no moving have variants without it (it cost them 0.03 us a launch, 0.3 - 0.5 %).
@@ -495,8 +495,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void decode_stream_kernel(const Par
         return make_uint4(a, b, a, b);
     };
 
-    // ---- prologue.  Activations first (small, and the first thing the matrix cores need), then the
-    //      codes of the ring and the small inputs.
+    // ---- prologue.  Activations first (the first thing the matrix cores need; a kilobyte per row and wavefront of four groups, at
+    //      16 rows 128 KB per block, as much as the codes of four tiles), then the codes of the ring and the small inputs.
     // activations of the wavefront's groups as A operands: lane (m = n, q), MFMA j of group gi holds
     // x[m][(gw0 + gi) * 128 + q * 32 + j * 8 .. + 8]; rows m >= M and missing groups are zero.
     // The wavefront fetches each row's GW * 128 activations with ONE 16-byte load per lane (a
@@ -946,8 +946,8 @@ static hipError_t launch_stream_t(const Params& p, int grid, hipStream_t stream)
     return hipGetLastError();
 }
 
-// the variants of one kind by groups per wavefront.  Without shared small inputs: rows of fewer than four groups, which
-// plan_stream gives wavefronts of one or two, and any2 with groups of 64.
+// the variants of one kind by groups per wavefront.  Without shared small inputs: wavefronts of one or two groups where plan_stream
+// says so, and any2 with groups of 64.
 template <int BITS, bool NOLUT, bool REPACK, bool COARSE, bool FINE, bool F16>
 static hipError_t launch_stream_gw(const Params& p, const StreamPlan& sp, int grid, hipStream_t stream) {
     constexpr bool SHARE = !(FINE && BITS == 2);

@@ -83,9 +83,9 @@ static_assert(furthest(kNarrowK) < ((int64_t)1 << 31) && furthest(2 * kNarrowK) 
 // X[m][g] = sum of the 128 activations of group g, in fp32, stored as two bf16 (high part,
 // remainder) at xs[m][2g], xs[m][2g+1]; columns 2G .. KP-1 are zero.  16 lanes per (m, g).
 // `fine`: groups of 64 activations, 8 lanes each.
-// Also sets the words that count the arrivals of K slices to 0, so that those find no earlier call's leftovers: claiming
-// such words by compare-and-swap, as the other kernels do, has every part of every slice of a tile queue up at one word (four
-// linears at M = 512, scratch allocated by the call: 314 us against 295).
+// Also sets the words of K slices, so that those find no earlier call's leftovers: to an empty meeting (kMeetTag) where the slices
+// meet, `word_step` words apart, otherwise to counts of 0.  Claiming such words by compare-and-swap, as the other kernels do, has
+// every part of every slice of a tile queue up at one word (four linears at M = 512, scratch allocated by the call: 314 us against 295).
 template <bool F16>
 __global__ __launch_bounds__(256) void group_sums_kernel(const uint16_t* __restrict__ x, int64_t M,
                                                          int64_t K, int KP, int fine, uint16_t* __restrict__ xs,
